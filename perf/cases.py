@@ -86,7 +86,7 @@ def _draw_once(rng):
     if kind == "f32":
         heads = rng.choice((4, 6, 8, 12))
         return _branch(None, rng.choice(("branch", "step")), synth.CFG1, blocks=rng.randint(1, 4), hidden=64 * heads, heads=heads,
-                       latent_hw=2 * _log_int(rng, 4, 28), latent_c=rng.choice((4, 16)), n_txt=rng.randint(0, 154),
+                       latent_hw=2 * _log_int(rng, 4, 28), latent_c=rng.choice((4, 16)), n_txt=rng.randint(1, 154),
                        ctx_dim=rng.choice((256, 2048)))
     heads = rng.choice((12, 18, 24, 24, 24))
     # (a step's branches have to differ by more than the rounding of bf16: with few blocks the text reaches little)
