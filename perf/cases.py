@@ -145,7 +145,8 @@ class _Draws:
         return self.dev(shape, std, mean).cpu().numpy()
 
 
-def _mmdit(case, d):
+def _mmdit_weights(case, d):
+    """(weights outside the blocks, weights of each block) as host arrays."""
     cfg = _cfg(case)
     D = cfg.hidden
     shapes = {"pe_w": (D, cfg.patch_dim), "pe_b": (D,), "ce_w": (D, cfg.ctx_dim), "ce_b": (D,), "t1_w": (D, cfg.temb_dim),
@@ -158,48 +159,61 @@ def _mmdit(case, d):
     globals_np = {n: d.host(s) for n, s in shapes.items()}
     # Two different blocks, alternating: every block still has its own copy of its weights on the GPU.
     two = [{s: {n: d.host(sh) for n, sh in block.items()} for s in ("img", "txt")} for _ in range(min(2, cfg.blocks))]
-    return cfg, model.MMDiT(cfg, globals_np, (two[i % 2] for i in range(cfg.blocks)),
-                            txt_pre_only_last=case["txt_pre_only_last"])
+    return globals_np, [two[i % 2] for i in range(cfg.blocks)]
 
 
-def _sdxl(case, d):
-    cfg = _cfg(case)
-    C, X = cfg.channels, cfg.ctx_dim
+def _sdxl_weights(case, d):
+    C, X = case["channels"], case["ctx_dim"]
     shapes = {"q1_w": (C, C), "k1_w": (C, C), "v1_w": (C, C), "o1_w": (C, C), "o1_b": (C,), "q2_w": (C, C), "k2_w": (C, X),
               "v2_w": (C, X), "o2_w": (C, C), "o2_b": (C,), "ff1_w": (8 * C, C), "ff1_b": (8 * C,), "ff2_w": (C, 4 * C),
               "ff2_b": (C,)}
     shapes.update({n + s: (C,) for n in ("gn", "ln1", "ln2", "ln3") for s in ("_g", "_b")})
-    two = [{n: d.host(sh, mean=1.0 if n.endswith("_g") else 0.0) for n, sh in shapes.items()} for _ in range(min(2, cfg.blocks))]
-    return cfg, model.SDXLStage(cfg, (two[i % 2] for i in range(cfg.blocks)))
+    two = [{n: d.host(sh, mean=1.0 if n.endswith("_g") else 0.0) for n, sh in shapes.items()} for _ in range(min(2, case["blocks"]))]
+    return [two[i % 2] for i in range(case["blocks"])]
+
+
+def _inputs(case, d):
+    """What a call is given besides the weights, made after them; tensors on the GPU."""
+    kind, B = case["kind"], case["batch"]
+    if kind == "guidance":
+        # branch velocities that differ by a tenth, as conditional and unconditional predictions do; fp32 latent
+        n, dt = case["elems"], DT[case["dtype"]]
+        v_u = d.dev((B, n))
+        v_c = (v_u + 0.1 * d.dev((B, n))).to(dt)
+        return {"v_c": v_c, "v_u": v_u.to(dt), "x": torch.randn((B, n), generator=d.g, device="cuda")}
+    if kind == "attention":
+        return {n: d.dev((B, case["heads"], case[m], 64)).to(DT[case["dtype"]]) for n, m in (("q", "n_q"), ("k", "n_kv"), ("v", "n_kv"))}
+    if kind == "stage":
+        x = d.dev((B, case["tokens"], case["channels"]))
+        return {"x": x, "ctx": d.tokens((B, case["n_ctx"], case["ctx_dim"]))}
+    hw, c = case["latent_hw"], case["latent_c"]
+    ctx = d.tokens((B, case["n_txt"], case["ctx_dim"]))
+    if kind == "step":
+        return {"ctx": ctx, "x": d.dev((hw, hw, c))}
+    latent = d.dev((B, hw, hw, c))
+    return {"ctx": ctx, "latent": latent, "t": torch.full((B,), 0.5, device="cuda"),
+            "pooled": d.dev((B, case["pooled_dim"])) if case["pooled_dim"] else None}
 
 
 def prepare(case, seed):
     kind = case["kind"]
     d = _Draws(seed, case["dtype"])
-    if kind == "guidance":
-        # branch velocities that differ by a tenth, as conditional and unconditional predictions do; fp32 latent
-        B, n, dt = case["batch"], case["elems"], DT[case["dtype"]]
-        v_u = d.dev((B, n))
-        v_c = (v_u + 0.1 * d.dev((B, n))).to(dt)
-        x = torch.randn((B, n), generator=d.g, device="cuda")
-        return {"kind": kind, "v_c": v_c, "v_u": v_u.to(dt), "x": x, "x_out": torch.empty_like(x),
-                "l1": torch.empty(B, device="cuda"), "l2": torch.empty(B, device="cuda"),
-                "ws": torch.empty(max(hb.hyb_discrepancy_workspace_bytes(B, n), 256), device="cuda", dtype=torch.uint8)}
-    if kind == "attention":
-        B, H, dt = case["batch"], case["heads"], DT[case["dtype"]]
-        q, k, v = (d.dev((B, H, case[n], 64)).to(dt) for n in ("n_q", "n_kv", "n_kv"))
-        return {"kind": kind, "q": q, "k": k, "v": v, "o": torch.empty(B, case["n_q"], H * 64, device="cuda", dtype=dt)}
+    state = {"kind": kind}
     if kind == "stage":
-        cfg, st = _sdxl(case, d)
-        return {"kind": kind, "stage": st, "x": d.dev((cfg.batch, cfg.tokens, cfg.channels)),
-                "ctx": d.tokens((cfg.batch, cfg.n_ctx, cfg.ctx_dim))}
-    cfg, m = _mmdit(case, d)
-    ctx = d.tokens((cfg.batch, cfg.n_txt, cfg.ctx_dim))
-    if kind == "step":
-        return {"kind": kind, "sampler": model.GuidedSampler(m, cfg.guidance), "ctx": ctx,
-                "x": d.dev((cfg.latent_hw, cfg.latent_hw, cfg.latent_c))}
-    return {"kind": kind, "model": m, "ctx": ctx, "latent": d.dev((cfg.batch, cfg.latent_hw, cfg.latent_hw, cfg.latent_c)),
-            "t": torch.full((cfg.batch,), 0.5, device="cuda"), "pooled": d.dev((cfg.batch, cfg.pooled_dim)) if cfg.pooled_dim else None}
+        state["stage"] = model.SDXLStage(_cfg(case), _sdxl_weights(case, d))
+    elif kind in ("branch", "step"):
+        globals_np, blocks = _mmdit_weights(case, d)
+        m = state["model"] = model.MMDiT(_cfg(case), globals_np, blocks, txt_pre_only_last=case["txt_pre_only_last"])
+        if kind == "step":
+            state["sampler"] = model.GuidedSampler(m, _cfg(case).guidance)
+    state.update(_inputs(case, d))
+    B = case["batch"]
+    if kind == "guidance":
+        state.update(x_out=torch.empty_like(state["x"]), l1=torch.empty(B, device="cuda"), l2=torch.empty(B, device="cuda"),
+                     ws=torch.empty(max(hb.hyb_discrepancy_workspace_bytes(B, case["elems"]), 256), device="cuda", dtype=torch.uint8))
+    if kind == "attention":
+        state["o"] = torch.empty(B, case["n_q"], case["heads"] * 64, device="cuda", dtype=DT[case["dtype"]])
+    return state
 
 
 def run(state):
@@ -253,4 +267,111 @@ def tolerance(case):
         return {"rel": 1e-5 if case["kind"] == "step" else 2e-6}
     if case["kind"] == "stage":     # 1.0e-3 (the residual stream carries most of the result)
         return {"rel": 4e-3}
-    return {"rel": 1e-2}            # 3.7e-3 on velocities, 2.3e-3 on attention rows; discrepancies of a step likewise
+    if case["kind"] == "step":      # up to 1.2e-2 on the discrepancies, ratios of small differences of bf16 velocities
+        return {"rel": 3e-2}
+    return {"rel": 1e-2}            # 3.7e-3 on velocities, 2.3e-3 on attention rows
+
+
+# ---- the same results in 64 bits, in plain torch ----------------------------------------------------------------
+
+def _f64(a):
+    return (a if isinstance(a, torch.Tensor) else torch.from_numpy(a).cuda()).double()
+
+
+def _linear64(x, w, b=None):
+    y = x @ _f64(w).t()
+    return y if b is None else y + _f64(b)
+
+
+def _norm64(x, eps):
+    return (x - x.mean(-1, keepdim=True)) / torch.sqrt(x.var(-1, keepdim=True, unbiased=False) + eps)
+
+
+def _attention64(q, k, v, heads):
+    """Rows of heads merged along features [B, N, heads * 64], one (sample, head) and 2048 query rows at a time."""
+    o = torch.empty_like(q)
+    for b in range(q.shape[0]):
+        for h in range(heads):
+            i = slice(64 * h, 64 * h + 64)
+            kt, vh = k[b, :, i].t().contiguous(), v[b, :, i].contiguous()
+            for r in range(0, q.shape[1], 2048):
+                s = q[b, r:r + 2048, i].contiguous() @ kt
+                o[b, r:r + 2048, i] = torch.softmax(s.mul_(0.125), -1) @ vh
+    return o
+
+
+def _branch64(case, P, blocks, latent, ctx, t, pooled):
+    silu = torch.nn.functional.silu
+    B, hw, c, heads = latent.shape[0], case["latent_hw"], case["latent_c"], case["heads"]
+    p = _cfg(case).patch
+    n = (hw // p) ** 2
+    tok = latent.double().view(B, hw // p, p, hw // p, p, c).permute(0, 1, 3, 2, 4, 5).reshape(B, n, p * p * c)
+    x = {"img": _linear64(tok, P["pe_w"], P["pe_b"]) + _f64(P["pos"]), "txt": _linear64(ctx.double(), P["ce_w"], P["ce_b"])}
+    half = P["t1_w"].shape[1] // 2
+    ang = 1000.0 * t.double()[:, None] * torch.exp(-math.log(10000.0) * torch.arange(half, device="cuda", dtype=torch.float64) / half)
+    temb = _linear64(silu(_linear64(torch.cat([ang.cos(), ang.sin()], 1), P["t1_w"], P["t1_b"])), P["t2_w"], P["t2_b"])
+    if pooled is not None:
+        temb = temb + _linear64(silu(_linear64(pooled.double(), P["p1_w"], P["p1_b"])), P["p2_w"], P["p2_b"])
+    temb = silu(temb)[:, None]
+    for i, w in enumerate(blocks):
+        mod = {s: _linear64(temb, w[s]["ada_w"], w[s]["ada_b"]).chunk(6, -1) for s in w}
+        qkv = [_linear64(_norm64(x[s], 1e-6) * (1 + mod[s][1]) + mod[s][0], w[s]["qkv_w"], w[s]["qkv_b"]) for s in ("img", "txt")]
+        o = _attention64(*torch.cat(qkv, 1).chunk(3, -1), heads)
+        for s, part in (("img", o[:, :n]), ("txt", o[:, n:])):
+            if s == "txt" and case["txt_pre_only_last"] and i == len(blocks) - 1:
+                continue
+            _, _, g1, sh2, sc2, g2 = mod[s]
+            x[s] = x[s] + g1 * _linear64(part, w[s]["out_w"], w[s]["out_b"])
+            h = _linear64(_norm64(x[s], 1e-6) * (1 + sc2) + sh2, w[s]["fc1_w"], w[s]["fc1_b"])
+            x[s] = x[s] + g2 * _linear64(torch.nn.functional.gelu(h, approximate="tanh"), w[s]["fc2_w"], w[s]["fc2_b"])
+    sh, sc = _linear64(temb, P["f_ada_w"], P["f_ada_b"]).chunk(2, -1)
+    y = _linear64(_norm64(x["img"], 1e-6) * (1 + sc) + sh, P["f_w"], P["f_b"])
+    return y.view(B, hw // p, hw // p, p, p, c).permute(0, 1, 3, 2, 4, 5).reshape(B, hw, hw, c)
+
+
+def _stage64(case, blocks, x, ctx):
+    x, ctx, heads = x.double(), ctx.double(), case["heads"]
+    B, T, C = x.shape
+    for w in blocks:
+        ln = lambda y, n: _norm64(y, 1e-5) * _f64(w[n + "_g"]) + _f64(w[n + "_b"])
+        g = x.view(B, T, 32, C // 32).transpose(1, 2).reshape(B, 32, -1)
+        g = _norm64(g, 1e-5).view(B, 32, T, C // 32).transpose(1, 2).reshape(B, T, C) * _f64(w["gn_g"]) + _f64(w["gn_b"])
+        h = ln(g, "ln1")
+        a = g + _linear64(_attention64(*(_linear64(h, w[n]) for n in ("q1_w", "k1_w", "v1_w")), heads), w["o1_w"], w["o1_b"])
+        h = ln(a, "ln2")
+        h = _attention64(_linear64(h, w["q2_w"]), _linear64(ctx, w["k2_w"]), _linear64(ctx, w["v2_w"]), heads)
+        a = a + _linear64(h, w["o2_w"], w["o2_b"])
+        u, gate = _linear64(ln(a, "ln3"), w["ff1_w"], w["ff1_b"]).chunk(2, -1)
+        x = x + a + _linear64(u * torch.nn.functional.gelu(gate), w["ff2_w"], w["ff2_b"])
+    return x
+
+
+def _guidance64(v_c, v_u, x, scale, t, t_next):
+    v_c, v_u = v_c.double(), v_u.double()
+    diff = v_c - v_u
+    return (x.double() + (t_next - t) * (v_u + scale * diff), diff.abs().sum(1) / v_u.abs().sum(1),
+            diff.norm(dim=1) / v_u.norm(dim=1))
+
+
+def exact(case, seed):
+    """What run() returns on new inputs, in 64 bits."""
+    kind = case["kind"]
+    d = _Draws(seed, case["dtype"])
+    if kind == "stage":
+        blocks = _sdxl_weights(case, d)
+    elif kind in ("branch", "step"):
+        P, blocks = _mmdit_weights(case, d)
+    i = _inputs(case, d)
+    if kind == "guidance":
+        return _guidance64(i["v_c"], i["v_u"], i["x"], 7.0, 0.5, 0.45)
+    if kind == "attention":
+        q, k, v = (i[n].double().transpose(1, 2).reshape(case["batch"], -1, 64 * case["heads"]) for n in ("q", "k", "v"))
+        return _attention64(q, k, v, case["heads"])
+    if kind == "stage":
+        return _stage64(case, blocks, i["x"], i["ctx"])
+    if kind == "branch":
+        return _branch64(case, P, blocks, i["latent"], i["ctx"], i["t"], i["pooled"])
+    x = i["x"]
+    v = _branch64(case, P, blocks, torch.stack([x, x]), i["ctx"], torch.full((2,), 0.5, device="cuda"), None)
+    y, l1, l2 = _guidance64(v[:1].reshape(1, -1), v[1:].reshape(1, -1), x.view(1, -1), _cfg(case).guidance, 0.5, 0.45)
+    return y.view(x.shape), torch.stack([l1, l2])
