@@ -47,12 +47,14 @@ struct GemmGroup {
 
 // Plain tiled FMA kernel: any shape, fp32 or bf16 operands, fp32 accumulation.
 int hyb_launch_gemm_simple(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st);
+// fp32 MFMA kernel (k % 16 == 0, n % 4 == 0; every epilogue); returns -1 if the shape is not supported.
+int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
 // bf16 MFMA kernel (k % 64 == 0, n % 8 == 0); returns -1 if the shape is not supported.
 int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
 // Large-tile bf16 MFMA kernel (256 x 128 tiles, one workgroup per CU).  Same accumulation order as the kernel above, hence
 // the same bits per token.  -1 when the shape or the epilogue has no large-tile form.
 int hyb_launch_gemm_mfma_big(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
-// Dispatch: MFMA for bf16 when supported, else the plain kernel.
+// Dispatch: the MFMA kernel of the operand type when it takes the shape, else the plain kernel.
 int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st);
 
 // Scalar epilogue shared by both kernels' tails (v = acc + bias already applied by the caller

@@ -1,6 +1,5 @@
 // Plain LDS-tiled FMA GEMM: out = epilogue(A W^T + bias) for any shape, fp32 or bf16 operands,
-// fp32 accumulation in a fixed k order.  It is the fp32 (reference-precision) path of the
-// denoiser forward and the fallback for shapes the MFMA kernel does not take.
+// fp32 accumulation in a fixed k order: the fallback for the shapes that the MFMA kernels do not take.
 #include "gemm.h"
 
 namespace {
@@ -94,10 +93,8 @@ int hyb_launch_gemm_simple(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out
 }
 
 int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st) {
-    if (in_dtype == HYB_BF16) {
-        const int rc = hyb_launch_gemm_mfma(g, out_dtype, epi, st);
-        if (rc >= 0) return rc;
-    }
+    const int rc = in_dtype == HYB_BF16 ? hyb_launch_gemm_mfma(g, out_dtype, epi, st) : hyb_launch_gemm_f32_mfma(g, out_dtype, epi, st);
+    if (rc >= 0) return rc;
     return hyb_launch_gemm_simple(g, in_dtype, out_dtype, epi, st);
 }
 

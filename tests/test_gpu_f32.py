@@ -1,0 +1,47 @@
+"""GPU parity of the fp32 MFMA GEMM (its two tile shapes) against float64 on the CPU."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import hyb_oracle as O
+from gpu_util import dev, host, err
+
+pytestmark = pytest.mark.gpu
+
+# fp32 products summed in fp32: the relative error of a row stays below sqrt(k) 2^-24, 3.3e-6 at k = 3072.
+TOL = 4e-6
+
+
+@pytest.fixture(scope="module")
+def hb():
+    from paper_2602_21760_amd import binding
+    binding.lib()
+    return binding
+
+
+# both tile shapes (64 x 64 where it fills the chip as well as 32 x 32), one row, ragged rows and columns around the tile
+# sizes, one slab of k, fewer slabs than waves, an odd number of slabs, long k; half a slab; n % 4 != 0 and k % 16 != 0 take the plain kernel
+@pytest.mark.parametrize("m,n,k", [(1, 4, 32), (2, 256, 96), (31, 36, 160), (33, 28, 64), (65, 100, 1056), (653, 768, 3072),
+                                   (4097, 2052, 64), (100, 40, 16), (70, 64, 112), (4100, 2048, 80), (40, 30, 64), (40, 32, 72)])
+def test_linear_f32(hb, m, n, k):
+    g = torch.Generator().manual_seed(m + n + k)
+    a, w, b = (torch.randn(s, generator=g).numpy() for s in ((m, k), (n, k), (n,)))
+    res, gate = torch.randn(m, n, generator=g).numpy(), torch.randn(2, n + 4, generator=g).numpy()
+    y = O.linear(a.astype(np.float64), w.astype(np.float64), b.astype(np.float64))
+    da, dw, db = dev(a), dev(w), dev(b)
+    out = torch.empty(m, n, device="cuda")
+    hb.hyb_linear(da, dw, db, out)
+    assert err(host(out), y) < TOL
+    whole = host(out)
+    hb.hyb_linear(da[m // 2:m // 2 + 1].clone(), dw, db, out[:1])
+    if n % 4 == 0 and k % 16 == 0:      # a row has the same bits whatever the tile shape and the rows beside it
+        assert np.array_equal(host(out[:1])[0], whole[m // 2])
+    dres, rpg = dev(res), (m + 1) // 2
+    if n % 4 == 0:
+        hb.hyb_linear(da, dw, db, dres, hb.HYB_EPI_GATE_RESIDUAL, residual=dres, gate=dev(gate), rows_per_gate=rpg, gate_stride=n + 4)
+        assert err(host(dres), res + gate[np.arange(m) // rpg, :n].astype(np.float64) * y) < TOL
+    if n % 8 == 0:                      # u and gate halves of the same weights
+        out = torch.empty(m, n // 2, device="cuda")
+        hb.hyb_linear(da, dw, db, out, hb.HYB_EPI_GEGLU)
+        u, v = torch.from_numpy(y).chunk(2, 1)
+        assert err(host(out), (u * torch.nn.functional.gelu(v)).numpy()) < TOL
