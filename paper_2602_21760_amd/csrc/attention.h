@@ -24,8 +24,7 @@ struct AttnArgs {
 // Scratch the bf16 MFMA kernel wants for its split tail (see attention_mfma.hip); 0 when it would not split.
 size_t hyb_attention_split_bytes(int batch, int heads, int n_q);
 
-// Plain kernel (fp32 or bf16 storage, fp32 math with accurate expf).
-int hyb_launch_attention_simple(const AttnArgs& a, hyb_dtype dtype, hipStream_t st);
 // bf16 flash-style MFMA kernel.
 int hyb_launch_attention_mfma(const AttnArgs& a, hipStream_t st);
+// Dispatch by type: the bf16 kernel above or the fp32 kernel of attention_f32.hip.
 int hyb_launch_attention(const AttnArgs& a, hyb_dtype dtype, hipStream_t st);

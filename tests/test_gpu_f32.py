@@ -1,4 +1,4 @@
-"""GPU parity of the fp32 MFMA GEMM (its two tile shapes) against float64 on the CPU."""
+"""GPU parity of the fp32 MFMA kernels (GEMM with its two tile shapes, attention) against float64 on the CPU."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +8,8 @@ from gpu_util import dev, host, err
 
 pytestmark = pytest.mark.gpu
 
-# fp32 products summed in fp32: the relative error of a row stays below sqrt(k) 2^-24, 3.3e-6 at k = 3072.
+# fp32 products summed in fp32: the relative error of a row stays below sqrt(k) 2^-24, 3.3e-6 at k = 3072; attention adds
+# its exponentials (2 ulp each, arguments below 2^4: 1e-6).
 TOL = 4e-6
 
 
@@ -45,3 +46,20 @@ def test_linear_f32(hb, m, n, k):
         hb.hyb_linear(da, dw, db, out, hb.HYB_EPI_GEGLU)
         u, v = torch.from_numpy(y).chunk(2, 1)
         assert err(host(out), (u * torch.nn.functional.gelu(v)).numpy()) < TOL
+
+
+# keys: fewer than one tile, exactly one, one more, fewer tiles than waves, ragged; queries around the 32-row blocks
+@pytest.mark.parametrize("batch,heads,n_q,n_kv", [(1, 1, 1, 1), (2, 3, 31, 32), (1, 5, 33, 33), (2, 4, 80, 80), (1, 2, 64, 129), (2, 8, 97, 653)])
+def test_attention_f32(hb, batch, heads, n_q, n_kv):
+    g = torch.Generator().manual_seed(n_q + n_kv)
+    q, k, v = (torch.randn(batch, heads, n, 64, generator=g) for n in (n_q, n_kv, n_kv))
+    o = torch.empty(batch, n_q, heads * 64, device="cuda")
+    hb.hyb_joint_attention(q.cuda(), k.cuda(), v.cuda(), o)
+    ref = torch.softmax(q.double() @ k.double().transpose(2, 3) / 8, -1) @ v.double()
+    assert err(host(o), ref.transpose(1, 2).reshape(batch, n_q, -1).numpy()) < TOL
+    # scores of several hundred, largest in the first key or growing along the keys
+    for ramp in (torch.arange(n_kv, 0, -1), torch.arange(1, n_kv + 1)):
+        kr = k * (1 + 40 * ramp / n_kv).view(1, 1, -1, 1)
+        hb.hyb_joint_attention(q.cuda(), kr.cuda(), v.cuda(), o)
+        ref = torch.softmax(q.double() @ kr.double().transpose(2, 3) / 8, -1) @ v.double()
+        assert err(host(o), ref.transpose(1, 2).reshape(batch, n_q, -1).numpy()) < 40 * TOL   # the exponents' rounding, 40 times larger
