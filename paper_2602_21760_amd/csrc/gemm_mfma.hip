@@ -49,11 +49,12 @@ constexpr int BN = 128, BK = 64;
 constexpr int ROWB = BK * 2;                    // bytes per LDS row of a slab
 // The tile height is 64 TMW tokens (TMW = MFMA token tiles per wave): 128 for the large GEMMs, 64 for
 // launches that would otherwise leave most of the chip idle (fewer than three quarters of a wave of tiles).
-template <int TMW> struct Geo {
+template <int TMW, int NST = 2> struct Geo {
     static constexpr int BM = 64 * TMW;
     static constexpr int STAGE_BYTES = (BM + BN) * ROWB;   // 32 KB / 24 KB
     static constexpr int CPW = STAGE_BYTES / 1024 / 4;     // 1 KB chunks per wave per slab (8 / 6)
-    static constexpr int SMEM_BYTES = 2 * STAGE_BYTES;     // 64 KB -> two workgroups per CU / 48 KB -> three
+    static constexpr int SMEM_BYTES = NST * STAGE_BYTES;   // two slab buffers: 64 KB -> two workgroups per CU / 48 KB -> three
+    static constexpr int WG_PER_CU = TMW == 2 ? 2 : (NST == 2 ? 3 : (NST == 3 ? 2 : 1));
 };
 constexpr int VEC_BYTES = 2 * BN * 4;           // the tile's bias and gate values, behind the slab buffers
 constexpr int OUT_STRIDE_B16 = BN * 2 + 16;     // staging row strides (bytes), padded against conflicts
@@ -72,10 +73,10 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned byt
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)lds, 16, voffset, soffset, 0, 0);
 }
 
-template <typename OT, int EPI, int TMW>
-__global__ __launch_bounds__(256, TMW == 2 ? 2 : 3) void gemm_mfma_kernel(GemmGroup g, int tiles_n, int tiles0, int total, int xcd_run, int ksplit) {
+template <typename OT, int EPI, int TMW, int NST>
+__global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_kernel(GemmGroup g, int tiles_n, int tiles0, int total, int xcd_run, int ksplit) {
     constexpr int BM = Geo<TMW>::BM, STAGE_BYTES = Geo<TMW>::STAGE_BYTES, CPW = Geo<TMW>::CPW;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[Geo<TMW>::SMEM_BYTES + VEC_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char smem[Geo<TMW, NST>::SMEM_BYTES + VEC_BYTES];
 
     // Workgroups go round-robin to the 8 XCDs (each with its own L2) in launch order.  With few tile columns the
     // tiles that an XCD works on at a time then share hardly any operand panel (every 8th tile: all tile rows, a
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(256, TMW == 2 ? 2 : 3) void gemm_mfma_kernel(GemmGr
     // one value per thread now, parked in LDS behind the slab buffers once the first slab's wait has passed.
     // (The gate row must be the same for all rows of the tile; tiles that straddle samples read it from
     // global memory in the epilogue.)
-    float* vec_lds = reinterpret_cast<float*>(smem + Geo<TMW>::SMEM_BYTES);
+    float* vec_lds = reinterpret_cast<float*>(smem + Geo<TMW, NST>::SMEM_BYTES);
     bool gate_in_lds = true;   // no gate: ones
     if constexpr (EPI == EPI_GATE_RES) {
         if (p.gate) gate_in_lds = row0 / p.rows_per_gate == min(row0 + BM - 1, m - 1) / p.rows_per_gate;
@@ -205,12 +206,20 @@ __global__ __launch_bounds__(256, TMW == 2 ? 2 : 3) void gemm_mfma_kernel(GemmGr
             val = 1.f;
             if (p.gate && gate_in_lds) val = p.gate[(size_t)(row0 / p.rows_per_gate) * p.gate_stride + f];
         }
-        issue(0, 0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (NST == 2) {
+            issue(0, 0);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        } else {
+#pragma unroll
+            for (int j = 0; j < NST; j++)
+                if (j < nslab) issue(j, j);
+            if (nslab >= NST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * CPW) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
         vec_lds[tid] = val;
     }
     __builtin_amdgcn_s_barrier();
-    if (nslab > 1) issue(1, 1);
+    if (NST == 2 && nslab > 1) issue(1, 1);
     read_set(0, 0);
     constexpr bool GEGLU = EPI == EPI_GEGLU;
     [[maybe_unused]] const int q_cols = EPI == EPI_QKV && p.q_scale != 0.f ? p.heads * 64 : 0;   // columns of the q part that are scaled
@@ -262,13 +271,15 @@ __global__ __launch_bounds__(256, TMW == 2 ? 2 : 3) void gemm_mfma_kernel(GemmGr
 #pragma unroll
         for (int ks = 0; ks < BK / 32; ks++) {
             if (ks == 1 && s + 1 < nslab) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's share of slab s + 1 has landed
+                // this wave's share of slab s + 1 has landed (up to NST - 2 younger slabs may be in flight)
+                if (NST > 2 && s + NST - 1 < nslab) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * CPW) : "memory");
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // ... and its reads of slab s are complete
                 __builtin_amdgcn_s_barrier();
-                if (s + 2 < nslab) issue(s + 2, STG);
+                if (s + NST < nslab) issue(s + NST, STG);
             }
             if (ks == 0) read_set(STG, 1);
-            else if (s + 1 < nslab) read_set(STG ^ 1, 0);
+            else if (s + 1 < nslab) read_set((STG + 1) % NST, 0);
 #pragma unroll
             for (int fi = 0; fi < 4; fi++)
 #pragma unroll
@@ -281,9 +292,17 @@ __global__ __launch_bounds__(256, TMW == 2 ? 2 : 3) void gemm_mfma_kernel(GemmGr
             }
         }
     };
-    for (int s = 0; s < nslab; s += 2) {
+    for (int s = 0; s < nslab; s += NST) {
         slab_step(s, std::integral_constant<int, 0>{});
         if (s + 1 < nslab) slab_step(s + 1, std::integral_constant<int, 1>{});
+        if constexpr (NST > 2) {
+            if (s + 2 < nslab) slab_step(s + 2, std::integral_constant<int, 2>{});
+        }
+        if constexpr (NST > 3) {
+            if (s + 3 < nslab) slab_step(s + 3, std::integral_constant<int, 3>{});
+            if (s + 4 < nslab) slab_step(s + 4, std::integral_constant<int, 4>{});
+            if (s + 5 < nslab) slab_step(s + 5, std::integral_constant<int, 5>{});
+        }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();                          // every wave is done with the slab buffers
@@ -402,6 +421,12 @@ __global__ __launch_bounds__(256, TMW == 2 ? 2 : 3) void gemm_mfma_kernel(GemmGr
     }
 }
 
+// A launch of 64-row tiles that leaves room on the CUs is bound by the latency of its slab copies, one after the other: it
+// takes more slab buffers, six when every workgroup can have a CU of its own (256 tiles), three for up to two per CU.
+// Two against six: 333 x 1536 x 4096 49 -> 26 us, one row x 1536 x 1536 24 -> 13 us; two against three: 2048 x 1280 x 1280
+// with residual 20 -> 18 us.  Up to two k-slabs have nothing to run ahead of.
+constexpr int kDeepTiles = 256;
+
 // Up to this many tile columns a launch hands each XCD a run of consecutive tiles (see the kernel).
 constexpr int kNarrowTileCols = 16;
 
@@ -431,7 +456,14 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
     const int total = (tiles0 + tiles1) * ksplit;
     const int xcd_run = tiles_n <= kNarrowTileCols ? (total + 7) / 8 : 0;
     const int grid = xcd_run ? 8 * xcd_run : total;
-    hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, TMW>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+    if constexpr (TMW == 1) {
+        const int nslab = g.k / BK / ksplit;
+        if (total <= kDeepTiles && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 6>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+        else if (total <= 2 * kDeepTiles && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 3>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+        else hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 2>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+    } else {
+        hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, TMW, 2>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+    }
     return hyb_check_launch("gemm_mfma");
 }
 
@@ -499,7 +531,7 @@ int launch_epi(const GemmGroup& g, hipStream_t st) {
             return hyb_check_launch("gemm_splitk_merge");
         }
     }
-    if (tiles128 <= kSmallGridTiles && g.p[0].m + rows1 > 64) return launch_tiles<OT, EPI, 1>(g, tiles_n, st);
+    if (tiles128 <= kSmallGridTiles) return launch_tiles<OT, EPI, 1>(g, tiles_n, st);
     return launch_tiles<OT, EPI, 2>(g, tiles_n, st);
 }
 

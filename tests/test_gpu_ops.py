@@ -397,3 +397,24 @@ def test_linear_large_tile_path(hb):
     hb.hyb_trace_enable(False)
     assert list(names) == ["gemm_mfma_256x128.epi%d.n%d.k%d" % (hb.HYB_EPI_GELU_TANH, n, k)], names
     assert torch.equal(two[:m], one) and torch.equal(two[m:], one)
+
+
+@pytest.mark.parametrize("m,n,slabs", [(1, 136, 1), (5, 1536, 2), (64, 72, 3), (65, 136, 5), (333, 264, 6), (100, 128, 7), (129, 8, 8),
+                                       (70, 200, 11), (70, 200, 12), (70, 200, 13), (1985, 1280, 3), (2048, 1288, 4), (2048, 1280, 7)])
+def test_linear_slab_buffer_counts(hb, m, n, slabs):
+    """Launches of few 64 x 128 tiles run with six or three slab buffers: fewer, as many and more k-slabs than buffers, ragged
+    rows and columns; against the oracle (bf16 products are exact in fp32, so the bound is that of fp32 sums), and the bits a
+    row gets in a launch that is large enough for the 128 x 128 tiles."""
+    k = 64 * slabs
+    a, w, b = _data(400 + slabs, (m, k), "bf16"), _data(401, (n, k), "bf16", 0.02), _data(402, (n,), "f32", 0.02)
+    da, dw, db = dev(a, torch.bfloat16), dev(w, torch.bfloat16), dev(b)
+    res = dev(_data(403, (m, n), "f32"))
+    out, out_r = (torch.empty(m, n, device="cuda", dtype=torch.float32) for _ in range(2))
+    hb.hyb_linear(da, dw, db, out)
+    hb.hyb_linear(da, dw, db, out_r, hb.HYB_EPI_GATE_RESIDUAL, residual=res)
+    y = O.linear(a, w, b)
+    assert err(host(out), y) < 1e-5 and err(host(out_r), host(res) + y) < 1e-5
+    copies = (128 * 400 // ((n + 127) // 128) + m) // m + 1
+    many = torch.empty(copies * m, n, device="cuda", dtype=torch.float32)
+    hb.hyb_linear(da.repeat(copies, 1), dw, db, many)
+    assert torch.equal(many.view(copies, m, n), out.expand(copies, m, n))
