@@ -16,6 +16,20 @@ namespace {
 // ------------------------------------------------------------------------------------------
 constexpr int kLnMaxVec = 8;   // float4 per lane -> hidden <= 8 * 64 * 4 = 2048
 
+// launch(integral_constant<float4 per lane of a row of `hidden`>)
+template <typename F> void with_vectors_per_lane(int hidden, F launch) {
+    switch ((hidden / 4 + HYB_WAVE - 1) / HYB_WAVE) {
+        case 1: launch(std::integral_constant<int, 1>{}); break;
+        case 2: launch(std::integral_constant<int, 2>{}); break;
+        case 3: launch(std::integral_constant<int, 3>{}); break;
+        case 4: launch(std::integral_constant<int, 4>{}); break;
+        case 5: launch(std::integral_constant<int, 5>{}); break;
+        case 6: launch(std::integral_constant<int, 6>{}); break;
+        case 7: launch(std::integral_constant<int, 7>{}); break;
+        default: launch(std::integral_constant<int, kLnMaxVec>{}); break;
+    }
+}
+
 // Up to two independent row sets (the image and the text stream of a joint block) share one launch:
 // workgroups [0, blocks0) serve set 0, the rest set 1.
 struct LnSet {
@@ -33,7 +47,12 @@ struct LnArgs {
     float eps;
 };
 
-template <typename OT, bool AFFINE>
+// What bounds it: all rows of a launch are resident at once (one wave each), so a launch takes as long as one wave's chain
+// of memory latencies.  The row's vectors are therefore requested together (NV = vectors per lane is a template parameter,
+// addresses past the row's end are clamped: a load under a condition is waited for inside its branch, one latency per
+// vector), and shift and scale before the reductions.  4429 rows of 1536 inside a step 11.1 -> 9.4 us, 2048 rows of 1280
+// 6.9 -> 5.3 us (2.0 -> 3.0 TB/s).
+template <typename OT, bool AFFINE, int NV>
 __global__ __launch_bounds__(256) void layernorm_kernel(LnArgs a) {
     const int wave = threadIdx.x / HYB_WAVE, lane = threadIdx.x % HYB_WAVE;
     const int blk = (int)blockIdx.x;
@@ -50,46 +69,56 @@ __global__ __launch_bounds__(256) void layernorm_kernel(LnArgs a) {
     const float eps = a.eps;
     const int nvec = hidden / 4;
     const f32x4* xr = reinterpret_cast<const f32x4*>(x + (size_t)row * hidden);
-    f32x4 r[kLnMaxVec];
+    f32x4 r[NV], sc[NV], sh[NV];
+#pragma unroll
+    for (int i = 0; i < NV; i++) r[i] = xr[min(lane + i * HYB_WAVE, nvec - 1)];
+    const size_t b = AFFINE ? 0 : (size_t)(row / tokens);
+    const f32x4* shr = reinterpret_cast<const f32x4*>(shift + b * mod_stride);
+    const f32x4* scr = reinterpret_cast<const f32x4*>(scale + b * mod_stride);
+    if (scale) {
+#pragma unroll
+        for (int i = 0; i < NV; i++) sc[i] = scr[min(lane + i * HYB_WAVE, nvec - 1)];
+    } else {
+#pragma unroll
+        for (int i = 0; i < NV; i++) sc[i] = AFFINE ? (f32x4){1.f, 1.f, 1.f, 1.f} : (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    if (shift) {
+#pragma unroll
+        for (int i = 0; i < NV; i++) sh[i] = shr[min(lane + i * HYB_WAVE, nvec - 1)];
+    } else {
+#pragma unroll
+        for (int i = 0; i < NV; i++) sh[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < kLnMaxVec; i++) {
-        const int c = lane + i * HYB_WAVE;
-        if (c < nvec) {
-            r[i] = xr[c];
-            s += (r[i][0] + r[i][1]) + (r[i][2] + r[i][3]);
-        }
+    for (int i = 0; i < NV; i++) {
+        const float t = (r[i][0] + r[i][1]) + (r[i][2] + r[i][3]);
+        if (lane + i * HYB_WAVE < nvec) s += t;
     }
     const float mean = wave_sum(s) / (float)hidden;
     float q = 0.f;
 #pragma unroll
-    for (int i = 0; i < kLnMaxVec; i++) {
-        const int c = lane + i * HYB_WAVE;
-        if (c < nvec) {
+    for (int i = 0; i < NV; i++) {
+        float t = q;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const float d = r[i][j] - mean;
-                q = fmaf(d, d, q);
-            }
+        for (int j = 0; j < 4; j++) {
+            const float d = r[i][j] - mean;
+            t = fmaf(d, d, t);
         }
+        if (lane + i * HYB_WAVE < nvec) q = t;
     }
     const float rstd = rsqrtf(wave_sum(q) / (float)hidden + eps);
-    const size_t b = (size_t)(row / tokens);
-    const f32x4* sh = shift ? reinterpret_cast<const f32x4*>(shift + (AFFINE ? 0 : b * mod_stride)) : nullptr;
-    const f32x4* sc = scale ? reinterpret_cast<const f32x4*>(scale + (AFFINE ? 0 : b * mod_stride)) : nullptr;
     OT* orow = out + (size_t)row * hidden;
 #pragma unroll
-    for (int i = 0; i < kLnMaxVec; i++) {
+    for (int i = 0; i < NV; i++) {
         const int c = lane + i * HYB_WAVE;
         if (c < nvec) {
             f32x4 y;
-            const f32x4 a = sc ? sc[c] : (f32x4){0.f, 0.f, 0.f, 0.f};
-            const f32x4 bb = sh ? sh[c] : (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < 4; j++) {
                 const float xh = (r[i][j] - mean) * rstd;
-                const float g = AFFINE ? (sc ? a[j] : 1.f) : 1.f + a[j];
-                y[j] = fmaf(xh, g, bb[j]);
+                const float g = AFFINE ? sc[i][j] : 1.f + sc[i][j];
+                y[j] = fmaf(xh, g, sh[i][j]);
             }
             if constexpr (sizeof(OT) == 4) {
                 *reinterpret_cast<f32x4*>(orow + 4 * c) = y;
@@ -322,13 +351,17 @@ namespace {
 int launch_layernorm(const LnArgs& a, int blocks, double rows, hyb_dtype out_dtype, bool affine, hipStream_t st) {
     dim3 grid(blocks), block(256);
     HybTraceScope trace("layernorm", "byte", rows * a.hidden * (4 + hyb_dtype_size(out_dtype)), st);
-    if (out_dtype == HYB_F32) {
-        if (affine) hipLaunchKernelGGL((layernorm_kernel<float, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((layernorm_kernel<float, false>), grid, block, 0, st, a);
-    } else {
-        if (affine) hipLaunchKernelGGL((layernorm_kernel<bf16_t, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((layernorm_kernel<bf16_t, false>), grid, block, 0, st, a);
-    }
+    auto launch = [&](auto nv_tag) {
+        constexpr int NV = decltype(nv_tag)::value;
+        if (out_dtype == HYB_F32) {
+            if (affine) hipLaunchKernelGGL((layernorm_kernel<float, true, NV>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((layernorm_kernel<float, false, NV>), grid, block, 0, st, a);
+        } else {
+            if (affine) hipLaunchKernelGGL((layernorm_kernel<bf16_t, true, NV>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((layernorm_kernel<bf16_t, false, NV>), grid, block, 0, st, a);
+        }
+    };
+    with_vectors_per_lane(a.hidden, launch);
     return hyb_check_launch("layernorm");
 }
 }  // namespace

@@ -418,3 +418,23 @@ def test_linear_slab_buffer_counts(hb, m, n, slabs):
     many = torch.empty(copies * m, n, device="cuda", dtype=torch.float32)
     hb.hyb_linear(da.repeat(copies, 1), dw, db, many)
     assert torch.equal(many.view(copies, m, n), out.expand(copies, m, n))
+
+
+@pytest.mark.parametrize("hidden", [4, 252, 256, 260, 512, 764, 1024, 1280, 1284, 1792, 2044, 2048])
+def test_layernorm_every_vector_count(hb, hidden):
+    """One to eight 4-element vectors per lane, whole and partial: the masked lanes of a row's last vector repeat its last elements,
+    here large ones, and must not count; the neighbouring rows are NaN.  Bounds: sums of at most 2048 terms in fp32."""
+    x = _data(430, (2, 6, hidden), "f32")
+    x[:, :, -4:] += 5.0
+    x[0, 2] = x[1, 4] = np.nan
+    mod = _data(431, (2, 2 * hidden), "f32", 0.3)
+    good = np.ones((2, 6), bool)
+    good[0, 2] = good[1, 4] = False
+    out = torch.empty(2, 6, hidden, device="cuda")
+    dmod = dev(mod)
+    hb.hyb_layernorm_modulate(dev(x), dmod, dmod[:, hidden:], 2 * hidden, out, 1e-6)
+    ref = O.modulate(O.layer_norm(x, 1e-6), mod[:, :hidden], mod[:, hidden:])
+    assert err(host(out)[good], ref[good]) < 1e-5 and np.isnan(host(out)[~good]).all()
+    hb.hyb_layernorm_affine(dev(x), dev(mod[0, :hidden]), dev(mod[1, hidden:]), out, 1e-5)
+    ref = O.layer_norm(x, 1e-5) * mod[0, :hidden] + mod[1, hidden:]
+    assert err(host(out)[good], ref[good]) < 1e-5
