@@ -545,20 +545,31 @@ int launch_epi(const GemmGroup& g, hipStream_t st) {
 // four rounds).
 constexpr int kLargeTileMinSlabs = 48;          // launches of several rounds
 constexpr int kLargeTileMinSlabsOneRound = 32;  // launches of one round (the SDXL-shaped down-projection, k = 2560)
-bool use_large_tiles(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
+// Tile height: 256 or 192 rows, whichever makes the launch shorter (rounds of tiles times the height; a CU holds one tile);
+// 192 for the gate + residual epilogue only, the one that the blocks' long-k launches have.
+// 256 against 192 rows: 2048 + 666 rows x 1536, k 6144 (136 against 180 tiles) 85 -> 75 us; 8192 x 640, k 2560 (160 against 215)
+// 47 -> 41 us; 6075 + 462 rows x 1536, k 6144 (two rounds of either) about 185 -> 147 us.
+int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     const bool f32 = out_dtype == HYB_F32;
     const bool has_form = epi == EPI_BIAS || epi == EPI_GELU_TANH || epi == EPI_SILU || (epi == EPI_GATE_RES && f32);
-    if (!has_form || g.k / BK < kLargeTileMinSlabsOneRound) return false;
-    int tiles = 0;
-    for (int i = 0; i < g.count; i++) {
-        tiles += ((g.p[i].m + 255) / 256) * ((g.n + 127) / 128);
-    }
+    const int nslab = g.k / BK;
+    if (!has_form || nslab < kLargeTileMinSlabsOneRound) return 0;
     static int cus = 0;
     if (cus == 0) {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) cus = 256;
     }
-    return 2 * tiles > cus && (tiles <= cus || g.k / BK >= kLargeTileMinSlabs);
+    long best = 0;
+    int rows = 0;
+    for (int h = 256; h >= (epi == EPI_GATE_RES ? 192 : 256); h -= 64) {
+        long tiles = 0;
+        for (int i = 0; i < g.count; i++) tiles += (long)((g.p[i].m + h - 1) / h) * ((g.n + 127) / 128);
+        const bool enough = h == 256 ? 2 * tiles > cus : 3 * tiles > 2 * cus;
+        if (!enough || (tiles > cus && nslab < kLargeTileMinSlabs)) continue;
+        const long length = (tiles + cus - 1) / cus * h;
+        if (rows == 0 || length < best) { best = length; rows = h; }
+    }
+    return rows;
 }
 
 }  // namespace
@@ -575,8 +586,8 @@ int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipSt
         if (epi == EPI_QKV && (p.heads <= 0 || g.n % (p.heads * 64) != 0 || g.n / (p.heads * 64) > 3)) return -1;
     }
     const bool f32 = out_dtype == HYB_F32;
-    if (use_large_tiles(g, out_dtype, epi)) {
-        const int rc = hyb_launch_gemm_mfma_big(g, out_dtype, epi, st);
+    if (const int rows = large_tile_rows(g, out_dtype, epi)) {
+        const int rc = hyb_launch_gemm_mfma_big(g, out_dtype, epi, rows, st);
         if (rc >= 0) return rc;
     }
     switch (epi) {

@@ -26,6 +26,9 @@
 // gate of the tile's columns are fetched in the prologue and parked in LDS; the residual of piece i + 1 is fetched
 // while piece i is staged and stored.
 //
+// Tiles of 192 x 128 (the gate + residual epilogue only) are for launches whose 256-row tiles fill their last round badly; the
+// dispatch picks the height.
+//
 // Tile order: XCD x (workgroups x, x + 8, ...) gets one run of consecutive tiles of an order that walks
 // groups of four tile rows column by column, so the tiles an XCD works on at a time share few operand
 // panels (its L2 is 4 MB).
@@ -86,7 +89,7 @@ template <typename OT, int EPI, int TMW, int TFW>
 __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles_n, int tiles0, int total, int xcd_run) {
     using G = BigGeo<TMW, TFW>;
     constexpr int BM = G::BM, BN = G::BN, STAGE_BYTES = G::STAGE_BYTES, CPW = G::CPW, NST = G::NST;
-    static_assert(TMW % 2 == 0 && TFW % 2 == 0, "wave row offsets must be multiples of 64 (swizzle)");
+    static_assert(TFW % 2 == 0, "wave feature offsets must be multiples of 64 (swizzle)");
     // One array per slab buffer: distinct objects, so the compiler knows that a copy into one buffer and a fragment read
     // from another do not alias and may interleave them freely between the MFMAs.
     __shared__ __attribute__((aligned(16))) unsigned char stage0[STAGE_BYTES], stage1[STAGE_BYTES], stage2[NST > 2 ? STAGE_BYTES : 16];
@@ -156,7 +159,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
     // slab multiplies into a constant-zero C operand (an accumulator file of 256 registers initialised through
     // vector registers would evict every long-lived address of the main loop).
     constexpr int FT = 2 * TFW, TT = 2 * TMW;      // MFMA tiles of 16 features / 16 tokens per wave
-    static_assert(TT % 2 == 0 && TT / 2 == 4, "a k-step is taken in two halves of four token tiles");
+    static_assert(TT % 2 == 0, "a k-step is taken in two halves of the token tiles");
     f32x4 acc[FT][TT];
 
     // Fragment addresses inside a stage, as in gemm_mfma.hip: lane (l16, q4) of a 16 x 16 x 32 fragment reads the 16-byte
@@ -167,10 +170,12 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
     // multiples of 64 and leave the swizzle alone).
     const int kq = (q4 >> 1) | ((q4 & 1) << 1);
     const int lb = (kq ^ (l16 & 7) ^ (l16 >> 3)) & 7;
+    // (an odd TMW puts the second wave's rows at an odd multiple of 32, which flips bit 2 of the swizzle)
+    const int lb_a = TMW % 2 ? lb ^ (4 * wt) : lb;
     int a_base[4], w_base[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) {
-        a_base[c] = (wt * 32 * TMW + l16) * ROWB + ((lb ^ (2 * c)) * 16);
+        a_base[c] = (wt * 32 * TMW + l16) * ROWB + ((lb_a ^ (2 * c)) * 16);
         w_base[c] = BM * ROWB + (wf * 32 * TFW + l16) * ROWB + ((lb ^ (2 * c)) * 16);
     }
     // A k-step of 32 is taken in two halves of four token tiles each (16 MFMAs): half-step hs = 2 ks + half of a slab
@@ -233,7 +238,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
     constexpr int PPR = WCOLS * SE / 16;                     // 16-byte pieces per staged row
     constexpr int ITERS = 32 * PPR / 64;                     // pieces per lane per 32-token piece of the wave tile
     constexpr int CHUNK_ELEMS = 16 / SE;
-    static_assert(32 * STRIDE <= (NST == 2 ? STAGE_BYTES / 2 : 12 * 1024), "a wave's staging piece must fit its part of the slab buffers");
+    static_assert(32 * STRIDE <= (NST == 2 ? STAGE_BYTES / 2 : 12 * 1024) && STAGE_BYTES >= 24 * 1024, "a wave's staging piece must fit its part of the slab buffers");
     // gate * y + residual: the residual pieces are fetched ahead (piece 0 during the last slab, piece i + 1 while
     // piece i is staged and stored), with clamped addresses; out may alias res, every element is read before the
     // same lane writes it.
@@ -282,8 +287,8 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
     // share of slab s + 1 has landed (vmcnt: only the copies of younger slabs may be outstanding) and its reads of
     // slab s are complete (lgkmcnt), so behind the barrier slab s + 1 is readable and stage s % NST can be refilled
     // with slab s + NST.
-    constexpr int CQ = CPW / 4;                                // copies per half-step in the steady state
-    static_assert(CPW % 4 == 0, "a wave's copies of a slab are spread over the four half-steps");
+    // a wave's copies of a slab are spread over the four half-steps: up to CQ1, CQ2, CQ3, CPW of them after each
+    constexpr int CQ1 = CPW / 4, CQ2 = CPW / 2, CQ3 = 3 * CPW / 4;
     auto slab_step = [&](int s, auto stage_tag, auto first_tag, bool first_quarter_only) {
         constexpr int STG = decltype(stage_tag)::value;
         constexpr bool FIRST_SLAB = decltype(first_tag)::value;
@@ -297,7 +302,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 if (s + NST < nslab) {
-                    if (first_quarter_only) issue_chunks(s + NST, STG, std::integral_constant<int, 0>{}, std::integral_constant<int, CQ>{});
+                    if (first_quarter_only) issue_chunks(s + NST, STG, std::integral_constant<int, 0>{}, std::integral_constant<int, CQ1>{});
                     else issue(s + NST, STG);
                 }
                 read_half((STG + 1) % NST, 0);
@@ -322,20 +327,20 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
     auto slab_step_mid = [&](int s, auto stage_tag) {
         constexpr int STG = decltype(stage_tag)::value;
         read_half(STG, 1);
-        issue_chunks(s + NST - 1, (STG + NST - 1) % NST, std::integral_constant<int, CQ>{}, std::integral_constant<int, 2 * CQ>{});
-        mfma_half(std::integral_constant<int, 0>{}, std::false_type{}, std::integral_constant<int, CQ>{});
+        issue_chunks(s + NST - 1, (STG + NST - 1) % NST, std::integral_constant<int, CQ1>{}, std::integral_constant<int, CQ2>{});
+        mfma_half(std::integral_constant<int, 0>{}, std::false_type{}, std::integral_constant<int, CQ2 - CQ1>{});
         read_half(STG, 2);
-        issue_chunks(s + NST - 1, (STG + NST - 1) % NST, std::integral_constant<int, 2 * CQ>{}, std::integral_constant<int, 3 * CQ>{});
-        mfma_half(std::integral_constant<int, 1>{}, std::false_type{}, std::integral_constant<int, CQ>{});
+        issue_chunks(s + NST - 1, (STG + NST - 1) % NST, std::integral_constant<int, CQ2>{}, std::integral_constant<int, CQ3>{});
+        mfma_half(std::integral_constant<int, 1>{}, std::false_type{}, std::integral_constant<int, CQ3 - CQ2>{});
         read_half(STG, 3);
-        issue_chunks(s + NST - 1, (STG + NST - 1) % NST, std::integral_constant<int, 3 * CQ>{}, std::integral_constant<int, CPW>{});
-        mfma_half(std::integral_constant<int, 2>{}, std::false_type{}, std::integral_constant<int, CQ>{});
+        issue_chunks(s + NST - 1, (STG + NST - 1) % NST, std::integral_constant<int, CQ3>{}, std::integral_constant<int, CPW>{});
+        mfma_half(std::integral_constant<int, 2>{}, std::false_type{}, std::integral_constant<int, CPW - CQ3>{});
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * CPW) : "memory");
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         read_half((STG + 1) % NST, 0);
-        issue_chunks(s + NST, STG, std::integral_constant<int, 0>{}, std::integral_constant<int, CQ>{});
-        mfma_half(std::integral_constant<int, 3>{}, std::false_type{}, std::integral_constant<int, CQ>{});
+        issue_chunks(s + NST, STG, std::integral_constant<int, 0>{}, std::integral_constant<int, CQ1>{});
+        mfma_half(std::integral_constant<int, 3>{}, std::false_type{}, std::integral_constant<int, CQ1>{});
     };
     const bool steady = 2 * NST < nslab;                    // the steady-state loop below runs at least once
     slab_step(0, std::integral_constant<int, 0>{}, std::true_type{}, steady);
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
         if constexpr (NST > 2) slab_step_mid(s + 2, std::integral_constant<int, 3 % NST>{});
     }
     // the other quarters of the slab whose first quarter the last steady step requested (stage (s + NST - 1) % NST = 0)
-    if (steady) issue_chunks(s + NST - 1, 0, std::integral_constant<int, CQ>{}, std::integral_constant<int, CPW>{});
+    if (steady) issue_chunks(s + NST - 1, 0, std::integral_constant<int, CQ1>{}, std::integral_constant<int, CPW>{});
     for (; s < nslab; s += NST) {
         slab_step(s, std::integral_constant<int, 1 % NST>{}, std::false_type{}, false);
         if (s + 1 < nslab) slab_step(s + 1, std::integral_constant<int, 2 % NST>{}, std::false_type{}, false);
@@ -358,10 +363,10 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
     // ---- epilogue: per wave, registers -> its own LDS staging piece -> row-contiguous global stores --------
     // Register i of tile (fi, ti): feature = wf*WCOLS + fi*16 + 4 q4 + i, token = wt*32*TMW + ti*16 + l16; piece tm of 32
     // tokens is the pair of token tiles 2 tm, 2 tm + 1.
-    // staging area of wave w: with two slab buffers half a buffer each, with three the first 36 KB of buffers 0, 1, 2 and
-    // the remaining 12 KB of buffer 0
+    // staging area of wave w: with two slab buffers half a buffer each, with three the start of buffers 0, 1, 2 and
+    // the last 12 KB of buffer 0
     unsigned char* stg = NST == 2 ? stage_base(wave & 1) + (wave >> 1) * (STAGE_BYTES / 2)
-                                  : (wave < 3 ? stage_base(wave) : stage0 + 36 * 1024);
+                                  : (wave < 3 ? stage_base(wave) : stage0 + STAGE_BYTES - 12 * 1024);
     [[maybe_unused]] const float* gate_ptr = p.gate;
     [[maybe_unused]] const int gate_rows = p.rows_per_gate;
     [[maybe_unused]] const size_t gate_stride = p.gate_stride;
@@ -460,14 +465,15 @@ int launch_big(const GemmGroup& g, hipStream_t st) {
 
 }  // namespace
 
-// Large-tile launch (256 x 128 tiles) of a group of up to two problems.  Epilogues: bias, GELU-tanh, SiLU (either output
-// type), gate * y + residual(s) (fp32 output).  Returns -1 when the shape or the epilogue has no large-tile
-// form.  The caller has validated the group as for hyb_launch_gemm_mfma.
-int hyb_launch_gemm_mfma_big(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st) {
+// Large-tile launch (tiles of `rows` tokens x 128 features, 256, or 192 with the gate + residual epilogue) of a group of up to two
+// problems.  Epilogues: bias, GELU-tanh, SiLU (either output type), gate * y + residual(s) (fp32 output).  Returns -1 when the
+// shape or the epilogue has no large-tile form.  The caller has validated the group as for hyb_launch_gemm_mfma.
+int hyb_launch_gemm_mfma_big(const GemmGroup& g, hyb_dtype out_dtype, int epi, int rows, hipStream_t st) {
     if (g.k <= 0 || g.k % BK != 0 || g.n % 8 != 0 || g.n < 8) return -1;
     if ((size_t)g.k * 2 * 256 >= ((size_t)1 << 31)) return -1;    // per-lane byte offsets inside a tile's operand rows are 32-bit
     if (g.k / BK < 3) return -1;                                  // the prologue requests the first three slabs
     const bool f32 = out_dtype == HYB_F32;
+    if (rows == 192) return epi == EPI_GATE_RES && f32 ? launch_big<float, EPI_GATE_RES, 3, 2>(g, st) : -1;
     switch (epi) {
         case EPI_BIAS: return f32 ? launch_big<float, EPI_BIAS, 4, 2>(g, st) : launch_big<bf16_t, EPI_BIAS, 4, 2>(g, st);
         case EPI_GELU_TANH: return f32 ? launch_big<float, EPI_GELU_TANH, 4, 2>(g, st) : launch_big<bf16_t, EPI_GELU_TANH, 4, 2>(g, st);

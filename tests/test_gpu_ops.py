@@ -438,3 +438,30 @@ def test_layernorm_every_vector_count(hb, hidden):
     hb.hyb_layernorm_affine(dev(x), dev(mod[0, :hidden]), dev(mod[1, hidden:]), out, 1e-5)
     ref = O.layer_norm(x, 1e-5) * mod[0, :hidden] + mod[1, hidden:]
     assert err(host(out)[good], ref[good]) < 1e-5
+
+
+@pytest.mark.parametrize("m,n,slabs", [(2714, 1544, 32), (2881, 1536, 33), (2689, 1536, 34), (8192, 640, 38), (6400, 1536, 48)])
+def test_linear_192_row_tiles(hb, m, n, slabs):
+    """Gate + residual launches take 192-row tiles where that makes the launch shorter: ragged rows and columns, gate rows that change
+    inside a tile, the pipeline's remainders, several rounds; against the oracle (bf16 products are exact in fp32: the
+    bound of fp32 sums), and the first rows alone get the same bits from the small tiles."""
+    k = 64 * slabs
+    a, w, b = _data(420 + slabs, (m, k), "bf16"), _data(421, (n, k), "bf16", 0.02), _data(422, (n,), "f32", 0.02)
+    res, gate = _data(423, (m, n), "f32"), _data(424, (m // 1500 + 1, n), "f32")
+    da, dw, db, dr = dev(a, torch.bfloat16), dev(w, torch.bfloat16), dev(b), dev(res)
+    kw = dict(gate=dev(gate), rows_per_gate=1500, gate_stride=n)
+    out, small = torch.empty(m, n, device="cuda"), torch.empty(100, n, device="cuda")
+    hb.hyb_trace_enable(True)
+    hb.hyb_linear(da, dw, db, out, hb.HYB_EPI_GATE_RESIDUAL, residual=dr, **kw)
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert list(names) == ["gemm_mfma_192x128.epi%d.n%d.k%d" % (hb.HYB_EPI_GATE_RESIDUAL, n, k)], names
+    rows = np.unique(np.concatenate([np.arange(0, m, 97), np.arange(m - 70, m), np.arange(1490, 1510)]))
+    ref = res[rows] + gate[rows // 1500] * O.linear(a[rows], w, b)
+    assert err(host(out)[rows], ref) < 1e-5
+    hb.hyb_linear(da[:100], dw, db, small, hb.HYB_EPI_GATE_RESIDUAL, residual=dr[:100], **kw)
+    assert torch.equal(out[:100], small)
+    x = dr.clone()   # in place, as in a block
+    hb.hyb_linear(da, dw, db, x, hb.HYB_EPI_GATE_RESIDUAL, residual=x, **kw)
+    assert torch.equal(x, out)
