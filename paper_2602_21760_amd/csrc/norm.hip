@@ -202,8 +202,7 @@ __global__ __launch_bounds__(256) void adaln_kernel(const WT* __restrict__ w, co
 // that a launch has thousands of workgroups with all their loads in flight at once:
 //  1. each workgroup sums x and x^2 over its chunk of tokens (fp32 per thread, then the threads of a
 //     group are added in a fixed order in fp64) -> partial[b][chunk][group][2];
-//  2. one workgroup per sample adds the partials (fp64; a few interleaved partial sums per group, each in
-//     chunk order, then those in lane order) and forms mean and 1/std per group;
+//  2. one workgroup per sample and group adds the partials (fp64, in a fixed order) and forms mean and 1/std;
 //  3. each workgroup normalises its chunk: y = (x - mean) rstd gamma + beta.
 // No atomics: the result is deterministic and independent of the batch index.
 // ------------------------------------------------------------------------------------------
@@ -247,34 +246,34 @@ __global__ void groupnorm_stats_kernel(const float* __restrict__ x, double* __re
     }
 }
 
-// One workgroup per sample, `lanes` threads per group, thread = j * groups + g so that the threads of a wave
-// read consecutive (sum, sum of squares) pairs: thread (g, j) adds the partials of chunks j, j + lanes, ... in
-// that order (fp64), thread (g, 0) then adds the `lanes` sums in lane order and leaves (mean, 1/std) as two
-// floats per group.  blockDim.x = groups * lanes.
-__global__ void groupnorm_finalize_kernel(const double* __restrict__ partial, float* __restrict__ stats, int nchunks,
-                                          int groups, int lanes, double count, float eps) {
+// One workgroup per (group, sample): thread j adds the partials of chunks j, j + 256, ... in that order (fp64), the waves add
+// their lanes by halving and thread 0 the four waves in order; it leaves (mean, 1/std) as two floats.  One workgroup per
+// sample, which read all 512 KB of a sample's partials by itself, took 7.3 us at 2 x 4096 tokens where this takes 4.6 (4.6 us
+// either way at 2 x 1024).
+__global__ __launch_bounds__(256) void groupnorm_finalize_kernel(const double* __restrict__ partial, float* __restrict__ stats, int nchunks,
+                                                                 int groups, double count, float eps) {
     typedef double f64x2 __attribute__((ext_vector_type(2)));
-    extern __shared__ double gn_fin[];   // [lanes][groups][2]
-    const int g = threadIdx.x % groups, j = threadIdx.x / groups, b = blockIdx.x;
+    constexpr int kLoads = (kGnChunks + 255) / 256;
+    __shared__ double red[4][2];
+    const int g = blockIdx.x, b = blockIdx.y, j = threadIdx.x;
     const f64x2* p = reinterpret_cast<const f64x2*>(partial) + (size_t)b * nchunks * groups + g;
+    f64x2 v[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; u++) v[u] = p[(size_t)min(j + 256 * u, nchunks - 1) * groups];   // clamped: in bounds
     double ds = 0.0, dq = 0.0;
-    for (int c0 = j; c0 < nchunks; c0 += 8 * lanes) {     // eight loads in flight, added in chunk order
-        f64x2 v[8];
 #pragma unroll
-        for (int u = 0; u < 8; u++) v[u] = p[(size_t)min(c0 + u * lanes, nchunks - 1) * groups];   // clamped: in bounds
-#pragma unroll
-        for (int u = 0; u < 8; u++)
-            if (c0 + u * lanes < nchunks) { ds += v[u][0]; dq += v[u][1]; }
+    for (int u = 0; u < kLoads; u++)
+        if (j + 256 * u < nchunks) { ds += v[u][0]; dq += v[u][1]; }
+    ds = wave_sum(ds);
+    dq = wave_sum(dq);
+    if (j % HYB_WAVE == 0) {
+        red[j / HYB_WAVE][0] = ds;
+        red[j / HYB_WAVE][1] = dq;
     }
-    gn_fin[(j * groups + g) * 2] = ds;
-    gn_fin[(j * groups + g) * 2 + 1] = dq;
     __syncthreads();
     if (j != 0) return;
-    ds = 0.0; dq = 0.0;
-    for (int i = 0; i < lanes; i++) {
-        ds += gn_fin[(i * groups + g) * 2];
-        dq += gn_fin[(i * groups + g) * 2 + 1];
-    }
+    ds = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
+    dq = (red[0][1] + red[1][1]) + (red[2][1] + red[3][1]);
     const double mean_d = ds / count;
     const double var_d = fmax(dq / count - mean_d * mean_d, 0.0);
     stats[((size_t)b * groups + g) * 2] = (float)mean_d;
@@ -304,6 +303,84 @@ __global__ void groupnorm_apply_kernel(const float* __restrict__ x, const float*
 #pragma unroll
                 for (int e = 0; e < 4; e++) y[e] = fmaf((v[j][e] - mean) * rstd, gm[e], bt[e]);
                 ob[(size_t)(t + j) * nvec + vec] = y;
+            }
+        }
+    }
+}
+
+// The apply pass and the affine LayerNorm that follows it in a transformer stage, in one: a wave owns a row, writes
+// g = GroupNorm(x) and, from the registers, LayerNorm(g).  Bound by memory latency like the LayerNorm (all loads requested
+// together, addresses past the row's end clamped); against the two passes it saves one read of g and a launch: 2 x 4096 tokens of
+// 640 channels 6.7 + 7.1 -> 11.0 us, 2 x 1024 of 1280 5.9 + 5.3 -> 7.1 us.
+// Same operations in the same order as the two kernels, so the same bits.
+template <typename OT, int NV>
+__global__ __launch_bounds__(256) void groupnorm_apply_ln_kernel(const float* __restrict__ x, const float* __restrict__ stats,
+                                                                 const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                                 const float* __restrict__ ln_g, const float* __restrict__ ln_b,
+                                                                 float* __restrict__ out, OT* __restrict__ ln_out, int rows, int tokens,
+                                                                 int channels, int groups, float ln_eps) {
+    const int wave = threadIdx.x / HYB_WAVE, lane = threadIdx.x % HYB_WAVE;
+    const int row = blockIdx.x * 4 + wave;
+    if (row >= rows) return;
+    const int nvec = channels / 4, vpg = nvec / groups;
+    const f32x4* xr = reinterpret_cast<const f32x4*>(x + (size_t)row * channels);
+    const float2* st = reinterpret_cast<const float2*>(stats) + (size_t)(row / tokens) * groups;   // (mean, 1/std) per group
+    f32x4 r[NV], gm[NV], bt[NV];
+    float2 gs[NV];
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        const int c = min(lane + i * HYB_WAVE, nvec - 1);
+        r[i] = xr[c];
+        gs[i] = st[c / vpg];
+        gm[i] = reinterpret_cast<const f32x4*>(gamma)[c];
+        bt[i] = reinterpret_cast<const f32x4*>(beta)[c];
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) r[i][e] = fmaf((r[i][e] - gs[i].x) * gs[i].y, gm[i][e], bt[i][e]);
+        const float t = (r[i][0] + r[i][1]) + (r[i][2] + r[i][3]);
+        if (lane + i * HYB_WAVE < nvec) s += t;
+    }
+#pragma unroll
+    for (int i = 0; i < NV; i++) {   // the affine LayerNorm's vectors, in flight across the reductions
+        const int c = min(lane + i * HYB_WAVE, nvec - 1);
+        gm[i] = reinterpret_cast<const f32x4*>(ln_g)[c];
+        bt[i] = reinterpret_cast<const f32x4*>(ln_b)[c];
+    }
+    f32x4* gr = reinterpret_cast<f32x4*>(out + (size_t)row * channels);
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        const int c = lane + i * HYB_WAVE;
+        if (c < nvec) gr[c] = r[i];
+    }
+    const float mean = wave_sum(s) / (float)channels;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        float t = q;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const float d = r[i][j] - mean;
+            t = fmaf(d, d, t);
+        }
+        if (lane + i * HYB_WAVE < nvec) q = t;
+    }
+    const float rstd = rsqrtf(wave_sum(q) / (float)channels + ln_eps);
+    OT* orow = ln_out + (size_t)row * channels;
+#pragma unroll
+    for (int i = 0; i < NV; i++) {
+        const int c = lane + i * HYB_WAVE;
+        if (c < nvec) {
+            f32x4 y;
+#pragma unroll
+            for (int j = 0; j < 4; j++) y[j] = fmaf((r[i][j] - mean) * rstd, gm[i][j], bt[i][j]);
+            if constexpr (sizeof(OT) == 4) {
+                *reinterpret_cast<f32x4*>(orow + 4 * c) = y;
+            } else {
+                bf16x4 o = {(bf16_t)y[0], (bf16_t)y[1], (bf16_t)y[2], (bf16_t)y[3]};
+                *reinterpret_cast<bf16x4*>(orow + 4 * c) = o;
             }
         }
     }
@@ -406,10 +483,9 @@ size_t hyb_groupnorm_scratch_bytes(int batch, int groups) {
     return gn_partial_bytes(batch, groups) + hyb_align_up((size_t)batch * groups * 2 * sizeof(float), 256);
 }
 
-// channels % (4 * groups) == 0 and channels <= 4096 (one thread per 4-channel vector, <= 1024 threads).
-int hyb_launch_groupnorm(const float* x, const float* gamma, const float* beta, float* out, int batch, int tokens,
-                         int channels, int groups, float eps, void* scratch, hipStream_t st) {
-    if (batch == 0 || tokens == 0) return HYB_OK;
+// Mean and 1/std of every (sample, group), left in the scratch; channels % (4 * groups) == 0 and channels <= 4096 (one thread
+// per 4-channel vector, <= 1024 threads).
+static int launch_groupnorm_stats(const float* x, int batch, int tokens, int channels, int groups, float eps, void* scratch, hipStream_t st) {
     HYB_REQUIRE(channels % (4 * groups) == 0 && channels <= 4096 && groups <= channels / 4, HYB_ERR_SHAPE,
                 "groupnorm: channels %d must be a multiple of 4 * groups (%d) and at most 4096", channels, groups);
     const int nvec = channels / 4;
@@ -417,16 +493,48 @@ int hyb_launch_groupnorm(const float* x, const float* gamma, const float* beta, 
     const int nchunks = want < kGnChunks ? want : kGnChunks;
     const int tpc = (tokens + nchunks - 1) / nchunks;
     const int used = (tokens + tpc - 1) / tpc;     // chunks that actually hold tokens (<= kGnChunks)
-    dim3 grid(used, batch), block(nvec);
-    HybTraceScope trace("groupnorm", "byte", (double)batch * tokens * channels * 12, st);
-    hipLaunchKernelGGL(groupnorm_stats_kernel, grid, block, nvec * 2 * sizeof(float), st, x, (double*)scratch, tokens, channels, groups, tpc);
+    hipLaunchKernelGGL(groupnorm_stats_kernel, dim3(used, batch), dim3(nvec), nvec * 2 * sizeof(float), st, x, (double*)scratch, tokens, channels, groups, tpc);
     float* stats = reinterpret_cast<float*>(static_cast<char*>(scratch) + gn_partial_bytes(batch, groups));
-    int lanes = 32;                                   // groups * lanes <= 1024 threads
-    while (groups * lanes > 1024) lanes /= 2;
-    hipLaunchKernelGGL(groupnorm_finalize_kernel, dim3(batch), dim3(groups * lanes), groups * lanes * 2 * sizeof(double), st,
-                       (const double*)scratch, stats, used, groups, lanes, (double)tokens * (channels / groups), eps);
-    hipLaunchKernelGGL(groupnorm_apply_kernel, grid, block, 0, st, x, (const float*)stats, gamma, beta, out, tokens, channels, groups, tpc);
+    hipLaunchKernelGGL(groupnorm_finalize_kernel, dim3(groups, batch), dim3(256), 0, st, (const double*)scratch, stats, used, groups,
+                       (double)tokens * (channels / groups), eps);
     return hyb_check_launch("groupnorm");
+}
+
+int hyb_launch_groupnorm(const float* x, const float* gamma, const float* beta, float* out, int batch, int tokens,
+                         int channels, int groups, float eps, void* scratch, hipStream_t st) {
+    if (batch == 0 || tokens == 0) return HYB_OK;
+    HybTraceScope trace("groupnorm", "byte", (double)batch * tokens * channels * 12, st);
+    const int rc = launch_groupnorm_stats(x, batch, tokens, channels, groups, eps, scratch, st);
+    if (rc) return rc;
+    const float* stats = reinterpret_cast<const float*>(static_cast<char*>(scratch) + gn_partial_bytes(batch, groups));
+    const int chunks = (tokens + kGnTokens - 1) / kGnTokens, used = chunks < kGnChunks ? chunks : kGnChunks;
+    const int tpc = (tokens + used - 1) / used;
+    hipLaunchKernelGGL(groupnorm_apply_kernel, dim3((tokens + tpc - 1) / tpc, batch), dim3(channels / 4), 0, st, x, stats, gamma, beta, out,
+                       tokens, channels, groups, tpc);
+    return hyb_check_launch("groupnorm");
+}
+
+// out = GroupNorm(x) and ln_out = LayerNorm(out) (gain and bias per channel); channels <= 2048, otherwise as above.
+int hyb_launch_groupnorm_layernorm(const float* x, const float* gamma, const float* beta, float* out, const float* ln_g, const float* ln_b,
+                                   void* ln_out, int batch, int tokens, int channels, int groups, float eps, float ln_eps, hyb_dtype ln_dtype,
+                                   void* scratch, hipStream_t st) {
+    if (batch == 0 || tokens == 0) return HYB_OK;
+    const int rows = batch * tokens;
+    HybTraceScope trace("groupnorm_layernorm", "byte", (double)rows * channels * (12 + hyb_dtype_size(ln_dtype)), st);
+    const int rc = launch_groupnorm_stats(x, batch, tokens, channels, groups, eps, scratch, st);
+    if (rc) return rc;
+    const float* stats = reinterpret_cast<const float*>(static_cast<char*>(scratch) + gn_partial_bytes(batch, groups));
+    const dim3 grid((rows + 3) / 4), block(256);
+    with_vectors_per_lane(channels, [&](auto nv_tag) {
+        constexpr int NV = decltype(nv_tag)::value;
+        if (ln_dtype == HYB_F32)
+            hipLaunchKernelGGL((groupnorm_apply_ln_kernel<float, NV>), grid, block, 0, st, x, stats, gamma, beta, ln_g, ln_b, out,
+                               static_cast<float*>(ln_out), rows, tokens, channels, groups, ln_eps);
+        else
+            hipLaunchKernelGGL((groupnorm_apply_ln_kernel<bf16_t, NV>), grid, block, 0, st, x, stats, gamma, beta, ln_g, ln_b, out,
+                               static_cast<bf16_t*>(ln_out), rows, tokens, channels, groups, ln_eps);
+    });
+    return hyb_check_launch("groupnorm_layernorm");
 }
 
 extern "C" int hyb_layernorm_modulate(const float* x, const float* shift, const float* scale, size_t mod_stride,

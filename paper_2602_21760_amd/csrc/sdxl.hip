@@ -2,7 +2,7 @@
 // stage is the second workload shape of the guidance-branch forward, Sec. 4.1 / Sec. 5 setup):
 //   g = GroupNorm32(x);  a = g + SelfAttn(LN(g));  b = a + CrossAttn(LN(a), ctx);
 //   out = x + b + W2 (u * GELUerf(gate)) + b2,  [u, gate] = LN(b) W1^T + b1
-// Thirteen launches: GroupNorm, LN, fused QKV GEMM (head-major scatter), self-attention, out-projection
+// Fourteen launches: GroupNorm statistics (two), GroupNorm + LN, fused QKV GEMM (head-major scatter), self-attention, out-projection
 // (+ residual), LN, Q GEMM, K/V GEMM on the text context, cross-attention, out-projection (+ residual),
 // LN, GEGLU GEMM, down-projection (+ both residuals).
 #include "attention.h"
@@ -12,6 +12,9 @@ int hyb_launch_layernorm(const float* x, const float* shift, const float* scale,
                          int batch, int tokens, int hidden, float eps, hyb_dtype out_dtype, bool affine, hipStream_t st);
 int hyb_launch_groupnorm(const float* x, const float* gamma, const float* beta, float* out, int batch, int tokens,
                          int channels, int groups, float eps, void* scratch, hipStream_t st);
+int hyb_launch_groupnorm_layernorm(const float* x, const float* gamma, const float* beta, float* out, const float* ln_g, const float* ln_b,
+                                   void* ln_out, int batch, int tokens, int channels, int groups, float eps, float ln_eps, hyb_dtype ln_dtype,
+                                   void* scratch, hipStream_t st);
 size_t hyb_groupnorm_scratch_bytes(int batch, int groups);
 
 namespace {
@@ -106,10 +109,10 @@ extern "C" int hyb_sdxl_block_forward(const hyb_sdxl_block_desc* desc, const hyb
         return hyb_launch_attention(a, dt, st);
     };
 
-    // g = GroupNorm(x): the residual stream of the block
-    if ((rc = hyb_launch_groupnorm(x_in, w->gn_g, w->gn_b, g, B, T, C, d.groups, d.gn_eps, ws + L.gn, st))) return rc;
+    // g = GroupNorm(x): the residual stream of the block; h = LN(g) in the same pass
+    if ((rc = hyb_launch_groupnorm_layernorm(x_in, w->gn_g, w->gn_b, g, w->ln1_g, w->ln1_b, h, B, T, C, d.groups, d.gn_eps, d.ln_eps, dt,
+                                             ws + L.gn, st))) return rc;
     // self-attention: a = g + (softmax(q k^T / 8) v) Wo^T + bo   (in place on g)
-    if ((rc = hyb_launch_layernorm(g, w->ln1_b, w->ln1_g, 0, h, B, T, C, d.ln_eps, dt, true, st))) return rc;
     {
         GemmGroup gg = one(M, 3 * C, C);
         GemmProblem& p = gg.p[0];

@@ -71,6 +71,17 @@ def test_sdxl_block_reduced(hb, dt):
     assert err(got - x, ref - x) < (3e-2 if dt == "bf16" else 1e-3)
 
 
+@pytest.mark.parametrize("dt,heads,n_ctx,ctx_dim", [("bf16", 2, 1, 64), ("bf16", 6, 77, 192), ("bf16", 14, 154, 96), ("bf16", 32, 77, 256),
+                                                   ("f32", 2, 3, 64), ("f32", 6, 77, 192)])
+def test_sdxl_block_widths_and_contexts(hb, dt, heads, n_ctx, ctx_dim):
+    """GroupNorm + LayerNorm in one pass over half a vector per lane up to eight; the context's keys and values in one launch with
+    the queries (context width a multiple of 64) and apart from them."""
+    cfg = synth.SDXLStageConfig("t", blocks=1, tokens=37, channels=64 * heads, heads=heads, n_ctx=n_ctx, ctx_dim=ctx_dim, batch=2, dtype=dt)
+    got, ref, x = _stage_case(cfg, 1, scale_w=2.0)
+    assert err(got, ref) < tol(dt)
+    assert err(got - x, ref - x) < (3e-2 if dt == "bf16" else 1e-3)
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("stage", ["A", "B"])
 def test_sdxl_stage_real_shapes_one_block(hb, stage):
