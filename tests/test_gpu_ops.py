@@ -465,3 +465,18 @@ def test_linear_192_row_tiles(hb, m, n, slabs):
     x = dr.clone()   # in place, as in a block
     hb.hyb_linear(da, dw, db, x, hb.HYB_EPI_GATE_RESIDUAL, residual=x, **kw)
     assert torch.equal(x, out)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,hidden,batch", [(1, 8, 1), (3, 504, 2), (37, 520, 3), (32769, 64, 4), (70003, 1032, 5), (130, 4096, 4)])
+def test_adaln_modulation_row_groups(hb, dt, rows, hidden, batch):
+    """One group of four rows per wave and several, partial groups, partial 512-column chunks, one to four samples per launch; NaN
+    behind the last column must not be read into a sum."""
+    w, b = _data(440, (rows, hidden), dt, 0.05), _data(441, (rows,), "f32")
+    temb = _data(442, (batch, hidden), "f32")
+    buf = torch.full((rows * hidden + 4096,), float("nan"), device="cuda", dtype=tdt(dt))
+    dw = buf[:rows * hidden].view(rows, hidden)
+    dw.copy_(dev(w, tdt(dt)))
+    out = torch.full((batch, rows), float("nan"), device="cuda")
+    hb.hyb_adaln_modulation(dw, dev(b), dev(temb), out)
+    assert err(host(out), O.linear(O.silu(temb), w, b)) < 1e-5
