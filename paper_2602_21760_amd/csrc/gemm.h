@@ -40,6 +40,7 @@ struct GemmGroup {
     GemmProblem p[kMaxGroup];
     int count;
     int n, k;
+    int n2, k2;          // of the second problem where they differ from the first's (bf16 EPI_QKV launches only); 0: the same
     // Scratch for the MFMA path's k split (single problem, few tiles, long k: see gemm_mfma.hip), or nullptr.
     void* splitk_ws;
     size_t splitk_bytes;

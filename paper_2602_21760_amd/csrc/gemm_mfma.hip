@@ -75,6 +75,7 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned byt
 
 template <typename OT, int EPI, int TMW, int NST>
 __global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_kernel(GemmGroup g, int tiles_n, int tiles0, int total, int xcd_run, int ksplit) {
+    constexpr bool MIXED = EPI == EPI_QKV;   // the two problems may differ in (n, k)
     constexpr int BM = Geo<TMW>::BM, STAGE_BYTES = Geo<TMW>::STAGE_BYTES, CPW = Geo<TMW>::CPW;
     __shared__ __attribute__((aligned(16))) unsigned char smem[Geo<TMW, NST>::SMEM_BYTES + VEC_BYTES];
 
@@ -97,10 +98,11 @@ __global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_ker
     const int pi = tile >= tiles0 ? 1 : 0;
     if (pi) tile -= tiles0;
     const GemmProblem& p = g.p[pi];
+    if (MIXED && pi && g.n2) tiles_n = (g.n2 + BN - 1) / BN;
     const int row0 = (tile / tiles_n) * BM;
     // EPI_GEGLU: a tile covers 64 output features; its 128 weight rows are 64 "u" rows and the 64 "gate" rows n above
     const int col0 = (tile % tiles_n) * (EPI == EPI_GEGLU ? BN / 2 : BN);
-    const int m = p.m, n = g.n, k = g.k;
+    const int m = p.m, n = MIXED && pi && g.n2 ? g.n2 : g.n, k = MIXED && pi && g.n2 ? g.k2 : g.k;
     const bf16_t* A = static_cast<const bf16_t*>(p.a);
     const bf16_t* W = static_cast<const bf16_t*>(p.w);
 
@@ -424,7 +426,8 @@ __global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_ker
 // A launch of 64-row tiles that leaves room on the CUs is bound by the latency of its slab copies, one after the other: it
 // takes more slab buffers, six when every workgroup can have a CU of its own (256 tiles), three for up to two per CU.
 // Two against six: 333 x 1536 x 4096 49 -> 26 us, one row x 1536 x 1536 24 -> 13 us; two against three: 2048 x 1280 x 1280
-// with residual 20 -> 18 us.  Up to two k-slabs have nothing to run ahead of.
+// with residual 21 -> 18 us.  Up to two k-slabs have nothing to run ahead of.  A launch of two problems of different shapes takes at
+// least three: its long tiles decide how long it lasts (8192 x 640, k 640, beside 154 x 1280, k 2048: 31 -> 27 us).
 constexpr int kDeepTiles = 256;
 
 // Up to this many tile columns a launch hands each XCD a run of consecutive tiles (see the kernel).
@@ -436,19 +439,19 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
     GemmGroup gg = g;
     // The smaller problem goes first: its tiles fetch a whole weight matrix from HBM for few rows, which is better
     // hidden under the start of the large problem than left for the end of the launch.
-    if (gg.count > 1 && gg.p[1].m < gg.p[0].m) {
+    if (gg.count > 1 && !gg.n2 && gg.p[1].m < gg.p[0].m) {
         const GemmProblem t = gg.p[0];
         gg.p[0] = gg.p[1];
         gg.p[1] = t;
     }
     const int tiles0 = ((gg.p[0].m + BM - 1) / BM) * tiles_n;
-    const int tiles1 = gg.count > 1 ? ((gg.p[1].m + BM - 1) / BM) * tiles_n : 0;
+    const int tiles1 = gg.count > 1 ? ((gg.p[1].m + BM - 1) / BM) * (gg.n2 ? (gg.n2 + BN - 1) / BN : tiles_n) : 0;
     char name[96];
     snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", BM, BN, EPI, g.n, g.k);
-    double rows = g.p[0].m + (g.count > 1 ? g.p[1].m : 0);
-    HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k, st);
+    const double flop0 = 2.0 * g.p[0].m * g.n * g.k, flop1 = g.count > 1 ? 2.0 * g.p[1].m * (g.n2 ? g.n2 : g.n) * (g.n2 ? g.k2 : g.k) : 0;
+    HybTraceScope trace(name, "flop", flop0 + flop1, st);
     int t0 = tiles0;
-    if (tiles0 == 0) {  // keep problem 0 non-empty so that the tile -> problem split stays simple
+    if (tiles0 == 0 && !gg.n2) {  // keep problem 0 non-empty so that the tile -> problem split stays simple
         gg.p[0] = gg.p[1];
         gg.count = 1;
         t0 = tiles1;
@@ -459,7 +462,7 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
     if constexpr (TMW == 1) {
         const int nslab = g.k / BK / ksplit;
         if (total <= kDeepTiles && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 6>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
-        else if (total <= 2 * kDeepTiles && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 3>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+        else if ((total <= 2 * kDeepTiles || gg.n2) && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 3>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
         else hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 2>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
     } else {
         hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, TMW, 2>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
@@ -506,7 +509,7 @@ int launch_epi(const GemmGroup& g, hipStream_t st) {
     const int tile_cols = EPI == EPI_GEGLU ? BN / 2 : BN;
     const int tiles_n = (g.n + tile_cols - 1) / tile_cols;
     const int rows1 = g.count > 1 ? g.p[1].m : 0;
-    const int tiles128 = ((g.p[0].m + 127) / 128 + (rows1 + 127) / 128) * tiles_n;
+    const int tiles128 = (g.p[0].m + 127) / 128 * tiles_n + (rows1 + 127) / 128 * (g.n2 ? (g.n2 + BN - 1) / BN : tiles_n);
     if (tiles128 == 0) return HYB_OK;
     if constexpr (EPI != EPI_GEGLU) {
         // 128-row tiles stream a third fewer operand bytes: preferred whenever they allow a split at all
@@ -580,10 +583,12 @@ int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipSt
     // gated epilogue the gate rows n rows further down
     if ((size_t)g.k * 2 * 256 >= ((size_t)1 << 31)) return -1;
     if (epi == EPI_GEGLU && ((size_t)g.n + 128) * g.k * 2 >= ((size_t)1 << 31)) return -1;
+    if (g.n2 && (epi != EPI_QKV || g.k2 <= 0 || g.k2 % BK != 0 || g.n2 % 8 != 0 || (size_t)g.k2 * 2 * 256 >= ((size_t)1 << 31))) return -1;
     for (int i = 0; i < g.count; i++) {
         const GemmProblem& p = g.p[i];
         if (epi == EPI_GATE_RES && p.gate && (p.gate_stride % 4 != 0)) return -1;
-        if (epi == EPI_QKV && (p.heads <= 0 || g.n % (p.heads * 64) != 0 || g.n / (p.heads * 64) > 3)) return -1;
+        const int n = i == 1 && g.n2 ? g.n2 : g.n;
+        if (epi == EPI_QKV && (p.heads <= 0 || n % (p.heads * 64) != 0 || n / (p.heads * 64) > 3)) return -1;
     }
     const bool f32 = out_dtype == HYB_F32;
     if (const int rows = large_tile_rows(g, out_dtype, epi)) {

@@ -95,6 +95,7 @@ int hyb_launch_gemm_simple(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out
 int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st) {
     const int rc = in_dtype == HYB_BF16 ? hyb_launch_gemm_mfma(g, out_dtype, epi, st) : hyb_launch_gemm_f32_mfma(g, out_dtype, epi, st);
     if (rc >= 0) return rc;
+    HYB_REQUIRE(g.n2 == 0, HYB_ERR_SHAPE, "gemm: no kernel takes this pair of problems of different shapes");
     return hyb_launch_gemm_simple(g, in_dtype, out_dtype, epi, st);
 }
 

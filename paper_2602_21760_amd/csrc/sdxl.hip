@@ -2,9 +2,9 @@
 // stage is the second workload shape of the guidance-branch forward, Sec. 4.1 / Sec. 5 setup):
 //   g = GroupNorm32(x);  a = g + SelfAttn(LN(g));  b = a + CrossAttn(LN(a), ctx);
 //   out = x + b + W2 (u * GELUerf(gate)) + b2,  [u, gate] = LN(b) W1^T + b1
-// Fourteen launches: GroupNorm statistics (two), GroupNorm + LN, fused QKV GEMM (head-major scatter), self-attention, out-projection
-// (+ residual), LN, Q GEMM, K/V GEMM on the text context, cross-attention, out-projection (+ residual),
-// LN, GEGLU GEMM, down-projection (+ both residuals).
+// Thirteen launches: GroupNorm statistics (two), GroupNorm + LN, fused QKV GEMM (head-major scatter), self-attention, out-projection
+// (+ residual), LN, Q GEMM together with the K/V GEMM on the text context, cross-attention, out-projection (+ residual),
+// LN, GEGLU GEMM, down-projection (+ both residuals; a k split adds its merge).
 #include "attention.h"
 #include "gemm.h"
 
@@ -131,19 +131,24 @@ extern "C" int hyb_sdxl_block_forward(const hyb_sdxl_block_desc* desc, const hyb
     // cross-attention to the text context: b = a + (softmax(q kc^T / 8) vc) Wo2^T + bo2
     if ((rc = hyb_launch_layernorm(g, w->ln2_b, w->ln2_g, 0, h, B, T, C, d.ln_eps, dt, true, st))) return rc;
     {
-        GemmGroup gg = one(M, C, C);
-        GemmProblem& p = gg.p[0];
-        p.a = h; p.w = w->w_q2; p.q = ws + L.q;
-        p.tokens = T; p.tok_offset = 0; p.n_total = T; p.heads = d.heads;
-        if (dt == HYB_BF16) p.q_scale = kQScale;
-        if ((rc = hyb_launch_gemm(gg, dt, dt, EPI_QKV, st))) return rc;
-    }
-    {
-        GemmGroup gg = one(B * S, 2 * C, d.ctx_dim);
-        GemmProblem& p = gg.p[0];
-        p.a = ctx; p.w = w->w_kv2; p.q = ws + L.ck; p.k = ws + L.cv;
-        p.tokens = S; p.tok_offset = 0; p.n_total = S; p.heads = d.heads;
-        if ((rc = hyb_launch_gemm(gg, dt, dt, EPI_QKV, st))) return rc;
+        // the context's keys and values have few rows and a long k: their tiles start first, the queries' fill the chip beside
+        // them.  Two launches (with k split and its merge) against one: 18 + 10 + 5 -> 25 us (2048 x 1280 beside 154 x 2560,
+        // k 2048), 16 + 9 + 5 -> 27 us (8192 x 640 beside 154 x 1280)
+        GemmGroup kv = one(B * S, 2 * C, d.ctx_dim), qg = one(M, C, C);
+        GemmProblem& pk = kv.p[0];
+        pk.a = ctx; pk.w = w->w_kv2; pk.q = ws + L.ck; pk.k = ws + L.cv;
+        pk.tokens = S; pk.tok_offset = 0; pk.n_total = S; pk.heads = d.heads;
+        GemmProblem& pq = qg.p[0];
+        pq.a = h; pq.w = w->w_q2; pq.q = ws + L.q;
+        pq.tokens = T; pq.tok_offset = 0; pq.n_total = T; pq.heads = d.heads;
+        if (dt == HYB_BF16) pq.q_scale = kQScale;
+        if (dt == HYB_BF16 && d.ctx_dim % 64 == 0 && d.ctx_dim <= 65536) {   // (what the MFMA kernel takes)
+            kv.count = 2; kv.p[1] = pq; kv.n2 = C; kv.k2 = C;
+            if ((rc = hyb_launch_gemm(kv, dt, dt, EPI_QKV, st))) return rc;
+        } else {
+            if ((rc = hyb_launch_gemm(qg, dt, dt, EPI_QKV, st))) return rc;
+            if ((rc = hyb_launch_gemm(kv, dt, dt, EPI_QKV, st))) return rc;
+        }
     }
     if ((rc = attn(ws + L.q, ws + L.ck, ws + L.cv, S))) return rc;
     {
