@@ -121,7 +121,11 @@ def _check(rc):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """torch's current stream on the current device, as the integer that ctypes takes for a pointer (a small call is bound by the
+    host: neither a Stream object nor a c_void_p is made per call)."""
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dt(t):
@@ -133,7 +137,7 @@ def _dt(t):
 
 
 def _p(t, dtype=None):
-    """Device pointer of a contiguous CUDA tensor (None -> NULL)."""
+    """Device pointer of a contiguous CUDA tensor (None -> NULL), as an integer."""
     if t is None:
         return None
     if not t.is_cuda:
@@ -142,7 +146,7 @@ def _p(t, dtype=None):
         raise ValueError("tensor must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError("expected %s, got %s" % (dtype, t.dtype))
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _nbytes(t):
@@ -248,8 +252,8 @@ def hyb_adaln_modulation(w, bias, temb, out):
 def hyb_layernorm_modulate(x, shift, scale, mod_stride, out, eps):
     """x: f32[B, T, D]; shift/scale: f32 views (first element of sample 0) or None; out: [B, T, D]."""
     B, T, D = x.shape
-    ps = None if shift is None else C.c_void_p(shift.data_ptr())
-    pc = None if scale is None else C.c_void_p(scale.data_ptr())
+    ps = None if shift is None else shift.data_ptr()
+    pc = None if scale is None else scale.data_ptr()
     _check(lib().hyb_layernorm_modulate(_p(x, torch.float32), ps, pc, mod_stride, _p(out), B, T, D, eps, _dt(out),
                                         _stream()))
     return out
@@ -259,7 +263,7 @@ def hyb_linear(a, w, bias, out, epi=HYB_EPI_BIAS, residual=None, gate=None, rows
     """a: [m, k]; w: [n, k] (HYB_EPI_GEGLU: [2n, k]); out: [m, n]."""
     m, k = a.shape
     n = out.shape[1]
-    pg = None if gate is None else C.c_void_p(gate.data_ptr())
+    pg = None if gate is None else gate.data_ptr()
     _check(lib().hyb_linear(_p(a), _p(w, a.dtype), _p(bias, torch.float32), _p(out), m, n, k, _dt(a), _dt(out), epi,
                             _p(residual, torch.float32), pg, rows_per_gate, gate_stride, _stream()))
     return out
@@ -285,8 +289,7 @@ def hyb_block_forward(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_s
                       workspace):
     """mod_img / mod_txt: f32 views whose data_ptr is the first modulation value of sample 0."""
     _check(lib().hyb_block_forward(C.byref(desc), C.byref(weights), _p(x_img_in, torch.float32),
-                                   _p(x_txt_in, torch.float32), C.c_void_p(mod_img.data_ptr()),
-                                   C.c_void_p(mod_txt.data_ptr()), mod_stride, _p(x_img_out, torch.float32),
+                                   _p(x_txt_in, torch.float32), mod_img.data_ptr(), mod_txt.data_ptr(), mod_stride, _p(x_img_out, torch.float32),
                                    _p(x_txt_out, torch.float32), _p(workspace), _nbytes(workspace), _stream()))
 
 

@@ -72,6 +72,13 @@ class MMDiT:
         self.y = torch.empty(B, cfg.n_img, D, **act)
         self.out_tok = torch.empty(B, cfg.n_img, cfg.patch_dim, **act)
         self.v = torch.empty(B, cfg.latent_hw, cfg.latent_hw, cfg.latent_c, **act)
+        # views of these buffers that every forward hands over (making one costs the host as much as a small call)
+        self._mod_views = [(self.mod[:, (2 * i) * 6 * D:], self.mod[:, (2 * i + 1) * 6 * D:]) for i in range(len(self.blocks))]
+        fo = len(self.blocks) * 2 * 6 * D
+        self._mod_final = self.mod[:, fo:], self.mod[:, fo + D:]
+        self._embed_views = [(self.tok[b], self.x_img[b]) for b in range(B)]
+        self._ctx_rows, self._txt_rows = self.ctx_act.view(-1, cfg.ctx_dim), self.x_txt.view(-1, D)
+        self._y_rows, self._out_rows = self.y.view(-1, D), self.out_tok.view(-1, cfg.patch_dim)
 
     def reconfigure(self, cfg, batch=None, pos_np=None):
         """Re-allocate the activation buffers for another token count / batch of the SAME network
@@ -97,27 +104,25 @@ class MMDiT:
             hb.hyb_linear(self.p_hid, g["p2_w"], g["p2_b"], self.temb, hb.HYB_EPI_GATE_RESIDUAL, residual=self.temb)
         hb.hyb_adaln_modulation(self.ada_w, self.ada_b, self.temb, self.mod)
         hb.hyb_patchify(latent, self.tok, cfg.patch)
-        for b in range(self.B):    # the positional table is the "residual" of the patch projection
-            hb.hyb_linear(self.tok[b], g["pe_w"], g["pe_b"], self.x_img[b], hb.HYB_EPI_GATE_RESIDUAL, residual=self.pos)
+        for tok, x_img in self._embed_views:    # the positional table is the "residual" of the patch projection
+            hb.hyb_linear(tok, g["pe_w"], g["pe_b"], x_img, hb.HYB_EPI_GATE_RESIDUAL, residual=self.pos)
         if cfg.n_txt:
             hb.hyb_convert(ctx, self.ctx_act)
-            hb.hyb_linear(self.ctx_act.view(-1, cfg.ctx_dim), g["ce_w"], g["ce_b"], self.x_txt.view(-1, cfg.hidden))
+            hb.hyb_linear(self._ctx_rows, g["ce_w"], g["ce_b"], self._txt_rows)
 
     def run_blocks(self, first=0, last=None):
-        D = self.cfg.hidden
         last = len(self.blocks) if last is None else last
         for i in range(first, last):
-            mi = self.mod[:, (2 * i) * 6 * D:]
-            mt = self.mod[:, (2 * i + 1) * 6 * D:]
+            mi, mt = self._mod_views[i]
             desc = self.desc_pre if (self.txt_pre_only_last and i == len(self.blocks) - 1) else self.desc
             hb.hyb_block_forward(desc, self.blocks[i], self.x_img, self.x_txt, mi, mt, self.mod_rows,
                                  self.x_img, self.x_txt, self.ws)
 
     def final(self):
-        cfg, g, D = self.cfg, self.g, self.cfg.hidden
-        fo = len(self.blocks) * 2 * 6 * D
-        hb.hyb_layernorm_modulate(self.x_img, self.mod[:, fo:], self.mod[:, fo + D:], self.mod_rows, self.y, 1e-6)
-        hb.hyb_linear(self.y.view(-1, D), g["f_w"], g["f_b"], self.out_tok.view(-1, cfg.patch_dim))
+        cfg, g = self.cfg, self.g
+        shift, scale = self._mod_final
+        hb.hyb_layernorm_modulate(self.x_img, shift, scale, self.mod_rows, self.y, 1e-6)
+        hb.hyb_linear(self._y_rows, g["f_w"], g["f_b"], self._out_rows)
         hb.hyb_unpatchify(self.out_tok, self.v, cfg.patch)
         return self.v
 
@@ -144,8 +149,7 @@ class GuidedSampler:
 
     def step(self, x, ctx2, t, t_next, i=0):
         """x: f32[Hh, Ww, C] master latent (updated in place); ctx2: f32[2, Nt, ctx_dim]."""
-        self.lat2[0].copy_(x)
-        self.lat2[1].copy_(x)
+        self.lat2.copy_(x.expand(self.lat2.shape[1:]))      # to both branches
         self.t2.fill_(t)
         v = self.m.forward(self.lat2, ctx2, self.t2)
         hb.hyb_cfg_disc_euler(v[0:1], v[1:2], x.view(1, -1), x.view(1, -1), self.scale, t, t_next,
