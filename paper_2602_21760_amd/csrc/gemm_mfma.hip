@@ -547,6 +547,9 @@ int launch_epi(const GemmGroup& g, hipStream_t st) {
 // (measured at k = 1536 inside the step: out-projection 35.0 against 35.4 us in one round, fc1 110 against 98 us in
 // four rounds).
 constexpr int kLargeTileMinSlabs = 48;          // launches of several rounds
+constexpr int kLargeTileMinSlabs192 = 10;       // 192-row tiles in one round, whose launch has 64-row tiles otherwise: a 512 x 512 step of 8
+                                                // blocks (out-projection 2714 x 1536, k 1536) 2428 -> 2411 us, the 640-channel stage
+                                                // (8192 x 640, k 640) 3490 -> 3466 us
 constexpr int kLargeTileMinSlabsOneRound = 32;  // launches of one round (the SDXL-shaped down-projection, k = 2560)
 // Tile height: 256 or 192 rows, whichever makes the launch shorter (rounds of tiles times the height; a CU holds one tile);
 // 192 for the gate + residual epilogue only, the one that the blocks' long-k launches have.
@@ -556,7 +559,7 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     const bool f32 = out_dtype == HYB_F32;
     const bool has_form = epi == EPI_BIAS || epi == EPI_GELU_TANH || epi == EPI_SILU || (epi == EPI_GATE_RES && f32);
     const int nslab = g.k / BK;
-    if (!has_form || nslab < kLargeTileMinSlabsOneRound) return 0;
+    if (!has_form || nslab < (epi == EPI_GATE_RES ? kLargeTileMinSlabs192 : kLargeTileMinSlabsOneRound)) return 0;
     static int cus = 0;
     if (cus == 0) {
         int dev = 0;
@@ -568,7 +571,7 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
         long tiles = 0;
         for (int i = 0; i < g.count; i++) tiles += (long)((g.p[i].m + h - 1) / h) * ((g.n + 127) / 128);
         const bool enough = h == 256 ? 2 * tiles > cus : 3 * tiles > 2 * cus;
-        if (!enough || (tiles > cus && nslab < kLargeTileMinSlabs)) continue;
+        if (!enough || (tiles > cus && nslab < kLargeTileMinSlabs) || (h == 256 && nslab < kLargeTileMinSlabsOneRound)) continue;
         const long length = (tiles + cus - 1) / cus * h;
         if (rows == 0 || length < best) { best = length; rows = h; }
     }
