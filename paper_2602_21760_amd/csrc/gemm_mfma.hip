@@ -547,9 +547,9 @@ int launch_epi(const GemmGroup& g, hipStream_t st) {
 // (measured at k = 1536 inside the step: out-projection 35.0 against 35.4 us in one round, fc1 110 against 98 us in
 // four rounds).
 constexpr int kLargeTileMinSlabs = 48;          // launches of several rounds
-constexpr int kLargeTileMinSlabs192 = 10;       // 192-row tiles in one round, whose launch has 64-row tiles otherwise: a 512 x 512 step of 8
-                                                // blocks (out-projection 2714 x 1536, k 1536) 2428 -> 2411 us, the 640-channel stage
-                                                // (8192 x 640, k 640) 3490 -> 3466 us
+constexpr int kLargeTileMinSlabs192 = 20;       // 192-row tiles in one round, whose launch has 64-row tiles otherwise: a 512 x 512 step of 8
+                                                // blocks (out-projection 2714 x 1536, 24 slabs) 2401 -> 2385 us; with ten slabs (8192 x 640,
+                                                // the 640-channel stage) 3350 us either way
 constexpr int kLargeTileMinSlabsOneRound = 32;  // launches of one round (the SDXL-shaped down-projection, k = 2560)
 // Tile height: 256 or 192 rows, whichever makes the launch shorter (rounds of tiles times the height; a CU holds one tile);
 // 192 for the gate + residual epilogue only, the one that the blocks' long-k launches have.

@@ -440,7 +440,7 @@ def test_layernorm_every_vector_count(hb, hidden):
     assert err(host(out)[good], ref[good]) < 1e-5
 
 
-@pytest.mark.parametrize("m,n,slabs", [(2714, 1536, 24), (8185, 640, 10), (2714, 1544, 32), (2881, 1536, 33), (2689, 1536, 34), (8192, 640, 38), (6400, 1536, 48)])
+@pytest.mark.parametrize("m,n,slabs", [(2714, 1536, 24), (8185, 640, 20), (2714, 1544, 32), (2881, 1536, 33), (2689, 1536, 34), (8192, 640, 38), (6400, 1536, 48)])
 def test_linear_192_row_tiles(hb, m, n, slabs):
     """Gate + residual launches take 192-row tiles where that makes the launch shorter: ragged rows and columns, gate rows that change
     inside a tile, the pipeline's remainders, several rounds; against the oracle (bf16 products are exact in fp32: the
