@@ -14,8 +14,8 @@
 // Main loop: k is cut into slabs of 64.  A slab of both operands (128 + 128 rows of 128 bytes) is
 // copied global -> LDS by 16-byte direct-to-LDS buffer loads (buffer_load_dwordx4 ... lds: a wave fills 1 KB
 // of LDS per instruction, no VGPR staging, no ds_write; the slab's byte offset is the scalar operand and the
-// per-lane offsets are loop invariants, so a slab costs no vector address arithmetic), double buffered: the copy
-// of slab s + 1 runs while slab s is multiplied.  LDS rows are unpadded; the 16-byte slots of a row are XOR-swizzled
+// per-lane offsets are loop invariants, so a slab costs no vector address arithmetic), double buffered (launches of few
+// tiles: three or six buffers, see kDeepTiles): the copy of slab s + 1 runs while slab s is multiplied.  LDS rows are unpadded; the 16-byte slots of a row are XOR-swizzled
 // with (row ^ row >> 3) & 7 so that the 16-byte fragment reads that are served together hit distinct
 // banks (the swizzle is applied on the global side: each lane picks which 16 bytes it fetches).
 // Waits on the copies are explicit (s_waitcnt vmcnt + s_barrier); a full __syncthreads() would
@@ -35,7 +35,7 @@
 // before every LDS read.)
 //
 // Up to two problems with the same (n, k) share a launch (image and text stream of a joint
-// block), the smaller one first.  Tile order: plain, or one run of consecutive tiles per XCD when
+// block), the smaller one first; the two of a QKV launch may differ in (n, k), in the caller's order.  Tile order: plain, or one run of consecutive tiles per XCD when
 // there are few tile columns (see the kernel).  Ragged edges: row / feature indices are clamped on load and masked on store.  The
 // reduction order over k is fixed and a token's result does not depend on its tile row, so
 // results are deterministic and batch-invariant.
