@@ -36,8 +36,9 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int q
     __shared__ float part_o[WAVES][2][4][4][64];   // [wave][query tile][feature tile][register][lane]
     __shared__ float part_ml[WAVES][2][2][16];     // [wave][query tile][maximum, normaliser][query]
     // XCD x serves consecutive query blocks of consecutive (batch, head) pairs: their K and V stay in its L2
-    const int blk = (blockIdx.x % 8) * xcd_run + blockIdx.x / 8;
-    if (blk >= total) return;
+    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
+    const int blk = (int)(id % 8) * xcd_run + (int)(id / 8);
+    if ((int)(id / 8) >= xcd_run || blk >= total) return;
     const int pair = blk / qblocks, qb = blk % qblocks;
     const int h = pair % a.heads, b = pair / a.heads;
     const int lane = threadIdx.x % 64, l16 = lane % 16, q4 = lane / 16;
@@ -188,13 +189,18 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int q
     }
 }
 
+// A grid dimension holds less than 2^32 threads, and a larger one is cut off without an error: blocks beyond this many
+// (a multiple of 8, for the XCD order) go into the second dimension.
+constexpr int kMaxGridX = 1 << 23;
+
 int launch_f32(const AttnArgs& a, hipStream_t st) {
     const int qblocks = (a.n_q + BQ - 1) / BQ;
     const size_t total = (size_t)qblocks * a.heads * a.batch;
     HYB_REQUIRE(total < 0x7ffffff0u, HYB_ERR_SHAPE, "attention: too many query blocks (%zu)", total);
     const int xcd_run = ((int)total + 7) / 8;
+    const int grid_x = 8 * xcd_run < kMaxGridX ? 8 * xcd_run : kMaxGridX, grid_y = (8 * xcd_run - 1) / grid_x + 1;
     HybTraceScope trace("attention_f32", "flop", 4.0 * a.batch * a.heads * (double)a.n_q * a.n_kv * 64, st);
-    hipLaunchKernelGGL(attention_f32_kernel, dim3(8 * xcd_run), dim3(256), 0, st, a, qblocks, (int)total, xcd_run);
+    hipLaunchKernelGGL(attention_f32_kernel, dim3(grid_x, grid_y), dim3(256), 0, st, a, qblocks, (int)total, xcd_run);
     return hyb_check_launch("attention_f32");
 }
 

@@ -63,3 +63,12 @@ def test_attention_f32(hb, batch, heads, n_q, n_kv):
         hb.hyb_joint_attention(q.cuda(), kr.cuda(), v.cuda(), o)
         ref = torch.softmax(q.double() @ kr.double().transpose(2, 3) / 8, -1) @ v.double()
         assert err(host(o), ref.transpose(1, 2).reshape(batch, n_q, -1).numpy()) < 40 * TOL   # the exponents' rounding, 40 times larger
+
+
+def test_attention_f32_more_blocks_than_one_grid_dimension_holds(hb):
+    """65535 samples of 257 heads are more than 2^24 workgroups of 256 threads; with one key the output is its value, exactly."""
+    q, k = (torch.zeros(65535, 257, 1, 64, device="cuda") for _ in range(2))
+    v = torch.randn(65535, 257, 1, 64, device="cuda")
+    o = torch.full((65535, 1, 257 * 64), float("nan"), device="cuda")
+    hb.hyb_joint_attention(q, k, v, o)
+    assert torch.equal(o.view(-1), v.view(-1))
