@@ -102,8 +102,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
 
     // XCD x gets the tiles [x xcd_run, (x + 1) xcd_run) of an order that walks down the rows first: neighbours share their
     // weight rows, and the activations of these models stay in every L2
-    const int tile = (blockIdx.x % 8) * xcd_run + blockIdx.x / 8;
-    if (tile >= total) return;
+    const unsigned id = blockIdx.y * gridDim.x + blockIdx.x;
+    const int tile = (int)(id % 8) * xcd_run + (int)(id / 8);
+    if ((int)(id / 8) >= xcd_run || tile >= total) return;
     int tm = tile % tiles_m;
     const int col0 = (tile / tiles_m) * OUT_COLS;
     const int pi = tm >= tiles_m0 ? 1 : 0;
@@ -275,6 +276,10 @@ int cu_count() {
     return n;
 }
 
+// A grid dimension holds less than 2^32 threads, and a larger one is cut off without an error: tiles beyond this many
+// (a multiple of 8, for the XCD order) go into the second dimension.
+constexpr int kMaxGridX = 1 << 23;
+
 template <typename OT, int KW, bool GEGLU>
 int launch(const GemmGroup& g, int epi, hipStream_t st) {
     constexpr int T = KW == 1 ? 64 : 32;
@@ -286,7 +291,8 @@ int launch(const GemmGroup& g, int epi, hipStream_t st) {
     const double rows = g.p[0].m + (g.count > 1 ? g.p[1].m : 0);
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k * (GEGLU ? 2 : 1), st);
     const int xcd_run = (total + 7) / 8;
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<OT, KW, GEGLU>), dim3(8 * xcd_run), dim3(256), 0, st, g, epi, tiles_m0, tiles_m0 + tiles_m1, total, xcd_run);
+    const int grid_x = 8 * xcd_run < kMaxGridX ? 8 * xcd_run : kMaxGridX, grid_y = (8 * xcd_run - 1) / grid_x + 1;
+    hipLaunchKernelGGL((gemm_f32_mfma_kernel<OT, KW, GEGLU>), dim3(grid_x, grid_y), dim3(256), 0, st, g, epi, tiles_m0, tiles_m0 + tiles_m1, total, xcd_run);
     return hyb_check_launch("gemm_f32_mfma");
 }
 

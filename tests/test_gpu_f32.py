@@ -72,3 +72,14 @@ def test_attention_f32_more_blocks_than_one_grid_dimension_holds(hb):
     o = torch.full((65535, 1, 257 * 64), float("nan"), device="cuda")
     hb.hyb_joint_attention(q, k, v, o)
     assert torch.equal(o.view(-1), v.view(-1))
+
+
+def test_linear_f32_more_tiles_than_one_grid_dimension_holds(hb):
+    """65535 x 257 tiles are more than 2^24 workgroups of 256 threads.  (69 GB of output, the least that this many tiles can have here.)"""
+    m, n, k = 65535 * 64, 8196, 16
+    a, w = torch.randn(m, k, device="cuda"), torch.randn(2 * n, k, device="cuda")
+    out = torch.empty(m, n, device="cuda", dtype=torch.bfloat16)
+    hb.hyb_linear(a, w, None, out, hb.HYB_EPI_GEGLU)
+    rows = torch.tensor([0, 63, 64, m // 2, m - 65, m - 1], device="cuda")
+    u, v = (a[rows].double() @ w.double().t()).chunk(2, 1)
+    assert err(host(out[rows]), (u * torch.nn.functional.gelu(v)).cpu().numpy()) < 4e-3
