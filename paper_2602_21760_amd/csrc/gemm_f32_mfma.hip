@@ -309,7 +309,8 @@ int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, h
     // per-lane byte offsets inside a tile's operand rows are 32-bit; for GEGLU the gate rows lie n rows further down
     if ((size_t)g.k * 4 * ((epi == EPI_GEGLU ? (size_t)g.n : 0) + 64) >= ((size_t)1 << 31)) return -1;
     double tiles64 = 0, tiles32 = 0;
-    const double cols64 = (g.n + 63) / 64, cols32 = (g.n + 31) / 32;
+    const int T64 = epi == EPI_GEGLU ? 32 : 64, T32 = T64 / 2;      // output columns of a tile
+    const double cols64 = (g.n + T64 - 1) / T64, cols32 = (g.n + T32 - 1) / T32;
     for (int i = 0; i < g.count; i++) {
         const GemmProblem& p = g.p[i];
         if (epi == EPI_GATE_RES && p.gate && p.gate_stride % 4 != 0) return -1;
@@ -319,11 +320,14 @@ int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, h
     }
     if (tiles32 == 0) return HYB_OK;
     if (tiles32 > 1e9) return -1;
-    // A 64 x 64 tile takes a CU four times as long as a 32 x 32 one: the small tiles where they divide the work of the
-    // busiest CU better, the large ones (half the operand traffic) where it makes no difference.  (653 x 768 x 3072: 30 us
-    // with small tiles, 61 with large ones; 1306 x 3072 x 768: 65 and 52; equal at 1306 x 768 x 3072, one round of either.)
+    // A 64 x 64 tile takes a CU four times as long as a 32 x 32 one: the small tiles where they take a fifth or more off the
+    // work of the busiest CU, the large ones (half the operand traffic) otherwise; small against large tiles over 124 random shapes:
+    // 0.30-1.08 of the time where that work is 0.75 or less, 0.97-1.73 where it is more.  (653 x 768 x 3072: 30 against
+    // 61 us; 1306 x 3072 x 768: 65 against 52; 1306 x 768 x 3072: 61 either way; 2704 x 1024 x 320: 32 against 22.)  A single round of
+    // large tiles that leaves CUs idle takes as long as a full one; with a long k the small tiles gain from that what they lose on
+    // operands (198-210 tiles: 1.15-1.22 at k 320, 0.97-0.99 at 768, 0.86-0.91 at 4096; 252-256 tiles: 0.98-1.03 from 768 on).
     const int cus = cu_count();
     const double busy64 = 4.0 * (double)(((long long)tiles64 + cus - 1) / cus), busy32 = (double)(((long long)tiles32 + cus - 1) / cus);
-    const bool small = busy32 < 0.95 * busy64;
+    const bool small = busy32 < 0.8 * busy64 || (tiles64 < 0.85 * cus && g.k >= 768);
     return out_dtype == HYB_F32 ? launch_any<float>(g, epi, small, st) : launch_any<bf16_t>(g, epi, small, st);
 }

@@ -20,6 +20,14 @@ def hb():
     return binding
 
 
+def _traced(hb, call):
+    hb.hyb_trace_enable(True)
+    call()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    return list(names)
+
+
 # both tile shapes (64 x 64 where it fills the chip as well as 32 x 32), one row, ragged rows and columns around the tile
 # sizes, one slab of k, fewer slabs than waves, an odd number of slabs, long k; half a slab; n % 4 != 0 and k % 16 != 0 take the plain kernel
 @pytest.mark.parametrize("m,n,k", [(1, 4, 32), (2, 256, 96), (31, 36, 160), (33, 28, 64), (65, 100, 1056), (653, 768, 3072),
@@ -83,3 +91,13 @@ def test_linear_f32_more_tiles_than_one_grid_dimension_holds(hb):
     rows = torch.tensor([0, 63, 64, m // 2, m - 65, m - 1], device="cuda")
     u, v = (a[rows].double() @ w.double().t()).chunk(2, 1)
     assert err(host(out[rows]), (u * torch.nn.functional.gelu(v)).cpu().numpy()) < 4e-3
+
+
+def test_geglu_f32_tile_shape_counts_its_own_columns(hb):
+    """A GEGLU tile has half as many output columns as the others: 1000 x 508 is one round of 64 x 64 tiles, 1000 x 380 (192 tiles) leaves a
+    quarter of the chip idle that 32 x 32 tiles fill."""
+    a, w = torch.randn(1000, 32, device="cuda"), torch.randn(1016, 32, device="cuda")
+    for n, shape in ((508, "64x64"), (380, "32x32")):
+        out = torch.empty(1000, n, device="cuda")
+        names = _traced(hb, lambda: hb.hyb_linear(a, w[:2 * n], None, out, hb.HYB_EPI_GEGLU))
+        assert names == ["gemm_f32_mfma_%s.epi5.n%d.k32" % (shape, n)], names
