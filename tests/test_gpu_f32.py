@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from oracle import hyb_oracle as O
+from paper_2602_21760_amd import synth
 from gpu_util import dev, host, err
 
 pytestmark = pytest.mark.gpu
@@ -28,8 +29,9 @@ def _traced(hb, call):
     return list(names)
 
 
-# both tile shapes (64 x 64 where it fills the chip as well as 32 x 32), one row, ragged rows and columns around the tile
-# sizes, one slab of k, fewer slabs than waves, an odd number of slabs, long k; half a slab; n % 4 != 0 and k % 16 != 0 take the plain kernel
+# 32 x 32 tiles, and 64 x 64 ones for the two shapes of more than 4000 rows (the 64 x 64 tiles have their own test below): one row, ragged
+# rows and columns around the tile sizes, one slab of k, fewer slabs than waves, an odd number of slabs, long k; half a slab;
+# n % 4 != 0 and k % 16 != 0 take the plain kernel
 @pytest.mark.parametrize("m,n,k", [(1, 4, 32), (2, 256, 96), (31, 36, 160), (33, 28, 64), (65, 100, 1056), (653, 768, 3072),
                                    (4097, 2052, 64), (100, 40, 16), (70, 64, 112), (4100, 2048, 80), (40, 30, 64), (40, 32, 72)])
 def test_linear_f32(hb, m, n, k):
@@ -101,3 +103,50 @@ def test_geglu_f32_tile_shape_counts_its_own_columns(hb):
         out = torch.empty(1000, n, device="cuda")
         names = _traced(hb, lambda: hb.hyb_linear(a, w[:2 * n], None, out, hb.HYB_EPI_GEGLU))
         assert names == ["gemm_f32_mfma_%s.epi5.n%d.k32" % (shape, n)], names
+
+
+# Shapes whose 64 x 64 tiles fill whole rounds of 256 CUs, so that the dispatch takes them: one slab of k and less, fewer slabs than
+# running sums, 4 q + 1 of them, half last slabs, ragged rows and columns, long k.
+@pytest.mark.parametrize("m,n,k", [(1000, 1020, 16), (1000, 1020, 32), (961, 1012, 48), (961, 1012, 64), (2040, 508, 80), (2040, 508, 96),
+                                   (4090, 252, 160), (1000, 1000, 272), (16370, 60, 288), (1306, 768, 3072)])
+def test_linear_f32_64x64_tiles(hb, m, n, k):
+    g = torch.Generator().manual_seed(m + n + k)
+    nh = n // 8 * 4                                  # GEGLU outputs: u and gate rows of one weight matrix
+    a, w, b = (torch.randn(s, generator=g) * f for s, f in (((m, k), 1), ((n, k), k ** -0.5), ((n,), 1)))
+    res, gate = torch.randn(m, n, generator=g), torch.randn(2, n, generator=g)
+    da, dw, db = a.cuda(), w.cuda(), b.cuda()
+    y = torch.from_numpy(O.linear(a.double().numpy(), w.double().numpy(), b.double().numpy()))
+    u, v = y[:, :nh], y[:, nh:2 * nh]
+    F = torch.nn.functional
+    rpg = (m + 1) // 2
+    cases = [(hb.HYB_EPI_BIAS, n, {}, y), (hb.HYB_EPI_GELU_TANH, n, {}, F.gelu(y, approximate="tanh")), (hb.HYB_EPI_SILU, n, {}, F.silu(y)),
+             (hb.HYB_EPI_GATE_RESIDUAL, n, dict(residual=res.cuda(), gate=gate.cuda(), rows_per_gate=rpg, gate_stride=n),
+              res + gate.double()[torch.arange(m) // rpg] * y),
+             (hb.HYB_EPI_GEGLU, nh, {}, u * F.gelu(v))]
+    for epi, cols, kw, ref in cases:
+        out, one = torch.empty(m, cols, device="cuda"), torch.empty(1, cols, device="cuda")
+        rows = 2 * nh if epi == hb.HYB_EPI_GEGLU else n
+        names = _traced(hb, lambda: hb.hyb_linear(da, dw[:rows], db[:rows], out, epi, **kw))
+        assert names == ["gemm_f32_mfma_64x64.epi%d.n%d.k%d" % (epi, cols, k)], names
+        assert err(host(out), ref.numpy()) < TOL, epi
+        # the 32 x 32 tiles, which a single row takes, give the same bits
+        r = m // 2
+        if kw:
+            kw = dict(kw, residual=kw["residual"][r:r + 1], gate=kw["gate"][r // rpg:])
+        names = _traced(hb, lambda: hb.hyb_linear(da[r:r + 1].clone(), dw[:rows], db[:rows], one, epi, **kw))
+        assert names == ["gemm_f32_mfma_32x32.epi%d.n%d.k%d" % (epi, cols, k)], names
+        assert torch.equal(one[0], out[r]), epi
+    low = torch.empty(m, n, device="cuda", dtype=torch.bfloat16)
+    hb.hyb_linear(da, dw, db, low)
+    assert err(host(low), y.numpy()) < 4e-3          # one rounding to bf16: 2^-8 at most, half of it in the mean square
+
+
+def test_qkv_scatter_f32_64x64_tiles(hb):
+    """The head-major scatter from the 64 x 64 tiles: an fp32 block of two samples with ragged image and text rows, 252 tiles."""
+    from test_gpu_block import _block_case
+    cfg = synth.scaled(synth.CFG1, hidden=128, heads=2, latent_hw=72, n_txt=25, ctx_dim=64, batch=2)
+    got = []
+    names = _traced(hb, lambda: got.append(_block_case(hb, cfg)))
+    assert "gemm_f32_mfma_64x64.epi4.n384.k128" in names, names
+    g_img, g_txt, r_img, r_txt, (x_img, x_txt) = got[0]
+    assert err(g_img - x_img, r_img - x_img) < 1e-4 and err(g_txt - x_txt, r_txt - x_txt) < 1e-4
