@@ -22,14 +22,14 @@ constexpr int BQ = 32;    // query rows per workgroup
 constexpr int BKV = 32;   // keys per tile
 constexpr int WAVES = 4;
 
-// e^x for x <= 0 to about 1.5 ulp, without the library routine's range handling: x log2(e) as a rounded product plus the error
-// of its rounding, 2^(hi + lo) = 2^hi (1 + lo ln 2).  Below e^-87 the result is 0; NaN stays NaN.
+// e^x for x <= 0, without the library routine's range handling: e^x = 2^n 2^f with n = x log2(e) rounded to a whole number and f
+// the rest, taken with log2(e) in two parts, so that neither the product's rounding nor that of log2(e) counts.  The
+// power of two is applied by ldexp, which rounds into the subnormal numbers as a product would (1.5 ulp at most, tested); NaN stays NaN.
 __device__ __forceinline__ float exp_neg(float x) {
-    x = x < -200.f ? -200.f : x;      // (minus infinity would make the error term NaN)
-    const float hi = x * 1.44269502162933349609375f;
-    const float lo = fmaf(x, 1.44269502162933349609375f, -hi) + x * 1.92596299112661746887e-8f;
-    const float e = __builtin_amdgcn_exp2f(hi);
-    return fmaf(e * lo, 0.6931471805599453f, e);
+    x = x < -200.f ? -200.f : x;      // 0 well before; minus infinity would make f NaN
+    const float n = rintf(x * 1.44269502162933349609375f);
+    const float f = fmaf(x, 1.92596299112661746887e-8f, fmaf(x, 1.44269502162933349609375f, -n));
+    return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
 
 __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int qblocks, int total, int xcd_run) {

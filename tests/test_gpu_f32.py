@@ -10,7 +10,7 @@ from gpu_util import dev, host, err
 pytestmark = pytest.mark.gpu
 
 # fp32 products summed in fp32: the relative error of a row stays below sqrt(k) 2^-24, 3.3e-6 at k = 3072; attention adds
-# its exponentials (2 ulp each, arguments below 2^4: 1e-6).
+# its exponentials (1.5 ulp each, test_attention_f32_exponentials; arguments below 2^4: 1e-6).
 TOL = 4e-6
 
 
@@ -150,3 +150,22 @@ def test_qkv_scatter_f32_64x64_tiles(hb):
     assert "gemm_f32_mfma_64x64.epi4.n384.k128" in names, names
     g_img, g_txt, r_img, r_txt, (x_img, x_txt) = got[0]
     assert err(g_img - x_img, r_img - x_img) < 1e-4 and err(g_txt - x_txt, r_txt - x_txt) < 1e-4
+
+
+def test_attention_f32_exponentials(hb):
+    """Two keys with scores 0 and -x and values 0 and 1: the output is p / (1 + p), p = e^-x, over the whole range of the exponential, the
+    subnormal numbers included.  Bounds: 1.5 ulp (2^-23 each) of the exponential, half an ulp each for sum and quotient; below 2^-126
+    the spacing of the subnormal numbers, 2^-149, takes the ulp's place."""
+    n = 1 << 16
+    x = torch.linspace(0, 104, n, dtype=torch.float64).float()
+    q, k, v = torch.zeros(1, 1, n, 64), torch.zeros(1, 1, 2, 64), torch.zeros(1, 1, 2, 64)
+    q[0, 0, :, 5], k[0, 0, 1, 5], v[0, 0, 1] = x, -1.0, 1.0
+    o = torch.empty(1, n, 64, device="cuda")
+    hb.hyb_joint_attention(q.cuda(), k.cuda(), v.cuda(), o, 1.0)
+    ref = (1 / (1 + torch.exp(x.double())))[:, None]
+    got = o[0].double().cpu()
+    assert (got == got[:, :1]).all()
+    off = (got[:, :1] - ref).abs()
+    print("largest error in units of 2^-23: %.2f; below 2^-126 in units of 2^-149: %.2f" % (
+        (off / ref)[x < 87].max() * 2 ** 23, off[x >= 87].max() * 2.0 ** 149))
+    assert (off <= 2.5 * 2.0 ** -23 * ref + 1.5 * 2.0 ** -149).all()
