@@ -52,6 +52,8 @@ int hyb_launch_gemm_simple(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out
 int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
 // bf16 MFMA kernel (k % 64 == 0, n % 8 == 0); returns -1 if the shape is not supported.
 int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
+// 128 x 128 tiles of an m x n product (two of them fit a CU).
+int hyb_gemm_mfma_tiles(int m, int n);
 // Large-tile bf16 MFMA kernel (256 x 128 or 192 x 128 tiles, one workgroup per CU).  Same accumulation order as the kernel above, hence
 // the same bits per token.  -1 when the shape or the epilogue has no large-tile form.
 int hyb_launch_gemm_mfma_big(const GemmGroup& g, hyb_dtype out_dtype, int epi, int rows, hipStream_t st);

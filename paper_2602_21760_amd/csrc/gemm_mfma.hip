@@ -82,11 +82,23 @@ __global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_ker
     // Workgroups go round-robin to the 8 XCDs (each with its own L2) in launch order.  With few tile columns the
     // tiles that an XCD works on at a time then share hardly any operand panel (every 8th tile: all tile rows, a
     // few columns), so XCD x is given the run of consecutive tiles [x * xcd_run, (x + 1) * xcd_run) instead
-    // (a few whole tile rows).  xcd_run == 0: plain order.
+    // (a few whole tile rows).  xcd_run == 0: plain order.  Two problems of different shapes have runs of their own: with
+    // one run over both, the first's tiles, few and long, would all come to the first XCD (a stage block of 4 x 1024 tokens of 640
+    // channels and 4 x 333 context rows: 197 us so, 182 us as it is).
     int tile = blockIdx.x;
     if (xcd_run > 0) {
-        tile = (tile % 8) * xcd_run + tile / 8;
-        if (tile >= total) return;
+        int first = 0, end = total, run = xcd_run;
+        if (MIXED && g.n2) {
+            const int run0 = (tiles0 + 7) / 8;
+            if (tile < 8 * run0) {
+                end = tiles0; run = run0;
+            } else {
+                first = tiles0;
+                tile -= 8 * run0;
+            }
+        }
+        tile = first + (tile % 8) * run + tile / 8;
+        if (tile >= end) return;
     }
     // k split (ksplit > 1, single problem, plain fp32 output): ksplit consecutive workgroups share a tile; each
     // multiplies its share of the k-slabs and writes the raw sums to its own [m, n] plane of p.out
@@ -457,8 +469,9 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
         t0 = tiles1;
     }
     const int total = (tiles0 + tiles1) * ksplit;
-    const int xcd_run = tiles_n <= kNarrowTileCols ? (total + 7) / 8 : 0;
-    const int grid = xcd_run ? 8 * xcd_run : total;
+    const int first = gg.n2 ? t0 : 0;   // tiles of a problem of another shape, in runs of their own
+    const int xcd_run = tiles_n <= kNarrowTileCols ? (total - first + 7) / 8 : 0;
+    const int grid = xcd_run ? 8 * ((first + 7) / 8 + xcd_run) : total;
     if constexpr (TMW == 1) {
         const int nslab = g.k / BK / ksplit;
         if (total <= kDeepTiles && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 6>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
@@ -579,6 +592,8 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
 }
 
 }  // namespace
+
+int hyb_gemm_mfma_tiles(int m, int n) { return ((m + 127) / 128) * ((n + BN - 1) / BN); }
 
 int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st) {
     if (g.k <= 0 || g.k % BK != 0 || g.n % 8 != 0 || g.n < 8) return -1;

@@ -43,7 +43,8 @@ SdxlLayout sdxl_layout(const hyb_sdxl_block_desc& d) {
     L.cv = take(B * S * C * es);
     L.ff = take(B * T * 4 * C * es);    // GEGLU output
     L.gn = take(hyb_groupnorm_scratch_bytes(d.batch, d.groups));
-    // fp32 planes of the GEMMs' k split: up to 8 for the context K/V projection (few rows), 3 for the down-projection
+    // fp32 planes of the GEMMs' k split: up to 8 for a context K/V projection that is split (few rows, see below), 3 for the
+    // down-projection, which takes more where this scratch holds them
     const size_t kv_planes = 8 * B * S * 2 * C * 4, ff2_planes = 3 * B * T * C * 4;
     L.splitk_bytes = kv_planes > ff2_planes ? kv_planes : ff2_planes;
     L.splitk = take(L.splitk_bytes);
@@ -131,9 +132,16 @@ extern "C" int hyb_sdxl_block_forward(const hyb_sdxl_block_desc* desc, const hyb
     // cross-attention to the text context: b = a + (softmax(q kc^T / 8) vc) Wo2^T + bo2
     if ((rc = hyb_launch_layernorm(g, w->ln2_b, w->ln2_g, 0, h, B, T, C, d.ln_eps, dt, true, st))) return rc;
     {
-        // the context's keys and values have few rows and a long k: their tiles start first, the queries' fill the chip beside
-        // them.  Two launches (with k split and its merge) against one: 18 + 10 + 5 -> 25 us (2048 x 1280 beside 154 x 2560,
-        // k 2048), 16 + 9 + 5 -> 27 us (8192 x 640 beside 154 x 1280)
+        // The context's keys and values have few rows and a long k: their tiles start first, the queries' fill the chip beside
+        // them.  Two launches against one: 18 + 10 + 5 -> 25 us (2048 x 1280 beside 154 x 2560, k 2048).  They are a launch of their own
+        //  - where their tiles fill a round of workgroup slots, so that the queries' start a new one (a block of 2 x 64 tokens of
+        //    2048 channels, 2 x 1024 context rows: 184 us in two launches, 202 in one; with a quarter of the slots left, or room for
+        //    all of the queries, one launch takes 0.83-1.01 of the time of two).  The number of samples counts in this, so neither of the two
+        //    launches splits k and the bits are the same either way;
+        //  - where k is so long that its tiles outlast the queries', and is better split (hyb_launch_gemm does that in a launch of
+        //    their own).  A block in one launch against two, on average over 200-16384 tokens and 1-4 samples: 256 channels
+        //    1.00 at k 3072, 1.03 at 4096, 1.13 at 8192; 512 channels 0.98, 1.00, 1.10; 640 channels 0.97, 0.99, 1.08; 1280 channels 0.96,
+        //    0.98, 1.03.
         GemmGroup kv = one(B * S, 2 * C, d.ctx_dim), qg = one(M, C, C);
         GemmProblem& pk = kv.p[0];
         pk.a = ctx; pk.w = w->w_kv2; pk.q = ws + L.ck; pk.k = ws + L.cv;
@@ -142,7 +150,12 @@ extern "C" int hyb_sdxl_block_forward(const hyb_sdxl_block_desc* desc, const hyb
         pq.a = h; pq.w = w->w_q2; pq.q = ws + L.q;
         pq.tokens = T; pq.tok_offset = 0; pq.n_total = T; pq.heads = d.heads;
         if (dt == HYB_BF16) pq.q_scale = kQScale;
-        if (dt == HYB_BF16 && d.ctx_dim % 64 == 0 && d.ctx_dim <= 65536) {   // (what the MFMA kernel takes)
+        const int kSlots = 512;
+        const int left = kSlots - 1 - (hyb_gemm_mfma_tiles(B * S, 2 * C) - 1) % kSlots;   // slots in the last round of keys and values
+        const int longest = 6 * C > 4096 ? 6 * C : (C >= 640 ? 4096 : 3072);
+        const bool undivided = dt == HYB_BF16 && d.ctx_dim % 64 == 0 && d.ctx_dim <= longest;
+        if (undivided) qg.splitk_ws = kv.splitk_ws = nullptr;
+        if (undivided && (left >= kSlots / 4 || hyb_gemm_mfma_tiles(M, C) <= left)) {
             kv.count = 2; kv.p[1] = pq; kv.n2 = C; kv.k2 = C;
             if ((rc = hyb_launch_gemm(kv, dt, dt, EPI_QKV, st))) return rc;
         } else {

@@ -82,6 +82,23 @@ def test_sdxl_block_widths_and_contexts(hb, dt, heads, n_ctx, ctx_dim):
     assert err(got - x, ref - x) < (3e-2 if dt == "bf16" else 1e-3)
 
 
+@pytest.mark.parametrize("heads,tokens,n_ctx,ctx_dim,batch,launch", [
+    (2, 37, 333, 256, 1, "one"), (10, 200, 300, 128, 2, "one"), (10, 64, 1024, 64, 2, "one"), (14, 130, 77, 576, 2, "one"),
+    (32, 37, 700, 64, 2, "one"), (32, 700, 800, 64, 2, "own"), (32, 37, 1024, 64, 2, "own"), (32, 37, 1100, 64, 2, "one"), (2, 37, 77, 4096, 2, "split")])
+def test_sdxl_block_context_projection_launches(hb, heads, tokens, n_ctx, ctx_dim, batch, launch):
+    """The context's keys and values share a launch with the queries, in few tile columns (each in runs of tiles per XCD) and in many,
+    unless their tiles of 128 x 128 fill their last round of 512 slots or their k is long (then it is split)."""
+    cfg = synth.SDXLStageConfig("t", blocks=1, tokens=tokens, channels=64 * heads, heads=heads, n_ctx=n_ctx, ctx_dim=ctx_dim, batch=batch, dtype="bf16")
+    hb.hyb_trace_enable(True)
+    got, ref, x = _stage_case(cfg, 1, scale_w=2.0)
+    names = [n.split(".", 1)[-1] for n in hb.hyb_trace_summary()]
+    hb.hyb_trace_enable(False)
+    C = cfg.channels
+    assert ("epi%d.n%d.k%d" % (0 if launch == "split" else 4, 2 * C, ctx_dim)) in names, names
+    assert ("epi4.n%d.k%d" % (C, C) in names) == (launch != "one"), names
+    assert err(got, ref) < tol("bf16") and err(got - x, ref - x) < 3e-2
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("stage", ["A", "B"])
 def test_sdxl_stage_real_shapes_one_block(hb, stage):
