@@ -572,7 +572,11 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     const bool f32 = out_dtype == HYB_F32;
     const bool has_form = epi == EPI_BIAS || epi == EPI_GELU_TANH || epi == EPI_SILU || (epi == EPI_GATE_RES && f32);
     const int nslab = g.k / BK;
-    if (!has_form || nslab < (epi == EPI_GATE_RES ? kLargeTileMinSlabs192 : kLargeTileMinSlabsOneRound)) return 0;
+    // A second residual is added in another order by the large tiles, (y + res) + res2, than by the 64- and 128-row ones, y + (res + res2).
+    // So with two of them no launch short of 32 slabs takes large tiles, and a row has the same bits whatever the number of
+    // rows (from 32 on the k split of such launches depends on the rows as well).
+    const bool two_res = epi == EPI_GATE_RES && (g.p[0].res2 || (g.count > 1 && g.p[1].res2));
+    if (!has_form || nslab < (epi == EPI_GATE_RES && !two_res ? kLargeTileMinSlabs192 : kLargeTileMinSlabsOneRound)) return 0;
     static int cus = 0;
     if (cus == 0) {
         int dev = 0;

@@ -99,6 +99,19 @@ def test_sdxl_block_context_projection_launches(hb, heads, tokens, n_ctx, ctx_di
     assert err(got, ref) < tol("bf16") and err(got - x, ref - x) < 3e-2
 
 
+def test_sdxl_block_down_projection_batch_invariance(hb):
+    """A sample's bits do not depend on the batch where the down-projection is not split (k = 1536): 12288 rows x 384 would fill the
+    chip with 192-row tiles, whose kernel adds the two residuals in another order than the small tiles that 4096 rows take."""
+    from paper_2602_21760_amd import model
+    cfg = synth.SDXLStageConfig("t", blocks=1, tokens=4096, channels=384, heads=6, n_ctx=77, ctx_dim=128, batch=3, dtype="bf16")
+    w, x = [synth.sdxl_block_weights(cfg, 0)], synth.normal(90, (3, cfg.tokens, cfg.channels))
+    ctx = synth.normal(91, (3, cfg.n_ctx, cfg.ctx_dim), 1.0, "bf16")
+    three = model.SDXLStage(cfg, w).forward(dev(x), dev(ctx))
+    single = model.SDXLStage(synth.scaled(cfg, batch=1), w)
+    for b in range(3):
+        assert torch.equal(single.forward(dev(x[b:b + 1]), dev(ctx[b:b + 1]))[0], three[b]), b
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("stage", ["A", "B"])
 def test_sdxl_stage_real_shapes_one_block(hb, stage):
