@@ -24,6 +24,15 @@ int hyb_check_launch(const char* what) {
     return HYB_OK;
 }
 
+int hyb_cu_count() {
+    static const int count = [] {
+        int dev = 0, n = 0;
+        const bool ok = hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+        return ok && n >= 8 ? n : 256;
+    }();
+    return count;
+}
+
 extern "C" int hyb_version(void) { return 100; }
 
 extern "C" const char* hyb_last_error_string(void) { return g_err; }

@@ -582,12 +582,7 @@ TailSplit tail_split(int batch, int heads, int n_q) {
     TailSplit t = {0, 0, 1, 0};
     const int pairs = batch * heads;
     if (pairs == 0 || pairs % 8 != 0) return t;
-    static int cus_per_xcd = 0;
-    if (cus_per_xcd == 0) {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) cus = 256;
-        cus_per_xcd = cus / 8;
-    }
+    const int cus_per_xcd = hyb_cu_count() / 8;
     const int ppx = pairs / 8, qblocks = (n_q + BQ - 1) / BQ;
     const int w = ppx * qblocks;
     int per_pair, parts;

@@ -34,6 +34,10 @@ int hyb_set_error(int code, const char* fmt, ...);
 
 int hyb_check_launch(const char* what);
 
+// Compute units of the device that was current at the first call (asked for once: a query per launch costs the host more than the launch
+// rule that needs it).
+int hyb_cu_count();
+
 // ---- optional per-launch timing (hyb_trace_*) ----------------------------------------------
 // A scope object brackets one kernel launch with two events on the launch stream when tracing
 // is on; `work` is the algorithmic work of the launch (flops or bytes, `unit` says which).

@@ -270,12 +270,6 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
     }
 }
 
-int cu_count() {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
-    return n;
-}
-
 // A grid dimension holds less than 2^32 threads, and a larger one is cut off without an error: tiles beyond this many
 // (a multiple of 8, for the XCD order) go into the second dimension.
 constexpr int kMaxGridX = 1 << 23;
@@ -326,7 +320,7 @@ int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, h
     // 61 us; 1306 x 3072 x 768: 65 against 52; 1306 x 768 x 3072: 61 either way; 2704 x 1024 x 320: 32 against 22.)  A single round of
     // large tiles that leaves CUs idle takes as long as a full one; with a long k the small tiles gain from that what they lose on
     // operands (198-210 tiles: 1.15-1.22 at k 320, 0.97-0.99 at 768, 0.86-0.91 at 4096; 252-256 tiles: 0.98-1.03 from 768 on).
-    const int cus = cu_count();
+    const int cus = hyb_cu_count();
     const double busy64 = 4.0 * (double)(((long long)tiles64 + cus - 1) / cus), busy32 = (double)(((long long)tiles32 + cus - 1) / cus);
     const bool small = busy32 < 0.8 * busy64 || (tiles64 < 0.85 * cus && g.k >= 768);
     return out_dtype == HYB_F32 ? launch_any<float>(g, epi, small, st) : launch_any<bf16_t>(g, epi, small, st);

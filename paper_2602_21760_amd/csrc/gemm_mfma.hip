@@ -15,7 +15,7 @@
 // copied global -> LDS by 16-byte direct-to-LDS buffer loads (buffer_load_dwordx4 ... lds: a wave fills 1 KB
 // of LDS per instruction, no VGPR staging, no ds_write; the slab's byte offset is the scalar operand and the
 // per-lane offsets are loop invariants, so a slab costs no vector address arithmetic), double buffered (launches of few
-// tiles: three or six buffers, see kDeepTiles): the copy of slab s + 1 runs while slab s is multiplied.  LDS rows are unpadded; the 16-byte slots of a row are XOR-swizzled
+// tiles: three or six buffers, see launch_tiles): the copy of slab s + 1 runs while slab s is multiplied.  LDS rows are unpadded; the 16-byte slots of a row are XOR-swizzled
 // with (row ^ row >> 3) & 7 so that the 16-byte fragment reads that are served together hit distinct
 // banks (the swizzle is applied on the global side: each lane picks which 16 bytes it fetches).
 // Waits on the copies are explicit (s_waitcnt vmcnt + s_barrier); a full __syncthreads() would
@@ -435,13 +435,6 @@ __global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_ker
     }
 }
 
-// A launch of 64-row tiles that leaves room on the CUs is bound by the latency of its slab copies, one after the other: it
-// takes more slab buffers, six when every workgroup can have a CU of its own (256 tiles), three for up to two per CU.
-// Two against six: 333 x 1536 x 4096 49 -> 26 us, one row x 1536 x 1536 24 -> 13 us; two against three: 2048 x 1280 x 1280
-// with residual 21 -> 18 us.  Up to two k-slabs have nothing to run ahead of.  A launch of two problems of different shapes takes at
-// least three: its long tiles decide how long it lasts (8192 x 640, k 640, beside 154 x 1280, k 2048: 31 -> 27 us).
-constexpr int kDeepTiles = 256;
-
 // Up to this many tile columns a launch hands each XCD a run of consecutive tiles (see the kernel).
 constexpr int kNarrowTileCols = 16;
 
@@ -472,10 +465,15 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
     const int first = gg.n2 ? t0 : 0;   // tiles of a problem of another shape, in runs of their own
     const int xcd_run = tiles_n <= kNarrowTileCols ? (total - first + 7) / 8 : 0;
     const int grid = xcd_run ? 8 * ((first + 7) / 8 + xcd_run) : total;
+    // A launch of 64-row tiles that leaves room on the CUs is bound by the latency of its slab copies, one after the other: it
+    // takes more slab buffers, six when every workgroup can have a CU of its own, three for up to two per CU.
+    // Two against six: 333 x 1536 x 4096 49 -> 26 us, one row x 1536 x 1536 24 -> 13 us; two against three: 2048 x 1280 x 1280
+    // with residual 21 -> 18 us.  Up to two k-slabs have nothing to run ahead of.  A launch of two problems of different shapes takes
+    // at least three: its long tiles decide how long it lasts (8192 x 640, k 640, beside 154 x 1280, k 2048: 31 -> 27 us).
     if constexpr (TMW == 1) {
-        const int nslab = g.k / BK / ksplit;
-        if (total <= kDeepTiles && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 6>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
-        else if ((total <= 2 * kDeepTiles || gg.n2) && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 3>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+        const int nslab = g.k / BK / ksplit, cus = hyb_cu_count();
+        if (total <= cus && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 6>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
+        else if ((total <= 2 * cus || gg.n2) && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 3>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
         else hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 2>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
     } else {
         hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, TMW, 2>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
@@ -577,11 +575,7 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     // rows (from 32 on the k split of such launches depends on the rows as well).
     const bool two_res = epi == EPI_GATE_RES && (g.p[0].res2 || (g.count > 1 && g.p[1].res2));
     if (!has_form || nslab < (epi == EPI_GATE_RES && !two_res ? kLargeTileMinSlabs192 : kLargeTileMinSlabsOneRound)) return 0;
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) cus = 256;
-    }
+    const int cus = hyb_cu_count();
     long best = 0;
     int rows = 0;
     for (int h = 256; h >= (epi == EPI_GATE_RES ? 192 : 256); h -= 64) {

@@ -150,12 +150,12 @@ extern "C" int hyb_sdxl_block_forward(const hyb_sdxl_block_desc* desc, const hyb
         pq.a = h; pq.w = w->w_q2; pq.q = ws + L.q;
         pq.tokens = T; pq.tok_offset = 0; pq.n_total = T; pq.heads = d.heads;
         if (dt == HYB_BF16) pq.q_scale = kQScale;
-        const int kSlots = 512;
-        const int left = kSlots - 1 - (hyb_gemm_mfma_tiles(B * S, 2 * C) - 1) % kSlots;   // slots in the last round of keys and values
+        const int slots = 2 * hyb_cu_count();
+        const int left = slots - 1 - (hyb_gemm_mfma_tiles(B * S, 2 * C) - 1) % slots;   // slots in the last round of keys and values
         const int longest = 6 * C > 4096 ? 6 * C : (C >= 640 ? 4096 : 3072);
         const bool undivided = dt == HYB_BF16 && d.ctx_dim % 64 == 0 && d.ctx_dim <= longest;
         if (undivided) qg.splitk_ws = kv.splitk_ws = nullptr;
-        if (undivided && (left >= kSlots / 4 || hyb_gemm_mfma_tiles(M, C) <= left)) {
+        if (undivided && (left >= slots / 4 || hyb_gemm_mfma_tiles(M, C) <= left)) {
             kv.count = 2; kv.p[1] = pq; kv.n2 = C; kv.k2 = C;
             if ((rc = hyb_launch_gemm(kv, dt, dt, EPI_QKV, st))) return rc;
         } else {
