@@ -25,7 +25,9 @@
  *  - Linear weights are stored [out_features, in_features] row-major; biases are fp32.
  *  - Token tensors are token-major [batch, tokens, features].
  *  - Results are deterministic and batch-invariant: a sample's result does not depend on
- *    its batch index or on what else is in the batch (no floating-point atomics).
+ *    its batch index or on what else is in the batch (no floating-point atomics).  One exception: the bf16
+ *    stage block of the U-Net shape with 512 channels or more, or a long context feature axis, splits sums over k by the
+ *    number of rows, so the last bits of a sample may depend on the batch size there.
  */
 #ifndef HYB_H
 #define HYB_H
@@ -174,7 +176,7 @@ int hyb_adaln_modulation(const void* w, const float* bias, const float* temb, fl
 /* out[b, n, :] = LN(x[b, n, :]) * (1 + scale[b, :]) + shift[b, :], LN over the feature axis with
  * biased variance and no affine.  x: device float[batch, tokens, hidden]; shift, scale: device
  * float, element (b, j) at shift[b * mod_stride + j]; out: device [batch, tokens, hidden] of
- * `out_dtype`.  shift == scale == NULL gives the plain LayerNorm.  hidden % 4 == 0, <= 8192. */
+ * `out_dtype`.  shift == scale == NULL gives the plain LayerNorm.  hidden % 4 == 0, <= 2048. */
 int hyb_layernorm_modulate(const float* x, const float* shift, const float* scale, size_t mod_stride,
                            void* out, int batch, int tokens, int hidden, float eps,
                            hyb_dtype out_dtype, void* stream);

@@ -8,14 +8,14 @@
 // token per lane).  The 16 x 16 x 32 form is used because it is the cheaper one on this chip: it
 // moves half the accumulator bytes per multiply-add of the 32 x 32 x 16 form, and under the power
 // limit that sets the clock of these kernels the main loop runs 5-6 % faster with it (QKV-shaped and
-// fc1 launches of the SD3-shaped workload); the sums come out bit for bit the same as with the
-// 32 x 32 x 16 form that the large-tile kernel uses (the tests compare the two kernels' outputs).
+// fc1 launches of the SD3-shaped workload), with the same bits.
 //
 // Main loop: k is cut into slabs of 64.  A slab of both operands (128 + 128 rows of 128 bytes) is
 // copied global -> LDS by 16-byte direct-to-LDS buffer loads (buffer_load_dwordx4 ... lds: a wave fills 1 KB
 // of LDS per instruction, no VGPR staging, no ds_write; the slab's byte offset is the scalar operand and the
 // per-lane offsets are loop invariants, so a slab costs no vector address arithmetic), double buffered (launches of few
-// tiles: three or six buffers, see launch_tiles): the copy of slab s + 1 runs while slab s is multiplied.  LDS rows are unpadded; the 16-byte slots of a row are XOR-swizzled
+// tiles: three or six buffers, see launch_tiles): the copy of slab s + 1 runs while slab s is multiplied.  LDS rows are
+// unpadded; the 16-byte slots of a row are XOR-swizzled
 // with (row ^ row >> 3) & 7 so that the 16-byte fragment reads that are served together hit distinct
 // banks (the swizzle is applied on the global side: each lane picks which 16 bytes it fetches).
 // Waits on the copies are explicit (s_waitcnt vmcnt + s_barrier); a full __syncthreads() would
@@ -27,18 +27,19 @@
 // buffers) and written out row-contiguously, 16 bytes per lane, so that global stores and the
 // residual reads are whole 128-byte lines.  (Storing straight from the MFMA layout issues 8-byte
 // pieces to 32 different rows per instruction; at these sizes that made the epilogue cost a third
-// of the tile time.)  What the epilogue reads from global memory is requested where the latency is
-// hidden: the tile's bias and gate values at the start of the tile (parked in LDS behind the slab
-// buffers), the residual during the last k-slab; every such access uses clamped addresses instead
-// of predicates, and the staging loops are free of branches.  (With a branch that chooses between
+// of the tile time.)  What the epilogue reads from global memory is requested early: the tile's bias and gate values
+// at the start of the tile (parked in LDS behind the slab buffers), the residual during the last k-slab; every such access uses clamped
+// addresses instead of predicates, and the staging loops are free of branches.  (The start is not as well hidden as it could
+// be: the compiler waits for bias and gate before the first slab copy in the gate + residual forms and in some of the others,
+// and with three buffers, or six and a bf16 output, it waits for all of the prologue's copies before it parks the bias.)  (With a branch that chooses between
 // a global and an LDS source inside the loop, the compiler waits for ALL outstanding global loads
 // before every LDS read.)
 //
 // Up to two problems with the same (n, k) share a launch (image and text stream of a joint
-// block), the smaller one first; the two of a QKV launch may differ in (n, k), in the caller's order.  Tile order: plain, or one run of consecutive tiles per XCD when
-// there are few tile columns (see the kernel).  Ragged edges: row / feature indices are clamped on load and masked on store.  The
-// reduction order over k is fixed and a token's result does not depend on its tile row, so
-// results are deterministic and batch-invariant.
+// block), the smaller one first; the two of a QKV launch may differ in (n, k), in the caller's order.  Tile order: plain, or
+// runs of consecutive tiles per XCD when there are few tile columns (see the kernel).  Ragged edges: row / feature indices are
+// clamped on load and masked on store.  The reduction order over k is fixed and a token's result does not depend on its tile
+// row, so results are deterministic, and batch-invariant where k is not split (the number of shares follows from the rows).
 #include "gemm.h"
 
 #include <type_traits>
@@ -196,11 +197,11 @@ __global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_ker
             wfr[ks][t] = *reinterpret_cast<const bf16x8*>(base + w_base[((2 * ks) ^ t) & 3] + t * 16 * ROWB);
     };
 
-    // Main loop.  Slab s sits in stage s % 2.  ONE barrier per slab, before its second k-step: by then every wave has
-    // issued (and, after the lgkmcnt wait, completed) all its reads of slab s, so stage s % 2 can be refilled with
-    // slab s + 2 right behind the barrier, and the copy of slab s + 1 (issued one slab earlier) is awaited just
+    // Main loop.  Slab s sits in stage s % NST.  ONE barrier per slab, before its second k-step: by then every wave has
+    // issued (and, after the lgkmcnt wait, completed) all its reads of slab s, so stage s % NST can be refilled with
+    // slab s + NST right behind the barrier, and the copy of slab s + 1 (issued NST - 1 slabs earlier) is awaited just
     // before it, so that the second k-step can already fetch the first fragments of slab s + 1.
-    // Epilogue operands are fetched where their latency is hidden.  Bias and gate of the tile's 128 columns:
+    // Epilogue operands are requested early.  Bias and gate of the tile's 128 columns:
     // one value per thread now, parked in LDS behind the slab buffers once the first slab's wait has passed.
     // (The gate row must be the same for all rows of the tile; tiles that straddle samples read it from
     // global memory in the epilogue.)
@@ -558,9 +559,10 @@ int launch_epi(const GemmGroup& g, hipStream_t st) {
 // (measured at k = 1536 inside the step: out-projection 35.0 against 35.4 us in one round, fc1 110 against 98 us in
 // four rounds).
 constexpr int kLargeTileMinSlabs = 48;          // launches of several rounds
-constexpr int kLargeTileMinSlabs192 = 20;       // 192-row tiles in one round, whose launch has 64-row tiles otherwise: a 512 x 512 step of 8
-                                                // blocks (out-projection 2714 x 1536, 24 slabs) 2401 -> 2385 us; with ten slabs (8192 x 640,
-                                                // the 640-channel stage) 3350 us either way
+// 192-row tiles in one round, whose launch has 64- or 128-row tiles otherwise; time against those at 176-256 tiles of seven shapes with gate
+// and residual (2050-8192 rows): ten slabs 0.90-1.13, 16 slabs 0.86-1.06, 18 slabs 0.85-1.01, 20 slabs 0.73-0.95, 24 slabs
+// 0.77-0.94, 31 slabs 0.75-0.87 (a 512 x 512 step of 8 blocks, out-projection 2714 x 1536 with 24 slabs: 2401 -> 2385 us).
+constexpr int kLargeTileMinSlabs192 = 20;
 constexpr int kLargeTileMinSlabsOneRound = 32;  // launches of one round (the SDXL-shaped down-projection, k = 2560)
 // Tile height: 256 or 192 rows, whichever makes the launch shorter (rounds of tiles times the height; a CU holds one tile);
 // 192 for the gate + residual epilogue only, the one that the blocks' long-k launches have.

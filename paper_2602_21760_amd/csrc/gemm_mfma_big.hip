@@ -1,7 +1,8 @@
 // Large-tile bf16 MFMA GEMM for gfx950: the same contraction as gemm_mfma.hip (out = epilogue(A W^T + bias),
 // A [m, k] tokens x features-in, W [n, k] features-out x features-in, fp32 accumulation in
 // v_mfma_f32_16x16x32_bf16, k in slabs of 64, identical order of accumulation, so a token's result has the
-// same bits whichever of the two kernels computes it), for long-k launches with enough 256 x 128 tiles for the chip.
+// same bits whichever of the two kernels computes it, but for a second residual, which this one adds after the first), for
+// long-k launches with enough 256 x 128 tiles for the chip.
 //
 // Why a second geometry.  With 128 x 128 tiles, two workgroups per CU, a launch of 420 tiles and 96 k-slabs (the
 // SD3-shaped fc2: n = 1536, k = 6144) is one round in which 164 CUs carry two tiles and 92 carry one, every tile pays
@@ -197,8 +198,8 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
         }
     };
 
-    // Epilogue operands where their latency hides: bias and gate of the tile's columns now (parked in LDS behind the
-    // slab buffers once the first slab has landed).  The gate row must be the same for all rows of the tile; tiles
+    // Epilogue operands early: bias and gate of the tile's columns now (parked in LDS behind the slab buffers once the first
+    // slab has landed; with gate + residual, and with a bf16 output, the compiler waits for them before the first copy).  The gate row must be the same for all rows of the tile; tiles
     // that straddle gate rows (samples) read it from global memory in the epilogue.
     bool gate_in_lds = true;   // no gate: ones
     if constexpr (EPI == EPI_GATE_RES) {

@@ -47,8 +47,9 @@ struct LnArgs {
     float eps;
 };
 
-// What bounds it: all rows of a launch are resident at once (one wave each), so a launch takes as long as one wave's chain
-// of memory latencies.  The row's vectors are therefore requested together (NV = vectors per lane is a template parameter,
+// What bounds it: up to some thousand rows are resident at once (one wave each: 5120 rows of 1536, five waves per SIMD; more of
+// shorter rows), and a launch of that many takes as long as one wave's chain of memory latencies; longer ones go
+// through in several such turns.  The row's vectors are therefore requested together (NV = vectors per lane is a template parameter,
 // addresses past the row's end are clamped: a load under a condition is waited for inside its branch, one latency per
 // vector), and shift and scale before the reductions.  4429 rows of 1536 inside a step 11.1 -> 9.4 us, 2048 rows of 1280
 // 6.9 -> 5.3 us (2.0 -> 3.0 TB/s).
@@ -140,7 +141,9 @@ __global__ __launch_bounds__(256) void layernorm_kernel(LnArgs a) {
 // ------------------------------------------------------------------------------------------
 constexpr int kAdaMaxBatch = 4;
 constexpr int kAdaRowsPerWave = 4;
-constexpr int kAdaWaves = 256 * 32;   // waves in flight: 32 per CU
+// Waves of a launch at most, 32 for each of 256 CUs.  As many are resident at once only for one sample in bf16; the others' registers leave room for
+// five to seven eighths of them (and 64 KB of activations, four samples of 4096, for two workgroups per CU), and the rest start as those end.
+constexpr int kAdaWaves = 256 * 32;
 
 // Eight weights of a row as they come from memory (streamed once per call: non-temporal loads, which do not displace what
 // the caches hold), and as fp32.
@@ -600,7 +603,7 @@ extern "C" int hyb_adaln_modulation(const void* w, const float* bias, const floa
     HYB_CHECK_PTR(w); HYB_CHECK_PTR(bias); HYB_CHECK_PTR(temb); HYB_CHECK_PTR(out);
     HYB_CHECK_ALIGN(w); HYB_CHECK_ALIGN(bias); HYB_CHECK_ALIGN(temb); HYB_CHECK_ALIGN(out);
     hipStream_t st = (hipStream_t)stream;
-    // as many groups of rows for every wave, as few as keep the waves to those in flight
+    // as many groups of rows for every wave, as few as keep the waves to kAdaWaves
     const int groups = (rows + kAdaRowsPerWave - 1) / kAdaRowsPerWave, each = (groups + kAdaWaves - 1) / kAdaWaves;
     const dim3 grid(((groups + each - 1) / each + 3) / 4), block(256);
     HybTraceScope trace("adaln_modulation", "byte", (double)rows * hidden * hyb_dtype_size(dtype) * ((batch + kAdaMaxBatch - 1) / kAdaMaxBatch), st);

@@ -3,7 +3,7 @@
 //   g = GroupNorm32(x);  a = g + SelfAttn(LN(g));  b = a + CrossAttn(LN(a), ctx);
 //   out = x + b + W2 (u * GELUerf(gate)) + b2,  [u, gate] = LN(b) W1^T + b1
 // Thirteen launches: GroupNorm statistics (two), GroupNorm + LN, fused QKV GEMM (head-major scatter), self-attention, out-projection
-// (+ residual), LN, Q GEMM together with the K/V GEMM on the text context, cross-attention, out-projection (+ residual),
+// (+ residual), LN, Q GEMM (together with the K/V GEMM on the text context where that pays), cross-attention, out-projection (+ residual),
 // LN, GEGLU GEMM, down-projection (+ both residuals; a k split adds its merge).
 #include "attention.h"
 #include "gemm.h"
