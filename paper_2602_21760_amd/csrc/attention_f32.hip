@@ -13,7 +13,7 @@
 //   S: a 16-byte load gives the lane 4 features of its key (query) row, which feed 4 MFMAs;
 //   PV: register i of the exponentiated S^T is the B operand of the MFMA over keys {4 q4 + i}, and the matching V operand
 //       is one 16-byte load of row 4 q4 + i: the lane's features 4 l16 .. 4 l16 + 3 are row l16 of the output tiles 0 .. 3.
-// Measured: batch 2, 12 heads, 653 tokens 41 us (64 TFLOP/s); one wave per query row on the vector ALU took 453 us.
+// Measured: batch 2, 12 heads, 653 tokens 41 us by itself, 43 us inside a model (64 and 60 TFLOP/s); one wave per query row on the vector ALU took 453 us.
 #include "attention.h"
 
 namespace {

@@ -470,7 +470,7 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
     // takes more slab buffers, six when every workgroup can have a CU of its own, three for up to two per CU.
     // Two against six: 333 x 1536 x 4096 49 -> 26 us, one row x 1536 x 1536 24 -> 13 us; two against three: 2048 x 1280 x 1280
     // with residual 21 -> 18 us.  Up to two k-slabs have nothing to run ahead of.  A launch of two problems of different shapes takes
-    // at least three: its long tiles decide how long it lasts (8192 x 640, k 640, beside 154 x 1280, k 2048: 31 -> 27 us).
+    // at least three: its long tiles decide how long it lasts (8192 x 640, k 640, beside 154 x 1280, k 2048: 31 -> 27 us, 24 us with tile runs of their own).
     if constexpr (TMW == 1) {
         const int nslab = g.k / BK / ksplit, cus = hyb_cu_count();
         if (total <= cus && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 6>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);
