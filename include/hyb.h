@@ -24,10 +24,11 @@
  *    and the residual stream are fp32.  dtype HYB_F32: everything is fp32.
  *  - Linear weights are stored [out_features, in_features] row-major; biases are fp32.
  *  - Token tensors are token-major [batch, tokens, features].
- *  - Results are deterministic and batch-invariant: a sample's result does not depend on
- *    its batch index or on what else is in the batch (no floating-point atomics).  One exception: the bf16
- *    stage block of the U-Net shape with 512 channels or more, or a long context feature axis, splits sums over k by the
- *    number of rows, so the last bits of a sample may depend on the batch size there.
+ *  - Results are deterministic and batch-invariant: a sample's result does not depend on its batch index or on what
+ *    else is in the batch (no floating-point atomics).  How many samples there are may decide its last bits where bf16
+ *    launches split sums by their size: attention with scratch (the _ws and _prescaled forms and hyb_block_forward cut some query
+ *    blocks along the keys), and the stage block of the U-Net shape with 512 channels or more, or with a long context feature
+ *    axis (GEMMs split along k).
  */
 #ifndef HYB_H
 #define HYB_H

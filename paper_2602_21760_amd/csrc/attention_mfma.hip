@@ -45,7 +45,8 @@
 // reference (0 or the running maximum) like any other, and the merge treats both alike.
 // The normaliser is the sum of the bf16-rounded probabilities that enter the second contraction (v_dot2 with
 // ones).  Tail keys are masked to -inf before the softmax; tail query rows are clamped on load
-// and not stored.  The reduction order is fixed: results are deterministic and batch-invariant.
+// and not stored.  The reduction order is fixed: results are deterministic and, but for the split tail, whose cuts follow from
+// the number of (sample, head) pairs, independent of the batch size.
 //
 // Split tail.  All workgroups of a launch are usually resident at once (4 per CU), and a CU with 4 of
 // them takes a quarter longer than one with 3.  When an XCD holds a few more workgroups than a multiple
