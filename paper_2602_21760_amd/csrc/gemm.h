@@ -55,7 +55,8 @@ int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipSt
 // 128 x 128 tiles of an m x n product (two of them fit a CU).
 int hyb_gemm_mfma_tiles(int m, int n);
 // Large-tile bf16 MFMA kernel (256 x 128 or 192 x 128 tiles, one workgroup per CU).  Same accumulation order as the kernel above, hence
-// the same bits per token, but for the order in which a second residual is added (from 32 k-slabs on).  -1 when the shape or the epilogue has no large-tile form.
+// the same bits per token, but for the order in which a second residual is added (from 32 k-slabs on).  -1 when the shape or
+// the epilogue has no large-tile form.
 int hyb_launch_gemm_mfma_big(const GemmGroup& g, hyb_dtype out_dtype, int epi, int rows, hipStream_t st);
 // Dispatch: the MFMA kernel of the operand type when it takes the shape, else the plain kernel.
 int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st);

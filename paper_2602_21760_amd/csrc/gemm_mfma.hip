@@ -29,9 +29,10 @@
 // pieces to 32 different rows per instruction; at these sizes that made the epilogue cost a third
 // of the tile time.)  What the epilogue reads from global memory is requested early: the tile's bias and gate values
 // at the start of the tile (parked in LDS behind the slab buffers), the residual during the last k-slab; every such access uses clamped
-// addresses instead of predicates, and the staging loops are free of branches.  (The start is not as well hidden as it could
-// be: the compiler waits for bias and gate before the first slab copy in the gate + residual forms and in some of the others,
-// and with three buffers, or six and a bf16 output, it waits for all of the prologue's copies before it parks the bias.)  (With a branch that chooses between
+// addresses instead of predicates, and the staging loops are free of branches.  The start is not as well hidden as it could
+// be: the compiler waits for bias and gate before the first slab copy in the gate + residual forms and in some of the
+// others, and with three buffers, or six and a bf16 output, it waits for all of the prologue's copies before it parks the
+// bias.  (With a branch that chooses between
 // a global and an LDS source inside the loop, the compiler waits for ALL outstanding global loads
 // before every LDS read.)
 //
@@ -470,7 +471,8 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
     // takes more slab buffers, six when every workgroup can have a CU of its own, three for up to two per CU.
     // Two against six: 333 x 1536 x 4096 49 -> 26 us, one row x 1536 x 1536 24 -> 13 us; two against three: 2048 x 1280 x 1280
     // with residual 21 -> 18 us.  Up to two k-slabs have nothing to run ahead of.  A launch of two problems of different shapes takes
-    // at least three: its long tiles decide how long it lasts (8192 x 640, k 640, beside 154 x 1280, k 2048: 31 -> 27 us, 24 us with tile runs of their own).
+    // at least three: its long tiles decide how long it lasts (8192 x 640, k 640, beside 154 x 1280, k 2048: 31 -> 27 us, 24 us
+    // with tile runs of their own).
     if constexpr (TMW == 1) {
         const int nslab = g.k / BK / ksplit, cus = hyb_cu_count();
         if (total <= cus && nslab > 2) hipLaunchKernelGGL((gemm_mfma_kernel<OT, EPI, 1, 6>), dim3(grid), dim3(256), 0, st, gg, tiles_n, t0, total, xcd_run, ksplit);

@@ -199,7 +199,8 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmGroup g, int tiles
     };
 
     // Epilogue operands early: bias and gate of the tile's columns now (parked in LDS behind the slab buffers once the first
-    // slab has landed; with gate + residual, and with a bf16 output, the compiler waits for them before the first copy).  The gate row must be the same for all rows of the tile; tiles
+    // slab has landed; with gate + residual, and with a bf16 output, the compiler waits for them before the first copy).
+    // The gate row must be the same for all rows of the tile; tiles
     // that straddle gate rows (samples) read it from global memory in the epilogue.
     bool gate_in_lds = true;   // no gate: ones
     if constexpr (EPI == EPI_GATE_RES) {
