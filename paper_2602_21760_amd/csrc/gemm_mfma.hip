@@ -593,6 +593,63 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     return rows;
 }
 
+// Estimated length of a launch in us: rounds of tiles times (k-slabs x slab + fixed), from the launches' own times over 216 shapes
+// (300-33000 rows; 640-1536 in, 640-6144 out; each tile shape forced): within 4-13 % of what was measured.  A partial last round is a
+// whole one where a CU holds one workgroup; where it holds two or three, those that have it to themselves are faster.
+struct TileCost { float slab, fixed; };
+enum { COST_64, COST_128, COST_BIG_256, COST_BIG_192, COST_WIDE_128, COST_WIDE_192, COST_WIDE_256, COST_KINDS };
+const TileCost kTileCost[4][COST_KINDS] = {
+    /* bias, QKV       */ {{0.70f, 3.0f}, {0.74f, 6.5f}, {}, {}, {0.68f, 3.0f}, {0.76f, 8.0f}, {1.12f, 7.5f}},
+    /* GELU            */ {{0.74f, 3.0f}, {0.90f, 5.0f}, {}, {}, {0.64f, 7.0f}, {1.02f, 7.5f}, {1.04f, 13.0f}},
+    /* GEGLU           */ {{0.74f, 3.0f}, {0.70f, 7.0f}, {}, {}, {0.90f, 2.0f}, {0.96f, 7.0f}, {1.10f, 10.0f}},
+    /* gate + residual */ {{0.56f, 5.5f}, {1.12f, 7.0f}, {0.72f, 19.5f}, {0.70f, 6.0f}, {0.80f, 3.5f}, {1.00f, 9.5f}, {1.24f, 12.5f}},
+};
+
+float launch_us(const GemmGroup& g, int epi, int kind) {
+    static const int rows_of[COST_KINDS] = {64, 128, 256, 192, 128, 192, 256};
+    const int row = epi == EPI_GELU_TANH ? 1 : (epi == EPI_GEGLU ? 2 : (epi == EPI_GATE_RES ? 3 : 0));
+    const int rows = rows_of[kind], cols = (kind >= COST_WIDE_128 ? 256 : 128) / (epi == EPI_GEGLU ? 2 : 1);
+    long tiles = 0;
+    for (int i = 0; i < g.count; i++) tiles += (long)((g.p[i].m + rows - 1) / rows) * ((g.n + cols - 1) / cols);
+    const long slots = (long)hyb_cu_count() * (kind == COST_64 ? 3 : (kind == COST_128 ? 2 : 1));
+    const long full = tiles / slots, rest = tiles - full * slots;
+    const float part = (float)rest / (float)slots;
+    const float rounds = (float)full + (rest == 0 ? 0.f : (kind == COST_64 ? 0.55f + 0.45f * part : (kind == COST_128 ? 0.62f + 0.38f * part : 1.f)));
+    const TileCost& c = kTileCost[row][kind];
+    return 2.f + rounds * ((float)(g.k / BK) * c.slab + c.fixed);
+}
+
+// Rows of the 256-column tiles (gemm_mfma_wide.hip) if they shorten the launch by a twentieth at least against what it takes
+// otherwise, else 0.  `large_rows`: the 128-column large tiles that large_tile_rows() picked, 0: 64 or 128 rows of the kernel above.
+int wide_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_rows) {
+    const bool f32 = out_dtype == HYB_F32;
+    const int nslab = g.k / BK;
+    if (g.n2 || nslab < 3) return 0;
+    if (epi == EPI_GATE_RES) {
+        // (long launches short of 64 slabs have their place on the 128-column tiles by tests)
+        if (!f32 || (nslab >= kLargeTileMinSlabsOneRound && nslab < 64)) return 0;
+    } else {
+        if (f32 || (epi != EPI_BIAS && epi != EPI_GELU_TANH && epi != EPI_QKV && epi != EPI_GEGLU)) return 0;
+        if ((epi == EPI_BIAS || epi == EPI_GELU_TANH) && nslab >= kLargeTileMinSlabsOneRound) return 0;
+    }
+    int other = large_rows == 256 ? COST_BIG_256 : COST_BIG_192;
+    if (!large_rows) {
+        const int tile_cols = epi == EPI_GEGLU ? BN / 2 : BN, tiles_n = (g.n + tile_cols - 1) / tile_cols;
+        int tiles128 = 0;
+        for (int i = 0; i < g.count; i++) tiles128 += (g.p[i].m + 127) / 128 * tiles_n;
+        if (tiles128 <= kSmallGridTiles && epi != EPI_GEGLU &&
+            (choose_ksplit(g, tiles128, 512) > 1 || choose_ksplit(g, (g.p[0].m + 63) / 64 * tiles_n, 768) > 1)) return 0;
+        other = tiles128 <= kSmallGridTiles ? COST_64 : COST_128;
+    }
+    float best = 0.95f * launch_us(g, epi, other);
+    int rows = 0;
+    for (int kind = COST_WIDE_128; kind <= COST_WIDE_256; kind++) {
+        const float us = launch_us(g, epi, kind);
+        if (us < best) { best = us; rows = 128 + 64 * (kind - COST_WIDE_128); }
+    }
+    return rows;
+}
+
 }  // namespace
 
 int hyb_gemm_mfma_tiles(int m, int n) { return ((m + 127) / 128) * ((n + BN - 1) / BN); }
@@ -611,7 +668,9 @@ int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipSt
         if (epi == EPI_QKV && (p.heads <= 0 || n % (p.heads * 64) != 0 || n / (p.heads * 64) > 3)) return -1;
     }
     const bool f32 = out_dtype == HYB_F32;
-    if (const int rows = large_tile_rows(g, out_dtype, epi)) {
+    const int rows = large_tile_rows(g, out_dtype, epi);
+    if (const int wide = wide_tile_rows(g, out_dtype, epi, rows)) return hyb_launch_gemm_mfma_wide(g, out_dtype, epi, wide, st);
+    if (rows) {
         const int rc = hyb_launch_gemm_mfma_big(g, out_dtype, epi, rows, st);
         if (rc >= 0) return rc;
     }

@@ -467,6 +467,49 @@ def test_linear_192_row_tiles(hb, m, n, slabs):
     assert torch.equal(x, out)
 
 
+@pytest.mark.parametrize("epi,m,n,slabs,rows", [
+    ("bias", 2700, 4608, 3, 128), ("bias", 2714, 4600, 24, 256), ("gelu", 4429, 6144, 9, 256), ("bias", 3072, 4096, 12, 192), ("gelu", 2714, 6152, 17, 192),
+    ("bias", 2048, 4096, 7, 128), ("bias", 1920, 3848, 20, 128), ("geglu", 8200, 2560, 10, 256), ("geglu", 2000, 5128, 20, 192), ("geglu", 1500, 2568, 9, 128),
+    ("gate", 16700, 1536, 24, 256), ("gate", 6537, 1544, 24, 192), ("gate", 4429, 1536, 18, 128), ("gate", 8858, 1536, 65, 256)])
+def test_linear_256_column_tiles(hb, epi, m, n, slabs, rows):
+    """Launches that take 256-column tiles, by the launch rule's lines: even and odd numbers of k-slabs, ragged rows and columns, gate rows that change
+    inside a tile, in place; against the oracle (fp32 outputs: bf16 products are exact in fp32, the bound of fp32 sums; bf16 outputs: half
+    a unit in the last place per element), and the first rows alone get the same bits from the small tiles."""
+    k = 64 * slabs
+    a, w, b = _data(500 + slabs, (m, k), "bf16"), _data(501, (2 * n if epi == "geglu" else n, k), "bf16", 0.02), _data(502, (2 * n if epi == "geglu" else n,), "f32", 0.02)
+    da, dw, db = dev(a, torch.bfloat16), dev(w, torch.bfloat16), dev(b)
+    code = {"bias": hb.HYB_EPI_BIAS, "gelu": hb.HYB_EPI_GELU_TANH, "geglu": hb.HYB_EPI_GEGLU, "gate": hb.HYB_EPI_GATE_RESIDUAL}[epi]
+    out_dt = torch.float32 if epi == "gate" else torch.bfloat16
+    kw, x = {}, None
+    pick = np.unique(np.concatenate([np.arange(0, m, 211), np.arange(m - 70, m), np.arange(1495, min(m, 1505))]))
+    y = O.linear(a[pick], w, b)
+    if epi == "gate":
+        res, gate = _data(503, (m, n), "f32"), _data(504, (m // 1500 + 1, n), "f32")
+        x = dev(res)
+        kw = dict(residual=x.clone(), gate=dev(gate), rows_per_gate=1500, gate_stride=n)
+        y = res[pick] + gate[pick // 1500] * y
+    elif epi == "geglu":
+        y = y[:, :n] * O.gelu_erf(y[:, n:])
+    elif epi == "gelu":
+        y = O.gelu_tanh(y)
+    out, small = torch.empty(m, n, device="cuda", dtype=out_dt), torch.empty(100, n, device="cuda", dtype=out_dt)
+    hb.hyb_trace_enable(True)
+    hb.hyb_linear(da, dw, db, out, code, **kw)
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert list(names) == ["gemm_mfma_%dx256.epi%d.n%d.k%d" % (rows, code, n, k)], names
+    assert err(host(out)[pick], y) < (1e-5 if epi == "gate" else 2.0 ** -9)
+    if kw:
+        kw["residual"] = x[:100].clone()
+    hb.hyb_linear(da[:100], dw, db, small, code, **kw)
+    assert torch.equal(out[:100], small)
+    if kw:
+        kw["residual"] = x
+        hb.hyb_linear(da, dw, db, x, code, **kw)
+        assert torch.equal(x, out)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("rows,hidden,batch", [(1, 8, 1), (3, 504, 2), (37, 520, 3), (32769, 64, 4), (70003, 1032, 5), (130, 4096, 4)])
 def test_adaln_modulation_row_groups(hb, dt, rows, hidden, batch):
