@@ -58,9 +58,15 @@ int hyb_gemm_mfma_tiles(int m, int n);
 // the same bits per token, but for the order in which a second residual is added (from 32 k-slabs on).  -1 when the shape or
 // the epilogue has no large-tile form.
 int hyb_launch_gemm_mfma_big(const GemmGroup& g, hyb_dtype out_dtype, int epi, int rows, hipStream_t st);
-// 256-column tiles of `rows` (128, 192 or 256) tokens, one workgroup of eight waves per CU; bf16 output with bias, GELU-tanh, QKV scatter or
+// Tiles of a launch of 256-column tiles: the first tall_rows[i] tile rows of problem i are `tall` tokens high, the others `shrt`
+// (256 and 192, or 192 and 128).
+struct WidePlan {
+    int tall, shrt;
+    int tall_rows[kMaxGroup];
+};
+// 256-column tiles, one workgroup of eight waves per CU; bf16 output with bias, GELU-tanh, QKV scatter or
 // GEGLU, fp32 output with gate * y + residual(s); at least three k-slabs of 64.  Same bits as the 64- and 128-row tiles.
-int hyb_launch_gemm_mfma_wide(const GemmGroup& g, hyb_dtype out_dtype, int epi, int rows, hipStream_t st);
+int hyb_launch_gemm_mfma_wide(const GemmGroup& g, hyb_dtype out_dtype, int epi, const WidePlan& plan, hipStream_t st);
 // Dispatch: the MFMA kernel of the operand type when it takes the shape, else the plain kernel.
 int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st);
 

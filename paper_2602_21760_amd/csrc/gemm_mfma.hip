@@ -593,61 +593,125 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     return rows;
 }
 
-// Estimated length of a launch in us: rounds of tiles times (k-slabs x slab + fixed), from the launches' own times over 216 shapes
-// (300-33000 rows; 640-1536 in, 640-6144 out; each tile shape forced): within 4-13 % of what was measured.  A partial last round is a
-// whole one where a CU holds one workgroup; where it holds two or three, those that have it to themselves are faster.
+// Estimated length of a launch in us, from the launches' own times over 216 shapes (300-33000 rows; 640-1536 in, 640-6144 out;
+// each tile shape forced): within 3-8 % of what was measured.  A tile costs k-slabs x slab + fixed.
 struct TileCost { float slab, fixed; };
-enum { COST_64, COST_128, COST_BIG_256, COST_BIG_192, COST_WIDE_128, COST_WIDE_192, COST_WIDE_256, COST_KINDS };
+enum { COST_128, COST_BIG_256, COST_BIG_192, COST_WIDE_128, COST_WIDE_192, COST_WIDE_256, COST_KINDS };
 const TileCost kTileCost[4][COST_KINDS] = {
-    /* bias, QKV       */ {{0.70f, 3.0f}, {0.74f, 6.5f}, {}, {}, {0.68f, 3.0f}, {0.76f, 8.0f}, {1.12f, 7.5f}},
-    /* GELU            */ {{0.74f, 3.0f}, {0.90f, 5.0f}, {}, {}, {0.64f, 7.0f}, {1.02f, 7.5f}, {1.04f, 13.0f}},
-    /* GEGLU           */ {{0.74f, 3.0f}, {0.70f, 7.0f}, {}, {}, {0.90f, 2.0f}, {0.96f, 7.0f}, {1.10f, 10.0f}},
-    /* gate + residual */ {{0.56f, 5.5f}, {1.12f, 7.0f}, {0.72f, 19.5f}, {0.70f, 6.0f}, {0.80f, 3.5f}, {1.00f, 9.5f}, {1.24f, 12.5f}},
+    /* bias, QKV       */ {{0.83f, 6.0f}, {}, {}, {0.71f, 5.5f}, {0.95f, 6.0f}, {1.20f, 7.7f}},
+    /* GELU            */ {{0.89f, 5.5f}, {}, {}, {0.71f, 6.5f}, {0.95f, 7.5f}, {1.20f, 10.0f}},
+    /* GEGLU           */ {{0.86f, 5.5f}, {}, {}, {0.71f, 5.0f}, {0.95f, 6.0f}, {1.20f, 9.5f}},
+    /* gate + residual */ {{1.13f, 8.5f}, {0.72f, 19.5f}, {0.70f, 6.0f}, {0.71f, 7.0f}, {0.95f, 9.0f}, {1.20f, 14.0f}},
 };
+// 64-row tiles, up to three on a CU: (slab + shared x tiles on the CU) per slab
+const float kSmallTileCost[4][3] = {{0.08f, 0.26f, 2.5f}, {0.16f, 0.20f, 2.0f}, {0.28f, 0.14f, 2.5f}, {0.04f, 0.30f, 3.0f}};
 
-float launch_us(const GemmGroup& g, int epi, int kind) {
-    static const int rows_of[COST_KINDS] = {64, 128, 256, 192, 128, 192, 256};
-    const int row = epi == EPI_GELU_TANH ? 1 : (epi == EPI_GEGLU ? 2 : (epi == EPI_GATE_RES ? 3 : 0));
-    const int rows = rows_of[kind], cols = (kind >= COST_WIDE_128 ? 256 : 128) / (epi == EPI_GEGLU ? 2 : 1);
-    long tiles = 0;
-    for (int i = 0; i < g.count; i++) tiles += (long)((g.p[i].m + rows - 1) / rows) * ((g.n + cols - 1) / cols);
-    const long slots = (long)hyb_cu_count() * (kind == COST_64 ? 3 : (kind == COST_128 ? 2 : 1));
-    const long full = tiles / slots, rest = tiles - full * slots;
-    const float part = (float)rest / (float)slots;
-    const float rounds = (float)full + (rest == 0 ? 0.f : (kind == COST_64 ? 0.55f + 0.45f * part : (kind == COST_128 ? 0.62f + 0.38f * part : 1.f)));
-    const TileCost& c = kTileCost[row][kind];
-    return 2.f + rounds * ((float)(g.k / BK) * c.slab + c.fixed);
+int cost_row(int epi) { return epi == EPI_GELU_TANH ? 1 : (epi == EPI_GEGLU ? 2 : (epi == EPI_GATE_RES ? 3 : 0)); }
+
+float tile_us(const GemmGroup& g, int epi, int kind) {
+    const TileCost& c = kTileCost[cost_row(epi)][kind];
+    return (float)(g.k / BK) * c.slab + c.fixed;
 }
 
-// Rows of the 256-column tiles (gemm_mfma_wide.hip) if they shorten the launch by a twentieth at least against what it takes
-// otherwise, else 0.  `large_rows`: the 128-column large tiles that large_tile_rows() picked, 0: 64 or 128 rows of the kernel above.
-int wide_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_rows) {
+// Launch of 128-column tiles of 64, 128 (two on a CU), 192 or 256 rows (one on a CU).  Where tiles share a CU, those of a partial last
+// round, which have it to themselves, are faster.
+float launch_us(const GemmGroup& g, int epi, int rows, bool alone) {
+    const int cols = epi == EPI_GEGLU ? BN / 2 : BN;
+    long tiles = 0;
+    for (int i = 0; i < g.count; i++) tiles += (long)((g.p[i].m + rows - 1) / rows) * ((g.n + cols - 1) / cols);
+    const long cus = hyb_cu_count();
+    if (rows == 64) {
+        const float* c = kSmallTileCost[cost_row(epi)];
+        return 2.f + c[2] + (float)(g.k / BK) * (c[0] + c[1] * (float)((tiles + cus - 1) / cus));
+    }
+    if (alone) return 2.f + (float)((tiles + cus - 1) / cus) * tile_us(g, epi, rows == 256 ? COST_BIG_256 : COST_BIG_192);
+    const long full = tiles / (2 * cus), rest = tiles - full * 2 * cus;
+    return 2.f + ((float)full + (rest ? 0.4f + 0.6f * (float)rest / (float)(2 * cus) : 0.f)) * tile_us(g, epi, COST_128);
+}
+
+// Launch of `tall` and then `shrt` tiles of the given costs on one workgroup per CU, each taken by the first CU that is free.
+float two_height_us(long tall, long shrt, float tall_us, float short_us) {
+    const long cus = hyb_cu_count();
+    const float even = (float)(tall / cus) * tall_us;            // every CU is busy until then ...
+    const long ahead = tall % cus;                               // ... and these for one tall tile more
+    const float late = ahead ? even + tall_us : even;
+    if (shrt <= 0) return 2.f + late;
+    // until `even` + j short tiles the CUs that are not ahead take j each, the others what fits behind their tall tile
+    for (long j = shrt / cus;; j++) {
+        const float until = even + (float)j * short_us;
+        const long on_late = until > late ? (long)((until - late) / short_us + 1e-3f) : 0;
+        if ((cus - ahead) * j + ahead * on_late >= shrt) return 2.f + (until > late ? until : late);
+    }
+}
+
+// Plan of a launch of 256-column tiles (gemm_mfma_wide.hip) if that shortens the launch by 6 % at least against what it takes
+// otherwise, else plan.tall = 0.  Tiles of one height fill their last round by chance (16717 x 6144: 6.2 rounds
+// of 256 x 256); with the first rounds tall and the others short the CUs finish together (that launch 284 -> 273 us, 6537 x 6144 121 -> 115 us).
+// `large_rows`: the 128-column large tiles that large_tile_rows() picked, 0: 64 or 128 rows of the kernel above.
+WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_rows) {
+    WidePlan plan = {};
     const bool f32 = out_dtype == HYB_F32;
     const int nslab = g.k / BK;
-    if (g.n2 || nslab < 3) return 0;
+    if (g.n2 || nslab < 3) return plan;
     if (epi == EPI_GATE_RES) {
         // (long launches short of 64 slabs have their place on the 128-column tiles by tests)
-        if (!f32 || (nslab >= kLargeTileMinSlabsOneRound && nslab < 64)) return 0;
+        if (!f32 || (nslab >= kLargeTileMinSlabsOneRound && nslab < 64)) return plan;
     } else {
-        if (f32 || (epi != EPI_BIAS && epi != EPI_GELU_TANH && epi != EPI_QKV && epi != EPI_GEGLU)) return 0;
-        if ((epi == EPI_BIAS || epi == EPI_GELU_TANH) && nslab >= kLargeTileMinSlabsOneRound) return 0;
+        if (f32 || (epi != EPI_BIAS && epi != EPI_GELU_TANH && epi != EPI_QKV && epi != EPI_GEGLU)) return plan;
+        if ((epi == EPI_BIAS || epi == EPI_GELU_TANH) && nslab >= kLargeTileMinSlabsOneRound) return plan;
     }
-    int other = large_rows == 256 ? COST_BIG_256 : COST_BIG_192;
+    int other = large_rows;
     if (!large_rows) {
         const int tile_cols = epi == EPI_GEGLU ? BN / 2 : BN, tiles_n = (g.n + tile_cols - 1) / tile_cols;
         int tiles128 = 0;
         for (int i = 0; i < g.count; i++) tiles128 += (g.p[i].m + 127) / 128 * tiles_n;
         if (tiles128 <= kSmallGridTiles && epi != EPI_GEGLU &&
-            (choose_ksplit(g, tiles128, 512) > 1 || choose_ksplit(g, (g.p[0].m + 63) / 64 * tiles_n, 768) > 1)) return 0;
-        other = tiles128 <= kSmallGridTiles ? COST_64 : COST_128;
+            (choose_ksplit(g, tiles128, 512) > 1 || choose_ksplit(g, (g.p[0].m + 63) / 64 * tiles_n, 768) > 1)) return plan;
+        other = tiles128 <= kSmallGridTiles ? 64 : 128;
     }
-    float best = 0.95f * launch_us(g, epi, other);
-    int rows = 0;
-    for (int kind = COST_WIDE_128; kind <= COST_WIDE_256; kind++) {
-        const float us = launch_us(g, epi, kind);
-        if (us < best) { best = us; rows = 128 + 64 * (kind - COST_WIDE_128); }
+    float best = 0.94f * launch_us(g, epi, other, large_rows != 0);
+    const int cols = epi == EPI_GEGLU ? BN : 2 * BN, cus = hyb_cu_count();
+    const long tiles_n = (g.n + cols - 1) / cols;
+    const float us[3] = {tile_us(g, epi, COST_WIDE_128), tile_us(g, epi, COST_WIDE_192), tile_us(g, epi, COST_WIDE_256)};
+    auto take = [&](float t, int tall, int shrt, int rows0, int rows1) {
+        if (t >= best) return;
+        best = t;
+        plan.tall = tall; plan.shrt = shrt;
+        plan.tall_rows[0] = rows0; plan.tall_rows[1] = rows1;
+    };
+    for (int h = 2; h >= 0; h--) {
+        const int height = 128 + 64 * h;
+        int rows[kMaxGroup] = {0, 0};
+        for (int i = 0; i < g.count; i++) rows[i] = (g.p[i].m + height - 1) / height;
+        const float t = two_height_us((rows[0] + rows[1]) * tiles_n, 0, us[h], 0.f);
+        if (h > 0) take(t, height, height - 64, rows[0], rows[1]);
+        else take(t, 192, 128, 0, 0);
     }
-    return rows;
+    // Two heights only where the estimate says a twentieth: where some CUs are idle the others are faster (fewer share the memory system and
+    // the power), which takes part of the gain away (8192 x 2560 GEGLU, k 640, in two heights: estimated a tenth shorter, measured 68 us against 65-69 in one).
+    best *= 0.95f;
+    const int m0 = g.p[0].m, m1 = g.count > 1 ? g.p[1].m : 0;
+    const bool swap = m1 > m0;                                   // x: the problem of more rows, y: the other
+    const int mx = swap ? m1 : m0, my = swap ? m0 : m1;
+    for (int h = 2; h > 0; h--) {
+        const int tall = 128 + 64 * h, shrt = tall - 64;
+        const int all_x = (mx + tall - 1) / tall, all_y = (my + tall - 1) / tall;
+        for (int y = 0; y <= all_y; y += all_y ? all_y : 1) {          // the smaller problem is tiled in one height
+            const int short_y = y ? 0 : (my + shrt - 1) / shrt;
+            // tall tile rows of the larger problem: none, all, and about as many as fill whole rounds
+            bool last = false;
+            for (long r = 0; !last; r++)
+                for (int up = 0; up < 2; up++) {
+                    long x = (r * cus - y * tiles_n + (up ? tiles_n - 1 : 0)) / tiles_n;
+                    if (x < 0) x = 0;
+                    if (x >= all_x) { x = all_x; last = true; }
+                    const int rest = mx - (int)x * tall;
+                    const long short_x = rest > 0 ? (rest + shrt - 1) / shrt : 0;
+                    take(two_height_us((x + y) * tiles_n, (short_x + short_y) * tiles_n, us[h], us[h - 1]), tall, shrt, swap ? y : (int)x, swap ? (int)x : y);
+                }
+        }
+    }
+    return plan;
 }
 
 }  // namespace
@@ -669,7 +733,8 @@ int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipSt
     }
     const bool f32 = out_dtype == HYB_F32;
     const int rows = large_tile_rows(g, out_dtype, epi);
-    if (const int wide = wide_tile_rows(g, out_dtype, epi, rows)) return hyb_launch_gemm_mfma_wide(g, out_dtype, epi, wide, st);
+    const WidePlan wide = wide_plan(g, out_dtype, epi, rows);
+    if (wide.tall) return hyb_launch_gemm_mfma_wide(g, out_dtype, epi, wide, st);
     if (rows) {
         const int rc = hyb_launch_gemm_mfma_big(g, out_dtype, epi, rows, st);
         if (rc >= 0) return rc;

@@ -69,39 +69,28 @@ __device__ __forceinline__ void interleave() {
     }
 }
 
+// The workgroup's LDS: both slab buffers, each as three arrays, and the bias and gate values of the tile's columns.  (Members, not arrays of
+// pointers: an array indexed at run time would be kept in memory, and the compiler could no longer tell the buffers apart.)
+struct WideLds {
+    unsigned char *a0_s0, *a0_s1, *a1_s0, *a1_s1, *w_s0, *w_s1;
+    float* vec;
+};
+
 template <typename OT, int EPI, int TT>
-__global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmGroup g, int tiles_n, int tiles0, int total, int xcd_run) {
+__device__ __forceinline__ void wide_tile(const GemmProblem& p, int n, int k, int row0, int col0, const WideLds& lds) {
     using G = WideGeo<TT>;
-    constexpr int BM = G::BM, STAGE_BYTES = G::STAGE_BYTES, CPW = G::CPW;
+    constexpr int BM = G::BM, CPW = G::CPW;
+    constexpr int T0 = G::T0, T1 = G::T1, TM = T0 > T1 ? T0 : T1, AR0 = 32 * T0, AR1 = 32 * T1;
     constexpr bool GEGLU = EPI == EPI_GEGLU, RES = EPI == EPI_GATE_RES;
     constexpr int OCOLS = GEGLU ? BN / 2 : BN;               // output features of a tile
-    constexpr int T0 = G::T0, T1 = G::T1, TM = T0 > T1 ? T0 : T1, AR0 = 32 * T0, AR1 = 32 * T1;
-    __shared__ __attribute__((aligned(16))) unsigned char a0_s0[AR0 * ROWB], a0_s1[AR0 * ROWB], a1_s0[AR1 * ROWB], a1_s1[AR1 * ROWB], w_s0[BN * ROWB], w_s1[BN * ROWB];
-    __shared__ __attribute__((aligned(16))) float vec_lds[2 * BN];
-    auto a0_lds = [&](int stage) -> unsigned char* { return stage == 0 ? a0_s0 : a0_s1; };
-    auto a1_lds = [&](int stage) -> unsigned char* { return stage == 0 ? a1_s0 : a1_s1; };
-    auto w_lds = [&](int stage) -> unsigned char* { return stage == 0 ? w_s0 : w_s1; };
-
-    int tile = (blockIdx.x % 8) * xcd_run + blockIdx.x / 8;
-    if (tile >= total) return;
-    const bool second = tile >= tiles0;
-    if (second) tile -= tiles0;
-    GemmProblem p;
-#define HYB_SEL(f) p.f = second ? g.p[1].f : g.p[0].f
-    HYB_SEL(a); HYB_SEL(w); HYB_SEL(bias); HYB_SEL(out); HYB_SEL(m);
-    HYB_SEL(res); HYB_SEL(res2); HYB_SEL(gate); HYB_SEL(rows_per_gate); HYB_SEL(gate_stride);
-    HYB_SEL(q); HYB_SEL(k); HYB_SEL(v); HYB_SEL(tokens); HYB_SEL(tok_offset); HYB_SEL(n_total); HYB_SEL(heads); HYB_SEL(q_scale);
-#undef HYB_SEL
-    const int m = p.m, n = g.n, k = g.k;
-    int row0, col0;
-    {
-        const int tiles_m = (m + BM - 1) / BM;
-        const int per_group = kGroupRows * tiles_n;
-        const int grp = tile / per_group, in = tile - grp * per_group;
-        const int rows_in = min(kGroupRows, tiles_m - grp * kGroupRows);
-        row0 = (grp * kGroupRows + in % rows_in) * BM;
-        col0 = (in / rows_in) * OCOLS;
-    }
+    float* const vec_lds = lds.vec;
+    auto a0_lds = [&](int stage) -> unsigned char* { return stage == 0 ? lds.a0_s0 : lds.a0_s1; };
+    auto a1_lds = [&](int stage) -> unsigned char* { return stage == 0 ? lds.a1_s0 : lds.a1_s1; };
+    auto w_lds = [&](int stage) -> unsigned char* { return stage == 0 ? lds.w_s0 : lds.w_s1; };
+    const int m = p.m;
+    [[maybe_unused]] void* const out_q = p.q;
+    [[maybe_unused]] void* const out_k = p.k;
+    [[maybe_unused]] void* const out_v = p.v;
     const bf16_t* A = static_cast<const bf16_t*>(p.a);
     const bf16_t* W = static_cast<const bf16_t*>(p.w);
 
@@ -290,7 +279,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmGroup g, int tiles
     [[maybe_unused]] int qkv_b0 = 0, qkv_t0 = 0;      // sample and token of the tile's first row
     if constexpr (EPI == EPI_QKV) {
         const int hd = p.heads * 64, c = min(wcol0, n - 64), which = c / hd, head = (c - which * hd) / 64;
-        qkv_base = static_cast<OT*>(which == 0 ? p.q : (which == 1 ? p.k : p.v)) + ((size_t)head * p.n_total + p.tok_offset) * 64;
+        qkv_base = static_cast<OT*>(which == 0 ? out_q : (which == 1 ? out_k : out_v)) + ((size_t)head * p.n_total + p.tok_offset) * 64;
         if (which == 0 && p.q_scale != 0.f) scale = p.q_scale;
         qkv_b0 = row0 / p.tokens;
         qkv_t0 = row0 - qkv_b0 * p.tokens;
@@ -368,40 +357,106 @@ __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmGroup g, int tiles
     }
 }
 
-template <typename OT, int EPI, int TT>
-int launch_wide(const GemmGroup& g, hipStream_t st) {
-    using G = WideGeo<TT>;
-    GemmGroup gg = g;
+// Tiles of a launch: XCD x (workgroups x, x + 8, ...) gets the run [x * tall_run, (x + 1) * tall_run) of the tall tiles, then its run of the short ones.
+struct WideGrid {
+    int tiles_n;
+    int tall_rows[kMaxGroup];      // tall tile rows of each problem: its first rows
+    int tall, shrt;                // tiles
+    int tall0, short0;             // of these, of the first problem
+    int tall_run, short_run;
+};
+
+// TA, TB: token tiles per wave of the tall and of the short tiles.
+template <typename OT, int EPI, int TA, int TB>
+__global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmGroup g, WideGrid t) {
     constexpr int OCOLS = EPI == EPI_GEGLU ? BN / 2 : BN;
-    const int tiles_n = (g.n + OCOLS - 1) / OCOLS;
-    if (gg.count > 1 && gg.p[1].m < gg.p[0].m) { const GemmProblem t = gg.p[0]; gg.p[0] = gg.p[1]; gg.p[1] = t; }
-    auto tiles_of = [&](const GemmProblem& p) { return ((p.m + G::BM - 1) / G::BM) * tiles_n; };
-    int tiles0 = tiles_of(gg.p[0]), tiles1 = gg.count > 1 ? tiles_of(gg.p[1]) : 0;
-    if (tiles0 == 0 && tiles1 > 0) { gg.p[0] = gg.p[1]; tiles0 = tiles1; tiles1 = 0; gg.count = 1; }
-    if (gg.count < 2) gg.p[1] = gg.p[0];
-    const int total = tiles0 + tiles1;
-    if (total <= 0) return HYB_OK;
+    constexpr int AR0 = 32 * (WideGeo<TA>::T0 > WideGeo<TB>::T0 ? WideGeo<TA>::T0 : WideGeo<TB>::T0);
+    constexpr int AR1 = 32 * (WideGeo<TA>::T1 > WideGeo<TB>::T1 ? WideGeo<TA>::T1 : WideGeo<TB>::T1);
+    __shared__ __attribute__((aligned(16))) unsigned char a0_s0[AR0 * ROWB], a0_s1[AR0 * ROWB], a1_s0[AR1 * ROWB], a1_s1[AR1 * ROWB], w_s0[BN * ROWB], w_s1[BN * ROWB];
+    __shared__ __attribute__((aligned(16))) float vec_lds[2 * BN];
+    WideLds lds;
+    lds.a0_s0 = a0_s0; lds.a0_s1 = a0_s1; lds.a1_s0 = a1_s0; lds.a1_s1 = a1_s1; lds.w_s0 = w_s0; lds.w_s1 = w_s1;
+    lds.vec = vec_lds;
+
+    const int xcd = blockIdx.x % 8, pos = blockIdx.x / 8;
+    const bool is_tall = pos < t.tall_run;
+    int tile = is_tall ? xcd * t.tall_run + pos : xcd * t.short_run + pos - t.tall_run;
+    if (tile >= (is_tall ? t.tall : t.shrt)) return;
+    const int first = is_tall ? t.tall0 : t.short0;
+    const bool second = tile >= first;
+    if (second) tile -= first;
+    // Problem of this tile, selected field by field (indexing the argument array with a run-time index would make the
+    // compiler keep a copy of the whole argument block in scratch memory).
+    GemmProblem p;
+#define HYB_SEL(f) p.f = second ? g.p[1].f : g.p[0].f
+    HYB_SEL(a); HYB_SEL(w); HYB_SEL(bias); HYB_SEL(out); HYB_SEL(m);
+    HYB_SEL(res); HYB_SEL(res2); HYB_SEL(gate); HYB_SEL(rows_per_gate); HYB_SEL(gate_stride);
+    HYB_SEL(q); HYB_SEL(k); HYB_SEL(v); HYB_SEL(tokens); HYB_SEL(tok_offset); HYB_SEL(n_total); HYB_SEL(heads); HYB_SEL(q_scale);
+#undef HYB_SEL
+    const int tall_rows = second ? t.tall_rows[1] : t.tall_rows[0];
+    const int height = is_tall ? 32 * TA : 32 * TB, base = is_tall ? 0 : tall_rows * 32 * TA;
+    const int tile_rows = is_tall ? tall_rows : (p.m - base + height - 1) / height;
+    const int per_group = kGroupRows * t.tiles_n;
+    const int grp = tile / per_group, in = tile - grp * per_group;
+    const int rows_in = min(kGroupRows, tile_rows - grp * kGroupRows);
+    const int row0 = base + (grp * kGroupRows + in % rows_in) * height, col0 = in / rows_in * OCOLS;
+    if (is_tall) wide_tile<OT, EPI, TA>(p, g.n, g.k, row0, col0, lds);
+    else wide_tile<OT, EPI, TB>(p, g.n, g.k, row0, col0, lds);
+}
+
+template <typename OT, int EPI, int TA, int TB>
+int launch_wide(const GemmGroup& g, const WidePlan& plan, hipStream_t st) {
+    GemmGroup gg = g;
+    WideGrid t = {};
+    constexpr int OCOLS = EPI == EPI_GEGLU ? BN / 2 : BN;
+    t.tiles_n = (g.n + OCOLS - 1) / OCOLS;
+    int order[kMaxGroup] = {0, 1};
+    if (gg.count < 2) gg.p[1] = gg.p[0];         // every field the kernel selects from is defined
+    // The smaller problem goes first: its tiles fetch a whole weight matrix for few rows, which is better hidden under the start
+    // of the large problem than left for the end of the launch.
+    if (gg.count > 1 && gg.p[1].m < gg.p[0].m) {
+        const GemmProblem x = gg.p[0];
+        gg.p[0] = gg.p[1];
+        gg.p[1] = x;
+        order[0] = 1; order[1] = 0;
+    }
+    for (int i = 0; i < gg.count; i++) {
+        const int a = plan.tall_rows[order[i]], rest = gg.p[i].m - a * 32 * TA;
+        const int b = rest > 0 ? (rest + 32 * TB - 1) / (32 * TB) : 0;
+        t.tall_rows[i] = a;
+        t.tall += a * t.tiles_n;
+        t.shrt += b * t.tiles_n;
+        if (i == 0) { t.tall0 = t.tall; t.short0 = t.shrt; }
+    }
+    if (t.tall + t.shrt <= 0) return HYB_OK;
+    t.tall_run = (t.tall + 7) / 8;
+    t.short_run = (t.shrt + 7) / 8;
     char name[96];
-    snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", G::BM, BN, EPI, g.n, g.k);
+    if (t.tall && t.shrt) snprintf(name, sizeof(name), "gemm_mfma_%d+%dx%d.epi%d.n%d.k%d", 32 * TA, 32 * TB, BN, EPI, g.n, g.k);
+    else snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", t.tall ? 32 * TA : 32 * TB, BN, EPI, g.n, g.k);
     double rows = 0;
     for (int i = 0; i < g.count; i++) rows += g.p[i].m;
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k, st);
-    const int xcd_run = (total + 7) / 8;
-    hipLaunchKernelGGL((gemm_wide_kernel<OT, EPI, TT>), dim3(8 * xcd_run), dim3(NT), 0, st, gg, tiles_n, tiles0, total, xcd_run);
+    hipLaunchKernelGGL((gemm_wide_kernel<OT, EPI, TA, TB>), dim3(8 * (t.tall_run + t.short_run)), dim3(NT), 0, st, gg, t);
     return hyb_check_launch("gemm_mfma_wide");
+}
+
+template <typename OT, int EPI>
+int launch_pair(const GemmGroup& g, const WidePlan& plan, hipStream_t st) {
+    if (plan.tall == 256 && plan.shrt == 192) return launch_wide<OT, EPI, 8, 6>(g, plan, st);
+    if (plan.tall == 192 && plan.shrt == 128) return launch_wide<OT, EPI, 6, 4>(g, plan, st);
+    return hyb_set_error(HYB_ERR_SHAPE, "gemm_mfma_wide: no tiles of %d and %d rows", plan.tall, plan.shrt);
 }
 
 }  // namespace
 
-int hyb_launch_gemm_mfma_wide(const GemmGroup& g, hyb_dtype out_dtype, int epi, int rows, hipStream_t st) {
+int hyb_launch_gemm_mfma_wide(const GemmGroup& g, hyb_dtype out_dtype, int epi, const WidePlan& plan, hipStream_t st) {
     if (g.k / BK < 3 || g.n2) return hyb_set_error(HYB_ERR_SHAPE, "gemm_mfma_wide: unsupported shape (k %d)", g.k);
     const bool f32 = out_dtype == HYB_F32;
-#define HYB_WIDE(OT, E) (rows == 256 ? launch_wide<OT, E, 8>(g, st) : (rows == 192 ? launch_wide<OT, E, 6>(g, st) : launch_wide<OT, E, 4>(g, st)))
-    if (!f32 && epi == EPI_BIAS) return HYB_WIDE(bf16_t, EPI_BIAS);
-    if (!f32 && epi == EPI_GELU_TANH) return HYB_WIDE(bf16_t, EPI_GELU_TANH);
-    if (!f32 && epi == EPI_QKV) return HYB_WIDE(bf16_t, EPI_QKV);
-    if (!f32 && epi == EPI_GEGLU) return HYB_WIDE(bf16_t, EPI_GEGLU);
-    if (f32 && epi == EPI_GATE_RES) return HYB_WIDE(float, EPI_GATE_RES);
-#undef HYB_WIDE
+    if (!f32 && epi == EPI_BIAS) return launch_pair<bf16_t, EPI_BIAS>(g, plan, st);
+    if (!f32 && epi == EPI_GELU_TANH) return launch_pair<bf16_t, EPI_GELU_TANH>(g, plan, st);
+    if (!f32 && epi == EPI_QKV) return launch_pair<bf16_t, EPI_QKV>(g, plan, st);
+    if (!f32 && epi == EPI_GEGLU) return launch_pair<bf16_t, EPI_GEGLU>(g, plan, st);
+    if (f32 && epi == EPI_GATE_RES) return launch_pair<float, EPI_GATE_RES>(g, plan, st);
     return hyb_set_error(HYB_ERR_SHAPE, "gemm_mfma_wide: no such epilogue (%d)", epi);
 }

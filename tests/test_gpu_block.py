@@ -136,8 +136,8 @@ def test_block_with_large_tile_fc2_batch_invariance_and_parity(hb):
     assert np.array_equal(a_img, b_img) and np.array_equal(a_txt, b_txt)
 
 
-@pytest.mark.parametrize("latent_hw,n_txt,batch,qkv_rows", [(48, 77, 5, (192, 256)), (36, 500, 6, (128, 192, 256)), (28, 33, 17, (128, 192, 256))])
-def test_block_with_256_column_tiles(hb, latent_hw, n_txt, batch, qkv_rows):
+@pytest.mark.parametrize("latent_hw,n_txt,batch", [(48, 77, 5), (36, 500, 6), (28, 33, 17)])
+def test_block_with_256_column_tiles(hb, latent_hw, n_txt, batch):
     """QKV, fc1 and out-projection launches of several samples on 256-column tiles (tiles that straddle samples; samples shorter than a tile):
     equal samples get equal bits wherever they lie in their tiles, and the oracle's results."""
     cfg = synth.scaled(synth.CFG2, blocks=1, hidden=1152, heads=18, latent_hw=latent_hw, n_txt=n_txt, ctx_dim=128, batch=batch)
@@ -145,7 +145,7 @@ def test_block_with_256_column_tiles(hb, latent_hw, n_txt, batch, qkv_rows):
     a_img, a_txt, r_img, r_txt, (x_img, _) = _block_case(hb, cfg, seed=60, same_rows=True)
     names = hb.hyb_trace_summary()
     hb.hyb_trace_enable(False)
-    assert any("gemm_mfma_%dx256.epi4.n%d.k%d" % (r, 3 * cfg.hidden, cfg.hidden) in names for r in qkv_rows), names
+    assert any("x256.epi4.n%d.k%d" % (3 * cfg.hidden, cfg.hidden) in n for n in names), names
     assert np.array_equal(a_img[0], a_img[1]) and np.array_equal(a_txt[0], a_txt[1])
     assert err(a_img, r_img) < TOL_BF16 and err(a_txt, r_txt) < TOL_BF16 and err(a_img - x_img, r_img - x_img) < 5e-2
 
