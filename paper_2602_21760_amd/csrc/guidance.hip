@@ -7,6 +7,8 @@
 // reduced thread -> wave -> workgroup in a fixed order into one fp64 partial per workgroup.  A
 // second, tiny kernel adds the partials of a sample in a fixed order, so results are
 // deterministic and independent of the batch index (no atomics anywhere).
+// A call on few small latents is all launch latency: there one more workgroup per sample reads v_c and v_u on its own and writes the
+// sample's discrepancies in the same launch (see kOneLaunchBytes).
 #include "common.h"
 
 #include <mutex>
@@ -150,6 +152,109 @@ __global__ __launch_bounds__(HYB_WAVE) void discrepancy_finalize_kernel(const do
     }
 }
 
+// The pass and the discrepancies of small samples in one launch: workgroups 1 .. of a sample do what guidance_kernel does without its
+// sums, workgroup 0 sums over the whole sample: kOneThreads threads, 16 bytes of v_c and v_u each per round, eight rounds of loads in flight (as
+// raw bits: 64 registers); the sums of a vector's elements are fp32 as there, everything above is added in fp64.
+constexpr int kOneThreads = 1024;
+constexpr int kOneRounds = 8;
+
+// 16 bytes of values (one element in the scalar path), as they were loaded and as floats
+template <typename VT, int V> struct Raw {
+    u32x4 bits;
+    static constexpr int N = 16 / (int)sizeof(VT);
+    __device__ __forceinline__ void load(const VT* p) { bits = *reinterpret_cast<const u32x4*>(p); }
+    __device__ __forceinline__ void zero() { bits = u32x4{0, 0, 0, 0}; }
+    __device__ __forceinline__ float get(int j) const {
+        if constexpr (sizeof(VT) == 4) return __uint_as_float(bits[j]);
+        else return __uint_as_float(j % 2 ? bits[j / 2] & 0xffff0000u : bits[j / 2] << 16);
+    }
+};
+template <typename VT> struct Raw<VT, 1> {
+    VT value;
+    static constexpr int N = 1;
+    __device__ __forceinline__ void load(const VT* p) { value = *p; }
+    __device__ __forceinline__ void zero() { value = (VT)0.f; }
+    __device__ __forceinline__ float get(int) const { return to_f32<VT>(value); }
+};
+
+template <typename VT, int V>
+__device__ __forceinline__ void whole_sample_sums(const VT* vc, const VT* vu, size_t n, float* d1, float* d2) {
+    using R = Raw<VT, V>;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (size_t base = 0; base < n; base += (size_t)kOneThreads * R::N * kOneRounds) {
+        R c[kOneRounds], u[kOneRounds];
+#pragma unroll
+        for (int r = 0; r < kOneRounds; r++) {
+            const size_t i = base + ((size_t)r * kOneThreads + threadIdx.x) * R::N;
+            if (i < n) {
+                c[r].load(vc + i);
+                u[r].load(vu + i);
+            } else {
+                c[r].zero();
+                u[r].zero();
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kOneRounds; r++) {
+            float s_d1 = 0.f, s_d2 = 0.f, s_u1 = 0.f, s_u2 = 0.f;
+#pragma unroll
+            for (int j = 0; j < R::N; j++) {
+                const float uj = u[r].get(j), d = c[r].get(j) - uj;
+                s_d1 += fabsf(d);
+                s_d2 = fmaf(d, d, s_d2);
+                s_u1 += fabsf(uj);
+                s_u2 = fmaf(uj, uj, s_u2);
+            }
+            acc[0] += (double)s_d1; acc[1] += (double)s_d2; acc[2] += (double)s_u1; acc[3] += (double)s_u2;
+        }
+    }
+    __shared__ double red[kOneThreads / HYB_WAVE][4];
+    const int wave = threadIdx.x / HYB_WAVE, lane = threadIdx.x % HYB_WAVE;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const double t = wave_sum(acc[j]);
+        if (lane == 0) red[wave][j] = t;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        double t[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            t[j] = lane < kOneThreads / HYB_WAVE ? red[lane][j] : 0.0;
+            t[j] = wave_sum(t[j]);
+        }
+        if (lane == 0) {
+            if (d1) *d1 = ratio(t[0], t[2]);
+            if (d2) *d2 = ratio(sqrt(t[1]), sqrt(t[3]));
+        }
+    }
+}
+
+template <typename VT, int V>
+__global__ __launch_bounds__(kOneThreads) void guidance_one_launch_kernel(GuidanceArgs g, float* d1, float* d2) {
+    const size_t sample = blockIdx.y, off = sample * g.n;
+    const VT* vc = static_cast<const VT*>(g.v_c) + off;
+    const VT* vu = static_cast<const VT*>(g.v_u) + off;
+    if (blockIdx.x == 0) {
+        whole_sample_sums<VT, V>(vc, vu, g.n, d1 ? d1 + sample : nullptr, d2 ? d2 + sample : nullptr);
+        return;
+    }
+    const size_t i = ((size_t)(blockIdx.x - 1) * kOneThreads + threadIdx.x) * V;
+    if (i >= g.n) return;
+    float c[V], u[V], xv[V], v[V];
+    Vec<VT, V>::load(vc + i, c);
+    Vec<VT, V>::load(vu + i, u);
+    Vec<float, V>::load(g.x + off + i, xv);
+#pragma unroll
+    for (int j = 0; j < V; j++) {
+        v[j] = fmaf(g.s, c[j] - u[j], u[j]);
+        xv[j] = fmaf(g.b, v[j], g.a * xv[j]);
+    }
+    if (g.v_out) Vec<VT, V>::store(static_cast<VT*>(g.v_out) + off + i, v);
+    Vec<float, V>::store(g.x_out + off + i, xv);
+    if (g.x_lowp) Vec<bf16_t, V>::store(g.x_lowp + off + i, xv);
+}
+
 template <typename XT, typename VT>
 __global__ __launch_bounds__(kThreads) void euler_kernel(const XT* x, const VT* v, XT* xo, size_t n, float dt) {
     const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
@@ -163,6 +268,28 @@ int blocks_for(size_t n, int vec) {
 
 // Largest blocks-per-sample over both code paths, so the workspace query does not depend on it.
 size_t partial_bytes(int batch, size_t n) { return (size_t)batch * blocks_for(n, 1) * 4 * sizeof(double); }
+
+// One launch where a sample's v_c and v_u together are at most kOneLaunchBytes and those of all samples kOneLaunchTotal.  Two launches against one,
+// us, in a stream of calls: 1 x 1024 fp32 9.3 -> 6.5, 1 x 65536 bf16 9.1 -> 7.0 (a call on its own that the host waits for 20.4 -> 21.3: the
+// summing workgroup has a CU's arithmetic), 16 x 65536 9.1 -> 7.7, 64 x 16384 fp32 9.0 -> 6.6; beyond the line 64 x 65536 13.3 -> 17.0;
+// element by element (n % 8 != 0) 1 x 32769 9.0 -> 11.5, so there up to kOneLaunchScalar elements.
+constexpr size_t kOneLaunchBytes = 256 * 1024, kOneLaunchTotal = 8 * 1024 * 1024, kOneLaunchScalar = 8192;
+
+// The summing workgroup reads v_c and v_u while others write: none of the outputs may overlap them.
+bool overlaps(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return a && b && x < y + b_bytes && y < x + a_bytes;
+}
+
+bool one_launch(const GuidanceArgs& g, int batch, size_t vs, const float* d1, const float* d2) {
+    if (!g.partial || (!d1 && !d2) || !g.x_out || 2 * g.n * vs > kOneLaunchBytes || (size_t)batch * 2 * g.n * vs > kOneLaunchTotal) return false;
+    if (g.n % kVec != 0 && g.n > kOneLaunchScalar) return false;
+    const size_t n = (size_t)batch * g.n;
+    for (const void* v : {g.v_c, g.v_u})
+        if (overlaps(v, n * vs, g.x_out, n * 4) || overlaps(v, n * vs, g.x_lowp, n * 2) || overlaps(v, n * vs, g.v_out, n * vs) ||
+            overlaps(v, n * vs, d1, (size_t)batch * 4) || overlaps(v, n * vs, d2, (size_t)batch * 4)) return false;
+    return true;
+}
 
 int launch_guidance(const char* who, GuidanceArgs g, int batch, hyb_dtype vd, float* d1, float* d2, hipStream_t st) {
     if (batch == 0 || g.n == 0) {
@@ -180,6 +307,19 @@ int launch_guidance(const char* who, GuidanceArgs g, int batch, hyb_dtype vd, fl
     // algorithmic bytes: v_c + v_u read, x read, x_out written, plus the optional outputs
     const double vs = (double)hyb_dtype_size(vd);
     const double per_elem = 2 * vs + (g.x_out ? 8 : 0) + (g.x_lowp ? 2 : 0) + (g.v_out ? vs : 0);
+    if (one_launch(g, batch, hyb_dtype_size(vd), d1, d2)) {
+        const size_t per_wg = (size_t)kOneThreads * (vec ? kVec : 1);
+        dim3 grid1(1 + (unsigned)((g.n + per_wg - 1) / per_wg), batch), block1(kOneThreads);
+        HybTraceScope trace("guidance_pass", "byte", per_elem * (double)batch * (double)g.n, st);
+        if (vd == HYB_BF16) {
+            if (vec) hipLaunchKernelGGL((guidance_one_launch_kernel<bf16_t, 8>), grid1, block1, 0, st, g, d1, d2);
+            else hipLaunchKernelGGL((guidance_one_launch_kernel<bf16_t, 1>), grid1, block1, 0, st, g, d1, d2);
+        } else {
+            if (vec) hipLaunchKernelGGL((guidance_one_launch_kernel<float, 8>), grid1, block1, 0, st, g, d1, d2);
+            else hipLaunchKernelGGL((guidance_one_launch_kernel<float, 1>), grid1, block1, 0, st, g, d1, d2);
+        }
+        return hyb_check_launch(who);
+    }
     {   // the pass itself; the tiny finalisation below is a launch of its own
         HybTraceScope trace("guidance_pass", "byte", per_elem * (double)batch * (double)g.n, st);
         if (vd == HYB_BF16) {

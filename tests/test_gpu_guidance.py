@@ -136,3 +136,25 @@ def test_empty_inputs_and_errors(hb):
     with pytest.raises(hb.HybError) as ei:
         hb.hyb_branch_discrepancy(v, v, 2, d, None)
     assert ei.value.code == 1
+
+
+@pytest.mark.parametrize("vd,batch,n", [("bf16", 1, 8), ("f32", 2, 7), ("bf16", 3, 8191), ("bf16", 2, 8193), ("f32", 2, 4096), ("f32", 1, 32768), ("f32", 1, 32776),
+                                        ("bf16", 2, 65536), ("bf16", 2, 65544), ("bf16", 32, 65536), ("bf16", 33, 65536), ("f32", 5, 32760)])
+def test_one_launch_for_small_samples(hb, vd, batch, n):
+    """Small samples are updated and summed in one launch, at both sides of its limits: the update has the bits of the pass without sums, the
+    discrepancies are those of sums in 64 bits (fp32 sums of eight elements: relative error below 8 units of 2^-24, and one rounding)."""
+    v_c, v_u, x = synth.guidance_inputs(n, batch, vd, seed=300 + n % 89)
+    dvc, dvu, dx = dev(v_c, tdt(vd)), dev(v_u, tdt(vd)), dev(x)
+    d = torch.full((2, batch), -1.0, device="cuda")
+    out, ref, v_out = torch.empty_like(dx), torch.empty_like(dx), torch.empty_like(dvc)
+    hb.hyb_cfg_disc_euler(dvc, dvu, dx, out, 7.0, 0.5, 0.45, d[0], d[1], _ws(hb, batch, n), v_out=v_out)
+    hb.hyb_cfg_disc_euler(dvc, dvu, dx, ref, 7.0, 0.5, 0.45)
+    assert torch.equal(out, ref)
+    c, u = host(dvc), host(dvu)
+    want = np.stack([np.abs(c - u).sum(1) / np.abs(u).sum(1), np.sqrt(((c - u) ** 2).sum(1) / (u ** 2).sum(1))])
+    np.testing.assert_allclose(host(d), want, rtol=10 * 2.0 ** -24)
+    # in place over x; and with an output over v_u, which only a pass of its own may overwrite before the sums are taken
+    d2 = torch.full((2, batch), -1.0, device="cuda")
+    hb.hyb_cfg_disc_euler(dvc, dvu, dx, dx, 7.0, 0.5, 0.45, d2[0], d2[1], _ws(hb, batch, n), v_out=dvu)
+    assert torch.equal(dx, ref) and torch.equal(dvu, v_out)
+    np.testing.assert_allclose(host(d2), want, rtol=10 * 2.0 ** -24)
