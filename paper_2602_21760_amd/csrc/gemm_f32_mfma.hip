@@ -6,7 +6,8 @@
 // reference-precision models is how evenly the tiles fill 256 CUs and how many k-slabs stand in a row.
 //
 // Two tile shapes, both of 4 waves that own 32 tokens x 32 features each (2 x 2 MFMA tiles):
-//   KW = 1: the waves form a 64 x 64 tile and share the slabs of a k panel (32 floats = 128-byte rows in LDS);
+//   KW = 1: the waves form a 64 x 64 tile and share the slabs of a k panel (32 floats = 128-byte rows in LDS)
+//           (a launch with one tile per CU: four slab buffers instead of two, and fragments read a slab ahead);
 //   KW = 4: the waves share ONE 32 x 32 tile and split k: wave w takes the slabs w, w + 4, ...  A wave copies and reads
 //           only its own slabs, so the main loop has no barrier at all; the four sums meet in LDS at the end.
 // Both keep FOUR running sums per output, slab s going to sum s % 4, and add them as (0 + 1) + (2 + 3): a result has the
@@ -18,7 +19,7 @@
 // the "A" operand, so the 4 accumulator registers of a tile are 4 consecutive features of one token: bias, gate, residual
 // and output are 16-byte accesses straight from the MFMA layout.
 // Measured (us; before: the plain FMA kernel): 1306 x 3072 x 768 GELU 52 (118 TFLOP/s of 157 nominal), 1306 x 768 x 3072
-// 63, 160 x 256 x 1024 9 (was 119), 2 rows x 768 x 768 9 (was 78); 4096 x 4096 x 1024 260 (132 TFLOP/s, the rate that the vendor library
+// 55, 160 x 256 x 1024 9 (was 119), 2 rows x 768 x 768 9 (was 78); 4096 x 4096 x 1024 260 (132 TFLOP/s, the rate that the vendor library
 // reaches on a large square fp32 product).  With the next slab's fragments prefetched into a second register set the wide
 // launches lose 15 % (three waves per SIMD instead of four).
 #include "gemm.h"
@@ -89,16 +90,32 @@ __device__ __forceinline__ void epilogue4(const GemmProblem& p, int epi, int n, 
     store4<OT>(static_cast<OT*>(p.out) + o, v);
 }
 
+// MN MFMAs with R fragment reads between the first half of them.
+template <int J, int MN, int R>
+__device__ __forceinline__ void interleave_reads() {
+    if constexpr (J < MN) {
+        constexpr int MR = MN / 2, r0 = J < MR ? R * J / MR : R, r1 = J + 1 < MR ? R * (J + 1) / MR : R;
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if constexpr (r1 != r0) __builtin_amdgcn_sched_group_barrier(0x100, r1 - r0, 0);
+        interleave_reads<J + 1, MN, R>();
+    }
+}
+
 // GEGLU: every 32 weight rows of a tile are 16 "u" rows and the 16 "gate" rows that belong to them (n rows further), so a
 // wave's two feature tiles are u and gate of the same 16 output features.
-template <typename OT, int KW, bool GEGLU>
+// NST slab buffers: two, or (KW = 1) four with the fragments of the next slab read while this one is multiplied.
+template <typename OT, int KW, bool GEGLU, int NST>
 __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int epi, int tiles_m0, int tiles_m, int total, int xcd_run) {
     constexpr int BM = KW == 1 ? 64 : 32, BN = BM;
     constexpr int GROUP_BYTES = (BM + BN) * ROWB;                  // one slab of the tile: 16 KB / 8 KB
     constexpr int STAGE_BYTES = GROUP_BYTES * KW;                  // every k-splitting wave has a slab of its own
     constexpr int CPW = GROUP_BYTES / 1024 / (KW == 1 ? 4 : 1);    // 1 KB chunks per wave per slab
     constexpr int OUT_COLS = GEGLU ? BN / 2 : BN;
-    __shared__ __attribute__((aligned(128))) unsigned char smem[2 * STAGE_BYTES];
+    constexpr bool DEEP = NST > 2;
+    __shared__ __attribute__((aligned(128))) unsigned char smem[DEEP ? STAGE_BYTES : 2 * STAGE_BYTES];
+    // further slab buffers, one array each: the compiler knows that a copy into one and a read from another do not alias
+    __shared__ __attribute__((aligned(128))) unsigned char smem1[DEEP ? STAGE_BYTES : 16], smem2[DEEP ? STAGE_BYTES : 16], smem3[DEEP ? STAGE_BYTES : 16];
+    auto buffer = [&](int i) -> unsigned char* { return i == 0 ? smem : (i == 1 ? smem1 : (i == 2 ? smem2 : smem3)); };
 
     // XCD x gets the tiles [x xcd_run, (x + 1) xcd_run) of an order that walks down the rows first: neighbours share their
     // weight rows, and the activations of these models stay in every L2
@@ -124,6 +141,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
     const float* w_tile = static_cast<const float*>(p.w) + (size_t)col0 * k;
     const unsigned a_bytes = (unsigned)(min(BM, m - row0) * row_bytes);
     const unsigned w_bytes = (unsigned)(((GEGLU ? n : 0) + min(OUT_COLS, n - col0)) * row_bytes);
+    const int nslab = (k + BK - 1) / BK;   // (k % 32 == 16: of the last slab only the first half counts)
     int voff[CPW];
 #pragma unroll
     for (int c = 0; c < CPW; c++) {
@@ -138,12 +156,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
         voff[c] = src * row_bytes + ((lane % 8) ^ swz(r)) * 16;
     }
     auto issue = [&](int slab, int stage) {
-        unsigned char* dst = smem + stage * STAGE_BYTES + (KW == 1 ? wave * 1024 : wave * GROUP_BYTES);
+        unsigned char* dst = (DEEP ? buffer(stage) : smem + stage * STAGE_BYTES) + (KW == 1 ? wave * 1024 : wave * GROUP_BYTES);
 #pragma unroll
         for (int c = 0; c < CPW; c++) {
             constexpr int STEP = KW == 1 ? 4096 : 1024;
-            if (c < CPW / 2) buffer_load_lds16(a_tile, a_bytes, dst + c * STEP, voff[c], slab * ROWB);
-            else buffer_load_lds16(w_tile, w_bytes, dst + c * STEP, voff[c], slab * ROWB);
+            // (deep form: slabs past the end are requested from buffers of no size, which keeps the count of the waits the same and copies nothing)
+            if (c < CPW / 2) buffer_load_lds16(a_tile, !DEEP || slab < nslab ? a_bytes : 0u, dst + c * STEP, voff[c], slab * ROWB);
+            else buffer_load_lds16(w_tile, !DEEP || slab < nslab ? w_bytes : 0u, dst + c * STEP, voff[c], slab * ROWB);
         }
     };
 
@@ -184,8 +203,61 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
         }
     };
 
-    const int nslab = (k + BK - 1) / BK;   // (k % 32 == 16: of the last slab only the first half counts)
-    if constexpr (KW == 1) {
+    if constexpr (DEEP) {
+        static_assert(NST == 4 || !DEEP, "slab s sits in buffer s % 4 and goes to sum s % 4");
+        f32x4 af[2][2][2], wv[2][2][2];          // [set][k-step][tile]
+        const unsigned a0 = (unsigned)(wt * 32 + l16) * ROWB, w0 = (unsigned)(BM + wf * 32 + l16) * ROWB;
+        auto read = [&](auto stage_tag, auto set_tag) {
+            constexpr int S = decltype(set_tag)::value;
+            const unsigned char* base = buffer(decltype(stage_tag)::value);
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+                for (int t = 0; t < 2; t++) {
+                    const int ra = wt * 32 + t * 16 + l16, rw = BM + wf * 32 + t * 16 + l16;
+                    af[S][ks][t] = *reinterpret_cast<const f32x4*>(base + a0 + t * 16 * ROWB + (((4 * ks + kq) ^ swz(ra)) * 16));
+                    wv[S][ks][t] = *reinterpret_cast<const f32x4*>(base + w0 + t * 16 * ROWB + (((4 * ks + kq) ^ swz(rw)) * 16));
+                }
+        };
+        // fragments of slab s are in set s % 2 on entry
+        auto step = [&](int s, auto i_tag) {
+            constexpr int I = decltype(i_tag)::value;
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * CPW) : "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            issue(s + NST, I % NST);
+            read(std::integral_constant<int, (I + 1) % NST>{}, std::integral_constant<int, (I + 1) % 2>{});
+            auto half = [&](auto ks_tag) {
+                constexpr int ks = decltype(ks_tag)::value;
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+#pragma unroll
+                    for (int fi = 0; fi < 2; fi++)
+#pragma unroll
+                        for (int ti = 0; ti < 2; ti++)
+                            acc[I % 4][fi][ti] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[I % 2][ks][fi][j], af[I % 2][ks][ti][j], acc[I % 4][fi][ti], 0, 0, 0);
+            };
+            half(std::integral_constant<int, 0>{});
+            interleave_reads<0, 16, 8>();
+            if ((s + 1) * BK <= k) half(std::integral_constant<int, 1>{});
+        };
+#pragma unroll
+        for (int j = 0; j < NST; j++) issue(j, j);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * CPW) : "memory");
+        __builtin_amdgcn_s_barrier();
+        read(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+        for (int s = 0;; s += NST) {
+            step(s, std::integral_constant<int, 0>{});
+            if (s + 1 >= nslab) break;
+            step(s + 1, std::integral_constant<int, 1>{});
+            if (s + 2 >= nslab) break;
+            step(s + 2, std::integral_constant<int, 2>{});
+            if (s + 3 >= nslab) break;
+            step(s + 3, std::integral_constant<int, 3>{});
+            if (s + 4 >= nslab) break;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // no copy is on its way to LDS when the workgroup ends
+    } else if constexpr (KW == 1) {
         // one barrier per slab: behind it slab s is there for everyone and the other buffer, whose fragments every wave
         // has taken into registers, can be refilled
         auto step = [&](int s, auto i_tag) {
@@ -202,6 +274,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
             if (s + 2 < nslab) step(s + 2, std::integral_constant<int, 2>{});
             if (s + 3 < nslab) step(s + 3, std::integral_constant<int, 3>{});
         }
+    }
+    if constexpr (KW == 1) {
 #pragma unroll
         for (int ti = 0; ti < 2; ti++) {
             const int r = row0 + wt * 32 + ti * 16 + l16;
@@ -274,7 +348,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
 // (a multiple of 8, for the XCD order) go into the second dimension.
 constexpr int kMaxGridX = 1 << 23;
 
-template <typename OT, int KW, bool GEGLU>
+template <typename OT, int KW, bool GEGLU, int NST>
 int launch(const GemmGroup& g, int epi, hipStream_t st) {
     constexpr int T = KW == 1 ? 64 : 32;
     const int tiles_m0 = (g.p[0].m + T - 1) / T, tiles_m1 = g.count > 1 ? (g.p[1].m + T - 1) / T : 0;
@@ -286,14 +360,15 @@ int launch(const GemmGroup& g, int epi, hipStream_t st) {
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k * (GEGLU ? 2 : 1), st);
     const int xcd_run = (total + 7) / 8;
     const int grid_x = 8 * xcd_run < kMaxGridX ? 8 * xcd_run : kMaxGridX, grid_y = (8 * xcd_run - 1) / grid_x + 1;
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<OT, KW, GEGLU>), dim3(grid_x, grid_y), dim3(256), 0, st, g, epi, tiles_m0, tiles_m0 + tiles_m1, total, xcd_run);
+    hipLaunchKernelGGL((gemm_f32_mfma_kernel<OT, KW, GEGLU, NST>), dim3(grid_x, grid_y), dim3(256), 0, st, g, epi, tiles_m0, tiles_m0 + tiles_m1, total, xcd_run);
     return hyb_check_launch("gemm_f32_mfma");
 }
 
 template <typename OT>
-int launch_any(const GemmGroup& g, int epi, bool small, hipStream_t st) {
-    if (epi == EPI_GEGLU) return small ? launch<OT, 4, true>(g, epi, st) : launch<OT, 1, true>(g, epi, st);
-    return small ? launch<OT, 4, false>(g, epi, st) : launch<OT, 1, false>(g, epi, st);
+int launch_any(const GemmGroup& g, int epi, bool small, bool deep, hipStream_t st) {
+    if (epi == EPI_GEGLU) return small ? launch<OT, 4, true, 2>(g, epi, st) : launch<OT, 1, true, 2>(g, epi, st);
+    if (deep) return launch<OT, 1, false, 4>(g, epi, st);
+    return small ? launch<OT, 4, false, 2>(g, epi, st) : launch<OT, 1, false, 2>(g, epi, st);
 }
 
 }  // namespace
@@ -323,5 +398,9 @@ int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, h
     const int cus = hyb_cu_count();
     const double busy64 = 4.0 * (double)(((long long)tiles64 + cus - 1) / cus), busy32 = (double)(((long long)tiles32 + cus - 1) / cus);
     const bool small = busy32 < 0.8 * busy64 || (tiles64 < 0.85 * cus && g.k >= 768);
-    return out_dtype == HYB_F32 ? launch_any<float>(g, epi, small, st) : launch_any<bf16_t>(g, epi, small, st);
+    // One large tile on nearly every CU, one wave per SIMD: nothing covers a wave's waits but its own deeper pipeline.  Two against four buffers:
+    // 1306 x 768 (252 tiles) 62 -> 55 us at k 3072, 19.8 -> 18.5 at 768; with two tiles per CU and more they cover each other (504 tiles of k
+    // 768: 28.8 against 28.1 us, 1008: 53 against 55).
+    const bool deep = !small && epi != EPI_GEGLU && tiles64 <= cus;
+    return out_dtype == HYB_F32 ? launch_any<float>(g, epi, small, deep, st) : launch_any<bf16_t>(g, epi, small, deep, st);
 }

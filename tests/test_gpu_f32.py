@@ -141,6 +141,22 @@ def test_linear_f32_64x64_tiles(hb, m, n, k):
     assert err(host(low), y.numpy()) < 4e-3          # one rounding to bf16: 2^-8 at most, half of it in the mean square
 
 
+@pytest.mark.parametrize("k", [16, 32, 48, 96, 128, 144, 160, 240, 256, 1040])
+def test_linear_f32_64x64_tiles_four_buffers(hb, k):
+    """A launch with one 64 x 64 tile per CU runs with four slab buffers, one of twice the rows with two: the same bits, from less than one slab
+    to more than the buffers hold, and the oracle's results."""
+    m, n = 1000, 1020
+    g = torch.Generator().manual_seed(k)
+    a, w, b, res = torch.randn(m, k, generator=g), torch.randn(n, k, generator=g) * k ** -0.5, torch.randn(n, generator=g), torch.randn(m, n, generator=g)
+    da, dw, db, dr = a.cuda(), w.cuda(), b.cuda(), res.cuda()
+    one, two = torch.empty(m, n, device="cuda"), torch.empty(2 * m, n, device="cuda")
+    hb.hyb_linear(da, dw, db, one, hb.HYB_EPI_GATE_RESIDUAL, residual=dr)
+    names = _traced(hb, lambda: hb.hyb_linear(da.repeat(2, 1), dw, db, two, hb.HYB_EPI_GATE_RESIDUAL, residual=dr.repeat(2, 1)))
+    assert names == ["gemm_f32_mfma_64x64.epi%d.n%d.k%d" % (hb.HYB_EPI_GATE_RESIDUAL, n, k)], names
+    assert torch.equal(two.view(2, m, n), one.expand(2, m, n))
+    assert err(host(one), res.numpy() + O.linear(a.double().numpy(), w.double().numpy(), b.double().numpy())) < TOL
+
+
 def test_qkv_scatter_f32_64x64_tiles(hb):
     """The head-major scatter from the 64 x 64 tiles: an fp32 block of two samples with ragged image and text rows, 252 tiles."""
     from test_gpu_block import _block_case
