@@ -250,6 +250,47 @@ int hyb_unpatchify(const void* tokens, void* latent, int batch, int hh, int ww, 
 /* Element-wise conversion fp32 -> `out_dtype` (n elements), e.g. context tokens to bf16. */
 int hyb_convert(const float* in, void* out, size_t n, hyb_dtype out_dtype, void* stream);
 
+/* A whole MMDiT-shaped denoiser evaluation from the calls above: v = f_theta(latent, ctx, t).  Sizes, weights and the buffers of the
+ * intermediate results are the caller's; all pointers are device memory but block_weights, a HOST array of `blocks` entries, and
+ * stay the caller's.  head_dim is 64. */
+typedef struct {
+    int batch, blocks, hidden, heads, mlp_ratio;
+    int latent_h, latent_w, latent_c, patch;         /* n_img = (latent_h / patch) (latent_w / patch) image tokens */
+    int n_txt, ctx_dim;
+    int temb_dim;                                    /* width of the sinusoidal timestep features */
+    int pooled_dim;                                  /* > 0: a pooled text vector is added to the timestep embedding */
+    hyb_dtype dtype;
+    float ln_eps;
+} hyb_mmdit_desc;
+
+typedef struct {
+    const void *t1_w, *t2_w, *p1_w, *p2_w;           /* timestep and pooled-text MLPs: [hidden, temb_dim], [hidden, hidden], [hidden, pooled_dim], [hidden, hidden] */
+    const void *pe_w, *ce_w, *f_w;                   /* patch, context and final projection: [hidden, p*p*c], [hidden, ctx_dim], [p*p*c, hidden] */
+    const void *ada_w;                               /* [(12 blocks + 2) hidden, hidden]: image, text per block, then the final layer */
+    const float *t1_b, *t2_b, *p1_b, *p2_b, *pe_b, *ce_b, *f_b, *ada_b;
+    const float *pos;                                /* [n_img, hidden] */
+    const hyb_block_weights* block_weights;
+} hyb_mmdit_weights;
+
+typedef struct {
+    void *t_feat, *t_hid;                            /* [batch, temb_dim], [batch, hidden] of dtype */
+    void *pooled_act, *p_hid;                        /* [batch, pooled_dim], [batch, hidden] (pooled_dim > 0) */
+    float *temb, *mod;                               /* [batch, hidden], [batch, (12 blocks + 2) hidden] */
+    void *tok, *ctx_act;                             /* [batch, n_img, p*p*c], [batch, n_txt, ctx_dim] of dtype */
+    float *x_img, *x_txt;                            /* [batch, n_img, hidden], [batch, n_txt, hidden] */
+    void *y, *out_tok;                               /* [batch, n_img, hidden], [batch, n_img, p*p*c] of dtype */
+    void *v;                                         /* result: [batch, latent_h, latent_w, latent_c] of dtype */
+    void *ws;                                        /* hyb_block_workspace_bytes() of the blocks */
+    size_t ws_bytes;
+} hyb_mmdit_buffers;
+
+/* latent: device float[batch, latent_h, latent_w, latent_c], or one latent for all samples (shared_latent != 0); ctx: device float[batch, n_txt, ctx_dim];
+ * t: device float[batch], or NULL: t_value for all samples; pooled: device float[batch, pooled_dim] when desc->pooled_dim > 0.
+ * txt_pre_only_last: the last block's text stream only supplies keys and values. */
+int hyb_mmdit_forward(const hyb_mmdit_desc* desc, const hyb_mmdit_weights* weights, const hyb_mmdit_buffers* buffers,
+                      const float* latent, int shared_latent, const float* ctx, const float* t, float t_value, const float* pooled,
+                      int txt_pre_only_last, void* stream);
+
 /* ------------------------------------------------------------------------------------------
  * Second denoiser shape (the U-Net family of Sec. 5's setup): one transformer block of an
  * SDXL-shaped attention stage on token-major activations.

@@ -37,6 +37,24 @@ class BlockWeights(C.Structure):
     _fields_ = [("img", StreamWeights), ("txt", StreamWeights)]
 
 
+class MMDiTDesc(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("batch", "blocks", "hidden", "heads", "mlp_ratio", "latent_h", "latent_w", "latent_c", "patch",
+                                       "n_txt", "ctx_dim", "temb_dim", "pooled_dim", "dtype")] + [("ln_eps", C.c_float)]
+
+
+MMDIT_WEIGHT_FIELDS = ("t1_w", "t2_w", "p1_w", "p2_w", "pe_w", "ce_w", "f_w", "ada_w", "t1_b", "t2_b", "p1_b", "p2_b", "pe_b", "ce_b",
+                       "f_b", "ada_b", "pos")
+MMDIT_BUFFER_FIELDS = ("t_feat", "t_hid", "pooled_act", "p_hid", "temb", "mod", "tok", "ctx_act", "x_img", "x_txt", "y", "out_tok", "v", "ws")
+
+
+class MMDiTWeights(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in MMDIT_WEIGHT_FIELDS] + [("block_weights", C.POINTER(BlockWeights))]
+
+
+class MMDiTBuffers(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in MMDIT_BUFFER_FIELDS] + [("ws_bytes", C.c_size_t)]
+
+
 class SdxlBlockDesc(C.Structure):
     _fields_ = [("batch", C.c_int), ("tokens", C.c_int), ("channels", C.c_int), ("heads", C.c_int),
                 ("head_dim", C.c_int), ("n_ctx", C.c_int), ("ctx_dim", C.c_int), ("groups", C.c_int),
@@ -81,6 +99,7 @@ SIGNATURES = {
     "hyb_block_forward": (_i, [C.POINTER(BlockDesc), C.POINTER(BlockWeights), _vp, _vp, _vp, _vp, _sz, _vp, _vp,
                                _vp, _sz, _vp]),
     "hyb_block_workspace_bytes": (_sz, [C.POINTER(BlockDesc)]),
+    "hyb_mmdit_forward": (_i, [C.POINTER(MMDiTDesc), C.POINTER(MMDiTWeights), C.POINTER(MMDiTBuffers), _vp, _i, _vp, _vp, _f, _vp, _i, _vp]),
     "hyb_timestep_embedding": (_i, [_vp, _vp, _i, _i, _i, _vp]),
     "hyb_patchify": (_i, [_vp, _vp, _i, _i, _i, _i, _i, _i, _vp]),
     "hyb_unpatchify": (_i, [_vp, _vp, _i, _i, _i, _i, _i, _i, _i, _vp]),
@@ -291,6 +310,25 @@ def hyb_block_forward(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_s
     _check(lib().hyb_block_forward(C.byref(desc), C.byref(weights), _p(x_img_in, torch.float32),
                                    _p(x_txt_in, torch.float32), mod_img.data_ptr(), mod_txt.data_ptr(), mod_stride, _p(x_img_out, torch.float32),
                                    _p(x_txt_out, torch.float32), _p(workspace), _nbytes(workspace), _stream()))
+
+
+def mmdit_weights(tensors, blocks):
+    """tensors: dict of device tensors named as the fields of hyb_mmdit_weights (missing ones: NULL); blocks: ctypes array of BlockWeights."""
+    return MMDiTWeights(*[tensors[n].data_ptr() if n in tensors else None for n in MMDIT_WEIGHT_FIELDS], blocks)
+
+
+def mmdit_buffers(tensors):
+    """tensors: dict of device tensors named as the fields of hyb_mmdit_buffers (missing ones: NULL)."""
+    return MMDiTBuffers(*[tensors[n].data_ptr() if n in tensors else None for n in MMDIT_BUFFER_FIELDS], _nbytes(tensors["ws"]))
+
+
+def hyb_mmdit_forward(desc, weights, buffers, latent, ctx, t, pooled=None, txt_pre_only_last=False, shared_latent=False):
+    """latent: f32[batch, h, w, c] (shared_latent: f32[h, w, c]); ctx: f32[batch, n_txt, ctx_dim] or None; t: f32[batch] or a number; pooled:
+    f32[batch, pooled_dim] or None; the result is in the buffer v."""
+    value = isinstance(t, float)
+    _check(lib().hyb_mmdit_forward(C.byref(desc), C.byref(weights), C.byref(buffers), _p(latent, torch.float32), shared_latent,
+                                   _p(ctx, torch.float32), None if value else _p(t, torch.float32), t if value else 0.0, _p(pooled, torch.float32),
+                                   txt_pre_only_last, _stream()))
 
 
 def hyb_timestep_embedding(t, out):

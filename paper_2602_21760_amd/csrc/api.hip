@@ -49,6 +49,8 @@ std::vector<TraceKey> g_keys;
 std::map<std::string, int> g_key_index;
 }  // namespace
 
+bool hyb_trace_on() { return g_trace_on; }
+
 HybTraceScope::HybTraceScope(const char* kernel, const char* unit, double work, hipStream_t stream) : slot(-1), st(stream) {
     if (!g_trace_on) return;
     std::lock_guard<std::mutex> lk(g_tmx);

@@ -39,6 +39,7 @@ int hyb_check_launch(const char* what);
 int hyb_cu_count();
 
 // ---- optional per-launch timing (hyb_trace_*) ----------------------------------------------
+bool hyb_trace_on();     // names of launches are put together only then
 // A scope object brackets one kernel launch with two events on the launch stream when tracing
 // is on; `work` is the algorithmic work of the launch (flops or bytes, `unit` says which).
 struct HybTraceScope {

@@ -354,8 +354,8 @@ int launch(const GemmGroup& g, int epi, hipStream_t st) {
     const int tiles_m0 = (g.p[0].m + T - 1) / T, tiles_m1 = g.count > 1 ? (g.p[1].m + T - 1) / T : 0;
     const int cols = GEGLU ? T / 2 : T;
     const int total = (tiles_m0 + tiles_m1) * ((g.n + cols - 1) / cols);
-    char name[96];
-    snprintf(name, sizeof(name), "gemm_f32_mfma_%dx%d.epi%d.n%d.k%d", T, T, epi, g.n, g.k);
+    char name[96] = "";
+    if (hyb_trace_on()) snprintf(name, sizeof(name), "gemm_f32_mfma_%dx%d.epi%d.n%d.k%d", T, T, epi, g.n, g.k);
     const double rows = g.p[0].m + (g.count > 1 ? g.p[1].m : 0);
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k * (GEGLU ? 2 : 1), st);
     const int xcd_run = (total + 7) / 8;

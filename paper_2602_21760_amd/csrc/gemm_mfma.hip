@@ -453,8 +453,8 @@ int launch_tiles(const GemmGroup& g, int tiles_n, hipStream_t st, int ksplit = 1
     }
     const int tiles0 = ((gg.p[0].m + BM - 1) / BM) * tiles_n;
     const int tiles1 = gg.count > 1 ? ((gg.p[1].m + BM - 1) / BM) * (gg.n2 ? (gg.n2 + BN - 1) / BN : tiles_n) : 0;
-    char name[96];
-    snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", BM, BN, EPI, g.n, g.k);
+    char name[96] = "";
+    if (hyb_trace_on()) snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", BM, BN, EPI, g.n, g.k);
     const double flop0 = 2.0 * g.p[0].m * g.n * g.k, flop1 = g.count > 1 ? 2.0 * g.p[1].m * (g.n2 ? g.n2 : g.n) * (g.n2 ? g.k2 : g.k) : 0;
     HybTraceScope trace(name, "flop", flop0 + flop1, st);
     int t0 = tiles0;

@@ -455,8 +455,8 @@ int launch_big(const GemmGroup& g, hipStream_t st) {
     if (gg.count < 2) gg.p[1] = gg.p[0];   // every field the kernel selects from is defined
     const int total = tiles0 + tiles1;
     if (total <= 0) return HYB_OK;
-    char name[96];
-    snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", G::BM, G::BN, EPI, g.n, g.k);
+    char name[96] = "";
+    if (hyb_trace_on()) snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", G::BM, G::BN, EPI, g.n, g.k);
     double rows = 0;
     for (int i = 0; i < g.count; i++) rows += g.p[i].m;
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k, st);

@@ -431,8 +431,9 @@ int launch_wide(const GemmGroup& g, const WidePlan& plan, hipStream_t st) {
     if (t.tall + t.shrt <= 0) return HYB_OK;
     t.tall_run = (t.tall + 7) / 8;
     t.short_run = (t.shrt + 7) / 8;
-    char name[96];
-    if (t.tall && t.shrt) snprintf(name, sizeof(name), "gemm_mfma_%d+%dx%d.epi%d.n%d.k%d", 32 * TA, 32 * TB, BN, EPI, g.n, g.k);
+    char name[96] = "";
+    if (!hyb_trace_on()) name[0] = 0;
+    else if (t.tall && t.shrt) snprintf(name, sizeof(name), "gemm_mfma_%d+%dx%d.epi%d.n%d.k%d", 32 * TA, 32 * TB, BN, EPI, g.n, g.k);
     else snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", t.tall ? 32 * TA : 32 * TB, BN, EPI, g.n, g.k);
     double rows = 0;
     for (int i = 0; i < g.count; i++) rows += g.p[i].m;

@@ -77,7 +77,7 @@ int launch(const GemmGroup& g, int epi, hipStream_t st) {
     dim3 grid((g.n + TS - 1) / TS, tiles_m0 + tiles_m1), block(256);
     HYB_REQUIRE(grid.y <= 65535, HYB_ERR_SHAPE, "gemm: too many row tiles (%u)", grid.y);
     char name[96];
-    snprintf(name, sizeof(name), "gemm_simple.epi%d.n%d.k%d", epi, g.n, g.k);
+    if (hyb_trace_on()) snprintf(name, sizeof(name), "gemm_simple.epi%d.n%d.k%d", epi, g.n, g.k);
     double rows = g.p[0].m + (g.count > 1 ? g.p[1].m : 0);
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k * (epi == EPI_GEGLU ? 2 : 1), st);
     if (epi == EPI_GEGLU) hipLaunchKernelGGL((gemm_simple_kernel<T, OT, true>), grid, block, 0, st, g, epi, tiles_m0);

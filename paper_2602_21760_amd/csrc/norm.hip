@@ -428,12 +428,12 @@ __global__ __launch_bounds__(256) void groupnorm_apply_ln_kernel(const float* __
 }
 
 template <typename OT>
-__global__ void timestep_embedding_kernel(const float* t, OT* out, int batch, int dim) {
+__global__ void timestep_embedding_kernel(const float* t, float t_value, OT* out, int batch, int dim) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= batch * dim) return;
     const int b = i / dim, j = i % dim, half = dim / 2;
     const int f = j < half ? j : j - half;
-    const double ang = 1000.0 * (double)t[b] * exp(-9.210340371976184 * (double)f / (double)half);  // ln(10000)
+    const double ang = 1000.0 * (double)(t ? t[b] : t_value) * exp(-9.210340371976184 * (double)f / (double)half);  // ln(10000)
     out[i] = from_f32<OT>((float)(j < half ? cos(ang) : sin(ang)));
 }
 
@@ -627,15 +627,20 @@ extern "C" int hyb_adaln_modulation(const void* w, const float* bias, const floa
     return HYB_OK;
 }
 
-extern "C" int hyb_timestep_embedding(const float* t, void* out, int batch, int dim, hyb_dtype out_dtype, void* stream) {
-    HYB_CHECK_DTYPE(out_dtype);
+// t == nullptr: t_value for all samples.
+int hyb_launch_timestep_embedding(const float* t, float t_value, void* out, int batch, int dim, hyb_dtype out_dtype, hipStream_t st) {
     HYB_REQUIRE(batch >= 0 && dim > 0 && dim % 2 == 0, HYB_ERR_SHAPE, "hyb_timestep_embedding: batch >= 0 and an even dim > 0 required");
     if (batch == 0) return HYB_OK;
-    HYB_CHECK_PTR(t); HYB_CHECK_PTR(out);
     const int n = batch * dim;
-    if (out_dtype == HYB_F32) hipLaunchKernelGGL((timestep_embedding_kernel<float>), dim3((n + 255) / 256), dim3(256), 0, (hipStream_t)stream, t, (float*)out, batch, dim);
-    else hipLaunchKernelGGL((timestep_embedding_kernel<bf16_t>), dim3((n + 255) / 256), dim3(256), 0, (hipStream_t)stream, t, (bf16_t*)out, batch, dim);
+    if (out_dtype == HYB_F32) hipLaunchKernelGGL((timestep_embedding_kernel<float>), dim3((n + 255) / 256), dim3(256), 0, st, t, t_value, (float*)out, batch, dim);
+    else hipLaunchKernelGGL((timestep_embedding_kernel<bf16_t>), dim3((n + 255) / 256), dim3(256), 0, st, t, t_value, (bf16_t*)out, batch, dim);
     return hyb_check_launch("hyb_timestep_embedding");
+}
+
+extern "C" int hyb_timestep_embedding(const float* t, void* out, int batch, int dim, hyb_dtype out_dtype, void* stream) {
+    HYB_CHECK_DTYPE(out_dtype);
+    if (batch > 0 && dim > 0 && dim % 2 == 0) { HYB_CHECK_PTR(t); HYB_CHECK_PTR(out); }
+    return hyb_launch_timestep_embedding(t, 0.f, out, batch, dim, out_dtype, (hipStream_t)stream);
 }
 
 static int check_patch(const char* who, int batch, int hh, int ww, int c, int p) {

@@ -225,6 +225,35 @@ def test_forward_replays_from_a_captured_graph_bit_identically(hb):
         torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("dt,batch,n_txt,pooled,pre_only", [("f32", 1, 5, 0, False), ("f32", 2, 5, 64, True), ("f32", 3, 0, 0, False),
+                                                            ("bf16", 1, 33, 0, True), ("bf16", 2, 33, 0, False), ("bf16", 3, 33, 192, False)])
+def test_forward_in_one_call_matches_its_parts(hb, dt, batch, n_txt, pooled, pre_only):
+    """The forward as one call of the library against embedding, blocks and final layer one by one: the same bits; text and pooled inputs at any
+    alignment; one latent and one timestep shared by all samples."""
+    from paper_2602_21760_amd import model
+    cfg = synth.scaled(synth.CFG1, blocks=2, hidden=128, heads=2, latent_hw=20, n_txt=n_txt, ctx_dim=128, batch=batch, dtype=dt, pooled_dim=pooled)
+    m = model.MMDiT(cfg, synth.mmdit_globals(cfg), synth.mmdit_blocks(cfg), txt_pre_only_last=pre_only)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    latent = rnd(*m._latent_shape)
+    flat = rnd(batch * max(n_txt, 1) * 128 + 1)
+    texts = [flat[o:o + batch * n_txt * 128].view(batch, n_txt, 128) if n_txt else None for o in (0, 1)]       # aligned, not aligned
+    pool = rnd(batch, pooled) if pooled else None
+    t = torch.full((batch,), 0.625, device="cuda")
+    for ctx in texts:
+        m.embed(latent, ctx, t, pool)
+        m.run_blocks()
+        want = m.final().clone()
+        m.v.zero_()
+        assert torch.equal(m.forward(latent, ctx, t, pool), want)
+        m.embed(latent[:1].expand(batch, -1, -1, -1).contiguous(), ctx, t, pool)
+        m.run_blocks()
+        want = m.final().clone()
+        m.v.zero_()
+        m._forward(latent[0], ctx, 0.625, pool, shared_latent=True)
+        assert torch.equal(m.v, want)
+
+
 def test_reduced_bf16_forward_and_guided_loop(hb):
     """The guided sampling loop (both branches batched, fused guidance pass every step) on a reduced
     SD3-shaped model: 4 blocks, hidden 256, 324 + 77 tokens, 6 steps of the shifted schedule."""
