@@ -26,7 +26,7 @@
 // of 256 x 256 tiles costs about 2.3 us before its first MFMA, 1.3 us per slab and 7 us for a bf16 tile's epilogue, of which 5.5
 // are the stores of all CUs at once.
 //
-// Tile order: XCD x (workgroups x, x + 8, ...) gets one run of consecutive tiles of an order that walks groups of four tile rows column by
+// Tile order: XCD x (workgroups x, x + 8, ...) gets one run of consecutive tiles of an order that walks groups of four or eight tile rows column by
 // column, so the tiles that an XCD works on at a time share few operand panels (its L2 is 4 MB).
 #include "gemm.h"
 
@@ -54,7 +54,10 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned byt
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)lds, 16, voffset, soffset, 0, 0);
 }
 
-constexpr int kGroupRows = 4;   // tile rows per group of the tile order
+// Tile rows per group of the tile order: with a short k the operand panels are small and four rows x eight columns at a time share them best (SDXL-shaped
+// stage of 640 channels: 3191 us, eight rows 3274); with longer ones eight rows by four columns read fewer (a guided step at 1024 x 1024 4571 ->
+// 4542 us, the others 0-0.3 %).
+__device__ __forceinline__ int group_rows(int k) { return k >= 1024 ? 8 : 4; }
 
 // MN MFMAs with R fragment reads between the first three quarters of them and V copies spread evenly.
 template <int J, int MN, int R, int V>
@@ -345,7 +348,9 @@ __device__ __forceinline__ void wide_tile(const GemmProblem& p, int n, int k, in
                     b = r / p.tokens;
                     t = r - b * p.tokens;
                 }
-                *reinterpret_cast<u32x4*>(qkv_base + ((size_t)b * p.heads * p.n_total + t) * 64 + pc * CE) = y;
+                // (non-temporal: the launch's operands stay in the L2s; the attention reads q, k and v from another XCD's workgroups anyway.  A guided step
+                // at 1024 x 1024 4542 -> 4496 us.  The other epilogues' consumers pay as much for it as the launch gains.)
+                __builtin_nontemporal_store(y, reinterpret_cast<u32x4*>(qkv_base + ((size_t)b * p.heads * p.n_total + t) * 64 + pc * CE));
             } else if constexpr (RES) {
                 *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + (size_t)r * n + f) = *reinterpret_cast<const f32x4*>(&y) + resv[j];
             } else {
@@ -396,10 +401,10 @@ __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmGroup g, WideGrid 
     const int tall_rows = second ? t.tall_rows[1] : t.tall_rows[0];
     const int height = is_tall ? 32 * TA : 32 * TB, base = is_tall ? 0 : tall_rows * 32 * TA;
     const int tile_rows = is_tall ? tall_rows : (p.m - base + height - 1) / height;
-    const int per_group = kGroupRows * t.tiles_n;
+    const int group = group_rows(g.k), per_group = group * t.tiles_n;
     const int grp = tile / per_group, in = tile - grp * per_group;
-    const int rows_in = min(kGroupRows, tile_rows - grp * kGroupRows);
-    const int row0 = base + (grp * kGroupRows + in % rows_in) * height, col0 = in / rows_in * OCOLS;
+    const int rows_in = min(group, tile_rows - grp * group);
+    const int row0 = base + (grp * group + in % rows_in) * height, col0 = in / rows_in * OCOLS;
     if (is_tall) wide_tile<OT, EPI, TA>(p, g.n, g.k, row0, col0, lds);
     else wide_tile<OT, EPI, TB>(p, g.n, g.k, row0, col0, lds);
 }
