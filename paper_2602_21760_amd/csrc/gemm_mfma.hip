@@ -732,6 +732,11 @@ int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipSt
         if (epi == EPI_QKV && (p.heads <= 0 || n % (p.heads * 64) != 0 || n / (p.heads * 64) > 3)) return -1;
     }
     const bool f32 = out_dtype == HYB_F32;
+    // (where a caller offers scratch for a split of k, its launches of few rows go that way)
+    if (!g.splitk_ws) {
+        const int rc = hyb_launch_gemm_mfma_rows(g, out_dtype, epi, st);
+        if (rc >= 0) return rc;
+    }
     const int rows = large_tile_rows(g, out_dtype, epi);
     const WidePlan wide = wide_plan(g, out_dtype, epi, rows);
     if (wide.tall) return hyb_launch_gemm_mfma_wide(g, out_dtype, epi, wide, st);

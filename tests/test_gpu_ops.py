@@ -467,6 +467,33 @@ def test_linear_192_row_tiles(hb, m, n, slabs):
     assert torch.equal(x, out)
 
 
+@pytest.mark.parametrize("m,n,slabs", [(1, 8, 1), (2, 24, 7), (16, 136, 8), (3, 1536, 9), (1, 1544, 15), (15, 40, 16), (16, 1536, 17), (4, 264, 24), (1, 72, 33)])
+def test_linear_at_most_16_rows(hb, m, n, slabs):
+    """Launches of at most 16 rows, a wave per 16 features: k on both sides of its register sets of eight slabs, ragged features; against the oracle (bf16
+    products are exact in fp32: the bound of fp32 sums), and the bits the same rows get from tiles in a launch of more."""
+    k = 64 * slabs
+    a, w, b = _data(600 + slabs, (m, k), "bf16"), _data(601, (n, k), "bf16", 0.02), _data(602, (n,), "f32", 0.02)
+    res, gate = _data(603, (m, n), "f32"), _data(604, (m, n), "f32")
+    da, dw, db = dev(a, torch.bfloat16), dev(w, torch.bfloat16), dev(b)
+    y = O.linear(a, w, b)
+    cases = [(hb.HYB_EPI_BIAS, torch.float32, {}, y, 1e-5), (hb.HYB_EPI_BIAS, torch.bfloat16, {}, y, 4e-3), (hb.HYB_EPI_GELU_TANH, torch.float32, {}, O.gelu_tanh(y), 1e-5),
+             (hb.HYB_EPI_SILU, torch.bfloat16, {}, O.silu(y), 4e-3),
+             (hb.HYB_EPI_GATE_RESIDUAL, torch.float32, dict(residual=dev(res), gate=dev(gate), rows_per_gate=1, gate_stride=n), res + gate * y, 1e-5)]
+    for epi, dt, kw, ref, bound in cases:
+        out, many = torch.empty(m, n, device="cuda", dtype=dt), torch.empty(20 * m, n, device="cuda", dtype=dt)
+        hb.hyb_trace_enable(True)
+        hb.hyb_linear(da, dw, db, out, epi, **kw)
+        torch.cuda.synchronize()
+        names = hb.hyb_trace_summary()
+        hb.hyb_trace_enable(False)
+        assert list(names) == ["gemm_mfma_16x16.epi%d.n%d.k%d" % (epi, n, k)], names
+        assert err(host(out), ref) < bound, epi
+        if kw:
+            kw = dict(kw, residual=kw["residual"].repeat(20, 1), gate=kw["gate"].repeat(20, 1))
+        hb.hyb_linear(da.repeat(20, 1), dw, db, many, epi, **kw)
+        assert torch.equal(many.view(20, m, n), out.expand(20, m, n)) or m * 20 <= 16, epi
+
+
 @pytest.mark.parametrize("epi,m,n,slabs,rows", [
     ("bias", 2700, 4608, 3, "256"), ("bias", 2714, 4600, 24, "256"), ("gelu", 4429, 6144, 9, "256"), ("bias", 3072, 4096, 12, "192"), ("gelu", 2714, 6152, 17, "192"),
     ("bias", 2048, 4096, 7, "128"), ("bias", 1920, 3848, 20, "128"), ("geglu", 3050, 2560, 11, "256"), ("geglu", 2000, 5128, 20, "192"), ("geglu", 1500, 2568, 9, "128"),
