@@ -13,7 +13,10 @@
 //   S: a 16-byte load gives the lane 4 features of its key (query) row, which feed 4 MFMAs;
 //   PV: register i of the exponentiated S^T is the B operand of the MFMA over keys {4 q4 + i}, and the matching V operand
 //       is one 16-byte load of row 4 q4 + i: the lane's features 4 l16 .. 4 l16 + 3 are row l16 of the output tiles 0 .. 3.
-// Measured: batch 2, 12 heads, 653 tokens 41 us by itself, 43 us inside a model (64 and 60 TFLOP/s); one wave per query row on the vector ALU took 453 us.
+// Two waves share a SIMD and start together, so neither covers the other's softmax: a wave runs the first contraction of its next tile beside the
+// softmax of this one (vector instructions between the MFMAs, no branches in it).
+// Measured: batch 2, 12 heads, 653 tokens 37.7 us by itself (70 TFLOP/s; softmax between the contractions 41.1), 2 x 24 x 1400 264 us (91; 275); one
+// wave per query row on the vector ALU took 453 us for the first.
 #include "attention.h"
 
 namespace {
@@ -30,6 +33,16 @@ __device__ __forceinline__ float exp_neg(float x) {
     const float n = rintf(x * 1.44269502162933349609375f);
     const float f = fmaf(x, 1.92596299112661746887e-8f, fmaf(x, 1.44269502162933349609375f, -n));
     return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
+}
+
+// 64 MFMAs with the vector instructions of the same block spread between them.
+template <int J>
+__device__ __forceinline__ void interleave_vector_work() {
+    if constexpr (J < 64) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x402, 6, 0);
+        interleave_vector_work<J + 1>();
+    }
 }
 
 __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int qblocks, int total, int xcd_run) {
@@ -76,11 +89,7 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int q
     for (int i = 0; i < 8; i++) o[i / 2][i % 2] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int nt = (a.n_kv + BKV - 1) / BKV;
-    if (wave < nt) load_k(wave);
-    for (int t = wave; t < nt; t += WAVES) {
-        load_v(t);                       // in flight under the first contraction
-        __builtin_amdgcn_sched_barrier(0);
-        f32x4 s[2][2];                   // [key tile][query tile]: keys 16 kt + 4 q4 + i
+    auto scores = [&](f32x4 (&s)[2][2]) {    // [key tile][query tile]: keys 16 kt + 4 q4 + i
 #pragma unroll
         for (int i = 0; i < 4; i++) s[i / 2][i % 2] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -92,41 +101,30 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int q
 #pragma unroll
                     for (int qt = 0; qt < 2; qt++)
                         s[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[kt][st][j], q[qt][st][j], s[kt][qt], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        load_k(t + WAVES);               // in flight under the softmax and the second contraction (past the end: the last row)
-        __builtin_amdgcn_sched_barrier(0);
-        const bool ragged = (t + 1) * BKV > a.n_kv;
+    };
+    // scores of tile t -> probabilities; running maximum, normaliser and output rescaled.  Without a branch, so that it can stand between
+    // the next tile's MFMAs (a factor of 1 changes nothing).
+    auto softmax = [&](f32x4 (&s)[2][2], int t) {
+        const int left = a.n_kv - t * BKV - 4 * q4;      // keys 16 kt + i >= left are past the end
 #pragma unroll
         for (int kt = 0; kt < 2; kt++)
 #pragma unroll
             for (int qt = 0; qt < 2; qt++)
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    s[kt][qt][i] *= a.scale;
-                    if (ragged && t * BKV + kt * 16 + 4 * q4 + i >= a.n_kv) s[kt][qt][i] = -__builtin_inff();
-                }
-        if (ragged) {   // (a masked key's probability is 0; its V must not turn that into NaN)
-#pragma unroll
-            for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-                for (int i = 0; i < 4; i++)
-                    if (t * BKV + kt * 16 + 4 * q4 + i >= a.n_kv) v[kt][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+                for (int i = 0; i < 4; i++) s[kt][qt][i] = kt * 16 + i >= left ? -__builtin_inff() : s[kt][qt][i] * a.scale;
 #pragma unroll
         for (int qt = 0; qt < 2; qt++) {
             float mx = fmaxf(fmaxf(fmaxf(s[0][qt][0], s[0][qt][1]), fmaxf(s[0][qt][2], s[0][qt][3])),
                              fmaxf(fmaxf(s[1][qt][0], s[1][qt][1]), fmaxf(s[1][qt][2], s[1][qt][3])));
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            if (__any(mx > m[qt])) {
-                const float m_new = fmaxf(m[qt], mx);
-                const float corr = m[qt] == m_new ? 1.f : exp_neg(m[qt] - m_new);   // first tile: exp(-inf) = 0
-                m[qt] = m_new;
-                l[qt] *= corr;
+            const float m_new = fmaxf(m[qt], mx);
+            const float corr = m[qt] == m_new ? 1.f : exp_neg(m[qt] - m_new);   // first tile: exp(-inf) = 0
+            m[qt] = m_new;
+            l[qt] *= corr;
 #pragma unroll
-                for (int dt = 0; dt < 4; dt++) o[dt][qt] *= corr;
-            }
-            const float ref = m[qt] == -__builtin_inff() ? 0.f : m[qt];          // only masked scores so far: all probabilities 0
+            for (int dt = 0; dt < 4; dt++) o[dt][qt] *= corr;
+            const float ref = m_new == -__builtin_inff() ? 0.f : m_new;          // only masked scores so far: all probabilities 0
 #pragma unroll
             for (int kt = 0; kt < 2; kt++)
 #pragma unroll
@@ -134,6 +132,15 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int q
                     s[kt][qt][i] = exp_neg(s[kt][qt][i] - ref);
                     l[qt] += s[kt][qt][i];
                 }
+        }
+    };
+    auto output = [&](f32x4 (&s)[2][2], int t) {
+        if ((t + 1) * BKV > a.n_kv) {   // (a masked key's probability is 0; its V must not turn that into NaN)
+#pragma unroll
+            for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    if (t * BKV + kt * 16 + 4 * q4 + i >= a.n_kv) v[kt][i] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
         for (int kt = 0; kt < 2; kt++)
@@ -144,6 +151,33 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(AttnArgs a, int q
 #pragma unroll
                     for (int qt = 0; qt < 2; qt++)
                         o[dt][qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[kt][i][dt], s[kt][qt][i], o[dt][qt], 0, 0, 0);
+    };
+    // The first contraction of a wave's next tile runs beside the softmax of this one.  K of the tile after that is requested once it is
+    // done, V of the next tile once this tile's output is.
+    if (wave < nt) {
+        f32x4 cur[2][2], next[2][2];
+        load_k(wave);
+        load_v(wave);
+        scores(cur);
+        __builtin_amdgcn_sched_barrier(0);
+        int t = wave;
+        if (t + WAVES < nt) load_k(t + WAVES);
+        for (; t + WAVES < nt; t += WAVES) {
+            __builtin_amdgcn_sched_barrier(0);
+            scores(next);
+            softmax(cur, t);
+            interleave_vector_work<0>();
+            __builtin_amdgcn_sched_barrier(0);
+            load_k(t + 2 * WAVES);           // (past the end: the last row)
+            __builtin_amdgcn_sched_barrier(0);
+            output(cur, t);
+            __builtin_amdgcn_sched_barrier(0);
+            load_v(t + WAVES);
+#pragma unroll
+            for (int i = 0; i < 4; i++) cur[i / 2][i % 2] = next[i / 2][i % 2];
+        }
+        softmax(cur, t);
+        output(cur, t);
     }
 
     // merge of the waves: row = sum_p o_p e^(m_p - M) / sum_p l_p e^(m_p - M), p in order
