@@ -139,7 +139,7 @@ class MMDiT:
 
     def forward(self, latent, ctx, t, pooled=None):
         """One denoiser evaluation for every batch row; returns v[B, Hh, Ww, C] (activation dtype)."""
-        if latent.shape == self._latent_shape and self._inputs_fit(ctx, pooled):
+        if isinstance(t, torch.Tensor) and latent.shape == self._latent_shape and self._inputs_fit(ctx, pooled):
             self._forward(latent, ctx, t, pooled)
             return self.v
         self.embed(latent, ctx, t, pooled)
