@@ -53,43 +53,6 @@ __device__ __forceinline__ void read_slab(const unsigned (&aa)[2][2], const unsi
                  : "memory");
 }
 
-template <typename OT>
-__device__ __forceinline__ void store4(OT* dst, f32x4 v) {
-    if constexpr (sizeof(OT) == 4) *reinterpret_cast<f32x4*>(dst) = v;
-    else *reinterpret_cast<bf16x4*>(dst) = bf16x4{(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
-}
-
-// Four consecutive features c .. c + 3 (c % 4 == 0, n % 4 == 0) of row r; sums without the bias.
-template <typename OT>
-__device__ __forceinline__ void epilogue4(const GemmProblem& p, int epi, int n, int r, int c, f32x4 v) {
-    if (p.bias) v += *reinterpret_cast<const f32x4*>(p.bias + c);
-    if (epi == EPI_QKV) {       // four features stay inside a head
-        const int hd = p.heads * 64;
-        const int which = c / hd, cc = c % hd, head = cc / 64, i = cc % 64;
-        const int b = r / p.tokens, t = r % p.tokens;
-        if (which == 0 && p.q_scale != 0.f) v *= p.q_scale;
-        OT* base = static_cast<OT*>(which == 0 ? p.q : (which == 1 ? p.k : p.v));
-        store4<OT>(base + (((size_t)b * p.heads + head) * p.n_total + p.tok_offset + t) * 64 + i, v);
-        return;
-    }
-    const size_t o = (size_t)r * n + c;
-    if (epi == EPI_GELU_TANH) {
-#pragma unroll
-        for (int j = 0; j < 4; j++) v[j] = gelu_tanh_f(v[j]);
-    } else if (epi == EPI_SILU) {
-#pragma unroll
-        for (int j = 0; j < 4; j++) v[j] = silu_f(v[j]);
-    } else if (epi == EPI_GATE_RES) {
-        const f32x4 res = *reinterpret_cast<const f32x4*>(p.res + o);
-        f32x4 g = {1.f, 1.f, 1.f, 1.f};
-        if (p.gate) g = *reinterpret_cast<const f32x4*>(p.gate + (size_t)(r / p.rows_per_gate) * p.gate_stride + c);
-#pragma unroll
-        for (int j = 0; j < 4; j++) v[j] = fmaf(g[j], v[j], res[j]);
-        if (p.res2) v += *reinterpret_cast<const f32x4*>(p.res2 + o);
-    }
-    store4<OT>(static_cast<OT*>(p.out) + o, v);
-}
-
 // MN MFMAs with R fragment reads between the first half of them.
 template <int J, int MN, int R>
 __device__ __forceinline__ void interleave_reads() {
@@ -292,12 +255,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
                 }
 #pragma unroll
                 for (int j = 0; j < 4; j++) v[0][j] *= gelu_erf_f(v[1][j]);
-                store4<OT>(static_cast<OT*>(p.out) + (size_t)r * n + c, v[0]);
+                gemm_write_four<OT>(static_cast<OT*>(p.out) + (size_t)r * n + c, v[0]);
             } else {
 #pragma unroll
                 for (int fi = 0; fi < 2; fi++) {
                     const int c = col0 + wf * 32 + fi * 16 + 4 * q4;
-                    if (c < n) epilogue4<OT>(p, epi, n, r, c, v[fi]);
+                    if (c < n) gemm_store_four<OT>(p, epi, n, r, c, v[fi]);
                 }
             }
         }
@@ -336,10 +299,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(GemmGroup g, int 
             }
 #pragma unroll
             for (int j = 0; j < 4; j++) u[j] *= gelu_erf_f(gt[j]);
-            store4<OT>(static_cast<OT*>(p.out) + (size_t)r * n + c, u);
+            gemm_write_four<OT>(static_cast<OT*>(p.out) + (size_t)r * n + c, u);
         } else {
             const int c = col0 + fi * 16 + 4 * q4;
-            if (c < n) epilogue4<OT>(p, epi, n, r, c, total_of(wave));
+            if (c < n) gemm_store_four<OT>(p, epi, n, r, c, total_of(wave));
         }
     }
 }

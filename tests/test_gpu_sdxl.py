@@ -153,6 +153,31 @@ def test_sdxl_block_is_deterministic_with_split_k(hb):
     assert np.array_equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("tokens,channels,n_ctx,planes", [(37, 640, 77, 8), (2305, 1280, 77, 2), (2051, 1280, 77, 3), (2051, 640, 800, 6)])
+def test_sdxl_block_split_k_merge(hb, tokens, channels, n_ctx, planes):
+    """The second pass of the down-projection's k split takes four elements per thread and has a form for each number of
+    planes: the fewest, the most and two between them, with a last workgroup that is not full, against the oracle."""
+    from paper_2602_21760_amd import model
+    cfg = synth.SDXLStageConfig("merge", blocks=1, tokens=tokens, channels=channels, heads=channels // 64, n_ctx=n_ctx, batch=1)
+    w = synth.sdxl_block_weights(cfg, 0)
+    x, ctx = synth.sdxl_inputs(cfg)
+    st = model.SDXLStage(cfg, [w])
+    dx = dev(x)
+    hb.hyb_trace_enable(True)
+    try:
+        st.forward(dx, dev(ctx))
+        torch.cuda.synchronize()
+        merge = hb.hyb_trace_summary()["gemm_splitk_merge"]
+    finally:
+        hb.hyb_trace_enable(False)
+    assert merge["launches"] == 1 and merge["work"] == tokens * channels * 4 * (planes + 1)
+    rows = np.unique(np.concatenate([[0, 1, tokens - 1], np.random.default_rng(9).integers(0, tokens, 30)]))
+    ref = O.sdxl_block_rows(x, ctx, w, cfg.heads, rows)
+    got = host(dx)[:, rows]
+    assert err(got, ref) < TOL_BF16
+    assert err(got - x[:, rows], ref - x[:, rows]) < 5e-2
+
+
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("stage", ["A", "B"])
 def test_sdxl_stage_2048_shapes_sampled_rows(hb, stage):
