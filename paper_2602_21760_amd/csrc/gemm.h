@@ -72,8 +72,7 @@ int hyb_launch_gemm_mfma_wide(const GemmGroup& g, hyb_dtype out_dtype, int epi, 
 // Dispatch: the MFMA kernel of the operand type when it takes the shape, else the plain kernel.
 int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st);
 
-// Scalar epilogue shared by both kernels' tails (v = acc + bias already applied by the caller
-// where the epilogue needs it).
+// Scalar epilogue of the plain kernel (v = acc + bias already applied by the caller where the epilogue needs it).
 template <typename OT>
 __device__ __forceinline__ void gemm_store_scalar(const GemmProblem& p, int epi, int n, int r, int c, float v) {
     if (epi == EPI_QKV) {
