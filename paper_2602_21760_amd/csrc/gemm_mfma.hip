@@ -611,13 +611,16 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
 
 // Estimated length of a launch in us, from the launches' own times over 216 shapes (300-33000 rows; 640-1536 in, 640-6144 out;
 // each tile shape forced): within 3-8 % of what was measured.  A tile costs k-slabs x slab + fixed.
+// 128 x 256 against 256 x 128 tiles with gate and residual are weighed by a step, whose weights come from memory: 4096 + 333 rows x 1536, k 6144
+// (one round of either) 90 against 83 us, the 24-block forward 9720 -> 9597 us with the latter.  (Alone, on weights in the cache, 4977 rows x 1280, k 4096
+// 56.6 against 52.7 us and x 1536 60.5 against 59.9, but 3197 x 1280 42.4 against 45.4 and up to 13 % the same way for 640-768 columns.)
 struct TileCost { float slab, fixed; };
 enum { COST_128, COST_BIG_256, COST_BIG_192, COST_WIDE_128, COST_WIDE_192, COST_WIDE_256, COST_KINDS };
 const TileCost kTileCost[4][COST_KINDS] = {
     /* bias, QKV       */ {{0.83f, 6.0f}, {}, {}, {0.71f, 5.5f}, {0.95f, 6.0f}, {1.20f, 7.7f}},
     /* GELU            */ {{0.89f, 5.5f}, {}, {}, {0.71f, 6.5f}, {0.95f, 7.5f}, {1.20f, 10.0f}},
     /* GEGLU           */ {{0.86f, 5.5f}, {}, {}, {0.71f, 5.0f}, {0.95f, 6.0f}, {1.20f, 9.5f}},
-    /* gate + residual */ {{1.13f, 8.5f}, {0.72f, 19.5f}, {0.70f, 6.0f}, {0.71f, 7.0f}, {0.95f, 9.0f}, {1.20f, 14.0f}},
+    /* gate + residual */ {{1.13f, 8.5f}, {0.66f, 19.5f}, {0.70f, 6.0f}, {0.79f, 9.0f}, {0.95f, 9.0f}, {1.20f, 14.0f}},
 };
 // 64-row tiles, up to three on a CU: (slab + shared x tiles on the CU) per slab
 const float kSmallTileCost[4][3] = {{0.08f, 0.26f, 2.5f}, {0.16f, 0.20f, 2.0f}, {0.28f, 0.14f, 2.5f}, {0.04f, 0.30f, 3.0f}};

@@ -498,7 +498,7 @@ def test_linear_at_most_16_rows(hb, m, n, slabs):
     ("bias", 2700, 4608, 3, "256"), ("bias", 2714, 4600, 24, "256"), ("gelu", 4429, 6144, 9, "256"), ("bias", 3072, 4096, 12, "192"), ("gelu", 2714, 6152, 17, "192"),
     ("bias", 2048, 4096, 7, "128"), ("bias", 1920, 3848, 20, "128"), ("geglu", 3050, 2560, 11, "256"), ("geglu", 2000, 5128, 20, "192"), ("geglu", 1500, 2568, 9, "128"),
     ("gate", 6537, 1544, 24, "192"), ("gate", 4429, 1536, 18, "128"), ("gate", 8858, 1536, 65, "256"),
-    ("gelu", 8858, 6144, 24, "256+192"), ("geglu", 5000, 5120, 20, "256+192"), ("bias", 9000, 4608, 18, "192+128"), ("gate", 16700, 1536, 24, "192+128")])
+    ("gelu", 8858, 6144, 24, "256+192"), ("geglu", 5000, 5120, 20, "256+192"), ("bias", 9000, 4608, 18, "192+128"), ("gate", 8885, 2048, 24, "192+128")])
 def test_linear_256_column_tiles(hb, epi, m, n, slabs, rows):
     """Launches that take 256-column tiles of one height or of two, by the launch rule: even and odd numbers of k-slabs, ragged rows and columns, gate rows that change
     inside a tile, in place; against the oracle (fp32 outputs: bf16 products are exact in fp32, the bound of fp32 sums; bf16 outputs: half
