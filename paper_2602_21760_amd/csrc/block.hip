@@ -4,6 +4,7 @@
 // scatter -> joint attention -> grouped out-projection with gate * y + residual -> LN+modulate ->
 // grouped fc1 with GELU -> grouped fc2 with gate * y + residual.
 #include "attention.h"
+#include "checks.h"
 #include "gemm.h"
 
 int hyb_launch_layernorm(const float* x, const float* shift, const float* scale, size_t mod_stride, void* out,
@@ -68,27 +69,26 @@ extern "C" size_t hyb_block_workspace_bytes(const hyb_block_desc* desc) {
     return block_layout(*desc).total;
 }
 
-extern "C" int hyb_block_forward(const hyb_block_desc* desc, const hyb_block_weights* weights,
-                                 const float* x_img_in, const float* x_txt_in,
-                                 const float* mod_img, const float* mod_txt, size_t mod_stride,
-                                 float* x_img_out, float* x_txt_out,
-                                 void* workspace, size_t workspace_bytes, void* stream) {
-    int rc = check_desc("hyb_block_forward", desc);
+int hyb_check_block_forward(const hyb_block_desc* desc, const hyb_block_weights* weights, const float* x_img_in, const float* x_txt_in,
+                            const float* mod_img, const float* mod_txt, size_t mod_stride, const float* x_img_out, const float* x_txt_out,
+                            const void* workspace, size_t workspace_bytes) {
+    const char* who = "hyb_block_forward";
+    const int rc = check_desc(who, desc);
     if (rc) return rc;
-    HYB_CHECK_PTR(weights);
+    HYB_ARG_PTR(who, weights);
     const hyb_block_desc& d = *desc;
     const int B = d.batch, Ni = d.n_img, Nt = d.n_txt, D = d.hidden, N = Ni + Nt;
     if (B == 0 || N == 0) return HYB_OK;
     const bool has_img = Ni > 0, has_txt = Nt > 0;
     if (has_img) {
-        HYB_CHECK_PTR(x_img_in); HYB_CHECK_PTR(x_img_out); HYB_CHECK_PTR(mod_img);
-        HYB_CHECK_ALIGN(x_img_in); HYB_CHECK_ALIGN(x_img_out); HYB_CHECK_ALIGN(mod_img);
+        HYB_ARG_PTR(who, x_img_in); HYB_ARG_PTR(who, x_img_out); HYB_ARG_PTR(who, mod_img);
+        HYB_ARG_ALIGN(who, x_img_in); HYB_ARG_ALIGN(who, x_img_out); HYB_ARG_ALIGN(who, mod_img);
     }
-    const bool txt_pre_only = d.txt_pre_only != 0 && has_txt;   // text: keys and values only, nothing written back
+    const bool txt_pre_only = d.txt_pre_only != 0 && has_txt;
     if (has_txt) {
-        HYB_CHECK_PTR(x_txt_in); HYB_CHECK_PTR(mod_txt);
-        HYB_CHECK_ALIGN(x_txt_in); HYB_CHECK_ALIGN(mod_txt);
-        if (!txt_pre_only) { HYB_CHECK_PTR(x_txt_out); HYB_CHECK_ALIGN(x_txt_out); }
+        HYB_ARG_PTR(who, x_txt_in); HYB_ARG_PTR(who, mod_txt);
+        HYB_ARG_ALIGN(who, x_txt_in); HYB_ARG_ALIGN(who, mod_txt);
+        if (!txt_pre_only) { HYB_ARG_PTR(who, x_txt_out); HYB_ARG_ALIGN(who, x_txt_out); }
     }
     HYB_REQUIRE(mod_stride % 4 == 0 && mod_stride >= (size_t)6 * D, HYB_ERR_SHAPE, "hyb_block_forward: mod_stride must be a multiple of 4 and at least 6 * hidden");
     const hyb_stream_weights* sw[2] = {&weights->img, &weights->txt};
@@ -101,10 +101,26 @@ extern "C" int hyb_block_forward(const hyb_block_desc* desc, const hyb_block_wei
             HYB_REQUIRE(((uintptr_t)ptrs[i] & 15u) == 0, HYB_ERR_ALIGN, "hyb_block_forward: a weight pointer of the %s stream is not 16-byte aligned", s ? "text" : "image");
         }
     }
-    const BlockLayout L = block_layout(d);
-    HYB_CHECK_PTR(workspace); HYB_CHECK_ALIGN(workspace);
-    HYB_REQUIRE(workspace_bytes >= L.total, HYB_ERR_WORKSPACE, "hyb_block_forward: workspace of %zu bytes is smaller than the %zu required", workspace_bytes, L.total);
+    const size_t need = block_layout(d).total;
+    HYB_ARG_PTR(who, workspace); HYB_ARG_ALIGN(who, workspace);
+    HYB_REQUIRE(workspace_bytes >= need, HYB_ERR_WORKSPACE, "hyb_block_forward: workspace of %zu bytes is smaller than the %zu required", workspace_bytes, need);
+    return HYB_OK;
+}
 
+extern "C" int hyb_block_forward(const hyb_block_desc* desc, const hyb_block_weights* weights,
+                                 const float* x_img_in, const float* x_txt_in,
+                                 const float* mod_img, const float* mod_txt, size_t mod_stride,
+                                 float* x_img_out, float* x_txt_out,
+                                 void* workspace, size_t workspace_bytes, void* stream) {
+    int rc = hyb_check_block_forward(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_stride, x_img_out, x_txt_out, workspace, workspace_bytes);
+    if (rc) return rc;
+    const hyb_block_desc& d = *desc;
+    const int B = d.batch, Ni = d.n_img, Nt = d.n_txt, D = d.hidden, N = Ni + Nt;
+    if (B == 0 || N == 0) return HYB_OK;
+    const bool has_img = Ni > 0, has_txt = Nt > 0;
+    const bool txt_pre_only = d.txt_pre_only != 0 && has_txt;   // text: keys and values only, nothing written back
+    const hyb_stream_weights* sw[2] = {&weights->img, &weights->txt};
+    const BlockLayout L = block_layout(d);
     hipStream_t st = (hipStream_t)stream;
     char* ws = static_cast<char*>(workspace);
     const hyb_dtype dt = d.dtype;

@@ -26,11 +26,13 @@ int hyb_set_error(int code, const char* fmt, ...);
         if (!(cond)) return hyb_set_error((code), __VA_ARGS__); \
     } while (0)
 
-#define HYB_CHECK_PTR(p) HYB_REQUIRE((p) != nullptr, HYB_ERR_NULL, "%s: argument '%s' is NULL", __func__, #p)
-#define HYB_CHECK_ALIGN(p) \
-    HYB_REQUIRE((((uintptr_t)(p)) & 15u) == 0, HYB_ERR_ALIGN, "%s: argument '%s' is not 16-byte aligned", __func__, #p)
-#define HYB_CHECK_DTYPE(d) \
-    HYB_REQUIRE((d) == HYB_F32 || (d) == HYB_BF16, HYB_ERR_DTYPE, "%s: argument '%s' is not a valid dtype", __func__, #d)
+// (who: name of the entry point, for checks that several of them make in one function)
+#define HYB_ARG_PTR(who, p) HYB_REQUIRE((p) != nullptr, HYB_ERR_NULL, "%s: argument '%s' is NULL", who, #p)
+#define HYB_ARG_ALIGN(who, p) HYB_REQUIRE((((uintptr_t)(p)) & 15u) == 0, HYB_ERR_ALIGN, "%s: argument '%s' is not 16-byte aligned", who, #p)
+#define HYB_ARG_DTYPE(who, d) HYB_REQUIRE((d) == HYB_F32 || (d) == HYB_BF16, HYB_ERR_DTYPE, "%s: argument '%s' is not a valid dtype", who, #d)
+#define HYB_CHECK_PTR(p) HYB_ARG_PTR(__func__, p)
+#define HYB_CHECK_ALIGN(p) HYB_ARG_ALIGN(__func__, p)
+#define HYB_CHECK_DTYPE(d) HYB_ARG_DTYPE(__func__, d)
 
 int hyb_check_launch(const char* what);
 

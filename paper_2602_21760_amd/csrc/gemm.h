@@ -46,11 +46,16 @@ struct GemmGroup {
     size_t splitk_bytes;
 };
 
+// Whether the MFMA kernel of the operand type takes a launch; the plain kernel has the others.
+bool hyb_gemm_f32_mfma_takes(const GemmGroup& g, int epi);
+bool hyb_gemm_mfma_takes(const GemmGroup& g, hyb_dtype out_dtype, int epi);
+// The error that hyb_launch_gemm would return for a launch that no kernel takes, without launching anything.
+int hyb_check_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi);
 // Plain tiled FMA kernel: any shape, fp32 or bf16 operands, fp32 accumulation.
 int hyb_launch_gemm_simple(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st);
-// fp32 MFMA kernel (k % 16 == 0, n % 4 == 0; every epilogue); returns -1 if the shape is not supported.
+// fp32 MFMA kernel (k % 16 == 0, n % 4 == 0; every epilogue), for what hyb_gemm_f32_mfma_takes.
 int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
-// bf16 MFMA kernel (k % 64 == 0, n % 8 == 0); returns -1 if the shape is not supported.
+// bf16 MFMA kernel (k % 64 == 0, n % 8 == 0), for what hyb_gemm_mfma_takes.
 int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
 // 128 x 128 tiles of an m x n product (two of them fit a CU).
 int hyb_gemm_mfma_tiles(int m, int n);

@@ -336,22 +336,29 @@ int launch_any(const GemmGroup& g, int epi, bool small, bool deep, hipStream_t s
 
 }  // namespace
 
-int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st) {
-    if (g.k <= 0 || g.k % (BK / 2) != 0 || g.n % 4 != 0 || g.n < 4) return -1;
+// Tiles of a launch: `rows` x `rows`, half as many output columns for GEGLU.
+static double tiles_of(const GemmGroup& g, int epi, int rows) {
+    const int cols = epi == EPI_GEGLU ? rows / 2 : rows;
+    double tiles = 0;
+    for (int i = 0; i < g.count; i++) tiles += ((g.p[i].m + rows - 1) / rows) * (double)((g.n + cols - 1) / cols);
+    return tiles;
+}
+
+bool hyb_gemm_f32_mfma_takes(const GemmGroup& g, int epi) {
+    if (g.k <= 0 || g.k % (BK / 2) != 0 || g.n % 4 != 0 || g.n < 4) return false;
     // per-lane byte offsets inside a tile's operand rows are 32-bit; for GEGLU the gate rows lie n rows further down
-    if ((size_t)g.k * 4 * ((epi == EPI_GEGLU ? (size_t)g.n : 0) + 64) >= ((size_t)1 << 31)) return -1;
-    double tiles64 = 0, tiles32 = 0;
-    const int T64 = epi == EPI_GEGLU ? 32 : 64, T32 = T64 / 2;      // output columns of a tile
-    const double cols64 = (g.n + T64 - 1) / T64, cols32 = (g.n + T32 - 1) / T32;
+    if ((size_t)g.k * 4 * ((epi == EPI_GEGLU ? (size_t)g.n : 0) + 64) >= ((size_t)1 << 31)) return false;
     for (int i = 0; i < g.count; i++) {
         const GemmProblem& p = g.p[i];
-        if (epi == EPI_GATE_RES && p.gate && p.gate_stride % 4 != 0) return -1;
-        if (((uintptr_t)p.gate & 15u) != 0) return -1;
-        tiles64 += ((p.m + 63) / 64) * cols64;
-        tiles32 += ((p.m + 31) / 32) * cols32;
+        if (epi == EPI_GATE_RES && p.gate && p.gate_stride % 4 != 0) return false;
+        if (((uintptr_t)p.gate & 15u) != 0) return false;
     }
+    return tiles_of(g, epi, 32) <= 1e9;
+}
+
+int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st) {
+    const double tiles64 = tiles_of(g, epi, 64), tiles32 = tiles_of(g, epi, 32);
     if (tiles32 == 0) return HYB_OK;
-    if (tiles32 > 1e9) return -1;
     // A 64 x 64 tile takes a CU four times as long as a 32 x 32 one: the small tiles where they take a fifth or more off the
     // work of the busiest CU, the large ones (half the operand traffic) otherwise; small against large tiles over 124 random shapes:
     // 0.30-1.08 of the time where that work is 0.75 or less, 0.97-1.73 where it is more.  (653 x 768 x 3072: 30 against

@@ -737,19 +737,24 @@ WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_r
 
 int hyb_gemm_mfma_tiles(int m, int n) { return ((m + 127) / 128) * ((n + BN - 1) / BN); }
 
-int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st) {
-    if (g.k <= 0 || g.k % BK != 0 || g.n % 8 != 0 || g.n < 8) return -1;
+bool hyb_gemm_mfma_takes(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
+    if (g.k <= 0 || g.k % BK != 0 || g.n % 8 != 0 || g.n < 8) return false;
     // per-lane byte offsets inside a tile's operand buffers are 32-bit: up to 128 rows of k elements, and for the
     // gated epilogue the gate rows n rows further down
-    if ((size_t)g.k * 2 * 256 >= ((size_t)1 << 31)) return -1;
-    if (epi == EPI_GEGLU && ((size_t)g.n + 128) * g.k * 2 >= ((size_t)1 << 31)) return -1;
-    if (g.n2 && (epi != EPI_QKV || g.k2 <= 0 || g.k2 % BK != 0 || g.n2 % 8 != 0 || (size_t)g.k2 * 2 * 256 >= ((size_t)1 << 31))) return -1;
+    if ((size_t)g.k * 2 * 256 >= ((size_t)1 << 31)) return false;
+    if (epi == EPI_GEGLU && ((size_t)g.n + 128) * g.k * 2 >= ((size_t)1 << 31)) return false;
+    if (g.n2 && (epi != EPI_QKV || g.k2 <= 0 || g.k2 % BK != 0 || g.n2 % 8 != 0 || (size_t)g.k2 * 2 * 256 >= ((size_t)1 << 31))) return false;
     for (int i = 0; i < g.count; i++) {
         const GemmProblem& p = g.p[i];
-        if (epi == EPI_GATE_RES && p.gate && (p.gate_stride % 4 != 0)) return -1;
+        if (epi == EPI_GATE_RES && p.gate && (p.gate_stride % 4 != 0)) return false;
         const int n = i == 1 && g.n2 ? g.n2 : g.n;
-        if (epi == EPI_QKV && (p.heads <= 0 || n % (p.heads * 64) != 0 || n / (p.heads * 64) > 3)) return -1;
+        if (epi == EPI_QKV && (p.heads <= 0 || n % (p.heads * 64) != 0 || n / (p.heads * 64) > 3)) return false;
     }
+    const bool f32 = out_dtype == HYB_F32;
+    return epi == EPI_GATE_RES ? f32 : (epi == EPI_QKV || epi == EPI_GEGLU ? !f32 : epi == EPI_BIAS || epi == EPI_GELU_TANH || epi == EPI_SILU);
+}
+
+int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st) {
     const bool f32 = out_dtype == HYB_F32;
     // (where a caller offers scratch for a split of k, its launches of few rows go that way)
     if (!g.splitk_ws) {
@@ -767,9 +772,9 @@ int hyb_launch_gemm_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipSt
         case EPI_BIAS: return f32 ? launch_epi<float, EPI_BIAS>(g, st) : launch_epi<bf16_t, EPI_BIAS>(g, st);
         case EPI_GELU_TANH: return f32 ? launch_epi<float, EPI_GELU_TANH>(g, st) : launch_epi<bf16_t, EPI_GELU_TANH>(g, st);
         case EPI_SILU: return f32 ? launch_epi<float, EPI_SILU>(g, st) : launch_epi<bf16_t, EPI_SILU>(g, st);
-        case EPI_GATE_RES: return f32 ? launch_epi<float, EPI_GATE_RES>(g, st) : -1;
-        case EPI_QKV: return f32 ? -1 : launch_epi<bf16_t, EPI_QKV>(g, st);
-        case EPI_GEGLU: return f32 ? -1 : launch_epi<bf16_t, EPI_GEGLU>(g, st);
-        default: return -1;
+        case EPI_GATE_RES: return launch_epi<float, EPI_GATE_RES>(g, st);
+        case EPI_QKV: return launch_epi<bf16_t, EPI_QKV>(g, st);
+        case EPI_GEGLU: return launch_epi<bf16_t, EPI_GEGLU>(g, st);
+        default: return hyb_set_error(HYB_ERR_DTYPE, "gemm: unknown epilogue %d", epi);
     }
 }

@@ -1,5 +1,6 @@
 // Plain LDS-tiled FMA GEMM: out = epilogue(A W^T + bias) for any shape, fp32 or bf16 operands,
 // fp32 accumulation in a fixed k order: the fallback for the shapes that the MFMA kernels do not take.
+#include "checks.h"
 #include "gemm.h"
 
 namespace {
@@ -75,7 +76,6 @@ int launch(const GemmGroup& g, int epi, hipStream_t st) {
     const int tiles_m1 = g.count > 1 ? (g.p[1].m + TS - 1) / TS : 0;
     if (tiles_m0 + tiles_m1 == 0 || g.n == 0) return HYB_OK;
     dim3 grid((g.n + TS - 1) / TS, tiles_m0 + tiles_m1), block(256);
-    HYB_REQUIRE(grid.y <= 65535, HYB_ERR_SHAPE, "gemm: too many row tiles (%u)", grid.y);
     char name[96];
     if (hyb_trace_on()) snprintf(name, sizeof(name), "gemm_simple.epi%d.n%d.k%d", epi, g.n, g.k);
     double rows = g.p[0].m + (g.count > 1 ? g.p[1].m : 0);
@@ -92,32 +92,60 @@ int hyb_launch_gemm_simple(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out
     return out_dtype == HYB_F32 ? launch<bf16_t, float>(g, epi, st) : launch<bf16_t, bf16_t>(g, epi, st);
 }
 
-int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st) {
-    const int rc = in_dtype == HYB_BF16 ? hyb_launch_gemm_mfma(g, out_dtype, epi, st) : hyb_launch_gemm_f32_mfma(g, out_dtype, epi, st);
-    if (rc >= 0) return rc;
+static bool mfma_takes(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi) {
+    return in_dtype == HYB_BF16 ? hyb_gemm_mfma_takes(g, out_dtype, epi) : hyb_gemm_f32_mfma_takes(g, epi);
+}
+
+int hyb_check_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi) {
+    if (mfma_takes(g, in_dtype, out_dtype, epi)) return HYB_OK;
     HYB_REQUIRE(g.n2 == 0, HYB_ERR_SHAPE, "gemm: no kernel takes this pair of problems of different shapes");
-    return hyb_launch_gemm_simple(g, in_dtype, out_dtype, epi, st);
+    long row_tiles = 0;
+    for (int i = 0; i < g.count; i++) row_tiles += (g.p[i].m + (long)TS - 1) / TS;
+    HYB_REQUIRE(row_tiles <= 65535, HYB_ERR_SHAPE, "gemm: too many row tiles (%ld)", row_tiles);
+    return HYB_OK;
+}
+
+int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype, int epi, hipStream_t st) {
+    if (mfma_takes(g, in_dtype, out_dtype, epi)) return in_dtype == HYB_BF16 ? hyb_launch_gemm_mfma(g, out_dtype, epi, st) : hyb_launch_gemm_f32_mfma(g, out_dtype, epi, st);
+    const int rc = hyb_check_gemm(g, in_dtype, out_dtype, epi);
+    return rc ? rc : hyb_launch_gemm_simple(g, in_dtype, out_dtype, epi, st);
+}
+
+// The arguments of hyb_linear: checked, and as one problem (count 0: nothing to do).
+static int linear_problem(GemmGroup& g, const void* a, const void* w, const float* bias, const void* out, int m, int n, int k, hyb_dtype dtype,
+                          hyb_dtype out_dtype, hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride) {
+    const char* who = "hyb_linear";
+    g = {};
+    HYB_ARG_DTYPE(who, dtype); HYB_ARG_DTYPE(who, out_dtype);
+    HYB_REQUIRE((epi >= HYB_EPI_BIAS && epi <= HYB_EPI_GATE_RESIDUAL) || epi == HYB_EPI_GEGLU, HYB_ERR_DTYPE, "hyb_linear: unknown epilogue %d", (int)epi);
+    HYB_REQUIRE(m >= 0 && n >= 0 && k >= 0, HYB_ERR_SHAPE, "hyb_linear: negative size");
+    if (m == 0 || n == 0) return HYB_OK;
+    HYB_ARG_PTR(who, a); HYB_ARG_PTR(who, w); HYB_ARG_PTR(who, out);
+    HYB_ARG_ALIGN(who, a); HYB_ARG_ALIGN(who, w); HYB_ARG_ALIGN(who, out); HYB_ARG_ALIGN(who, bias);
+    g.count = 1; g.n = n; g.k = k;
+    GemmProblem& p = g.p[0];
+    p.a = a; p.w = w; p.bias = bias; p.out = const_cast<void*>(out); p.m = m;
+    if (epi == HYB_EPI_GATE_RESIDUAL) {
+        HYB_REQUIRE(out_dtype == HYB_F32, HYB_ERR_DTYPE, "hyb_linear: HYB_EPI_GATE_RESIDUAL needs an fp32 output");
+        HYB_ARG_PTR(who, residual); HYB_ARG_ALIGN(who, residual); HYB_ARG_ALIGN(who, gate);
+        HYB_REQUIRE(gate == nullptr || rows_per_gate > 0, HYB_ERR_SHAPE, "hyb_linear: rows_per_gate must be positive");
+        p.res = residual; p.gate = gate; p.rows_per_gate = rows_per_gate > 0 ? rows_per_gate : 1; p.gate_stride = gate_stride;
+    }
+    return HYB_OK;
+}
+
+int hyb_check_linear(const void* a, const void* w, const float* bias, const void* out, int m, int n, int k, hyb_dtype dtype, hyb_dtype out_dtype,
+                     hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride) {
+    GemmGroup g;
+    const int rc = linear_problem(g, a, w, bias, out, m, n, k, dtype, out_dtype, epi, residual, gate, rows_per_gate, gate_stride);
+    return rc || g.count == 0 ? rc : hyb_check_gemm(g, dtype, out_dtype, (int)epi);
 }
 
 extern "C" int hyb_linear(const void* a, const void* w, const float* bias, void* out, int m, int n, int k,
                           hyb_dtype dtype, hyb_dtype out_dtype, hyb_epilogue epi,
                           const float* residual, const float* gate, int rows_per_gate, size_t gate_stride,
                           void* stream) {
-    HYB_CHECK_DTYPE(dtype); HYB_CHECK_DTYPE(out_dtype);
-    HYB_REQUIRE((epi >= HYB_EPI_BIAS && epi <= HYB_EPI_GATE_RESIDUAL) || epi == HYB_EPI_GEGLU, HYB_ERR_DTYPE, "hyb_linear: unknown epilogue %d", (int)epi);
-    HYB_REQUIRE(m >= 0 && n >= 0 && k >= 0, HYB_ERR_SHAPE, "hyb_linear: negative size");
-    if (m == 0 || n == 0) return HYB_OK;
-    HYB_CHECK_PTR(a); HYB_CHECK_PTR(w); HYB_CHECK_PTR(out);
-    HYB_CHECK_ALIGN(a); HYB_CHECK_ALIGN(w); HYB_CHECK_ALIGN(out); HYB_CHECK_ALIGN(bias);
-    GemmGroup g = {};
-    g.count = 1; g.n = n; g.k = k;
-    GemmProblem& p = g.p[0];
-    p.a = a; p.w = w; p.bias = bias; p.out = out; p.m = m;
-    if (epi == HYB_EPI_GATE_RESIDUAL) {
-        HYB_REQUIRE(out_dtype == HYB_F32, HYB_ERR_DTYPE, "hyb_linear: HYB_EPI_GATE_RESIDUAL needs an fp32 output");
-        HYB_CHECK_PTR(residual); HYB_CHECK_ALIGN(residual); HYB_CHECK_ALIGN(gate);
-        HYB_REQUIRE(gate == nullptr || rows_per_gate > 0, HYB_ERR_SHAPE, "hyb_linear: rows_per_gate must be positive");
-        p.res = residual; p.gate = gate; p.rows_per_gate = rows_per_gate > 0 ? rows_per_gate : 1; p.gate_stride = gate_stride;
-    }
-    return hyb_launch_gemm(g, dtype, out_dtype, (int)epi, (hipStream_t)stream);
+    GemmGroup g;
+    const int rc = linear_problem(g, a, w, bias, out, m, n, k, dtype, out_dtype, epi, residual, gate, rows_per_gate, gate_stride);
+    return rc || g.count == 0 ? rc : hyb_launch_gemm(g, dtype, out_dtype, (int)epi, (hipStream_t)stream);
 }

@@ -2,7 +2,7 @@
 // modulation GEMV, GroupNorm, timestep features, patchify / unpatchify, dtype conversion.
 // (The denoiser f_theta is a black box in the paper, Sec. 4.1; these are the parts of the
 // transformer block around the contractions.)
-#include "common.h"
+#include "checks.h"
 
 #include <type_traits>
 
@@ -578,30 +578,45 @@ int hyb_launch_groupnorm_layernorm(const float* x, const float* gamma, const flo
     return hyb_check_launch("groupnorm_layernorm");
 }
 
-extern "C" int hyb_layernorm_modulate(const float* x, const float* shift, const float* scale, size_t mod_stride,
-                                      void* out, int batch, int tokens, int hidden, float eps,
-                                      hyb_dtype out_dtype, void* stream) {
-    HYB_CHECK_DTYPE(out_dtype);
+int hyb_check_layernorm_modulate(const float* x, const float* shift, const float* scale, size_t mod_stride, const void* out, int batch, int tokens,
+                                 int hidden, hyb_dtype out_dtype) {
+    const char* who = "hyb_layernorm_modulate";
+    HYB_ARG_DTYPE(who, out_dtype);
     HYB_REQUIRE(batch >= 0 && tokens >= 0, HYB_ERR_SHAPE, "hyb_layernorm_modulate: negative size");
     HYB_REQUIRE(hidden > 0 && hidden % 4 == 0 && hidden <= kLnMaxVec * 256, HYB_ERR_SHAPE,
                 "hyb_layernorm_modulate: hidden %d must be a positive multiple of 4, at most %d", hidden, kLnMaxVec * 256);
     if (batch == 0 || tokens == 0) return HYB_OK;
-    HYB_CHECK_PTR(x); HYB_CHECK_PTR(out);
-    HYB_CHECK_ALIGN(x); HYB_CHECK_ALIGN(out); HYB_CHECK_ALIGN(shift); HYB_CHECK_ALIGN(scale);
+    HYB_ARG_PTR(who, x); HYB_ARG_PTR(who, out);
+    HYB_ARG_ALIGN(who, x); HYB_ARG_ALIGN(who, out); HYB_ARG_ALIGN(who, shift); HYB_ARG_ALIGN(who, scale);
     HYB_REQUIRE((shift == nullptr) == (scale == nullptr), HYB_ERR_NULL, "hyb_layernorm_modulate: shift and scale must both be given or both be NULL");
     HYB_REQUIRE(mod_stride % 4 == 0, HYB_ERR_ALIGN, "hyb_layernorm_modulate: mod_stride must be a multiple of 4");
+    return HYB_OK;
+}
+
+extern "C" int hyb_layernorm_modulate(const float* x, const float* shift, const float* scale, size_t mod_stride,
+                                      void* out, int batch, int tokens, int hidden, float eps,
+                                      hyb_dtype out_dtype, void* stream) {
+    const int rc = hyb_check_layernorm_modulate(x, shift, scale, mod_stride, out, batch, tokens, hidden, out_dtype);
+    if (rc || batch == 0 || tokens == 0) return rc;
     return hyb_launch_layernorm(x, shift, scale, mod_stride, out, batch, tokens, hidden, eps, out_dtype, false, (hipStream_t)stream);
 }
 
-extern "C" int hyb_adaln_modulation(const void* w, const float* bias, const float* temb, float* out,
-                                    int rows, int hidden, int batch, hyb_dtype dtype, void* stream) {
-    HYB_CHECK_DTYPE(dtype);
+int hyb_check_adaln_modulation(const void* w, const float* bias, const float* temb, const float* out, int rows, int hidden, int batch, hyb_dtype dtype) {
+    const char* who = "hyb_adaln_modulation";
+    HYB_ARG_DTYPE(who, dtype);
     HYB_REQUIRE(rows >= 0 && batch >= 0, HYB_ERR_SHAPE, "hyb_adaln_modulation: negative size");
     HYB_REQUIRE(hidden > 0 && hidden % 8 == 0 && hidden <= 4096, HYB_ERR_SHAPE,
                 "hyb_adaln_modulation: hidden %d must be a positive multiple of 8, at most 4096", hidden);
     if (rows == 0 || batch == 0) return HYB_OK;
-    HYB_CHECK_PTR(w); HYB_CHECK_PTR(bias); HYB_CHECK_PTR(temb); HYB_CHECK_PTR(out);
-    HYB_CHECK_ALIGN(w); HYB_CHECK_ALIGN(bias); HYB_CHECK_ALIGN(temb); HYB_CHECK_ALIGN(out);
+    HYB_ARG_PTR(who, w); HYB_ARG_PTR(who, bias); HYB_ARG_PTR(who, temb); HYB_ARG_PTR(who, out);
+    HYB_ARG_ALIGN(who, w); HYB_ARG_ALIGN(who, bias); HYB_ARG_ALIGN(who, temb); HYB_ARG_ALIGN(who, out);
+    return HYB_OK;
+}
+
+extern "C" int hyb_adaln_modulation(const void* w, const float* bias, const float* temb, float* out,
+                                    int rows, int hidden, int batch, hyb_dtype dtype, void* stream) {
+    const int bad = hyb_check_adaln_modulation(w, bias, temb, out, rows, hidden, batch, dtype);
+    if (bad || rows == 0 || batch == 0) return bad;
     hipStream_t st = (hipStream_t)stream;
     // as many groups of rows for every wave, as few as keep the waves to kAdaWaves
     const int groups = (rows + kAdaRowsPerWave - 1) / kAdaRowsPerWave, each = (groups + kAdaWaves - 1) / kAdaWaves;
@@ -627,9 +642,16 @@ extern "C" int hyb_adaln_modulation(const void* w, const float* bias, const floa
     return HYB_OK;
 }
 
-// t == nullptr: t_value for all samples.
-int hyb_launch_timestep_embedding(const float* t, float t_value, void* out, int batch, int dim, hyb_dtype out_dtype, hipStream_t st) {
+int hyb_check_timestep_embedding(const void* out, int batch, int dim, hyb_dtype out_dtype) {
+    const char* who = "hyb_timestep_embedding";
+    HYB_ARG_DTYPE(who, out_dtype);
     HYB_REQUIRE(batch >= 0 && dim > 0 && dim % 2 == 0, HYB_ERR_SHAPE, "hyb_timestep_embedding: batch >= 0 and an even dim > 0 required");
+    if (batch > 0) HYB_ARG_PTR(who, out);
+    return HYB_OK;
+}
+
+// t == nullptr: t_value for all samples.  (The arguments have been checked.)
+int hyb_launch_timestep_embedding(const float* t, float t_value, void* out, int batch, int dim, hyb_dtype out_dtype, hipStream_t st) {
     if (batch == 0) return HYB_OK;
     const int n = batch * dim;
     if (out_dtype == HYB_F32) hipLaunchKernelGGL((timestep_embedding_kernel<float>), dim3((n + 255) / 256), dim3(256), 0, st, t, t_value, (float*)out, batch, dim);
@@ -638,8 +660,9 @@ int hyb_launch_timestep_embedding(const float* t, float t_value, void* out, int 
 }
 
 extern "C" int hyb_timestep_embedding(const float* t, void* out, int batch, int dim, hyb_dtype out_dtype, void* stream) {
-    HYB_CHECK_DTYPE(out_dtype);
-    if (batch > 0 && dim > 0 && dim % 2 == 0) { HYB_CHECK_PTR(t); HYB_CHECK_PTR(out); }
+    const int rc = hyb_check_timestep_embedding(out, batch, dim, out_dtype);
+    if (rc) return rc;
+    if (batch > 0) HYB_CHECK_PTR(t);
     return hyb_launch_timestep_embedding(t, 0.f, out, batch, dim, out_dtype, (hipStream_t)stream);
 }
 
@@ -649,28 +672,40 @@ static int check_patch(const char* who, int batch, int hh, int ww, int c, int p)
     return HYB_OK;
 }
 
+int hyb_check_patchify(const float* latent, const void* tokens, int batch, int hh, int ww, int c, int p, hyb_dtype out_dtype) {
+    const char* who = "hyb_patchify";
+    HYB_ARG_DTYPE(who, out_dtype);
+    const int rc = check_patch(who, batch, hh, ww, c, p);
+    if (rc || (size_t)batch * hh * ww * c == 0) return rc;
+    HYB_ARG_PTR(who, latent); HYB_ARG_PTR(who, tokens);
+    return HYB_OK;
+}
+
 extern "C" int hyb_patchify(const float* latent, void* tokens, int batch, int hh, int ww, int c, int p,
                             hyb_dtype out_dtype, void* stream) {
-    HYB_CHECK_DTYPE(out_dtype);
-    int rc = check_patch("hyb_patchify", batch, hh, ww, c, p);
-    if (rc) return rc;
+    const int rc = hyb_check_patchify(latent, tokens, batch, hh, ww, c, p, out_dtype);
     const size_t n = (size_t)batch * hh * ww * c;
-    if (n == 0) return HYB_OK;
-    HYB_CHECK_PTR(latent); HYB_CHECK_PTR(tokens);
+    if (rc || n == 0) return rc;
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
     if (out_dtype == HYB_F32) hipLaunchKernelGGL((patch_kernel<float, const float, true>), grid, block, 0, (hipStream_t)stream, latent, (float*)tokens, batch, hh, ww, c, p);
     else hipLaunchKernelGGL((patch_kernel<bf16_t, const float, true>), grid, block, 0, (hipStream_t)stream, latent, (bf16_t*)tokens, batch, hh, ww, c, p);
     return hyb_check_launch("hyb_patchify");
 }
 
+int hyb_check_unpatchify(const void* tokens, const void* latent, int batch, int hh, int ww, int c, int p, hyb_dtype in_dtype, hyb_dtype out_dtype) {
+    const char* who = "hyb_unpatchify";
+    HYB_ARG_DTYPE(who, in_dtype); HYB_ARG_DTYPE(who, out_dtype);
+    const int rc = check_patch(who, batch, hh, ww, c, p);
+    if (rc || (size_t)batch * hh * ww * c == 0) return rc;
+    HYB_ARG_PTR(who, latent); HYB_ARG_PTR(who, tokens);
+    return HYB_OK;
+}
+
 extern "C" int hyb_unpatchify(const void* tokens, void* latent, int batch, int hh, int ww, int c, int p,
                               hyb_dtype in_dtype, hyb_dtype out_dtype, void* stream) {
-    HYB_CHECK_DTYPE(in_dtype); HYB_CHECK_DTYPE(out_dtype);
-    int rc = check_patch("hyb_unpatchify", batch, hh, ww, c, p);
-    if (rc) return rc;
+    const int rc = hyb_check_unpatchify(tokens, latent, batch, hh, ww, c, p, in_dtype, out_dtype);
     const size_t n = (size_t)batch * hh * ww * c;
-    if (n == 0) return HYB_OK;
-    HYB_CHECK_PTR(latent); HYB_CHECK_PTR(tokens);
+    if (rc || n == 0) return rc;
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
     hipStream_t st = (hipStream_t)stream;
     if (in_dtype == HYB_F32 && out_dtype == HYB_F32) hipLaunchKernelGGL((patch_kernel<const float, float, false>), grid, block, 0, st, (float*)latent, (const float*)tokens, batch, hh, ww, c, p);
@@ -680,10 +715,17 @@ extern "C" int hyb_unpatchify(const void* tokens, void* latent, int batch, int h
     return hyb_check_launch("hyb_unpatchify");
 }
 
-extern "C" int hyb_convert(const float* in, void* out, size_t n, hyb_dtype out_dtype, void* stream) {
-    HYB_CHECK_DTYPE(out_dtype);
+int hyb_check_convert(const float* in, const void* out, size_t n, hyb_dtype out_dtype) {
+    const char* who = "hyb_convert";
+    HYB_ARG_DTYPE(who, out_dtype);
     if (n == 0) return HYB_OK;
-    HYB_CHECK_PTR(in); HYB_CHECK_PTR(out);
+    HYB_ARG_PTR(who, in); HYB_ARG_PTR(who, out);
+    return HYB_OK;
+}
+
+extern "C" int hyb_convert(const float* in, void* out, size_t n, hyb_dtype out_dtype, void* stream) {
+    const int rc = hyb_check_convert(in, out, n, out_dtype);
+    if (rc || n == 0) return rc;
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
     if (out_dtype == HYB_F32) hipLaunchKernelGGL((convert_kernel<float>), grid, block, 0, (hipStream_t)stream, in, (float*)out, n);
     else hipLaunchKernelGGL((convert_kernel<bf16_t>), grid, block, 0, (hipStream_t)stream, in, (bf16_t*)out, n);

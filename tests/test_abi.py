@@ -93,6 +93,50 @@ def test_argument_validation_happens_before_any_gpu_work(lib):
     assert lib.hyb_linear(None, vp(16), None, vp(16), 8, 64, 64, 1, 1, 5, None, None, 1, 0, None) == 1    # NULL a
 
 
+FORWARD_ERRORS = [
+    # (what is wrong, error code): a descriptor field, a weight, a buffer, a weight of one block, an argument
+    ("desc.temb_dim=255", 2), ("desc.hidden=192", 2), ("desc.hidden=2112", 2), ("desc.heads=3", 2), ("desc.patch=3", 2), ("desc.dtype=7", 3), ("desc.mlp_ratio=0", 2), ("desc.batch=65536", 2),
+    ("weights.t1_w=0", 1), ("weights.t2_w=8", 4), ("weights.p1_w=0", 1), ("weights.p2_b=8", 4), ("weights.pe_w=0", 1), ("weights.pe_b=8", 4), ("weights.pos=0", 1),
+    ("weights.ce_w=0", 1), ("weights.ada_w=0", 1), ("weights.ada_b=0", 1), ("weights.f_w=0", 1), ("weights.f_b=8", 4), ("weights.block_weights=0", 1),
+    ("buffers.t_feat=0", 1), ("buffers.t_hid=8", 4), ("buffers.pooled_act=0", 1), ("buffers.p_hid=0", 1), ("buffers.temb=0", 1), ("buffers.mod=0", 1), ("buffers.tok=0", 1),
+    ("buffers.ctx_act=0", 1), ("buffers.x_img=0", 1), ("buffers.x_txt=0", 1), ("buffers.y=0", 1), ("buffers.out_tok=8", 4), ("buffers.v=0", 1), ("buffers.ws=0", 1), ("buffers.ws=8", 4),
+    ("buffers.ws_bytes=1024", 5), ("block.img.qkv_w=0", 1), ("block.txt.fc2_b=0", 1), ("block.img.fc1_w=8", 4), ("args.latent=0", 1), ("args.ctx=0", 1), ("args.pooled=0", 1)]
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("wrong,code", FORWARD_ERRORS)
+def test_forward_errors_come_before_any_launch(lib, wrong, code, dtype):
+    """hyb_mmdit_forward finds every error before it enqueues anything: without a device a launch is an error of its own
+    (HYB_ERR_LAUNCH), and the pointers here lead nowhere."""
+    from paper_2602_21760_amd import binding
+    lib.hyb_mmdit_forward.restype, lib.hyb_mmdit_forward.argtypes = binding.SIGNATURES["hyb_mmdit_forward"]
+    some = 4096
+    blocks = (binding.BlockWeights * 2)(*[binding.BlockWeights(*[binding.StreamWeights(*[some] * 8) for _ in range(2)]) for _ in range(2)])
+    desc = binding.MMDiTDesc(batch=2, blocks=2, hidden=128, heads=2, mlp_ratio=4, latent_h=8, latent_w=8, latent_c=16, patch=2, n_txt=5, ctx_dim=64, temb_dim=256,
+                             pooled_dim=64, dtype=dtype, ln_eps=1e-6)
+    weights = binding.MMDiTWeights(*[some] * len(binding.MMDIT_WEIGHT_FIELDS), blocks)
+    buffers = binding.MMDiTBuffers(*[some] * len(binding.MMDIT_BUFFER_FIELDS), 1 << 30)
+    args = {"latent": some, "ctx": some, "pooled": some}
+    where, field, value = re.match(r"(\w+)\.(.+)=(\d+)", wrong).groups()
+    if field in ("pooled_act", "ctx_act") and dtype == 0:      # fp32 models copy only what is not aligned
+        args[field.split("_")[0]] = some + 4
+    if where == "args":
+        args[field] = int(value) or None
+    elif where == "block":
+        stream, name = field.split(".")
+        part = getattr(blocks[1], stream)
+        names = ("qkv_w", "out_w", "fc1_w", "fc2_w", "qkv_b", "out_b", "fc1_b", "fc2_b")
+        setattr(part, binding.StreamWeights._fields_[names.index(name)][0], int(value) or None)
+    elif field == "block_weights":
+        weights.block_weights = None
+    else:
+        setattr({"desc": desc, "weights": weights, "buffers": buffers}[where], field, int(value) or (None if where != "desc" else 0))
+    rc = lib.hyb_mmdit_forward(ctypes.byref(desc), ctypes.byref(weights), ctypes.byref(buffers), args["latent"], 0, args["ctx"], None, 0.5, args["pooled"], 0, None)
+    lib.hyb_last_error_string.restype = ctypes.c_char_p
+    assert rc == code, (wrong, rc, lib.hyb_last_error_string())
+    assert lib.hyb_last_error_string().startswith(b"hyb_mmdit_forward: "), lib.hyb_last_error_string()
+
+
 def test_struct_layouts_match_the_header(tmp_path):
     """The ctypes structures of the binding against sizeof / offsetof of the C declarations (compiled with gcc:
     the header is plain C)."""
