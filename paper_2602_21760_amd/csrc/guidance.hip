@@ -153,79 +153,131 @@ __global__ __launch_bounds__(HYB_WAVE) void discrepancy_finalize_kernel(const do
 }
 
 // The pass and the discrepancies of small samples in one launch: workgroups 1 .. of a sample do what guidance_kernel does without its
-// sums, workgroup 0 sums over the whole sample: kOneThreads threads, 16 bytes of v_c and v_u each per round, eight rounds of loads in flight (as
-// raw bits: 64 registers); the sums of a vector's elements are fp32 as there, everything above is added in fp64.
+// sums, workgroup 0 sums over the whole sample, in the order of guidance_kernel and discrepancy_finalize_kernel: a sample has the same
+// discrepancies whichever form a call takes.  A "unit" is what a wave of guidance_kernel sums, 64 vectors; a wave here takes up to eight of them,
+// all loads in flight (as raw bits: 64 registers), and adds their lanes in one go (wave_sums).
 constexpr int kOneThreads = 1024;
-constexpr int kOneRounds = 8;
+constexpr int kOneWaves = kOneThreads / HYB_WAVE;
+constexpr int kUnitsPerChunk = kThreads / HYB_WAVE * kIters;       // of a workgroup of guidance_kernel
+constexpr int kOneUnits = 128;                                     // the most a sample has
+static_assert(kIters == 1 && kOneUnits / kUnitsPerChunk <= HYB_WAVE, "a lane of the finalisation has one chunk");
 
-// 16 bytes of values (one element in the scalar path), as they were loaded and as floats
+// V values, as they were loaded and as floats
 template <typename VT, int V> struct Raw {
-    u32x4 bits;
-    static constexpr int N = 16 / (int)sizeof(VT);
-    __device__ __forceinline__ void load(const VT* p) { bits = *reinterpret_cast<const u32x4*>(p); }
-    __device__ __forceinline__ void zero() { bits = u32x4{0, 0, 0, 0}; }
+    static constexpr int N = V * (int)sizeof(VT) / 16;
+    u32x4 bits[N];
+    __device__ __forceinline__ void load(const VT* p) {
+#pragma unroll
+        for (int i = 0; i < N; i++) bits[i] = reinterpret_cast<const u32x4*>(p)[i];
+    }
+    __device__ __forceinline__ void zero() {
+#pragma unroll
+        for (int i = 0; i < N; i++) bits[i] = u32x4{0, 0, 0, 0};
+    }
     __device__ __forceinline__ float get(int j) const {
-        if constexpr (sizeof(VT) == 4) return __uint_as_float(bits[j]);
-        else return __uint_as_float(j % 2 ? bits[j / 2] & 0xffff0000u : bits[j / 2] << 16);
+        if constexpr (sizeof(VT) == 4) return __uint_as_float(bits[j / 4][j % 4]);
+        else return __uint_as_float(j % 2 ? bits[j / 8][j % 8 / 2] & 0xffff0000u : bits[j / 8][j % 8 / 2] << 16);
     }
 };
 template <typename VT> struct Raw<VT, 1> {
     VT value;
-    static constexpr int N = 1;
     __device__ __forceinline__ void load(const VT* p) { value = *p; }
     __device__ __forceinline__ void zero() { value = (VT)0.f; }
     __device__ __forceinline__ float get(int) const { return to_f32<VT>(value); }
 };
 
+// a + a of lane ^ O in the lanes without bit O, b + b of lane ^ O in those with it.
+template <int O>
+__device__ __forceinline__ double exchange_add(double a, double b) {
+    if constexpr (O >= 16) {
+        const u32x2 x = __builtin_bit_cast(u32x2, a), y = __builtin_bit_cast(u32x2, b);
+        auto swap = [](unsigned p, unsigned q) {
+            if constexpr (O == 32) return __builtin_amdgcn_permlane32_swap(p, q, false, false);
+            else return __builtin_amdgcn_permlane16_swap(p, q, false, false);
+        };
+        const auto lo = swap(x[0], y[0]), hi = swap(x[1], y[1]);
+        return __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+    } else {
+        const bool upper = threadIdx.x & O;
+        const double keep = upper ? b : a, give = upper ? a : b;
+        return keep + __shfl_xor(give, O, 64);
+    }
+}
+
+// Sums over the lanes of N values, each with the additions of wave_sum(); lane l returns that of value l / (64 / N).  Two halves of the wave
+// go on with half of the values each, so N values cost N - 1 exchanges and those of the last 64 / N lanes, not six per value.
+template <int N, int O = 32, int C = N / 2>
+__device__ __forceinline__ double wave_sums(double (&v)[N]) {
+    if constexpr (O == 0) return v[0];
+    else {
+        if constexpr (C > 0) {
+#pragma unroll
+            for (int i = 0; i < C; i++) v[i] = exchange_add<O>(v[i], v[i + C]);
+        } else v[0] += __shfl_xor(v[0], O, 64);
+        return wave_sums<N, O / 2, C / 2>(v);
+    }
+}
+
+// Sums of the units wave, wave + 16, ... (ROUNDS of them) into red[unit][quantity].
+template <typename VT, int V, int ROUNDS>
+__device__ __forceinline__ void unit_sums(const VT* vc, const VT* vu, size_t n, double (*red)[4]) {
+    const int wave = threadIdx.x / HYB_WAVE, lane = threadIdx.x % HYB_WAVE;
+    Raw<VT, V> c[ROUNDS], u[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        const size_t i = ((size_t)r * kOneThreads + threadIdx.x) * V;
+        if (i < n) {
+            c[r].load(vc + i);
+            u[r].load(vu + i);
+        } else {
+            c[r].zero();
+            u[r].zero();
+        }
+    }
+    double sums[4 * ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        float s_d1 = 0.f, s_d2 = 0.f, s_u1 = 0.f, s_u2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < V; j++) {
+            const float uj = u[r].get(j), d = c[r].get(j) - uj;
+            s_d1 += fabsf(d);
+            s_d2 = fmaf(d, d, s_d2);
+            s_u1 += fabsf(uj);
+            s_u2 = fmaf(uj, uj, s_u2);
+        }
+        sums[4 * r] = (double)s_d1; sums[4 * r + 1] = (double)s_d2; sums[4 * r + 2] = (double)s_u1; sums[4 * r + 3] = (double)s_u2;
+    }
+    constexpr int LANES = HYB_WAVE / (4 * ROUNDS);       // that hold the same sum
+    const double t = wave_sums(sums);
+    const int value = lane / LANES;
+    if (lane % LANES == 0) red[value / 4 * kOneWaves + wave][value % 4] = t;
+}
+
 template <typename VT, int V>
 __device__ __forceinline__ void whole_sample_sums(const VT* vc, const VT* vu, size_t n, float* d1, float* d2) {
-    using R = Raw<VT, V>;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (size_t base = 0; base < n; base += (size_t)kOneThreads * R::N * kOneRounds) {
-        R c[kOneRounds], u[kOneRounds];
-#pragma unroll
-        for (int r = 0; r < kOneRounds; r++) {
-            const size_t i = base + ((size_t)r * kOneThreads + threadIdx.x) * R::N;
-            if (i < n) {
-                c[r].load(vc + i);
-                u[r].load(vu + i);
-            } else {
-                c[r].zero();
-                u[r].zero();
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < kOneRounds; r++) {
-            float s_d1 = 0.f, s_d2 = 0.f, s_u1 = 0.f, s_u2 = 0.f;
-#pragma unroll
-            for (int j = 0; j < R::N; j++) {
-                const float uj = u[r].get(j), d = c[r].get(j) - uj;
-                s_d1 += fabsf(d);
-                s_d2 = fmaf(d, d, s_d2);
-                s_u1 += fabsf(uj);
-                s_u2 = fmaf(uj, uj, s_u2);
-            }
-            acc[0] += (double)s_d1; acc[1] += (double)s_d2; acc[2] += (double)s_u1; acc[3] += (double)s_u2;
-        }
-    }
-    __shared__ double red[kOneThreads / HYB_WAVE][4];
-    const int wave = threadIdx.x / HYB_WAVE, lane = threadIdx.x % HYB_WAVE;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const double t = wave_sum(acc[j]);
-        if (lane == 0) red[wave][j] = t;
-    }
+    constexpr int ROUNDS = (sizeof(VT) == 4 && V > 1 ? kOneUnits / 2 : kOneUnits) / kOneWaves;      // (a sample of fp32 vectors has half as many units)
+    __shared__ double red[kOneUnits][4];
+    if (n <= (size_t)kOneThreads * V) unit_sums<VT, V, 1>(vc, vu, n, red);
+    else unit_sums<VT, V, ROUNDS>(vc, vu, n, red);
     __syncthreads();
-    if (wave == 0) {
-        double t[4];
+    if (threadIdx.x < HYB_WAVE) {
+        const int lane = threadIdx.x, chunks = (int)((n + kThreads * V - 1) / (kThreads * V));
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        if (lane < chunks) {
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-            t[j] = lane < kOneThreads / HYB_WAVE ? red[lane][j] : 0.0;
-            t[j] = wave_sum(t[j]);
+            for (int j = 0; j < 4; j++) {
+                double t = 0.0;
+#pragma unroll
+                for (int w = 0; w < kUnitsPerChunk; w++) t += red[lane * kUnitsPerChunk + w][j];
+                acc[j] += t;
+            }
         }
+        const double t = wave_sums(acc);
+        const double u1 = __shfl(t, 32, 64), d2sum = __shfl(t, 16, 64), u2 = __shfl(t, 48, 64);
         if (lane == 0) {
-            if (d1) *d1 = ratio(t[0], t[2]);
-            if (d2) *d2 = ratio(sqrt(t[1]), sqrt(t[3]));
+            if (d1) *d1 = ratio(t, u1);
+            if (d2) *d2 = ratio(sqrt(d2sum), sqrt(u2));
         }
     }
 }
@@ -270,10 +322,12 @@ int blocks_for(size_t n, int vec) {
 size_t partial_bytes(int batch, size_t n) { return (size_t)batch * blocks_for(n, 1) * 4 * sizeof(double); }
 
 // One launch where a sample's v_c and v_u together are at most kOneLaunchBytes and those of all samples kOneLaunchTotal.  Two launches against one,
-// us, in a stream of calls: 1 x 1024 fp32 9.3 -> 6.5, 1 x 65536 bf16 9.1 -> 7.0 (a call on its own that the host waits for 20.4 -> 21.3: the
-// summing workgroup has a CU's arithmetic), 16 x 65536 9.1 -> 7.7, 64 x 16384 fp32 9.0 -> 6.6; beyond the line 64 x 65536 13.3 -> 17.0;
-// element by element (n % 8 != 0) 1 x 32769 9.0 -> 11.5, so there up to kOneLaunchScalar elements.
+// us, in a stream of calls: 1 x 1024 fp32 8.6 -> 6.1, 1 x 65536 bf16 8.7 -> 6.6 (a call on its own that the host waits for 20.1 -> 20.4: the
+// summing workgroup has a CU's arithmetic), 16 x 65536 8.7 -> 7.6, 64 x 16384 fp32 8.7 -> 6.1; beyond the line 64 x 65536 13.3 -> 17.0.
+// Element by element (n % 8 != 0) a sample of kOneLaunchScalar elements has as many units as the summing workgroup takes (8191: 8.7 -> 6.1).
 constexpr size_t kOneLaunchBytes = 256 * 1024, kOneLaunchTotal = 8 * 1024 * 1024, kOneLaunchScalar = 8192;
+static_assert(kOneLaunchBytes / 2 / sizeof(bf16_t) <= (size_t)kOneUnits * HYB_WAVE * kVec && kOneLaunchBytes / 2 / sizeof(float) <= (size_t)kOneUnits / 2 * HYB_WAVE * kVec &&
+              kOneLaunchScalar <= (size_t)kOneUnits * HYB_WAVE, "a sample's units");
 
 // The summing workgroup reads v_c and v_u while others write: none of the outputs may overlap them.
 bool overlaps(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {

@@ -158,3 +158,26 @@ def test_one_launch_for_small_samples(hb, vd, batch, n):
     hb.hyb_cfg_disc_euler(dvc, dvu, dx, dx, 7.0, 0.5, 0.45, d2[0], d2[1], _ws(hb, batch, n), v_out=dvu)
     assert torch.equal(dx, ref) and torch.equal(dvu, v_out)
     np.testing.assert_allclose(host(d2), want, rtol=10 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("vd,batch,n", [("f32", 200, 8), ("f32", 200, 1024), ("f32", 60, 8200), ("f32", 30, 16384), ("f32", 16, 32768), ("f32", 60, 8191), ("f32", 200, 1025),
+                                        ("bf16", 200, 1024), ("bf16", 120, 8192), ("bf16", 60, 16400), ("bf16", 16, 65536), ("bf16", 200, 5001)])
+def test_one_launch_adds_in_the_order_of_two(hb, vd, batch, n):
+    """The discrepancies of small samples have the same bits from the one-launch form, from the pass with a finalisation of its own (as more samples or
+    an output over v_u take it) and from hyb_branch_discrepancy: one to 128 waves' worth of vectors, infinities among them."""
+    v_c, v_u, x = synth.guidance_inputs(n, batch, vd, seed=400 + n % 89)
+    v_c[1, 3] = np.inf
+    dvc, dvu, dx = dev(v_c, tdt(vd)), dev(v_u, tdt(vd)), dev(x)
+    out, ws = torch.empty_like(dx), _ws(hb, batch, n)
+    one, two, alone = (torch.full((2, batch), -1.0, device="cuda") for _ in range(3))
+    hb.hyb_trace_enable(True)
+    hb.hyb_cfg_disc_euler(dvc, dvu, dx, out, 7.0, 0.5, 0.45, one[0], one[1], ws)
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert list(names) == ["guidance_pass"], names
+    for i, p in enumerate((hb.HYB_NORM_L1, hb.HYB_NORM_L2)):
+        hb.hyb_branch_discrepancy(dvc, dvu, p, alone[i], ws)
+    hb.hyb_cfg_disc_euler(dvc, dvu, dx, out, 7.0, 0.5, 0.45, two[0], two[1], ws, v_out=dvu)
+    assert torch.equal(one, alone) and torch.equal(one, two)
+    assert torch.isinf(one[:, 1]).all() and torch.isfinite(one[:, 2:]).all()
