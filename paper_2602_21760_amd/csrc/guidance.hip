@@ -323,7 +323,10 @@ size_t partial_bytes(int batch, size_t n) { return (size_t)batch * blocks_for(n,
 
 // One launch where a sample's v_c and v_u together are at most kOneLaunchBytes and those of all samples kOneLaunchTotal.  Two launches against one,
 // us, in a stream of calls: 1 x 1024 fp32 8.6 -> 6.1, 1 x 65536 bf16 8.7 -> 6.6 (a call on its own that the host waits for 20.1 -> 20.4: the
-// summing workgroup has a CU's arithmetic), 16 x 65536 8.7 -> 7.6, 64 x 16384 fp32 8.7 -> 6.1; beyond the line 64 x 65536 13.3 -> 17.0.
+// summing workgroup has a CU's arithmetic), 28 x 65536 8.7 -> 8.2, 80 x 16384 8.5 -> 6.5, 32 x 32768 fp32 8.6 -> 6.1.
+// Not where its workgroups (one CU holds two of 1024 threads) are more than the CUs: 32 x 65536 8.5 -> 9.9, 128 x 16384 8.7 -> 9.1; samples with one updating
+// workgroup have four per CU: 512 x 4096 8.7 -> 8.4, 512 x 1024 fp32 8.8 -> 6.2, but 1024 x 1024 fp32 8.6 -> 10.2.  Element by element
+// the pass itself is the longer part: 256 x 8191 23.4 -> 13.6, 1024 x 1023 fp32 14.1 -> 9.4.
 // Element by element (n % 8 != 0) a sample of kOneLaunchScalar elements has as many units as the summing workgroup takes (8191: 8.7 -> 6.1).
 constexpr size_t kOneLaunchBytes = 256 * 1024, kOneLaunchTotal = 8 * 1024 * 1024, kOneLaunchScalar = 8192;
 static_assert(kOneLaunchBytes / 2 / sizeof(bf16_t) <= (size_t)kOneUnits * HYB_WAVE * kVec && kOneLaunchBytes / 2 / sizeof(float) <= (size_t)kOneUnits / 2 * HYB_WAVE * kVec &&
@@ -337,7 +340,12 @@ bool overlaps(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
 
 bool one_launch(const GuidanceArgs& g, int batch, size_t vs, const float* d1, const float* d2) {
     if (!g.partial || (!d1 && !d2) || !g.x_out || 2 * g.n * vs > kOneLaunchBytes || (size_t)batch * 2 * g.n * vs > kOneLaunchTotal) return false;
-    if (g.n % kVec != 0 && g.n > kOneLaunchScalar) return false;
+    if (g.n % kVec != 0) {
+        if (g.n > kOneLaunchScalar) return false;
+    } else {
+        const size_t updating = (g.n + kOneThreads * kVec - 1) / (kOneThreads * kVec), cus = (size_t)hyb_cu_count();
+        if ((size_t)batch * (1 + updating) > (updating == 1 ? 4 * cus : cus)) return false;
+    }
     const size_t n = (size_t)batch * g.n;
     for (const void* v : {g.v_c, g.v_u})
         if (overlaps(v, n * vs, g.x_out, n * 4) || overlaps(v, n * vs, g.x_lowp, n * 2) || overlaps(v, n * vs, g.v_out, n * vs) ||

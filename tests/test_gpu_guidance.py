@@ -181,3 +181,17 @@ def test_one_launch_adds_in_the_order_of_two(hb, vd, batch, n):
     hb.hyb_cfg_disc_euler(dvc, dvu, dx, out, 7.0, 0.5, 0.45, two[0], two[1], ws, v_out=dvu)
     assert torch.equal(one, alone) and torch.equal(one, two)
     assert torch.isinf(one[:, 1]).all() and torch.isfinite(one[:, 2:]).all()
+
+
+@pytest.mark.parametrize("vd,batch,n,one", [("bf16", 28, 65536, True), ("bf16", 29, 65536, False), ("bf16", 85, 16384, True), ("bf16", 86, 16384, False), ("f32", 33, 32768, False),
+                                            ("bf16", 512, 4096, True), ("f32", 512, 1024, True), ("f32", 513, 1024, False), ("f32", 1024, 1023, True), ("f32", 32, 32768, True)])
+def test_one_launch_has_no_more_workgroups_than_the_chip_takes(hb, vd, batch, n, one):
+    """Both sides of the line in the number of workgroups (256 CUs): more than one per CU, or four for samples with one updating workgroup, take longer than two launches."""
+    v_c, v_u, x = (torch.randn(batch, n, device="cuda") for _ in range(3))
+    d, ws = torch.empty(2, batch, device="cuda"), _ws(hb, batch, n)
+    hb.hyb_trace_enable(True)
+    hb.hyb_cfg_disc_euler(v_c.to(tdt(vd)), v_u.to(tdt(vd)), x, x, 7.0, 0.5, 0.45, d[0], d[1], ws)
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert list(names) == (["guidance_pass"] if one else ["guidance_pass", "discrepancy_finalize"]), names
