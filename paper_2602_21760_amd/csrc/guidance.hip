@@ -332,7 +332,8 @@ constexpr size_t kOneLaunchBytes = 256 * 1024, kOneLaunchTotal = 8 * 1024 * 1024
 static_assert(kOneLaunchBytes / 2 / sizeof(bf16_t) <= (size_t)kOneUnits * HYB_WAVE * kVec && kOneLaunchBytes / 2 / sizeof(float) <= (size_t)kOneUnits / 2 * HYB_WAVE * kVec &&
               kOneLaunchScalar <= (size_t)kOneUnits * HYB_WAVE, "a sample's units");
 
-// The summing workgroup reads v_c and v_u while others write: none of the outputs may overlap them.
+// The summing workgroup reads v_c and v_u while others write, and writes the discrepancies while others read x and write: no output may overlap
+// v_c or v_u, and the discrepancies none of the others (two launches read all of v_c, v_u and x first and write the discrepancies last).
 bool overlaps(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
     const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
     return a && b && x < y + b_bytes && y < x + a_bytes;
@@ -350,6 +351,10 @@ bool one_launch(const GuidanceArgs& g, int batch, size_t vs, const float* d1, co
     for (const void* v : {g.v_c, g.v_u})
         if (overlaps(v, n * vs, g.x_out, n * 4) || overlaps(v, n * vs, g.x_lowp, n * 2) || overlaps(v, n * vs, g.v_out, n * vs) ||
             overlaps(v, n * vs, d1, (size_t)batch * 4) || overlaps(v, n * vs, d2, (size_t)batch * 4)) return false;
+    for (const float* d : {d1, d2}) {
+        const size_t bytes = (size_t)batch * 4;
+        if (overlaps(d, bytes, g.x, n * 4) || overlaps(d, bytes, g.x_out, n * 4) || overlaps(d, bytes, g.x_lowp, n * 2) || overlaps(d, bytes, g.v_out, n * vs)) return false;
+    }
     return true;
 }
 

@@ -195,3 +195,25 @@ def test_one_launch_has_no_more_workgroups_than_the_chip_takes(hb, vd, batch, n,
     names = hb.hyb_trace_summary()
     hb.hyb_trace_enable(False)
     assert list(names) == (["guidance_pass"] if one else ["guidance_pass", "discrepancy_finalize"]), names
+
+
+@pytest.mark.parametrize("where", ["x", "x_out", "x_lowp", "v_out", "v_c", "v_u"])
+def test_discrepancies_that_overlap_another_argument_are_written_last(hb, where):
+    """A discrepancy that lies inside another argument is not written in the launch that reads or writes that argument: the update is that of a call
+    without overlap, and the two discrepancies are what is left in their places."""
+    batch, n = 3, 4096
+    a = {k: torch.randn(batch, n, device="cuda") for k in ("v_c", "v_u", "x")}
+    a.update({k: torch.empty(batch, n, device="cuda", dtype=torch.bfloat16 if k == "x_lowp" else torch.float32) for k in ("x_out", "x_lowp", "v_out")})
+    d, ws = torch.empty(2, batch, device="cuda"), _ws(hb, batch, n)
+    call = lambda d1, d2: hb.hyb_cfg_disc_euler(a["v_c"], a["v_u"], a["x"], a["x_out"], 7.0, 0.5, 0.45, d1, d2, ws, x_out_lowp=a["x_lowp"], v_out=a["v_out"])
+    call(d[0], d[1])
+    want = {k: t.clone() for k, t in a.items()}
+    place = a[where].view(-1).view(torch.float32)[2048:2048 + 2 * batch].view(2, batch)
+    hb.hyb_trace_enable(True)
+    call(place[0], place[1])
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert list(names) == ["guidance_pass", "discrepancy_finalize"], names
+    want[where].view(-1).view(torch.float32)[2048:2048 + 2 * batch] = d.view(-1)
+    assert all(torch.equal(a[k].view(torch.uint8), want[k].view(torch.uint8)) for k in a)
