@@ -3,6 +3,7 @@ the C entry point it calls (see include/hyb.h); tensors are torch CUDA tensors u
 device memory, work is enqueued on torch's current stream.  Loading fails loudly if the
 library has not been built: there is no fallback path."""
 import ctypes as C
+import operator
 import os
 
 import torch
@@ -45,6 +46,13 @@ class MMDiTDesc(C.Structure):
 MMDIT_WEIGHT_FIELDS = ("t1_w", "t2_w", "p1_w", "p2_w", "pe_w", "ce_w", "f_w", "ada_w", "t1_b", "t2_b", "p1_b", "p2_b", "pe_b", "ce_b",
                        "f_b", "ada_b", "pos")
 MMDIT_BUFFER_FIELDS = ("t_feat", "t_hid", "pooled_act", "p_hid", "temb", "mod", "tok", "ctx_act", "x_img", "x_txt", "y", "out_tok", "v", "ws")
+# (a model without a pooled text vector has no p1, p2, pooled_act and p_hid)
+_matrices, _biases = (operator.itemgetter(*(n + s for n in ("t1", "t2", "pe", "ce", "f"))) for s in ("_w", "_b"))
+_pooled_matrices, _pooled_biases = operator.itemgetter("p1_w", "p2_w"), operator.itemgetter("p1_b", "p2_b")
+_act_buffers = operator.attrgetter("t_feat", "t_hid", "tok", "ctx_act", "y", "out_tok", "v")
+_f32_buffers = operator.attrgetter("temb", "mod", "x_img", "x_txt")
+_pooled_buffers = operator.attrgetter("pooled_act", "p_hid")
+_is_cuda, _dtype_of = operator.attrgetter("is_cuda"), operator.attrgetter("dtype")
 
 
 class MMDiTWeights(C.Structure):
@@ -168,6 +176,13 @@ def _p(t, dtype=None):
     return t.data_ptr()
 
 
+def _pointers(tensors, dtype):
+    """_p of several tensors of one type, in a third of the host time."""
+    if all(map(_is_cuda, tensors)) and all(map(torch.Tensor.is_contiguous, tensors)) and [*map(_dtype_of, tensors)].count(dtype) == len(tensors):
+        return [*map(torch.Tensor.data_ptr, tensors)]
+    return [_p(t, dtype) for t in tensors]      # says what is wrong
+
+
 def _nbytes(t):
     return 0 if t is None else t.numel() * t.element_size()
 
@@ -209,6 +224,20 @@ def hyb_cfg_disc_euler(v_c, v_u, x, x_out, scale, t, t_next, disc_l1=None, disc_
                                     _p(disc_l1, torch.float32), _p(disc_l2, torch.float32), _dt(v_c),
                                     _p(workspace), _nbytes(workspace), _stream()))
     return x_out
+
+
+def cfg_disc_euler_of_branches(v, x, scale, t, t_next, disc, i, workspace):
+    """hyb_cfg_disc_euler of v[0:1] and v[1:2], in place over x, with the discrepancies in disc[0, i:i + 1] and disc[1, i:i + 1] (disc: f32[2, steps]), but
+    without these views, each of which costs the host a microsecond."""
+    if not (v.is_contiguous() and disc.is_contiguous()):
+        hyb_cfg_disc_euler(v[0:1], v[1:2], x.view(1, -1), x.view(1, -1), scale, t, t_next, disc[0, i:i + 1], disc[1, i:i + 1], workspace)
+        return
+    n, pv, px, pd = v.numel() // v.shape[0], _p(v), _p(x, torch.float32), _p(disc, torch.float32)
+    steps = disc.shape[1]
+    start, stop, _ = slice(i, i + 1).indices(steps)
+    l1, l2 = (pd + 4 * start, pd + 4 * (steps + start)) if start < stop else (None, None)
+    _check(lib().hyb_cfg_disc_euler(pv, pv + n * v.element_size(), px, px, None, None, 1, n, scale, t, t_next, l1, l2, _dt(v), _p(workspace), _nbytes(workspace),
+                                    _stream()))
 
 
 def hyb_cfg_disc_euler_noalloc(v_c, v_u, x, x_out, scale, t, t_next, disc_l1=None, disc_l2=None, x_out_lowp=None,
@@ -312,14 +341,23 @@ def hyb_block_forward(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_s
                                    _p(x_txt_out, torch.float32), _p(workspace), _nbytes(workspace), _stream()))
 
 
-def mmdit_weights(tensors, blocks):
-    """tensors: dict of device tensors named as the fields of hyb_mmdit_weights (missing ones: NULL); blocks: ctypes array of BlockWeights."""
-    return MMDiTWeights(*[tensors[n].data_ptr() if n in tensors else None for n in MMDIT_WEIGHT_FIELDS], blocks)
+def mmdit_weights(linears, ada_w, ada_b, pos, blocks, dtype):
+    """linears: dict of device tensors t1_w, t1_b, ... (p1, p2 may be missing: NULL); blocks: ctypes array of BlockWeights; dtype: of the matrices."""
+    f32, p_w, p_b = torch.float32, (None, None), (None, None)
+    if "p1_w" in linears:
+        p_w, p_b = _pointers(_pooled_matrices(linears), dtype), _pointers(_pooled_biases(linears), f32)
+    t1_w, t2_w, pe_w, ce_w, f_w, a_w = _pointers((*_matrices(linears), ada_w), dtype)
+    t1_b, t2_b, pe_b, ce_b, f_b, a_b, pos = _pointers((*_biases(linears), ada_b, pos), f32)
+    return MMDiTWeights(t1_w, t2_w, *p_w, pe_w, ce_w, f_w, a_w, t1_b, t2_b, *p_b, pe_b, ce_b, f_b, a_b, pos, blocks)
 
 
-def mmdit_buffers(tensors):
-    """tensors: dict of device tensors named as the fields of hyb_mmdit_buffers (missing ones: NULL)."""
-    return MMDiTBuffers(*[tensors[n].data_ptr() if n in tensors else None for n in MMDIT_BUFFER_FIELDS], _nbytes(tensors["ws"]))
+def mmdit_buffers(owner, dtype):
+    """owner: object whose attributes named as the fields of hyb_mmdit_buffers are the device tensors (pooled_act and p_hid may be missing: NULL);
+    dtype: of the activations."""
+    pooled = _pointers(_pooled_buffers(owner), dtype) if hasattr(owner, "p_hid") else (None, None)
+    t_feat, t_hid, tok, ctx_act, y, out_tok, v = _pointers(_act_buffers(owner), dtype)
+    temb, mod, x_img, x_txt = _pointers(_f32_buffers(owner), torch.float32)
+    return MMDiTBuffers(t_feat, t_hid, *pooled, temb, mod, tok, ctx_act, x_img, x_txt, y, out_tok, v, _p(owner.ws), _nbytes(owner.ws))
 
 
 def hyb_mmdit_forward(desc, weights, buffers, latent, ctx, t, pooled=None, txt_pre_only_last=False, shared_latent=False):

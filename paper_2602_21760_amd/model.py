@@ -45,7 +45,6 @@ class MMDiT:
         self.ada_w = torch.cat(ada_w, dim=0).contiguous()     # [(blocks * 2 * 6 + 2) * D, D]
         self.ada_b = torch.cat(ada_b, dim=0).contiguous()
         self.mod_rows = self.ada_w.shape[0]
-        self.blocks = (hb.BlockWeights * len(self.blocks))(*self.blocks)      # one host array, as hyb_mmdit_forward takes it
         self._alloc()
 
     def _alloc(self):
@@ -81,14 +80,9 @@ class MMDiT:
         self._ctx_rows, self._txt_rows = self.ctx_act.view(-1, cfg.ctx_dim), self.x_txt.view(-1, D)
         self._y_rows, self._out_rows = self.y.view(-1, D), self.out_tok.view(-1, cfg.patch_dim)
 
-        # the whole forward as one call of the library: its sizes, weights and buffers (and the tensors they point into)
-        weights = {**self.g, "ada_w": self.ada_w, "ada_b": self.ada_b, "pos": self.pos}
-        buffers = {n: getattr(self, n) for n in hb.MMDIT_BUFFER_FIELDS if hasattr(self, n)}
-        self._call = (
-            hb.MMDiTDesc(B, len(self.blocks), D, cfg.heads, cfg.mlp_ratio, cfg.latent_hw, cfg.latent_hw, cfg.latent_c, cfg.patch, cfg.n_txt,
-                         cfg.ctx_dim, cfg.temb_dim, cfg.pooled_dim, self.hdt, 1e-6),
-            hb.mmdit_weights(weights, self.blocks), hb.mmdit_buffers(buffers))
-        self._call_tensors = weights, buffers
+        # sizes of the whole forward as one call of the library
+        self._call_desc = hb.MMDiTDesc(B, len(self.blocks), D, cfg.heads, cfg.mlp_ratio, cfg.latent_hw, cfg.latent_hw, cfg.latent_c, cfg.patch, cfg.n_txt,
+                                       cfg.ctx_dim, cfg.temb_dim, cfg.pooled_dim, self.hdt, 1e-6)
         self._latent_shape = (B, cfg.latent_hw, cfg.latent_hw, cfg.latent_c)
 
     def reconfigure(self, cfg, batch=None, pos_np=None):
@@ -139,7 +133,7 @@ class MMDiT:
 
     def forward(self, latent, ctx, t, pooled=None):
         """One denoiser evaluation for every batch row; returns v[B, Hh, Ww, C] (activation dtype)."""
-        if isinstance(t, torch.Tensor) and latent.shape == self._latent_shape and self._inputs_fit(ctx, pooled):
+        if isinstance(t, torch.Tensor) and latent.shape == self._latent_shape and self._inputs_fit(ctx, pooled) and self._in_one_call():
             self._forward(latent, ctx, t, pooled)
             return self.v
         self.embed(latent, ctx, t, pooled)
@@ -152,11 +146,23 @@ class MMDiT:
         return ((not cfg.n_txt or (ctx is not None and ctx.numel() == self.ctx_act.numel())) and
                 (not cfg.pooled_dim or (pooled is not None and pooled.numel() == self.pooled_act.numel())))
 
+    def _in_one_call(self, *methods):
+        """Whether one call of the library does what embed(), run_blocks(), final() (and `methods`) do: none of them is overridden, in a class
+        or on the object, there are as many blocks as modulations were laid out for, and all matrices are of one type."""
+        cls, own = type(self), self.__dict__
+        return (len(self.blocks) == self._call_desc.blocks and self.ada_w.dtype == self.act and
+                all(n not in own and getattr(cls, n) is _METHODS[n] for n in ("embed", "run_blocks", "final") + methods))
+
     def _forward(self, latent, ctx, t, pooled=None, shared_latent=False):
-        """embed(), run_blocks() and final() in one call; t: f32[B], or a number for all samples."""
-        cfg = self.cfg
-        hb.hyb_mmdit_forward(*self._call, latent, ctx if cfg.n_txt else None, t, pooled if cfg.pooled_dim else None,
-                             self.txt_pre_only_last, shared_latent)
+        """embed(), run_blocks() and final() in one call; t: f32[B], or a number for all samples.  Weights and buffers are looked up and
+        checked on every call, as those three do: they are what the attributes hold now."""
+        cfg, act = self.cfg, self.act
+        blocks = (hb.BlockWeights * len(self.blocks))(*self.blocks)
+        hb.hyb_mmdit_forward(self._call_desc, hb.mmdit_weights(self.g, self.ada_w, self.ada_b, self.pos, blocks, act), hb.mmdit_buffers(self, act),
+                             latent, ctx if cfg.n_txt else None, t, pooled if cfg.pooled_dim else None, self.txt_pre_only_last, shared_latent)
+
+
+_METHODS = {n: getattr(MMDiT, n) for n in ("embed", "run_blocks", "final", "forward")}
 
 
 class GuidedSampler:
@@ -176,15 +182,15 @@ class GuidedSampler:
     def step(self, x, ctx2, t, t_next, i=0):
         """x: f32[Hh, Ww, C] master latent (updated in place); ctx2: f32[2, Nt, ctx_dim]."""
         m = self.m
-        if x.shape == m._latent_shape[1:] and x.dtype == torch.float32 and x.is_cuda and x.is_contiguous() and not m.cfg.pooled_dim and m._inputs_fit(ctx2):
+        if (isinstance(m, MMDiT) and self.lat2.shape == m._latent_shape and x.shape == m._latent_shape[1:] and x.dtype == torch.float32 and x.is_cuda and
+                x.is_contiguous() and not m.cfg.pooled_dim and m._inputs_fit(ctx2) and m._in_one_call("forward")):
             m._forward(x, ctx2, float(t), shared_latent=True)   # both branches read the one latent
             v = m.v
         else:
             self.lat2.copy_(x.expand(self.lat2.shape[1:]))      # to both branches
             self.t2.fill_(t)
             v = m.forward(self.lat2, ctx2, self.t2)
-        hb.hyb_cfg_disc_euler(v[0:1], v[1:2], x.view(1, -1), x.view(1, -1), self.scale, t, t_next,
-                              disc_l1=self.disc[0, i:i + 1], disc_l2=self.disc[1, i:i + 1], workspace=self.ws)
+        hb.cfg_disc_euler_of_branches(v, x, self.scale, t, t_next, self.disc, i, self.ws)
         return x
 
     def sample(self, x, ctx2, sigmas, switch=None):

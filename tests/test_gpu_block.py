@@ -254,6 +254,132 @@ def test_forward_in_one_call_matches_its_parts(hb, dt, batch, n_txt, pooled, pre
         assert torch.equal(m.v, want)
 
 
+def _parts(m, latent, ctx, t):
+    m.embed(latent, ctx, t)
+    m.run_blocks()
+    return m.final().clone()
+
+
+def _small_model(batch=2, **kw):
+    from paper_2602_21760_amd import model
+    cfg = synth.scaled(synth.CFG1, blocks=2, hidden=128, heads=2, latent_hw=8, n_txt=5, ctx_dim=128, batch=batch, **kw)
+    m = model.MMDiT(cfg, synth.mmdit_globals(cfg), synth.mmdit_blocks(cfg))
+    g = torch.Generator(device="cuda").manual_seed(11)
+    latent, ctx = (torch.randn(*s, generator=g, device="cuda") for s in (m._latent_shape, (batch, 5, 128)))
+    return m, latent, ctx, torch.full((batch,), 0.5, device="cuda")
+
+
+@pytest.mark.parametrize("what", ["g", "pos", "ada_w", "ada_b", "blocks item", "blocks", "fewer blocks", "v", "in place", "ada_w f32"])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_forward_and_step_use_what_the_model_holds_now(hb, what, dt):
+    """A weight, a block or the result's buffer that is replaced after the first forward counts from the next one on, in forward() and in a
+    guided step as in the three parts."""
+    from paper_2602_21760_amd import model
+    m, latent, ctx, t = _small_model(dtype=dt)
+    sampler = model.GuidedSampler(m, 5.0)
+    before = m.forward(latent, ctx, t).clone()
+    sampler.step(latent[0].clone(), ctx, 0.5, 0.4)
+    if what == "g":
+        m.g["pe_w"] = m.g["pe_w"] * 2
+    elif what in ("pos", "ada_b"):
+        setattr(m, what, getattr(m, what) + 1)
+    elif what == "ada_w":
+        m.ada_w = -m.ada_w
+    elif what == "ada_w f32":
+        m.ada_w = -m.ada_w.float()
+    elif what == "in place":
+        m.g["f_b"].data = m.g["f_b"] + 1
+    elif what == "blocks item":
+        m.blocks[0] = m.blocks[1]
+    elif what == "blocks":
+        m.blocks = list(reversed(m.blocks))
+    elif what == "fewer blocks":
+        m.blocks.pop()
+    else:
+        m.v = torch.zeros_like(m.v)
+    want = _parts(m, latent, ctx, t)
+    m.v.zero_()
+    got = m.forward(latent, ctx, t)
+    assert got is m.v and torch.equal(got, want) and (what == "v" or not torch.equal(want, before))
+    same = latent[:1].expand_as(latent).contiguous()
+    want = _parts(m, same, ctx, t)
+    x = latent[0].clone()
+    ref = torch.empty_like(x)
+    hb.hyb_cfg_disc_euler(want[0:1], want[1:2], x.view(1, -1), ref.view(1, -1), 5.0, 0.5, 0.4)
+    assert torch.equal(sampler.step(x, ctx, 0.5, 0.4), ref)
+
+
+def test_forward_refuses_replaced_weights_of_the_wrong_kind(hb):
+    """A replaced tensor that is not contiguous, of another type or not on the GPU is refused, as the three parts refuse it."""
+    m, latent, ctx, t = _small_model(dtype="bf16")
+    for bad, error in ((m.g["ce_w"].t(), ValueError), (m.g["ce_w"].float(), TypeError), (m.g["ce_w"].cpu(), ValueError)):
+        m.g["ce_w"] = bad
+        with pytest.raises(error):
+            m.embed(latent, ctx, t)
+        with pytest.raises(error):
+            m.forward(latent, ctx, t)
+
+
+@pytest.mark.parametrize("how", ["subclass", "object", "class"])
+@pytest.mark.parametrize("name", ["embed", "run_blocks", "final", "forward"])
+def test_overridden_parts_of_a_forward_are_called(hb, monkeypatch, name, how):
+    """embed(), run_blocks(), final() and forward() that a program overrides or wraps are called by forward() and by a guided step."""
+    from paper_2602_21760_amd import model
+    m, latent, ctx, t = _small_model()
+    calls, original = [], getattr(model.MMDiT, name)
+
+    def counted(self, *a, **k):
+        calls.append(name)
+        return original(self, *a, **k)
+    if how == "subclass":
+        m.__class__ = type("Mine", (model.MMDiT,), {name: counted})
+    elif how == "object":
+        setattr(m, name, counted.__get__(m))
+    else:
+        monkeypatch.setattr(model.MMDiT, name, counted)
+    m.forward(latent, ctx, t)
+    assert calls == [name]
+    model.GuidedSampler(m, 5.0).step(latent[0].clone(), ctx, 0.5, 0.4)
+    assert calls == [name] * 2
+
+
+@pytest.mark.parametrize("i", [0, 3, 63, 64, -1, -2])
+@pytest.mark.parametrize("strided", [False, True])
+def test_guided_step_writes_its_column_of_the_discrepancies(hb, i, strided):
+    """Both discrepancies of a step go to column i of the table, as a slice [i:i + 1] says, and nothing else of it changes."""
+    from paper_2602_21760_amd import model
+    m, latent, ctx, t = _small_model()
+    s = model.GuidedSampler(m, 5.0)
+    if strided:
+        s.disc = torch.zeros(2, 128, device="cuda")[:, ::2]
+    x = latent[0].clone()
+    v = _parts(m, x.expand_as(latent).contiguous(), ctx, t)
+    want, d, ref = torch.zeros(2, 64, device="cuda"), torch.empty(2, 1, device="cuda"), torch.empty_like(x)
+    hb.hyb_cfg_disc_euler(v[0:1], v[1:2], x.view(1, -1), ref.view(1, -1), 5.0, 0.5, 0.4, d[0], d[1], s.ws)
+    want[:, i:i + 1] = d
+    assert torch.equal(s.step(x, ctx, 0.5, 0.4, i), ref) and torch.equal(s.disc, want) and (d > 0).all()
+
+
+def test_guided_step_of_another_kind_of_model(hb):
+    """A guided step asks its model for B, cfg and forward() only; and one whose model was given another size since is refused."""
+    from paper_2602_21760_amd import model
+    m, latent, ctx, t = _small_model()
+
+    class Other:
+        B, cfg = m.B, m.cfg
+
+        def forward(self, latent, ctx, t):
+            return m.forward(latent, ctx, t)
+    xs = [latent[0].clone(), latent[0].clone()]
+    samplers = [model.GuidedSampler(m, 5.0), model.GuidedSampler(Other(), 5.0)]
+    for s, x in zip(samplers, xs):
+        s.step(x, ctx, 0.5, 0.4)
+    assert torch.equal(xs[0], xs[1])
+    m.reconfigure(synth.scaled(m.cfg, latent_hw=12), pos_np=np.zeros((36, 128), np.float32))
+    with pytest.raises(RuntimeError):
+        samplers[0].step(torch.zeros(m._latent_shape[1:], device="cuda"), ctx, 0.5, 0.4)
+
+
 def test_reduced_bf16_forward_and_guided_loop(hb):
     """The guided sampling loop (both branches batched, fused guidance pass every step) on a reduced
     SD3-shaped model: 4 blocks, hidden 256, 324 + 77 tokens, 6 steps of the shifted schedule."""
