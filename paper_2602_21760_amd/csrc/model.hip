@@ -41,10 +41,12 @@ int forward(const hyb_mmdit_desc& d, const hyb_mmdit_weights& w, const hyb_mmdit
         if constexpr (LAUNCH) return hyb_linear(a, weight, bias, out, m, n, k, dt, out_dtype, epi, residual, nullptr, 1, 0, stream);
         else return hyb_check_linear(a, weight, bias, out, m, n, k, dt, out_dtype, epi, residual, nullptr, 1, 0);
     };
-    // fp32 models read their inputs where they are (a copy where they are not aligned for 16-byte loads)
-    auto input = [&](const float* src, void* own, size_t n, const void** use) {
+    // fp32 models read their inputs where they are (a copy where they are not aligned for 16-byte loads, or share memory with the m results of the
+    // layer that reads them)
+    auto input = [&](const float* src, void* own, size_t n, const void* out, size_t m, const void** use) {
         *use = own;
-        if (dt == HYB_F32 && src && ((uintptr_t)src & 15u) == 0) {
+        const uintptr_t s0 = (uintptr_t)src, o0 = (uintptr_t)out;
+        if (dt == HYB_F32 && src && s0 % 16 == 0 && (s0 + 4 * n <= o0 || o0 + 4 * m <= s0)) {
             *use = src;
             return (int)HYB_OK;
         }
@@ -59,7 +61,7 @@ int forward(const hyb_mmdit_desc& d, const hyb_mmdit_weights& w, const hyb_mmdit
     if ((rc = linear(f.t_hid, w.t2_w, w.t2_b, f.temb, B, D, D, HYB_F32, HYB_EPI_BIAS, nullptr))) return rc;
     if (d.pooled_dim > 0) {          // temb += W_p2 SiLU(W_p1 pooled + b_p1) + b_p2 (the sum is the residual epilogue)
         const void* pooled_act;
-        if ((rc = input(in.pooled, f.pooled_act, (size_t)B * d.pooled_dim, &pooled_act))) return rc;
+        if ((rc = input(in.pooled, f.pooled_act, (size_t)B * d.pooled_dim, f.p_hid, (size_t)B * D, &pooled_act))) return rc;
         if ((rc = linear(pooled_act, w.p1_w, w.p1_b, f.p_hid, B, D, d.pooled_dim, dt, HYB_EPI_SILU, nullptr))) return rc;
         if ((rc = linear(f.p_hid, w.p2_w, w.p2_b, f.temb, B, D, D, HYB_F32, HYB_EPI_GATE_RESIDUAL, f.temb))) return rc;
     }
@@ -95,7 +97,7 @@ int forward(const hyb_mmdit_desc& d, const hyb_mmdit_weights& w, const hyb_mmdit
     }
     if (d.n_txt > 0) {
         const void* ctx_act;
-        if ((rc = input(in.ctx, f.ctx_act, (size_t)B * d.n_txt * d.ctx_dim, &ctx_act))) return rc;
+        if ((rc = input(in.ctx, f.ctx_act, (size_t)B * d.n_txt * d.ctx_dim, f.x_txt, (size_t)B * d.n_txt * D, &ctx_act))) return rc;
         if ((rc = linear(ctx_act, w.ce_w, w.ce_b, f.x_txt, B * d.n_txt, D, d.ctx_dim, HYB_F32, HYB_EPI_BIAS, nullptr))) return rc;
     }
     hyb_block_desc bd = {B, n_img, d.n_txt, D, d.heads, 64, d.mlp_ratio, dt, d.ln_eps, 0};

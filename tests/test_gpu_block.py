@@ -254,6 +254,28 @@ def test_forward_in_one_call_matches_its_parts(hb, dt, batch, n_txt, pooled, pre
         assert torch.equal(m.v, want)
 
 
+@pytest.mark.parametrize("which", ["ctx", "pooled"])
+@pytest.mark.parametrize("rows", [1, 3])
+def test_forward_with_text_inputs_in_its_own_buffers(hb, which, rows):
+    """Text inputs of an fp32 model that lie in the buffer which the layer reading them writes (the rows one by one, and shifted): the result of a copy elsewhere."""
+    from paper_2602_21760_amd import model
+    cfg = synth.scaled(synth.CFG1, blocks=1, hidden=128, heads=2, latent_hw=8, n_txt=40, ctx_dim=128, batch=3, pooled_dim=128)
+    m = model.MMDiT(cfg, synth.mmdit_globals(cfg), synth.mmdit_blocks(cfg))
+    g = torch.Generator(device="cuda").manual_seed(12)
+    latent, ctx, pooled = (torch.randn(*s, generator=g, device="cuda") for s in (m._latent_shape, (3, 40, 128), (3, 128)))
+    t = torch.full((3,), 0.5, device="cuda")
+    want = m.forward(latent, ctx, t, pooled).clone()
+    kept = torch.empty(4 * 3 * 40 * 128, device="cuda")          # the buffer and the input, `rows - 1` rows apart
+    if which == "ctx":
+        m.x_txt = kept[:3 * 40 * 128].view(3, 40, 128)
+        m._txt_rows = m.x_txt.view(-1, 128)
+        ctx = kept[(rows - 1) * 128:][:3 * 40 * 128].view(3, 40, 128).copy_(ctx)
+    else:
+        m.p_hid = kept[:3 * 128].view(3, 128)
+        pooled = kept[(rows - 1) * 128:][:3 * 128].view(3, 128).copy_(pooled)
+    assert torch.equal(m.forward(latent, ctx, t, pooled), want)
+
+
 def _parts(m, latent, ctx, t):
     m.embed(latent, ctx, t)
     m.run_blocks()
