@@ -52,7 +52,7 @@ std::map<std::string, int> g_key_index;
 bool hyb_trace_on() { return g_trace_on; }
 
 HybTraceScope::HybTraceScope(const char* kernel, const char* unit, double work, hipStream_t stream) : slot(-1), st(stream) {
-    if (!g_trace_on) return;
+    if (!g_trace_on || !kernel[0]) return;       // (a launch that was named while tracing was off has no name)
     std::lock_guard<std::mutex> lk(g_tmx);
     auto it = g_key_index.find(kernel);
     int key;

@@ -76,7 +76,7 @@ int launch(const GemmGroup& g, int epi, hipStream_t st) {
     const int tiles_m1 = g.count > 1 ? (g.p[1].m + TS - 1) / TS : 0;
     if (tiles_m0 + tiles_m1 == 0 || g.n == 0) return HYB_OK;
     dim3 grid((g.n + TS - 1) / TS, tiles_m0 + tiles_m1), block(256);
-    char name[96];
+    char name[96] = "";
     if (hyb_trace_on()) snprintf(name, sizeof(name), "gemm_simple.epi%d.n%d.k%d", epi, g.n, g.k);
     double rows = g.p[0].m + (g.count > 1 ? g.p[1].m : 0);
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k * (epi == EPI_GEGLU ? 2 : 1), st);
