@@ -23,6 +23,7 @@
 // reaches on a large square fp32 product).  With the next slab's fragments prefetched into a second register set the wide
 // launches lose 15 % (three waves per SIMD instead of four).
 #include "gemm.h"
+#include "gemm_lds.h"
 
 #include <type_traits>
 
@@ -30,15 +31,6 @@ namespace {
 
 constexpr int BK = 32;            // floats per slab
 constexpr int ROWB = BK * 4;      // bytes per LDS row of a slab
-
-typedef void __attribute__((address_space(3)))* lptr_t;
-
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
-
-__device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned bytes, void* lds, int voffset, int soffset) {
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)lds, 16, voffset, soffset, 0, 0);
-}
 
 // All eight fragments of a slab, complete on return (byte addresses in LDS, from `BASE` on).  Written as one asm statement with
 // its own wait: for a plain read the compiler would wait for every copy that is still on its way to LDS, the other buffer's

@@ -42,6 +42,7 @@
 // clamped on load and masked on store.  The reduction order over k is fixed and a token's result does not depend on its tile
 // row, so results are deterministic, and batch-invariant where k is not split (the number of shares follows from the rows).
 #include "gemm.h"
+#include "gemm_lds.h"
 
 #include <type_traits>
 
@@ -61,19 +62,6 @@ template <int TMW, int NST = 2> struct Geo {
 constexpr int VEC_BYTES = 2 * BN * 4;           // the tile's bias and gate values, behind the slab buffers
 constexpr int OUT_STRIDE_B16 = BN * 2 + 16;     // staging row strides (bytes), padded against conflicts
 constexpr int OUT_STRIDE_F32 = BN * 4 + 16;
-
-typedef const void __attribute__((address_space(1)))* gptr_t;
-typedef void __attribute__((address_space(3)))* lptr_t;
-
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
-
-// 16 bytes per lane from a raw buffer (base address, size in bytes) straight into LDS: lane i's bytes land at
-// lds + 16 i; the address is base + voffset (per lane) + soffset (scalar).  Not a template: the descriptor type
-// only exists in the device pass.
-__device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned bytes, void* lds, int voffset, int soffset) {
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)lds, 16, voffset, soffset, 0, 0);
-}
 
 template <typename OT, int EPI, int TMW, int NST>
 __global__ __launch_bounds__(256, (Geo<TMW, NST>::WG_PER_CU)) void gemm_mfma_kernel(GemmGroup g, int tiles_n, int tiles0, int total, int xcd_run, int ksplit) {

@@ -34,6 +34,7 @@
 // groups of four tile rows column by column, so the tiles an XCD works on at a time share few operand
 // panels (its L2 is 4 MB).
 #include "gemm.h"
+#include "gemm_lds.h"
 
 #include <type_traits>
 
@@ -53,15 +54,6 @@ template <int TMW, int TFW> struct BigGeo {
     static constexpr int SMEM_BYTES = NST * STAGE_BYTES;
     static constexpr int VEC_BYTES = 2 * BN * 4;              // bias and gate of the tile's columns
 };
-
-typedef void __attribute__((address_space(3)))* lptr_t;
-
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
-
-__device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned bytes, void* lds, int voffset, int soffset) {
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)lds, 16, voffset, soffset, 0, 0);
-}
 
 constexpr int kGroupRows = 4;   // tile rows per group of the tile order
 

@@ -29,6 +29,7 @@
 // Tile order: XCD x (workgroups x, x + 8, ...) gets one run of consecutive tiles of an order that walks groups of four or eight tile rows column by
 // column, so the tiles that an XCD works on at a time share few operand panels (its L2 is 4 MB).
 #include "gemm.h"
+#include "gemm_lds.h"
 
 #include <type_traits>
 
@@ -44,15 +45,6 @@ template <int TT> struct WideGeo {
     static constexpr int CPW = STAGE_BYTES / 1024 / NW;       // 1 KB chunks per wave per slab
     static constexpr int T0 = TT == 6 ? 4 : TT / 2, T1 = TT - T0;   // token tiles of the first and the second half of a wave
 };
-
-typedef void __attribute__((address_space(3)))* lptr_t;
-
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
-
-__device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned bytes, void* lds, int voffset, int soffset) {
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)lds, 16, voffset, soffset, 0, 0);
-}
 
 // Tile rows per group of the tile order: with a short k the operand panels are small and four rows x eight columns at a time share them best (SDXL-shaped
 // stage of 640 channels: 3191 us, eight rows 3274); with longer ones eight rows by four columns read fewer (a guided step at 1024 x 1024 4571 ->
@@ -312,9 +304,6 @@ __device__ __forceinline__ void wide_tile(const GemmProblem& p, int n, int k, in
                 } else if constexpr (EPI == EPI_GELU_TANH) {
 #pragma unroll
                     for (int j = 0; j < 4; j++) v[j] = gelu_tanh_f(v[j]);
-                } else if constexpr (EPI == EPI_SILU) {
-#pragma unroll
-                    for (int j = 0; j < 4; j++) v[j] = silu_f(v[j]);
                 } else if constexpr (EPI == EPI_QKV) {
                     v *= scale;
                 } else if constexpr (RES) {
@@ -437,9 +426,10 @@ int launch_wide(const GemmGroup& g, const WidePlan& plan, hipStream_t st) {
     t.tall_run = (t.tall + 7) / 8;
     t.short_run = (t.shrt + 7) / 8;
     char name[96] = "";
-    if (!hyb_trace_on()) name[0] = 0;
-    else if (t.tall && t.shrt) snprintf(name, sizeof(name), "gemm_mfma_%d+%dx%d.epi%d.n%d.k%d", 32 * TA, 32 * TB, BN, EPI, g.n, g.k);
-    else snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", t.tall ? 32 * TA : 32 * TB, BN, EPI, g.n, g.k);
+    if (hyb_trace_on()) {
+        if (t.tall && t.shrt) snprintf(name, sizeof(name), "gemm_mfma_%d+%dx%d.epi%d.n%d.k%d", 32 * TA, 32 * TB, BN, EPI, g.n, g.k);
+        else snprintf(name, sizeof(name), "gemm_mfma_%dx%d.epi%d.n%d.k%d", t.tall ? 32 * TA : 32 * TB, BN, EPI, g.n, g.k);
+    }
     double rows = 0;
     for (int i = 0; i < g.count; i++) rows += g.p[i].m;
     HybTraceScope trace(name, "flop", 2.0 * rows * g.n * g.k, st);
