@@ -597,61 +597,87 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     return rows;
 }
 
-// Estimated length of a launch in us, from the launches' own times over 216 shapes (300-33000 rows; 640-1536 in, 640-6144 out;
-// each tile shape forced): within 3-8 % of what was measured.  A tile costs k-slabs x slab + fixed.
-// 128 x 256 against 256 x 128 tiles with gate and residual are weighed by a step, whose weights come from memory: 4096 + 333 rows x 1536, k 6144
-// (one round of either) 90 against 83 us, the 24-block forward 9720 -> 9597 us with the latter.  (Alone, on weights in the cache, 4977 rows x 1280, k 4096
-// 56.6 against 52.7 us and x 1536 60.5 against 59.9, but 3197 x 1280 42.4 against 45.4 and up to 13 % the same way for 640-768 columns.)
-struct TileCost { float slab, fixed; };
-enum { COST_128, COST_BIG_256, COST_BIG_192, COST_WIDE_128, COST_WIDE_192, COST_WIDE_256, COST_KINDS };
+// Estimated length of a launch in us, fitted to 3700 launches of one problem (300-33000 rows, 512-8192 columns, k 256-8192; every tile shape forced)
+// whose weights come from memory, each launch another matrix, as inside a step: half of the estimates are within 4 % of what was
+// measured, nine tenths within 10 % (64-row tiles 6 and 16 %).  Of these launches 24 are more than 3 % longer than with the tiles of the kernels without 256
+// columns.  With costs fitted to weights in the cache 131 were: 8192 x 2560 GEGLU, k 1280 122 us on 128 x 256 tiles, 108 on 128 x 128
+// and 103 on 192 x 256; 11264 x 1408 with gate and residual, k 1536 71 us on 192- and 128-row tiles of 256 columns, 62 on 128 x 128.
+// A tile alone on its CU costs k-slabs x slab + fixed; `fill`: where all CUs are busy every one is slower (they share the memory
+// system and the power) than with three quarters of them, where fewer are, faster.
+struct TileCost { float slab, fixed, fill; };
+enum { COST_BIG_256, COST_BIG_192, COST_WIDE_128, COST_WIDE_192, COST_WIDE_256, COST_KINDS };
 const TileCost kTileCost[4][COST_KINDS] = {
-    /* bias, QKV       */ {{0.83f, 6.0f}, {}, {}, {0.71f, 5.5f}, {0.95f, 6.0f}, {1.20f, 7.7f}},
-    /* GELU            */ {{0.89f, 5.5f}, {}, {}, {0.71f, 6.5f}, {0.95f, 7.5f}, {1.20f, 10.0f}},
-    /* GEGLU           */ {{0.86f, 5.5f}, {}, {}, {0.71f, 5.0f}, {0.95f, 6.0f}, {1.20f, 9.5f}},
-    /* gate + residual */ {{1.13f, 8.5f}, {0.66f, 19.5f}, {0.70f, 6.0f}, {0.79f, 9.0f}, {0.95f, 9.0f}, {1.20f, 14.0f}},
+    /* bias, QKV       */ {{}, {}, {0.72f, 3.5f, 0.16f}, {0.95f, 4.5f, 0.32f}, {1.20f, 5.4f, 0.40f}},
+    /* GELU            */ {{}, {}, {0.72f, 5.2f, 0.11f}, {0.95f, 7.2f, 0.28f}, {1.14f, 8.6f, 0.33f}},
+    /* GEGLU           */ {{}, {}, {0.75f, 4.5f, 0.00f}, {1.05f, 6.4f, 0.19f}, {1.20f, 7.7f, 0.24f}},
+    /* gate + residual */ {{0.70f, 11.1f, 0.22f}, {0.56f, 8.9f, 0.10f}, {0.73f, 9.2f, 0.32f}, {0.88f, 12.1f, 0.44f}, {1.10f, 13.9f, 0.56f}},
 };
-// 64-row tiles, up to three on a CU: (slab + shared x tiles on the CU) per slab
-const float kSmallTileCost[4][3] = {{0.08f, 0.26f, 2.5f}, {0.16f, 0.20f, 2.0f}, {0.28f, 0.14f, 2.5f}, {0.04f, 0.30f, 3.0f}};
+// 128-row tiles, two on a CU: slab and fixed of a round of both, the share of it that a last round's first tile takes, and the start of the launch
+struct PairCost { float slab, fixed, part, start; };
+const PairCost kPairCost[4] = {{0.88f, 2.8f, 0.38f, 4.1f}, {0.91f, 4.1f, 0.41f, 4.6f}, {1.00f, 3.2f, 0.40f, 5.0f}, {0.95f, 7.1f, 0.49f, 4.3f}};
+// 64-row tiles, up to three on a CU: per slab, per slab and tile of the CU, and the rest
+struct SmallCost { float slab, shared, fixed; };
+const SmallCost kSmallCost[4] = {{0.16f, 0.27f, 4.5f}, {0.15f, 0.25f, 5.1f}, {0.10f, 0.27f, 4.7f}, {0.15f, 0.24f, 6.0f}};
+// 256-column tiles of one height whose tile rows are a multiple of eight: 128 and 256 rows are that much slower (8192 x 2560 GEGLU, k 640 69 and 71 us, 192 rows
+// 64); not those that store q, k and v past the L2 (a stage of 8192 rows x 1024 channels, 128 x 256 tiles 1563 us, 128 x 128 1619)
+constexpr float kWholeGroups128 = 1.09f, kWholeGroups256 = 1.04f;
 
 int cost_row(int epi) { return epi == EPI_GELU_TANH ? 1 : (epi == EPI_GEGLU ? 2 : (epi == EPI_GATE_RES ? 3 : 0)); }
 
-float tile_us(const GemmGroup& g, int epi, int kind) {
-    const TileCost& c = kTileCost[cost_row(epi)][kind];
-    return (float)(g.k / BK) * c.slab + c.fixed;
+float tile_us(const TileCost& c, int nslab) { return (float)nslab * c.slab + c.fixed; }
+
+// `tiles` tiles, one on a CU at a time
+float alone_us(const TileCost& c, int nslab, long tiles) {
+    const long cus = hyb_cu_count(), rounds = (tiles + cus - 1) / cus;
+    if (rounds == 0) return 0.f;
+    return 2.f + (float)rounds * tile_us(c, nslab) * (1.f + c.fill * ((float)tiles / (float)(rounds * cus) - 0.75f));
 }
 
 // Launch of 128-column tiles of 64, 128 (two on a CU), 192 or 256 rows (one on a CU).  Where tiles share a CU, those of a partial last
 // round, which have it to themselves, are faster.
 float launch_us(const GemmGroup& g, int epi, int rows, bool alone) {
-    const int cols = epi == EPI_GEGLU ? BN / 2 : BN;
+    const int cols = epi == EPI_GEGLU ? BN / 2 : BN, nslab = g.k / BK, row = cost_row(epi);
     long tiles = 0;
     for (int i = 0; i < g.count; i++) tiles += (long)((g.p[i].m + rows - 1) / rows) * ((g.n + cols - 1) / cols);
     const long cus = hyb_cu_count();
-    if (rows == 64) {
-        const float* c = kSmallTileCost[cost_row(epi)];
-        return 2.f + c[2] + (float)(g.k / BK) * (c[0] + c[1] * (float)((tiles + cus - 1) / cus));
-    }
-    if (alone) return 2.f + (float)((tiles + cus - 1) / cus) * tile_us(g, epi, rows == 256 ? COST_BIG_256 : COST_BIG_192);
+    if (rows == 64) return kSmallCost[row].fixed + (float)nslab * (kSmallCost[row].slab + kSmallCost[row].shared * (float)((tiles + cus - 1) / cus));
+    if (alone) return alone_us(kTileCost[row][rows == 256 ? COST_BIG_256 : COST_BIG_192], nslab, tiles);
+    const PairCost& c = kPairCost[row];
     const long full = tiles / (2 * cus), rest = tiles - full * 2 * cus;
-    return 2.f + ((float)full + (rest ? 0.4f + 0.6f * (float)rest / (float)(2 * cus) : 0.f)) * tile_us(g, epi, COST_128);
+    return c.start + ((float)full + (rest ? c.part + (1.f - c.part) * (float)rest / (float)(2 * cus) : 0.f)) * ((float)nslab * c.slab + c.fixed);
 }
 
 // Launch of `tall` and then `shrt` tiles of the given costs on one workgroup per CU, each taken by the first CU that is free.
-float two_height_us(long tall, long shrt, float tall_us, float short_us) {
+float two_height_us(long tall, long shrt, const TileCost& ct, const TileCost& cs, int nslab) {
+    const float tall_us = tile_us(ct, nslab), short_us = tile_us(cs, nslab);
     const long cus = hyb_cu_count();
     const float even = (float)(tall / cus) * tall_us;            // every CU is busy until then ...
     const long ahead = tall % cus;                               // ... and these for one tall tile more
     const float late = ahead ? even + tall_us : even;
-    if (shrt <= 0) return 2.f + late;
+    float end = late;
     // until `even` + j short tiles the CUs that are not ahead take j each, the others what fits behind their tall tile
     for (long j = shrt / cus;; j++) {
         const float until = even + (float)j * short_us;
         const long on_late = until > late ? (long)((until - late) / short_us + 1e-3f) : 0;
-        if ((cus - ahead) * j + ahead * on_late >= shrt) return 2.f + (until > late ? until : late);
+        if ((cus - ahead) * j + ahead * on_late >= shrt) {
+            end = until > late ? until : late;
+            break;
+        }
     }
+    const float busy_tall = (float)tall * tall_us, busy_short = (float)shrt * short_us, busy = busy_tall + busy_short;
+    const float fill = (busy_tall * ct.fill + busy_short * cs.fill) / busy;
+    return 2.f + end * (1.f + fill * (busy / ((float)cus * end) - 0.75f));
 }
 
-// Plan of a launch of 256-column tiles (gemm_mfma_wide.hip) if that shortens the launch by 6 % at least against what it takes
+// GEGLU launches of short k and more than one round of 128 x 128 tiles take 256-column tiles only where the estimate is a fifth shorter.  By itself such a launch is
+// as much shorter as estimated, but inside a stage the card then runs everything else, the attention above all, at a lower clock.  Stages with
+// 256-column against 128 x 128 tiles: 640 channels (ten slabs), 8192 rows 3302 against 3235 us (estimate 0.91; traced: GEGLU 69 -> 65.5 us, attention
+// 83 -> 88, LayerNorm 6.9 -> 7.2), 8361 rows 1.033 (0.81), 7079 rows 1.045 (0.83), 16384 rows 0.991 (0.78), 3000 rows 0.979 (0.74); 384 and 512 channels 1.00-1.03 (0.80-0.88);
+// from 14 slabs on 0.95-1.01 (0.70-0.86); launches of one round 0.98-1.00.
+constexpr int kShortGegluSlabs = 12;
+constexpr float kShortGegluGain = 0.80f;
+
+// Plan of a launch of 256-column tiles (gemm_mfma_wide.hip) if that shortens the launch by a twentieth at least (or as above) against what it takes
 // otherwise, else plan.tall = 0.  Tiles of one height fill their last round by chance (16717 x 6144: 6.2 rounds
 // of 256 x 256); with the first rounds tall and the others short the CUs finish together (that launch 284 -> 273 us, 6537 x 6144 121 -> 115 us).
 // `large_rows`: the 128-column large tiles that large_tile_rows() picked, 0: 64 or 128 rows of the kernel above.
@@ -668,6 +694,7 @@ WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_r
         if ((epi == EPI_BIAS || epi == EPI_GELU_TANH) && nslab >= kLargeTileMinSlabsOneRound) return plan;
     }
     int other = large_rows;
+    float gain = 0.95f;
     if (!large_rows) {
         const int tile_cols = epi == EPI_GEGLU ? BN / 2 : BN, tiles_n = (g.n + tile_cols - 1) / tile_cols;
         int tiles128 = 0;
@@ -675,11 +702,12 @@ WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_r
         if (tiles128 <= kSmallGridTiles && epi != EPI_GEGLU &&
             (choose_ksplit(g, tiles128, 512) > 1 || choose_ksplit(g, (g.p[0].m + 63) / 64 * tiles_n, 768) > 1)) return plan;
         other = tiles128 <= kSmallGridTiles ? 64 : 128;
+        if (epi == EPI_GEGLU && nslab <= kShortGegluSlabs && tiles128 > 2 * hyb_cu_count()) gain = kShortGegluGain;
     }
-    float best = 0.94f * launch_us(g, epi, other, large_rows != 0);
+    float best = gain * launch_us(g, epi, other, large_rows != 0);
     const int cols = epi == EPI_GEGLU ? BN : 2 * BN, cus = hyb_cu_count();
     const long tiles_n = (g.n + cols - 1) / cols;
-    const float us[3] = {tile_us(g, epi, COST_WIDE_128), tile_us(g, epi, COST_WIDE_192), tile_us(g, epi, COST_WIDE_256)};
+    const TileCost* cost = &kTileCost[cost_row(epi)][COST_WIDE_128];      // of 128, 192 and 256 rows
     auto take = [&](float t, int tall, int shrt, int rows0, int rows1) {
         if (t >= best) return;
         best = t;
@@ -690,13 +718,12 @@ WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_r
         const int height = 128 + 64 * h;
         int rows[kMaxGroup] = {0, 0};
         for (int i = 0; i < g.count; i++) rows[i] = (g.p[i].m + height - 1) / height;
-        const float t = two_height_us((rows[0] + rows[1]) * tiles_n, 0, us[h], 0.f);
+        float t = alone_us(cost[h], nslab, (rows[0] + rows[1]) * tiles_n);
+        if (rows[1] == 0 && rows[0] % 8 == 0 && h != 1 && epi != EPI_QKV) t *= h ? kWholeGroups256 : kWholeGroups128;
         if (h > 0) take(t, height, height - 64, rows[0], rows[1]);
         else take(t, 192, 128, 0, 0);
     }
-    // Two heights only where the estimate says a twentieth: where some CUs are idle the others are faster (fewer share the memory system and
-    // the power), which takes part of the gain away (8192 x 2560 GEGLU, k 640, in two heights: estimated a tenth shorter, measured 68 us against 65-69 in one).
-    best *= 0.95f;
+    best *= 0.97f;           // two heights only where they save that much
     const int m0 = g.p[0].m, m1 = g.count > 1 ? g.p[1].m : 0;
     const bool swap = m1 > m0;                                   // x: the problem of more rows, y: the other
     const int mx = swap ? m1 : m0, my = swap ? m0 : m1;
@@ -705,7 +732,7 @@ WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_r
         const int all_x = (mx + tall - 1) / tall, all_y = (my + tall - 1) / tall;
         for (int y = 0; y <= all_y; y += all_y ? all_y : 1) {          // the smaller problem is tiled in one height
             const int short_y = y ? 0 : (my + shrt - 1) / shrt;
-            // tall tile rows of the larger problem: none, all, and about as many as fill whole rounds
+            // tall tile rows of the larger problem: none, all, and about as many as fill whole rounds (together with the smaller one's)
             bool last = false;
             for (long r = 0; !last; r++)
                 for (int up = 0; up < 2; up++) {
@@ -714,7 +741,8 @@ WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_r
                     if (x >= all_x) { x = all_x; last = true; }
                     const int rest = mx - (int)x * tall;
                     const long short_x = rest > 0 ? (rest + shrt - 1) / shrt : 0;
-                    take(two_height_us((x + y) * tiles_n, (short_x + short_y) * tiles_n, us[h], us[h - 1]), tall, shrt, swap ? y : (int)x, swap ? (int)x : y);
+                    if (x + y == 0 || short_x + short_y == 0) continue;            // one height
+                    take(two_height_us((x + y) * tiles_n, (short_x + short_y) * tiles_n, cost[h], cost[h - 1], nslab), tall, shrt, swap ? y : (int)x, swap ? (int)x : y);
                 }
         }
     }

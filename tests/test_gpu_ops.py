@@ -538,6 +538,34 @@ def test_linear_256_column_tiles(hb, epi, m, n, slabs, rows):
         assert torch.equal(x, out)
 
 
+@pytest.mark.parametrize("epi,m,n,slabs,slower", [
+    ("geglu", 4096, 5120, 5, "128x256"), ("geglu", 4096, 5120, 10, "128x256"), ("geglu", 8192, 2560, 20, "128x256"), ("geglu", 6144, 5120, 5, "192x256"),
+    ("geglu", 8192, 2560, 10, "128x256"), ("geglu", 8361, 2560, 10, "192x256"), ("geglu", 7079, 2560, 10, "192x256"),
+    ("bias", 8192, 3072, 20, "128x256"), ("gelu", 8192, 3072, 18, "128x256"), ("gate", 11264, 1408, 24, "192x256"), ("gate", 20480, 1088, 9, "256x256"), ("gate", 4608, 1728, 5, "128x256")])
+def test_linear_leaves_256_column_tiles_where_they_are_slower(hb, epi, m, n, slabs, slower):
+    """Launches whose estimate once took them to tiles that are 5-25 % slower than those of the other kernels (full rounds of tiles on all CUs, short k), or make
+    the rest of a stage slower (GEGLU, ten slabs): another tile shape, and the results."""
+    k, wide = 64 * slabs, 2 if epi == "geglu" else 1
+    a, w, b = _data(700 + slabs, (m, k), "bf16"), _data(701, (wide * n, k), "bf16", 0.02), _data(702, (wide * n,), "f32", 0.02)
+    da, dw, db = dev(a, torch.bfloat16), dev(w, torch.bfloat16), dev(b)
+    code = {"bias": hb.HYB_EPI_BIAS, "gelu": hb.HYB_EPI_GELU_TANH, "geglu": hb.HYB_EPI_GEGLU, "gate": hb.HYB_EPI_GATE_RESIDUAL}[epi]
+    out = torch.zeros(m, n, device="cuda", dtype=torch.float32 if epi == "gate" else torch.bfloat16)
+    kw = dict(residual=torch.zeros(m, n, device="cuda")) if epi == "gate" else {}
+    hb.hyb_trace_enable(True)
+    hb.hyb_linear(da, dw, db, out, code, **kw)
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert len(names) == 1 and ("gemm_mfma_%s." % slower) not in list(names)[0], names
+    pick = np.unique(np.concatenate([np.arange(0, m, 211), np.arange(m - 70, m)]))
+    y = O.linear(a[pick], w, b)
+    if epi == "geglu":
+        y = y[:, :n] * O.gelu_erf(y[:, n:])
+    elif epi == "gelu":
+        y = O.gelu_tanh(y)
+    assert err(host(out)[pick], y) < (1e-5 if epi == "gate" else 2.0 ** -9)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("rows,hidden,batch", [(1, 8, 1), (3, 504, 2), (37, 520, 3), (32769, 64, 4), (70003, 1032, 5), (130, 4096, 4)])
 def test_adaln_modulation_row_groups(hb, dt, rows, hidden, batch):
