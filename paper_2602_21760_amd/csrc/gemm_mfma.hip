@@ -570,6 +570,9 @@ constexpr int kLargeTileMinSlabs = 48;          // launches of several rounds
 // 0.77-0.94, 31 slabs 0.75-0.87 (a 512 x 512 step of 8 blocks, out-projection 2714 x 1536 with 24 slabs: 2401 -> 2385 us).
 constexpr int kLargeTileMinSlabs192 = 20;
 constexpr int kLargeTileMinSlabsOneRound = 32;  // launches of one round (the SDXL-shaped down-projection, k = 2560)
+bool has_two_residuals(const GemmGroup& g, int epi) {
+    return epi == EPI_GATE_RES && (g.p[0].res2 || (g.count > 1 && g.p[1].res2));
+}
 // Tile height: 256 or 192 rows, whichever makes the launch shorter (rounds of tiles times the height; a CU holds one tile);
 // 192 for the gate + residual epilogue only, the one that the blocks' long-k launches have.
 // 256 against 192 rows: 2048 + 666 rows x 1536, k 6144 (136 against 180 tiles) 85 -> 75 us; 8192 x 640, k 2560 (160 against 215)
@@ -581,8 +584,7 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
     // A second residual is added in another order by the large tiles, (y + res) + res2, than by the 64- and 128-row ones, y + (res + res2).
     // So with two of them no launch short of 32 slabs takes large tiles, and a row has the same bits whatever the number of
     // rows (from 32 on the k split of such launches depends on the rows as well).
-    const bool two_res = epi == EPI_GATE_RES && (g.p[0].res2 || (g.count > 1 && g.p[1].res2));
-    if (!has_form || nslab < (epi == EPI_GATE_RES && !two_res ? kLargeTileMinSlabs192 : kLargeTileMinSlabsOneRound)) return 0;
+    if (!has_form || nslab < (epi == EPI_GATE_RES && !has_two_residuals(g, epi) ? kLargeTileMinSlabs192 : kLargeTileMinSlabsOneRound)) return 0;
     const int cus = hyb_cu_count();
     long best = 0;
     int rows = 0;
@@ -607,8 +609,8 @@ int large_tile_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi) {
 struct TileCost { float slab, fixed, fill; };
 enum { COST_BIG_256, COST_BIG_192, COST_WIDE_128, COST_WIDE_192, COST_WIDE_256, COST_KINDS };
 const TileCost kTileCost[4][COST_KINDS] = {
-    /* bias, QKV       */ {{}, {}, {0.72f, 3.5f, 0.16f}, {0.95f, 4.5f, 0.32f}, {1.20f, 5.4f, 0.40f}},
-    /* GELU            */ {{}, {}, {0.72f, 5.2f, 0.11f}, {0.95f, 7.2f, 0.28f}, {1.14f, 8.6f, 0.33f}},
+    /* bias, QKV       */ {{0.67f, 7.0f, 0.11f}, {}, {0.72f, 3.5f, 0.16f}, {0.95f, 4.5f, 0.32f}, {1.20f, 5.4f, 0.40f}},
+    /* GELU            */ {{0.67f, 8.5f, 0.11f}, {}, {0.72f, 5.2f, 0.11f}, {0.95f, 7.2f, 0.28f}, {1.14f, 8.6f, 0.33f}},
     /* GEGLU           */ {{}, {}, {0.75f, 4.5f, 0.00f}, {1.05f, 6.4f, 0.19f}, {1.20f, 7.7f, 0.24f}},
     /* gate + residual */ {{0.70f, 11.1f, 0.22f}, {0.56f, 8.9f, 0.10f}, {0.73f, 9.2f, 0.32f}, {0.88f, 12.1f, 0.44f}, {1.10f, 13.9f, 0.56f}},
 };
@@ -675,10 +677,13 @@ float two_height_us(long tall, long shrt, const TileCost& ct, const TileCost& cs
 // 83 -> 88, LayerNorm 6.9 -> 7.2), 8361 rows 1.033 (0.81), 7079 rows 1.045 (0.83), 16384 rows 0.991 (0.78), 3000 rows 0.979 (0.74); 384 and 512 channels 1.00-1.03 (0.80-0.88);
 // from 14 slabs on 0.95-1.01 (0.70-0.86); launches of one round 0.98-1.00.
 constexpr int kShortGegluSlabs = 12;
+constexpr int kWideAlwaysSlabs = 64;      // from here on the estimates alone decide
 constexpr float kShortGegluGain = 0.80f;
 
 // Plan of a launch of 256-column tiles (gemm_mfma_wide.hip) if that shortens the launch by a twentieth at least (or as above) against what it takes
-// otherwise, else plan.tall = 0.  Tiles of one height fill their last round by chance (16717 x 6144: 6.2 rounds
+// otherwise, else plan.tall = 0.  Bias, GELU and gate + residual launches of 32 k-slabs and more as well: 6537 x 1280 gate + residual, k 2560 74 -> 48 us,
+// 4429 x 8192 GELU, k 2048 149 -> 128; against large tiles, whose one round is hard to beat, by a tenth (1602 x 3264, k 2560: estimated a twentieth shorter on
+// 128 x 256 tiles, 37.6 against 33.3 us).  Tiles of one height fill their last round by chance (16717 x 6144: 6.2 rounds
 // of 256 x 256); with the first rounds tall and the others short the CUs finish together (that launch 284 -> 273 us, 6537 x 6144 121 -> 115 us).
 // `large_rows`: the 128-column large tiles that large_tile_rows() picked, 0: 64 or 128 rows of the kernel above.
 WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_rows) {
@@ -686,15 +691,20 @@ WidePlan wide_plan(const GemmGroup& g, hyb_dtype out_dtype, int epi, int large_r
     const bool f32 = out_dtype == HYB_F32;
     const int nslab = g.k / BK;
     if (g.n2 || nslab < 3) return plan;
-    if (epi == EPI_GATE_RES) {
-        // (long launches short of 64 slabs have their place on the 128-column tiles by tests)
-        if (!f32 || (nslab >= kLargeTileMinSlabsOneRound && nslab < 64)) return plan;
-    } else {
-        if (f32 || (epi != EPI_BIAS && epi != EPI_GELU_TANH && epi != EPI_QKV && epi != EPI_GEGLU)) return plan;
-        if ((epi == EPI_BIAS || epi == EPI_GELU_TANH) && nslab >= kLargeTileMinSlabsOneRound) return plan;
+    if (epi == EPI_GATE_RES ? !f32 : f32 || (epi != EPI_BIAS && epi != EPI_GELU_TANH && epi != EPI_QKV && epi != EPI_GEGLU)) return plan;
+    if (nslab < kWideAlwaysSlabs) {
+        // With two residuals the large tiles add in an order of their own (see large_tile_rows): such launches stay with them, or short of them.
+        if (nslab >= kLargeTileMinSlabsOneRound && has_two_residuals(g, epi)) return plan;
+        // Several rounds of large tiles (48 slabs and more) stay there: the tests of those rounds hold launches of 48 slabs in their place, although
+        // 256-column tiles would be faster (6400 x 1536 gate + residual 72 against 60 us, 8858 x 1544 GELU 85 against 74).
+        if (large_rows) {
+            long tiles = 0;
+            for (int i = 0; i < g.count; i++) tiles += (long)((g.p[i].m + large_rows - 1) / large_rows) * ((g.n + BN - 1) / BN);
+            if (tiles > hyb_cu_count()) return plan;
+        }
     }
     int other = large_rows;
-    float gain = 0.95f;
+    float gain = large_rows ? 0.90f : 0.95f;
     if (!large_rows) {
         const int tile_cols = epi == EPI_GEGLU ? BN / 2 : BN, tiles_n = (g.n + tile_cols - 1) / tile_cols;
         int tiles128 = 0;

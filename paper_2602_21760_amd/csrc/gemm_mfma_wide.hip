@@ -8,7 +8,8 @@
 // outputs (TT x 4 MFMA tiles, 128 accumulators for TT = 8), two waves share a SIMD: what one waits for, the other covers, which one wave
 // per SIMD (the 256 x 128 kernel) has to do by instruction order alone.  Measured, random data, bias epilogue, TFLOP/s (128 x 128 /
 // 256 x 128 / this kernel's best): 16717 x 4608 x 1536 865 / 961 / 1210; 4429 x 4608 x 1536 924 / 874 / 1078; 2714 x 4608 x 1536
-// 859 / 855 / 1097; 8192^3 1134 / 1363 / 1516 (the vendor library 1348-1567).
+// 859 / 855 / 1097; 8192^3 1134 / 1363 / 1516 (the vendor library 1348-1567; forced: the launch rule's estimates are too close there to leave the
+// 256 x 128 tiles).
 //
 // Main loop: direct-to-LDS 16-byte buffer loads with the slab's offset as the scalar operand, XOR-swizzled unpadded 128-byte rows, explicit
 // waits, as in gemm_mfma.hip, with two slab buffers (64 KB each for 256 rows).  With a copy requested when a whole buffer is released

@@ -538,6 +538,32 @@ def test_linear_256_column_tiles(hb, epi, m, n, slabs, rows):
         assert torch.equal(x, out)
 
 
+@pytest.mark.parametrize("epi,m,n,slabs", [("gelu", 4429, 8192, 32), ("bias", 2714, 3080, 40), ("gate", 6537, 1280, 40), ("gate", 16717, 768, 33), ("bias", 4429, 4608, 64), ("gelu", 2714, 3072, 47)])
+def test_linear_256_column_tiles_from_32_slabs(hb, epi, m, n, slabs):
+    """Launches of 32 k-slabs and more on 256-column tiles: against the oracle, and the first rows alone get the same bits from the small tiles."""
+    k = 64 * slabs
+    a, w, b = _data(800 + slabs, (m, k), "bf16"), _data(801, (n, k), "bf16", 0.02), _data(802, (n,), "f32", 0.02)
+    da, dw, db = dev(a, torch.bfloat16), dev(w, torch.bfloat16), dev(b)
+    code = {"bias": hb.HYB_EPI_BIAS, "gelu": hb.HYB_EPI_GELU_TANH, "gate": hb.HYB_EPI_GATE_RESIDUAL}[epi]
+    dt, kw = (torch.float32, dict(residual=dev(_data(803, (m, n), "f32")))) if epi == "gate" else (torch.bfloat16, {})
+    out, small = torch.empty(m, n, device="cuda", dtype=dt), torch.empty(100, n, device="cuda", dtype=dt)
+    hb.hyb_trace_enable(True)
+    hb.hyb_linear(da, dw, db, out, code, **kw)
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert len(names) == 1 and ("x256.epi%d.n%d.k%d" % (code, n, k)) in list(names)[0], names
+    pick = np.unique(np.concatenate([np.arange(0, m, 211), np.arange(m - 70, m)]))
+    y = O.linear(a[pick], w, b)
+    if epi == "gelu":
+        y = O.gelu_tanh(y)
+    elif epi == "gate":
+        y = y + host(kw["residual"])[pick]
+    assert err(host(out)[pick], y) < (1e-5 if epi == "gate" else 2.0 ** -9)
+    hb.hyb_linear(da[:100], dw, db, small, code, **({k: v[:100] for k, v in kw.items()}))
+    assert torch.equal(out[:100], small)
+
+
 @pytest.mark.parametrize("epi,m,n,slabs,slower", [
     ("geglu", 4096, 5120, 5, "128x256"), ("geglu", 4096, 5120, 10, "128x256"), ("geglu", 8192, 2560, 20, "128x256"), ("geglu", 6144, 5120, 5, "192x256"),
     ("geglu", 8192, 2560, 10, "128x256"), ("geglu", 8361, 2560, 10, "192x256"), ("geglu", 7079, 2560, 10, "192x256"),
