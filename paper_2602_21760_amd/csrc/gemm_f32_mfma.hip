@@ -352,14 +352,16 @@ int hyb_launch_gemm_f32_mfma(const GemmGroup& g, hyb_dtype out_dtype, int epi, h
     const double tiles64 = tiles_of(g, epi, 64), tiles32 = tiles_of(g, epi, 32);
     if (tiles32 == 0) return HYB_OK;
     // A 64 x 64 tile takes a CU four times as long as a 32 x 32 one: the small tiles where they take a fifth or more off the
-    // work of the busiest CU, the large ones (half the operand traffic) otherwise; small against large tiles over 124 random shapes:
+    // work of the busiest CU, the large ones (half the operand traffic) otherwise; small against large tiles of two slab buffers over 124 random shapes:
     // 0.30-1.08 of the time where that work is 0.75 or less, 0.97-1.73 where it is more.  (653 x 768 x 3072: 30 against
-    // 61 us; 1306 x 3072 x 768: 65 against 52; 1306 x 768 x 3072: 61 either way; 2704 x 1024 x 320: 32 against 22.)  A single round of
-    // large tiles that leaves CUs idle takes as long as a full one; with a long k the small tiles gain from that what they lose on
-    // operands (198-210 tiles: 1.15-1.22 at k 320, 0.97-0.99 at 768, 0.86-0.91 at 4096; 252-256 tiles: 0.98-1.03 from 768 on).
+    // 61 us; 1306 x 3072 x 768: 65 against 52; 2704 x 1024 x 320: 32 against 22.)
+    // A single round of large tiles that leaves CUs idle takes as long as a full one.  With four slab buffers (below) it is faster all the same: small against large
+    // tiles, 193-256 of the latter, 1.02-1.22 (k 256-4096; 192 and fewer, which the line above leaves to the small ones, 0.76-0.99, 1.08 at k 320).  With two
+    // (GEGLU) a long k gains from small tiles what they lose on operands: 198-210 tiles 1.15-1.22 at k 320, 0.97-0.99 at 768, 0.86-0.91 at 4096;
+    // 252-256 tiles 0.98-1.03 from 768 on.
     const int cus = hyb_cu_count();
     const double busy64 = 4.0 * (double)(((long long)tiles64 + cus - 1) / cus), busy32 = (double)(((long long)tiles32 + cus - 1) / cus);
-    const bool small = busy32 < 0.8 * busy64 || (tiles64 < 0.85 * cus && g.k >= 768);
+    const bool small = busy32 < 0.8 * busy64 || (epi == EPI_GEGLU && tiles64 < 0.85 * cus && g.k >= 768);
     // One large tile on nearly every CU, one wave per SIMD: nothing covers a wave's waits but its own deeper pipeline.  Two against four buffers:
     // 1306 x 768 (252 tiles) 62 -> 55 us at k 3072, 19.8 -> 18.5 at 768; with two tiles per CU and more they cover each other (504 tiles of k
     // 768: 28.8 against 28.1 us, 1008: 53 against 55).

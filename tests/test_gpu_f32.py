@@ -157,6 +157,25 @@ def test_linear_f32_64x64_tiles_four_buffers(hb, k):
     assert err(host(one), res.numpy() + O.linear(a.double().numpy(), w.double().numpy(), b.double().numpy())) < TOL
 
 
+@pytest.mark.parametrize("m,n,k,geglu,tiles", [(1060, 764, 768, False, "64x64"), (1088, 768, 4096, False, "64x64"), (890, 896, 1024, False, "64x64"), (1088, 384, 1024, True, "32x32"),
+                                               (1024, 768, 1024, False, "32x32")])
+def test_linear_f32_single_round_that_leaves_cus_idle(hb, m, n, k, geglu, tiles):
+    """A round of 193-217 tiles of 64 x 64 with a long k: large tiles where they have four slab buffers, small ones for GEGLU (two buffers) and for
+    192 tiles; the oracle's results, and the same rows the same bits in a launch of eight times as many."""
+    g = torch.Generator().manual_seed(m + k)
+    wide = 2 if geglu else 1
+    a, w, b = torch.randn(m, k, generator=g), torch.randn(wide * n, k, generator=g) * k ** -0.5, torch.randn(wide * n, generator=g)
+    da, dw, db = a.cuda(), w.cuda(), b.cuda()
+    out, many = torch.empty(m, n, device="cuda"), torch.empty(8 * m, n, device="cuda")
+    epi = hb.HYB_EPI_GEGLU if geglu else hb.HYB_EPI_BIAS
+    names = _traced(hb, lambda: hb.hyb_linear(da, dw, db, out, epi))
+    assert names == ["gemm_f32_mfma_%s.epi%d.n%d.k%d" % (tiles, epi, n, k)], names
+    y = O.linear(a.double().numpy(), w.double().numpy(), b.double().numpy())
+    assert err(host(out), y[:, :n] * O.gelu_erf(y[:, n:]) if geglu else y) < TOL
+    hb.hyb_linear(da.repeat(8, 1), dw, db, many, epi)
+    assert torch.equal(many.view(8, m, n), out.expand(8, m, n))
+
+
 def test_qkv_scatter_f32_64x64_tiles(hb):
     """The head-major scatter from the 64 x 64 tiles: an fp32 block of two samples with ragged image and text rows, 252 tiles."""
     from test_gpu_block import _block_case
