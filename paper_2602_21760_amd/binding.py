@@ -341,8 +341,19 @@ def hyb_block_forward(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_s
                                    _p(x_txt_out, torch.float32), _p(workspace), _nbytes(workspace), _stream()))
 
 
-def mmdit_weights(linears, ada_w, ada_b, pos, blocks, dtype):
-    """linears: dict of device tensors t1_w, t1_b, ... (p1, p2 may be missing: NULL); blocks: ctypes array of BlockWeights; dtype: of the matrices."""
+def mmdit_weights(tensors, blocks):
+    """tensors: dict of device tensors named as the fields of hyb_mmdit_weights (missing ones: NULL); blocks: ctypes array of BlockWeights."""
+    return MMDiTWeights(*[tensors[n].data_ptr() if n in tensors else None for n in MMDIT_WEIGHT_FIELDS], blocks)
+
+
+def mmdit_buffers(tensors):
+    """tensors: dict of device tensors named as the fields of hyb_mmdit_buffers (missing ones: NULL)."""
+    return MMDiTBuffers(*[tensors[n].data_ptr() if n in tensors else None for n in MMDIT_BUFFER_FIELDS], _nbytes(tensors["ws"]))
+
+
+def checked_mmdit_weights(linears, ada_w, ada_b, pos, blocks, dtype):
+    """hyb_mmdit_weights for one call, with the checks of the single calls.  linears: dict of device tensors t1_w, t1_b, ... (p1, p2 may be missing:
+    NULL); blocks: ctypes array of BlockWeights; dtype: of the matrices."""
     f32, p_w, p_b = torch.float32, (None, None), (None, None)
     if "p1_w" in linears:
         p_w, p_b = _pointers(_pooled_matrices(linears), dtype), _pointers(_pooled_biases(linears), f32)
@@ -351,9 +362,9 @@ def mmdit_weights(linears, ada_w, ada_b, pos, blocks, dtype):
     return MMDiTWeights(t1_w, t2_w, *p_w, pe_w, ce_w, f_w, a_w, t1_b, t2_b, *p_b, pe_b, ce_b, f_b, a_b, pos, blocks)
 
 
-def mmdit_buffers(owner, dtype):
-    """owner: object whose attributes named as the fields of hyb_mmdit_buffers are the device tensors (pooled_act and p_hid may be missing: NULL);
-    dtype: of the activations."""
+def checked_mmdit_buffers(owner, dtype):
+    """hyb_mmdit_buffers for one call, with the checks of the single calls.  owner: object whose attributes named as the fields are the device tensors
+    (pooled_act and p_hid may be missing: NULL); dtype: of the activations."""
     pooled = _pointers(_pooled_buffers(owner), dtype) if hasattr(owner, "p_hid") else (None, None)
     t_feat, t_hid, tok, ctx_act, y, out_tok, v = _pointers(_act_buffers(owner), dtype)
     temb, mod, x_img, x_txt = _pointers(_f32_buffers(owner), torch.float32)

@@ -158,7 +158,7 @@ class MMDiT:
         checked on every call, as those three do: they are what the attributes hold now."""
         cfg, act = self.cfg, self.act
         blocks = (hb.BlockWeights * len(self.blocks))(*self.blocks)
-        hb.hyb_mmdit_forward(self._call_desc, hb.mmdit_weights(self.g, self.ada_w, self.ada_b, self.pos, blocks, act), hb.mmdit_buffers(self, act),
+        hb.hyb_mmdit_forward(self._call_desc, hb.checked_mmdit_weights(self.g, self.ada_w, self.ada_b, self.pos, blocks, act), hb.checked_mmdit_buffers(self, act),
                              latent, ctx if cfg.n_txt else None, t, pooled if cfg.pooled_dim else None, self.txt_pre_only_last, shared_latent)
 
 

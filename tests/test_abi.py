@@ -147,7 +147,8 @@ def test_struct_layouts_match_the_header(tmp_path):
         pytest.skip("no gcc")
     structs = {"hyb_block_desc": binding.BlockDesc, "hyb_stream_weights": binding.StreamWeights,
                "hyb_block_weights": binding.BlockWeights, "hyb_sdxl_block_desc": binding.SdxlBlockDesc,
-               "hyb_sdxl_block_weights": binding.SdxlBlockWeights, "hyb_switch_state": binding.SwitchState}
+               "hyb_sdxl_block_weights": binding.SdxlBlockWeights, "hyb_switch_state": binding.SwitchState,
+               "hyb_mmdit_desc": binding.MMDiTDesc, "hyb_mmdit_weights": binding.MMDiTWeights, "hyb_mmdit_buffers": binding.MMDiTBuffers}
     lines = ['#include <stdio.h>', '#include <stddef.h>', '#include "hyb.h"', 'int main(void) {']
     for cname, ct in structs.items():
         lines.append('printf("%s size %%zu\\n", sizeof(%s));' % (cname, cname))
@@ -164,6 +165,19 @@ def test_struct_layouts_match_the_header(tmp_path):
         assert got[(cname, "size")] == ctypes.sizeof(ct), cname
         for fname, _ in ct._fields_:
             assert got[(cname, fname)] == getattr(ct, fname).offset, (cname, fname)
+
+
+def test_forward_structs_from_dicts_of_tensors():
+    """mmdit_weights / mmdit_buffers: fields by name, missing ones NULL."""
+    import torch
+    from paper_2602_21760_amd import binding
+    blocks = (binding.BlockWeights * 1)()
+    t = {n: torch.empty(8) for n in ("t1_w", "pos", "ada_b")}
+    w = binding.mmdit_weights(t, blocks)
+    assert (w.t1_w, w.pos, w.ada_b) == tuple(t[n].data_ptr() for n in ("t1_w", "pos", "ada_b")) and w.p1_w is None and w.f_b is None
+    t = {"v": torch.empty(8), "ws": torch.empty(24, dtype=torch.uint8)}
+    b = binding.mmdit_buffers(t)
+    assert (b.v, b.ws, b.ws_bytes, b.t_feat) == (t["v"].data_ptr(), t["ws"].data_ptr(), 24, None)
 
 
 def test_missing_library_is_an_error(monkeypatch, tmp_path):
