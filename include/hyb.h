@@ -286,7 +286,8 @@ typedef struct {
 
 /* latent: device float[batch, latent_h, latent_w, latent_c], or one latent for all samples (shared_latent != 0); ctx: device float[batch, n_txt, ctx_dim];
  * t: device float[batch], or NULL: t_value for all samples; pooled: device float[batch, pooled_dim] when desc->pooled_dim > 0.
- * txt_pre_only_last: the last block's text stream only supplies keys and values. */
+ * txt_pre_only_last: the last block's text stream only supplies keys and values.
+ * The arguments of all calls it is made of are checked before the first of them. */
 int hyb_mmdit_forward(const hyb_mmdit_desc* desc, const hyb_mmdit_weights* weights, const hyb_mmdit_buffers* buffers,
                       const float* latent, int shared_latent, const float* ctx, const float* t, float t_value, const float* pooled,
                       int txt_pre_only_last, void* stream);
