@@ -177,7 +177,7 @@ def _p(t, dtype=None):
 
 
 def _pointers(tensors, dtype):
-    """_p of several tensors of one type, in a third of the host time."""
+    """_p of several tensors of one type, in less than half of the host time."""
     if all(map(_is_cuda, tensors)) and all(map(torch.Tensor.is_contiguous, tensors)) and [*map(_dtype_of, tensors)].count(dtype) == len(tensors):
         return [*map(torch.Tensor.data_ptr, tensors)]
     return [_p(t, dtype) for t in tensors]      # says what is wrong
@@ -229,10 +229,10 @@ def hyb_cfg_disc_euler(v_c, v_u, x, x_out, scale, t, t_next, disc_l1=None, disc_
 def cfg_disc_euler_of_branches(v, x, scale, t, t_next, disc, i, workspace):
     """hyb_cfg_disc_euler of v[0:1] and v[1:2], in place over x, with the discrepancies in disc[0, i:i + 1] and disc[1, i:i + 1] (disc: f32[2, steps]), but
     without these views, each of which costs the host a microsecond."""
-    if not (v.is_contiguous() and disc.is_contiguous()):
+    if not (v.is_cuda and v.is_contiguous() and disc.is_cuda and disc.is_contiguous() and disc.dtype is torch.float32):
         hyb_cfg_disc_euler(v[0:1], v[1:2], x.view(1, -1), x.view(1, -1), scale, t, t_next, disc[0, i:i + 1], disc[1, i:i + 1], workspace)
         return
-    n, pv, px, pd = v.numel() // v.shape[0], _p(v), _p(x, torch.float32), _p(disc, torch.float32)
+    n, pv, px, pd = v.numel() // v.shape[0], v.data_ptr(), _p(x, torch.float32), disc.data_ptr()
     steps = disc.shape[1]
     start, stop, _ = slice(i, i + 1).indices(steps)
     l1, l2 = (pd + 4 * start, pd + 4 * (steps + start)) if start < stop else (None, None)
@@ -351,24 +351,20 @@ def mmdit_buffers(tensors):
     return MMDiTBuffers(*[tensors[n].data_ptr() if n in tensors else None for n in MMDIT_BUFFER_FIELDS], _nbytes(tensors["ws"]))
 
 
-def checked_mmdit_weights(linears, ada_w, ada_b, pos, blocks, dtype):
-    """hyb_mmdit_weights for one call, with the checks of the single calls.  linears: dict of device tensors t1_w, t1_b, ... (p1, p2 may be missing:
-    NULL); blocks: ctypes array of BlockWeights; dtype: of the matrices."""
-    f32, p_w, p_b = torch.float32, (None, None), (None, None)
-    if "p1_w" in linears:
-        p_w, p_b = _pointers(_pooled_matrices(linears), dtype), _pointers(_pooled_biases(linears), f32)
-    t1_w, t2_w, pe_w, ce_w, f_w, a_w = _pointers((*_matrices(linears), ada_w), dtype)
-    t1_b, t2_b, pe_b, ce_b, f_b, a_b, pos = _pointers((*_biases(linears), ada_b, pos), f32)
-    return MMDiTWeights(t1_w, t2_w, *p_w, pe_w, ce_w, f_w, a_w, t1_b, t2_b, *p_b, pe_b, ce_b, f_b, a_b, pos, blocks)
-
-
-def checked_mmdit_buffers(owner, dtype):
-    """hyb_mmdit_buffers for one call, with the checks of the single calls.  owner: object whose attributes named as the fields are the device tensors
-    (pooled_act and p_hid may be missing: NULL); dtype: of the activations."""
-    pooled = _pointers(_pooled_buffers(owner), dtype) if hasattr(owner, "p_hid") else (None, None)
-    t_feat, t_hid, tok, ctx_act, y, out_tok, v = _pointers(_act_buffers(owner), dtype)
-    temb, mod, x_img, x_txt = _pointers(_f32_buffers(owner), torch.float32)
-    return MMDiTBuffers(t_feat, t_hid, *pooled, temb, mod, tok, ctx_act, x_img, x_txt, y, out_tok, v, _p(owner.ws), _nbytes(owner.ws))
+def checked_mmdit_structs(model, blocks):
+    """hyb_mmdit_weights and hyb_mmdit_buffers of a model for one call, with the checks of the single calls: its matrices and activations are of type
+    model.act, everything else is fp32.  blocks: ctypes array of BlockWeights.  (Two passes over all tensors: a pass costs the host 1-2 us.)"""
+    g, act, f32 = model.g, model.act, torch.float32
+    p_w = p_b = p_buffers = (None, None)
+    if "p1_w" in g:
+        p_w, p_b = _pointers(_pooled_matrices(g), act), _pointers(_pooled_biases(g), f32)
+    if hasattr(model, "p_hid"):
+        p_buffers = _pointers(_pooled_buffers(model), act)
+    t1_w, t2_w, pe_w, ce_w, f_w, ada_w, t_feat, t_hid, tok, ctx_act, y, out_tok, v = _pointers((*_matrices(g), model.ada_w, *_act_buffers(model)), act)
+    t1_b, t2_b, pe_b, ce_b, f_b, ada_b, pos, temb, mod, x_img, x_txt = _pointers((*_biases(g), model.ada_b, model.pos, *_f32_buffers(model)), f32)
+    ws = model.ws
+    return (MMDiTWeights(t1_w, t2_w, *p_w, pe_w, ce_w, f_w, ada_w, t1_b, t2_b, *p_b, pe_b, ce_b, f_b, ada_b, pos, blocks),
+            MMDiTBuffers(t_feat, t_hid, *p_buffers, temb, mod, tok, ctx_act, x_img, x_txt, y, out_tok, v, _p(ws), _nbytes(ws)))
 
 
 def hyb_mmdit_forward(desc, weights, buffers, latent, ctx, t, pooled=None, txt_pre_only_last=False, shared_latent=False):

@@ -112,8 +112,13 @@ extern "C" int hyb_block_forward(const hyb_block_desc* desc, const hyb_block_wei
                                  const float* mod_img, const float* mod_txt, size_t mod_stride,
                                  float* x_img_out, float* x_txt_out,
                                  void* workspace, size_t workspace_bytes, void* stream) {
-    int rc = hyb_check_block_forward(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_stride, x_img_out, x_txt_out, workspace, workspace_bytes);
-    if (rc) return rc;
+    const int rc = hyb_check_block_forward(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_stride, x_img_out, x_txt_out, workspace, workspace_bytes);
+    return rc ? rc : hyb_run_block(desc, weights, x_img_in, x_txt_in, mod_img, mod_txt, mod_stride, x_img_out, x_txt_out, workspace, (hipStream_t)stream);
+}
+
+int hyb_run_block(const hyb_block_desc* desc, const hyb_block_weights* weights, const float* x_img_in, const float* x_txt_in, const float* mod_img,
+                  const float* mod_txt, size_t mod_stride, float* x_img_out, float* x_txt_out, void* workspace, hipStream_t st) {
+    int rc;
     const hyb_block_desc& d = *desc;
     const int B = d.batch, Ni = d.n_img, Nt = d.n_txt, D = d.hidden, N = Ni + Nt;
     if (B == 0 || N == 0) return HYB_OK;
@@ -121,7 +126,6 @@ extern "C" int hyb_block_forward(const hyb_block_desc* desc, const hyb_block_wei
     const bool txt_pre_only = d.txt_pre_only != 0 && has_txt;   // text: keys and values only, nothing written back
     const hyb_stream_weights* sw[2] = {&weights->img, &weights->txt};
     const BlockLayout L = block_layout(d);
-    hipStream_t st = (hipStream_t)stream;
     char* ws = static_cast<char*>(workspace);
     const hyb_dtype dt = d.dtype;
     void* h[2] = {ws + L.h_img, ws + L.h_txt};

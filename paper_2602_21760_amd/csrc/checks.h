@@ -1,10 +1,14 @@
 // Argument checks of the entry points that hyb_mmdit_forward strings together (each entry point makes its own before it launches anything): they
-// take the entry point's arguments but the stream, touch no device, and set the same errors.
+// take the entry point's arguments but the stream, touch no device, and set the same errors.  hyb_run_*: the launches alone, after the checks.
 #pragma once
 #include "common.h"
 
 int hyb_check_linear(const void* a, const void* w, const float* bias, const void* out, int m, int n, int k, hyb_dtype dtype, hyb_dtype out_dtype,
                      hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride);
+int hyb_run_linear(const void* a, const void* w, const float* bias, void* out, int m, int n, int k, hyb_dtype dtype, hyb_dtype out_dtype,
+                   hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride, hipStream_t st);
+int hyb_run_block(const hyb_block_desc* desc, const hyb_block_weights* weights, const float* x_img_in, const float* x_txt_in, const float* mod_img,
+                  const float* mod_txt, size_t mod_stride, float* x_img_out, float* x_txt_out, void* workspace, hipStream_t st);
 int hyb_check_block_forward(const hyb_block_desc* desc, const hyb_block_weights* weights, const float* x_img_in, const float* x_txt_in,
                             const float* mod_img, const float* mod_txt, size_t mod_stride, const float* x_img_out, const float* x_txt_out,
                             const void* workspace, size_t workspace_bytes);

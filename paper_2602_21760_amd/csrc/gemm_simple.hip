@@ -111,41 +111,43 @@ int hyb_launch_gemm(const GemmGroup& g, hyb_dtype in_dtype, hyb_dtype out_dtype,
     return rc ? rc : hyb_launch_gemm_simple(g, in_dtype, out_dtype, epi, st);
 }
 
-// The arguments of hyb_linear: checked, and as one problem (count 0: nothing to do).
-static int linear_problem(GemmGroup& g, const void* a, const void* w, const float* bias, const void* out, int m, int n, int k, hyb_dtype dtype,
-                          hyb_dtype out_dtype, hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride) {
+int hyb_run_linear(const void* a, const void* w, const float* bias, void* out, int m, int n, int k, hyb_dtype dtype, hyb_dtype out_dtype,
+                   hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride, hipStream_t st) {
+    if (m == 0 || n == 0) return HYB_OK;
+    GemmGroup g = {};
+    g.count = 1; g.n = n; g.k = k;
+    GemmProblem& p = g.p[0];
+    p.a = a; p.w = w; p.bias = bias; p.out = out; p.m = m;
+    if (epi == HYB_EPI_GATE_RESIDUAL) {
+        p.res = residual; p.gate = gate; p.rows_per_gate = rows_per_gate > 0 ? rows_per_gate : 1; p.gate_stride = gate_stride;
+    }
+    return hyb_launch_gemm(g, dtype, out_dtype, (int)epi, st);
+}
+
+int hyb_check_linear(const void* a, const void* w, const float* bias, const void* out, int m, int n, int k, hyb_dtype dtype, hyb_dtype out_dtype,
+                     hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride) {
     const char* who = "hyb_linear";
-    g = {};
     HYB_ARG_DTYPE(who, dtype); HYB_ARG_DTYPE(who, out_dtype);
     HYB_REQUIRE((epi >= HYB_EPI_BIAS && epi <= HYB_EPI_GATE_RESIDUAL) || epi == HYB_EPI_GEGLU, HYB_ERR_DTYPE, "hyb_linear: unknown epilogue %d", (int)epi);
     HYB_REQUIRE(m >= 0 && n >= 0 && k >= 0, HYB_ERR_SHAPE, "hyb_linear: negative size");
     if (m == 0 || n == 0) return HYB_OK;
     HYB_ARG_PTR(who, a); HYB_ARG_PTR(who, w); HYB_ARG_PTR(who, out);
     HYB_ARG_ALIGN(who, a); HYB_ARG_ALIGN(who, w); HYB_ARG_ALIGN(who, out); HYB_ARG_ALIGN(who, bias);
-    g.count = 1; g.n = n; g.k = k;
-    GemmProblem& p = g.p[0];
-    p.a = a; p.w = w; p.bias = bias; p.out = const_cast<void*>(out); p.m = m;
+    GemmGroup g = {};        // what decides whether a kernel takes the launch
+    g.count = 1; g.n = n; g.k = k; g.p[0].m = m;
     if (epi == HYB_EPI_GATE_RESIDUAL) {
         HYB_REQUIRE(out_dtype == HYB_F32, HYB_ERR_DTYPE, "hyb_linear: HYB_EPI_GATE_RESIDUAL needs an fp32 output");
         HYB_ARG_PTR(who, residual); HYB_ARG_ALIGN(who, residual); HYB_ARG_ALIGN(who, gate);
         HYB_REQUIRE(gate == nullptr || rows_per_gate > 0, HYB_ERR_SHAPE, "hyb_linear: rows_per_gate must be positive");
-        p.res = residual; p.gate = gate; p.rows_per_gate = rows_per_gate > 0 ? rows_per_gate : 1; p.gate_stride = gate_stride;
+        g.p[0].gate = gate; g.p[0].gate_stride = gate_stride;
     }
-    return HYB_OK;
-}
-
-int hyb_check_linear(const void* a, const void* w, const float* bias, const void* out, int m, int n, int k, hyb_dtype dtype, hyb_dtype out_dtype,
-                     hyb_epilogue epi, const float* residual, const float* gate, int rows_per_gate, size_t gate_stride) {
-    GemmGroup g;
-    const int rc = linear_problem(g, a, w, bias, out, m, n, k, dtype, out_dtype, epi, residual, gate, rows_per_gate, gate_stride);
-    return rc || g.count == 0 ? rc : hyb_check_gemm(g, dtype, out_dtype, (int)epi);
+    return hyb_check_gemm(g, dtype, out_dtype, (int)epi);
 }
 
 extern "C" int hyb_linear(const void* a, const void* w, const float* bias, void* out, int m, int n, int k,
                           hyb_dtype dtype, hyb_dtype out_dtype, hyb_epilogue epi,
                           const float* residual, const float* gate, int rows_per_gate, size_t gate_stride,
                           void* stream) {
-    GemmGroup g;
-    const int rc = linear_problem(g, a, w, bias, out, m, n, k, dtype, out_dtype, epi, residual, gate, rows_per_gate, gate_stride);
-    return rc || g.count == 0 ? rc : hyb_launch_gemm(g, dtype, out_dtype, (int)epi, (hipStream_t)stream);
+    const int rc = hyb_check_linear(a, w, bias, out, m, n, k, dtype, out_dtype, epi, residual, gate, rows_per_gate, gate_stride);
+    return rc ? rc : hyb_run_linear(a, w, bias, out, m, n, k, dtype, out_dtype, epi, residual, gate, rows_per_gate, gate_stride, (hipStream_t)stream);
 }

@@ -27,7 +27,7 @@ struct Inputs {
 };
 
 // The calls of a forward in order.  LAUNCH = false makes their argument checks only, so that an error is found before anything is enqueued, and
-// the same lines say what is checked and what is launched.
+// the same lines say what is checked and what is launched (LAUNCH = true leaves out the checks of the frequent calls).
 template <bool LAUNCH>
 int forward(const hyb_mmdit_desc& d, const hyb_mmdit_weights& w, const hyb_mmdit_buffers& f, const Inputs& in, void* stream) {
     const int B = d.batch, D = d.hidden, pd = d.patch * d.patch * d.latent_c;
@@ -38,7 +38,7 @@ int forward(const hyb_mmdit_desc& d, const hyb_mmdit_weights& w, const hyb_mmdit
     hipStream_t st = (hipStream_t)stream;
     int rc;
     auto linear = [&](const void* a, const void* weight, const float* bias, void* out, int m, int n, int k, hyb_dtype out_dtype, hyb_epilogue epi, const float* residual) {
-        if constexpr (LAUNCH) return hyb_linear(a, weight, bias, out, m, n, k, dt, out_dtype, epi, residual, nullptr, 1, 0, stream);
+        if constexpr (LAUNCH) return hyb_run_linear(a, weight, bias, out, m, n, k, dt, out_dtype, epi, residual, nullptr, 1, 0, st);
         else return hyb_check_linear(a, weight, bias, out, m, n, k, dt, out_dtype, epi, residual, nullptr, 1, 0);
     };
     // fp32 models read their inputs where they are (a copy where they are not aligned for 16-byte loads, or share memory with the m results of the
@@ -104,7 +104,7 @@ int forward(const hyb_mmdit_desc& d, const hyb_mmdit_weights& w, const hyb_mmdit
     for (int i = 0; i < d.blocks; i++) {
         bd.txt_pre_only = in.txt_pre_only_last && i == d.blocks - 1;      // nothing reads the text output of the last block
         const float* mod = f.mod + (size_t)12 * i * D;
-        if constexpr (LAUNCH) rc = hyb_block_forward(&bd, &w.block_weights[i], f.x_img, f.x_txt, mod, mod + 6 * D, mod_rows, f.x_img, f.x_txt, f.ws, f.ws_bytes, stream);
+        if constexpr (LAUNCH) rc = hyb_run_block(&bd, &w.block_weights[i], f.x_img, f.x_txt, mod, mod + 6 * D, mod_rows, f.x_img, f.x_txt, f.ws, st);
         else rc = hyb_check_block_forward(&bd, &w.block_weights[i], f.x_img, f.x_txt, mod, mod + 6 * D, mod_rows, f.x_img, f.x_txt, f.ws, f.ws_bytes);
         if (rc) return rc;
     }

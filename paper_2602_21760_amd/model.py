@@ -83,7 +83,9 @@ class MMDiT:
         # sizes of the whole forward as one call of the library
         self._call_desc = hb.MMDiTDesc(B, len(self.blocks), D, cfg.heads, cfg.mlp_ratio, cfg.latent_hw, cfg.latent_hw, cfg.latent_c, cfg.patch, cfg.n_txt,
                                        cfg.ctx_dim, cfg.temb_dim, cfg.pooled_dim, self.hdt, 1e-6)
-        self._latent_shape = (B, cfg.latent_hw, cfg.latent_hw, cfg.latent_c)
+        self._block_array = hb.BlockWeights * len(self.blocks)      # the type (made anew, it would cost a first call 10-50 us)
+        self._sample_shape = (cfg.latent_hw, cfg.latent_hw, cfg.latent_c)
+        self._latent_shape = (B, *self._sample_shape)
 
     def reconfigure(self, cfg, batch=None, pos_np=None):
         """Re-allocate the activation buffers for another token count / batch of the SAME network
@@ -156,10 +158,10 @@ class MMDiT:
     def _forward(self, latent, ctx, t, pooled=None, shared_latent=False):
         """embed(), run_blocks() and final() in one call; t: f32[B], or a number for all samples.  Weights and buffers are looked up and
         checked on every call, as those three do: they are what the attributes hold now."""
-        cfg, act = self.cfg, self.act
-        blocks = (hb.BlockWeights * len(self.blocks))(*self.blocks)
-        hb.hyb_mmdit_forward(self._call_desc, hb.checked_mmdit_weights(self.g, self.ada_w, self.ada_b, self.pos, blocks, act), hb.checked_mmdit_buffers(self, act),
-                             latent, ctx if cfg.n_txt else None, t, pooled if cfg.pooled_dim else None, self.txt_pre_only_last, shared_latent)
+        cfg = self.cfg
+        weights, buffers = hb.checked_mmdit_structs(self, self._block_array(*self.blocks))
+        hb.hyb_mmdit_forward(self._call_desc, weights, buffers, latent, ctx if cfg.n_txt else None, t, pooled if cfg.pooled_dim else None,
+                             self.txt_pre_only_last, shared_latent)
 
 
 _METHODS = {n: getattr(MMDiT, n) for n in ("embed", "run_blocks", "final", "forward")}
@@ -174,7 +176,8 @@ class GuidedSampler:
         self.m, self.scale = model, scale
         cfg = model.cfg
         n = cfg.latent_elems
-        self.lat2 = torch.empty(2, cfg.latent_hw, cfg.latent_hw, cfg.latent_c, device="cuda", dtype=torch.float32)
+        self._latent_shape = (2, cfg.latent_hw, cfg.latent_hw, cfg.latent_c)
+        self.lat2 = torch.empty(self._latent_shape, device="cuda", dtype=torch.float32)
         self.t2 = torch.empty(2, device="cuda", dtype=torch.float32)
         self.ws = torch.empty(max(hb.hyb_discrepancy_workspace_bytes(1, n), 256), device="cuda", dtype=torch.uint8)
         self.disc = torch.zeros(2, 64, device="cuda", dtype=torch.float32)   # [l1 | l2][step]
@@ -182,7 +185,7 @@ class GuidedSampler:
     def step(self, x, ctx2, t, t_next, i=0):
         """x: f32[Hh, Ww, C] master latent (updated in place); ctx2: f32[2, Nt, ctx_dim]."""
         m = self.m
-        if (isinstance(m, MMDiT) and self.lat2.shape == m._latent_shape and x.shape == m._latent_shape[1:] and x.dtype == torch.float32 and x.is_cuda and
+        if (isinstance(m, MMDiT) and m._latent_shape == self._latent_shape and x.shape == m._sample_shape and x.dtype is torch.float32 and x.is_cuda and
                 x.is_contiguous() and not m.cfg.pooled_dim and m._inputs_fit(ctx2) and m._in_one_call("forward")):
             m._forward(x, ctx2, float(t), shared_latent=True)   # both branches read the one latent
             v = m.v
