@@ -63,7 +63,8 @@ int hyb_gemm_mfma_tiles(int m, int n);
 // the same bits per token, but for the order in which a second residual is added (from 32 k-slabs on).  -1 when the shape or
 // the epilogue has no large-tile form.
 int hyb_launch_gemm_mfma_big(const GemmGroup& g, hyb_dtype out_dtype, int epi, int rows, hipStream_t st);
-// At most 16 rows, one wave per 16 features (bias, GELU-tanh, SiLU, gate * y + residual).  -1 for anything else.  Same bits as the tiles.
+// At most 16 rows, one wave per 16 features (bias, GELU-tanh, SiLU, gate * y + residual).  -1 for anything else and where the tiles are faster (very wide
+// launches).  Same bits as the tiles.
 int hyb_launch_gemm_mfma_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st);
 // Tiles of a launch of 256-column tiles: the first tall_rows[i] tile rows of problem i are `tall` tokens high, the others `shrt`
 // (256 and 192, or 192 and 128).

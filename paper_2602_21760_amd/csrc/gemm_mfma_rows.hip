@@ -79,11 +79,21 @@ int launch_rows(const GemmGroup& g, hipStream_t st) {
     return hyb_check_launch("gemm_mfma_rows");
 }
 
+// Where this kernel is the faster one (11 widths x 10 depths x 1, 4, 8 and 16 rows against the 64 x 128 tiles, weights from memory).  Up to one wave per SIMD
+// it always is (0.3-1.0 of the time), but for wide launches of a few steps, whose waves request 16 steps all the same (16 x 12288: k 64 4.8 against
+// 4.1 us, k 256 5.0 against 5.6).  With more waves the tiles, whose workgroups follow each other, are (3 x 24576, k 64 7.7 against 4.5, k 1536 20 against 18;
+// 16 x 24576, k 1536 26 against 18), until a long k with few rows (1 x 18432, k 2048 21 against 29; 1 x 49152, k 4096 79 against 107; 16 x 18432, k 4096 59 against 50).
+bool rows_kernel_is_faster(int m, int n, int k) {
+    const int per_simd = 16 * 4 * hyb_cu_count();      // features of one wave on every SIMD
+    if (n <= per_simd) return k >= 256 || n <= per_simd / 2;
+    return m <= 4 && k >= 2048;
+}
+
 }  // namespace
 
 int hyb_launch_gemm_mfma_rows(const GemmGroup& g, hyb_dtype out_dtype, int epi, hipStream_t st) {
     const bool f32 = out_dtype == HYB_F32;
-    if (g.count != 1 || g.n2 || g.p[0].m < 1 || g.p[0].m > 16) return -1;
+    if (g.count != 1 || g.n2 || g.p[0].m < 1 || g.p[0].m > 16 || !rows_kernel_is_faster(g.p[0].m, g.n, g.k)) return -1;
     switch (epi) {
         case EPI_BIAS: return f32 ? launch_rows<float, EPI_BIAS>(g, st) : launch_rows<bf16_t, EPI_BIAS>(g, st);
         case EPI_GELU_TANH: return f32 ? launch_rows<float, EPI_GELU_TANH>(g, st) : launch_rows<bf16_t, EPI_GELU_TANH>(g, st);

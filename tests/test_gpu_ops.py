@@ -494,6 +494,25 @@ def test_linear_at_most_16_rows(hb, m, n, slabs):
         assert torch.equal(many.view(20, m, n), out.expand(20, m, n)) or m * 20 <= 16, epi
 
 
+@pytest.mark.parametrize("m,n,k,rows", [(16, 8192, 64, True), (16, 8200, 64, False), (16, 16384, 256, True), (1, 16392, 256, False), (3, 24576, 64, False), (16, 24576, 1536, False),
+                                        (4, 18432, 2048, True), (5, 18432, 2048, False)])
+def test_linear_at_most_16_rows_where_it_is_faster(hb, m, n, k, rows):
+    """Both sides of the line of the 16-row kernel (256 CUs): very wide launches stay on the tiles; the oracle's results and the bits of the same rows in
+    a launch of more."""
+    a, w, b = _data(900 + m, (m, k), "bf16"), _data(901, (n, k), "bf16", 0.02), _data(902, (n,), "f32", 0.02)
+    da, dw, db = dev(a, torch.bfloat16), dev(w, torch.bfloat16), dev(b)
+    out, many = torch.empty(m, n, device="cuda"), torch.empty(20 * m, n, device="cuda")
+    hb.hyb_trace_enable(True)
+    hb.hyb_linear(da, dw, db, out)
+    torch.cuda.synchronize()
+    names = hb.hyb_trace_summary()
+    hb.hyb_trace_enable(False)
+    assert len(names) == 1 and list(names)[0].startswith("gemm_mfma_16x16.") == rows, names
+    assert err(host(out), O.linear(a, w, b)) < 1e-5
+    hb.hyb_linear(da.repeat(20, 1), dw, db, many)
+    assert torch.equal(many.view(20, m, n), out.expand(20, m, n))
+
+
 @pytest.mark.parametrize("epi,m,n,slabs,rows", [
     ("bias", 2700, 4608, 3, "256"), ("bias", 2714, 4600, 24, "256"), ("gelu", 4429, 6144, 9, "256"), ("bias", 3072, 4096, 12, "192"), ("gelu", 2714, 6152, 17, "192"),
     ("bias", 2048, 4096, 7, "128"), ("bias", 1920, 3848, 20, "128"), ("geglu", 3050, 2560, 11, "256"), ("geglu", 2000, 5128, 20, "192"), ("geglu", 1500, 2568, 9, "128"),
