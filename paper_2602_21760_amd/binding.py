@@ -228,8 +228,9 @@ def hyb_cfg_disc_euler(v_c, v_u, x, x_out, scale, t, t_next, disc_l1=None, disc_
 
 def cfg_disc_euler_of_branches(v, x, scale, t, t_next, disc, i, workspace):
     """hyb_cfg_disc_euler of v[0:1] and v[1:2], in place over x, with the discrepancies in disc[0, i:i + 1] and disc[1, i:i + 1] (disc: f32[2, steps]), but
-    without these views, each of which costs the host a microsecond."""
-    if not (v.is_cuda and v.is_contiguous() and disc.is_cuda and disc.is_contiguous() and disc.dtype is torch.float32):
+    without these views, each of which costs the host a microsecond (where one of them would not be there, slicing says so)."""
+    if not (v.is_cuda and v.is_contiguous() and v.shape[0] >= 2 and disc.is_cuda and disc.is_contiguous() and disc.dtype is torch.float32 and
+            disc.dim() == 2 and disc.shape[0] >= 2):
         hyb_cfg_disc_euler(v[0:1], v[1:2], x.view(1, -1), x.view(1, -1), scale, t, t_next, disc[0, i:i + 1], disc[1, i:i + 1], workspace)
         return
     n, pv, px, pd = v.numel() // v.shape[0], v.data_ptr(), _p(x, torch.float32), disc.data_ptr()

@@ -180,6 +180,36 @@ def test_forward_structs_from_dicts_of_tensors():
     assert (b.v, b.ws, b.ws_bytes, b.t_feat) == (t["v"].data_ptr(), t["ws"].data_ptr(), 24, None)
 
 
+@pytest.mark.parametrize("samples,rows,i", [(2, 2, 0), (2, 2, 5), (2, 2, 6), (2, 2, -1), (2, 2, -6), (3, 2, 1), (2, 3, 1), (1, 2, 1), (0, 2, 1), (2, 1, 1), (2, 0, 1)])
+def test_step_addresses_are_those_of_the_views(monkeypatch, samples, rows, i):
+    """The guidance pass of a step gets the addresses that slices of the branches and of the table have (NULL where a slice is empty), and an
+    index that is not there is an error."""
+    import torch
+    from paper_2602_21760_amd import binding
+
+    class OnGpu(torch.Tensor):
+        is_cuda = True
+    calls = []
+
+    class Recorder:
+        def hyb_cfg_disc_euler(self, *a):
+            calls.append(a)
+            return 0
+    monkeypatch.setattr(binding, "lib", Recorder)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    v, x, disc, ws = (torch.zeros(*s).as_subclass(OnGpu) for s in ((samples, 3, 4), (3, 4), (rows, 6), (64,)))
+    try:
+        binding.hyb_cfg_disc_euler(v[0:1], v[1:2], x.view(1, -1), x.view(1, -1), 5.0, 0.5, 0.4, disc[0, i:i + 1], disc[1, i:i + 1], ws)
+    except IndexError:
+        with pytest.raises(IndexError):
+            binding.cfg_disc_euler_of_branches(v, x, 5.0, 0.5, 0.4, disc, i, ws)
+        assert not calls
+        return
+    binding.cfg_disc_euler_of_branches(v, x, 5.0, 0.5, 0.4, disc, i, ws)
+    null = lambda call: [a or None if n in (0, 1, 11, 12) else a for n, a in enumerate(call)]      # noqa: E731
+    assert len(calls) == 2 and null(calls[0]) == null(calls[1])
+
+
 def test_missing_library_is_an_error(monkeypatch, tmp_path):
     """No fallback: without libhyb.so the binding raises."""
     from paper_2602_21760_amd import binding
