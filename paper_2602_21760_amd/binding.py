@@ -178,8 +178,11 @@ def _p(t, dtype=None):
 
 def _pointers(tensors, dtype):
     """_p of several tensors of one type, in less than half of the host time."""
-    if all(map(_is_cuda, tensors)) and all(map(torch.Tensor.is_contiguous, tensors)) and [*map(_dtype_of, tensors)].count(dtype) == len(tensors):
-        return [*map(torch.Tensor.data_ptr, tensors)]
+    try:
+        if all(map(_is_cuda, tensors)) and all(map(torch.Tensor.is_contiguous, tensors)) and [*map(_dtype_of, tensors)].count(dtype) == len(tensors):
+            return [*map(torch.Tensor.data_ptr, tensors)]
+    except AttributeError:                      # None among them
+        pass
     return [_p(t, dtype) for t in tensors]      # says what is wrong
 
 

@@ -210,6 +210,23 @@ def test_step_addresses_are_those_of_the_views(monkeypatch, samples, rows, i):
     assert len(calls) == 2 and null(calls[0]) == null(calls[1])
 
 
+def test_pointers_of_several_tensors_are_those_of_each():
+    """None (a layer without a bias) is NULL, wherever it stands; what a single tensor is refused for, several are."""
+    import torch
+    from paper_2602_21760_amd import binding
+
+    class OnGpu(torch.Tensor):
+        is_cuda = True
+    a, b, low = (torch.zeros(4, 4).as_subclass(OnGpu) for _ in range(3))
+    low = low.bfloat16()
+    for tensors in ((a, b), (None, a), (a, None, b), (a[1], None)):
+        assert binding._pointers(tensors, torch.float32) == [binding._p(t, torch.float32) for t in tensors]
+    for bad, error in ((low, TypeError), (b.t(), ValueError), (torch.zeros(4), ValueError)):
+        for tensors in ((a, bad), (a, None, bad), (bad, None)):
+            with pytest.raises(error):
+                binding._pointers(tensors, torch.float32)
+
+
 def test_missing_library_is_an_error(monkeypatch, tmp_path):
     """No fallback: without libhyb.so the binding raises."""
     from paper_2602_21760_amd import binding
