@@ -150,9 +150,9 @@ class MMDiT:
 
     def _in_one_call(self, *methods):
         """Whether one call of the library does what embed(), run_blocks(), final() (and `methods`) do: none of them is overridden, in a class
-        or on the object, there are as many blocks as modulations were laid out for, and all matrices are of one type."""
-        cls, own = type(self), self.__dict__
-        return (len(self.blocks) == self._call_desc.blocks and self.ada_w.dtype == self.act and
+        or on the object, there are as many blocks as modulations were laid out for, all matrices are of one type, and so is a result of full size."""
+        cls, own, v = type(self), self.__dict__, self.v
+        return (len(self.blocks) == self._call_desc.blocks and self.ada_w.dtype == self.act and v.dtype == self.act and v.shape == self._latent_shape and
                 all(n not in own and getattr(cls, n) is _METHODS[n] for n in ("embed", "run_blocks", "final") + methods))
 
     def _forward(self, latent, ctx, t, pooled=None, shared_latent=False):

@@ -291,7 +291,7 @@ def _small_model(batch=2, **kw):
     return m, latent, ctx, torch.full((batch,), 0.5, device="cuda")
 
 
-@pytest.mark.parametrize("what", ["g", "pos", "ada_w", "ada_b", "blocks item", "blocks", "fewer blocks", "v", "in place", "ada_w f32"])
+@pytest.mark.parametrize("what", ["g", "pos", "ada_w", "ada_b", "blocks item", "blocks", "fewer blocks", "v", "v of the other type", "in place", "ada_w f32"])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_forward_and_step_use_what_the_model_holds_now(hb, what, dt):
     """A weight, a block or the result's buffer that is replaced after the first forward counts from the next one on, in forward() and in a
@@ -317,12 +317,14 @@ def test_forward_and_step_use_what_the_model_holds_now(hb, what, dt):
         m.blocks = list(reversed(m.blocks))
     elif what == "fewer blocks":
         m.blocks.pop()
-    else:
+    elif what == "v":
         m.v = torch.zeros_like(m.v)
+    else:
+        m.v = torch.zeros_like(m.v, dtype=torch.float32 if dt == "bf16" else torch.bfloat16)
     want = _parts(m, latent, ctx, t)
     m.v.zero_()
     got = m.forward(latent, ctx, t)
-    assert got is m.v and torch.equal(got, want) and (what == "v" or not torch.equal(want, before))
+    assert got is m.v and torch.equal(got, want) and (what[0] == "v" or not torch.equal(want, before))
     same = latent[:1].expand_as(latent).contiguous()
     want = _parts(m, same, ctx, t)
     x = latent[0].clone()
