@@ -148,12 +148,13 @@ class MMDiT:
         return ((not cfg.n_txt or (ctx is not None and ctx.numel() == self.ctx_act.numel())) and
                 (not cfg.pooled_dim or (pooled is not None and pooled.numel() == self.pooled_act.numel())))
 
-    def _in_one_call(self, *methods):
-        """Whether one call of the library does what embed(), run_blocks(), final() (and `methods`) do: none of them is overridden, in a class
-        or on the object, there are as many blocks as modulations were laid out for, all matrices are of one type, and so is a result of full size."""
-        cls, own, v = type(self), self.__dict__, self.v
+    def _in_one_call(self, methods=("embed", "run_blocks", "final")):
+        """Whether one call of the library does what embed(), run_blocks(), final() (`methods`) do: none of them is overridden, in a class or on
+        the object, there are as many blocks as modulations were laid out for, all matrices are of one type, and so is a result of full size."""
+        cls, v = type(self), self.v
         return (len(self.blocks) == self._call_desc.blocks and self.ada_w.dtype == self.act and v.dtype == self.act and v.shape == self._latent_shape and
-                all(n not in own and getattr(cls, n) is _METHODS[n] for n in ("embed", "run_blocks", "final") + methods))
+                self.__dict__.keys().isdisjoint(methods) and
+                cls.embed is _METHODS["embed"] and cls.run_blocks is _METHODS["run_blocks"] and cls.final is _METHODS["final"])
 
     def _forward(self, latent, ctx, t, pooled=None, shared_latent=False):
         """embed(), run_blocks() and final() in one call; t: f32[B], or a number for all samples.  Weights and buffers are looked up and
@@ -186,7 +187,7 @@ class GuidedSampler:
         """x: f32[Hh, Ww, C] master latent (updated in place); ctx2: f32[2, Nt, ctx_dim]."""
         m = self.m
         if (isinstance(m, MMDiT) and m._latent_shape == self._latent_shape and x.shape == m._sample_shape and x.dtype is torch.float32 and x.is_cuda and
-                x.is_contiguous() and not m.cfg.pooled_dim and m._inputs_fit(ctx2) and m._in_one_call("forward")):
+                x.is_contiguous() and not m.cfg.pooled_dim and m._inputs_fit(ctx2) and type(m).forward is _METHODS["forward"] and m._in_one_call(_METHODS)):
             m._forward(x, ctx2, float(t), shared_latent=True)   # both branches read the one latent
             v = m.v
         else:

@@ -291,7 +291,7 @@ def _small_model(batch=2, **kw):
     return m, latent, ctx, torch.full((batch,), 0.5, device="cuda")
 
 
-@pytest.mark.parametrize("what", ["g", "pos", "ada_w", "ada_b", "blocks item", "blocks", "fewer blocks", "v", "v of the other type", "in place", "ada_w f32"])
+@pytest.mark.parametrize("what", ["g", "pos", "ada_w", "ada_b", "blocks item", "in a block", "blocks", "fewer blocks", "v", "v of the other type", "in place", "ada_w f32"])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_forward_and_step_use_what_the_model_holds_now(hb, what, dt):
     """A weight, a block or the result's buffer that is replaced after the first forward counts from the next one on, in forward() and in a
@@ -313,6 +313,8 @@ def test_forward_and_step_use_what_the_model_holds_now(hb, what, dt):
         m.g["f_b"].data = m.g["f_b"] + 1
     elif what == "blocks item":
         m.blocks[0] = m.blocks[1]
+    elif what == "in a block":
+        m.blocks[0].img = m.blocks[1].img
     elif what == "blocks":
         m.blocks = list(reversed(m.blocks))
     elif what == "fewer blocks":
